@@ -68,10 +68,7 @@ Layout make_layout(const Geo &g, int64_t n) {
   L.off_ix = o;       o = up256(o + (size_t)n * 4);
   L.off_kr = o;       o = up256(o + (size_t)n * 4);
   L.off_lb = o;       o = up256(o + C * ((size_t)L.gmax + 1) * g.Dk * 4);
-  L.off_cagg = o;     o = up256(o + C * (size_t)L.gmax * 8);
-  L.off_cgin = o;     o = up256(o + C * (size_t)L.gmax * 8);
   L.off_wst = o;      o = up256(o + 2 * C * (size_t)L.gmax * 8);
-  L.off_nbl = o;      o = up256(o + C * (size_t)L.gmax * 4);
   L.off_iss = o;      o = up256(o + (g.reg_block ? (size_t)n * 8 : 0));
   L.total = o;
   return L;

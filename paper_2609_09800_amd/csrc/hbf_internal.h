@@ -39,15 +39,11 @@ constexpr int DITEMS = 8;           // requests per thread per chunk
 constexpr int CHUNK = DBLK * DITEMS;  // 4096 requests staged per chunk
 constexpr int TARGET_TILES = 512;   // die-stage tiles: two 512-thread blocks per CU
 
-// Channel stage: a time cell of one channel is merged in LDS if it holds at
-// most MCAP requests, otherwise streamed in MCAP-sized rounds.
+// Channel stage: a time cell of one channel of minimum width holds at most
+// MCAP requests (one step of a wave), MAX_BUCKETS per die queue.  Time
+// buckets of width 2^floor(log2 tR) hold at most one request per die.
 constexpr int MCAP = 1024;
-// Time buckets of width 2^floor(log2 tR) hold at most one request per die;
-// a cell of at most 64 such buckets is ranked with per-die bucket masks.
 constexpr int MAX_BUCKETS = 64;
-// The channel stage hands each XCD (L2 domain) its own time windows, so the
-// requests of one window, from every channel, complete in one L2.
-constexpr int NXCD = 8;
 constexpr int MAX_RUNS = 64;        // die queues per channel (D, or D*P)
 // Closed-loop layers in one launch: one workgroup per layer ranks each
 // layer's requests, so layers are bounded; larger ones take a call per layer.
@@ -117,8 +113,7 @@ struct CallCtl {
   int64_t max_dd;     // largest die-done time of the call
   int64_t max_cpl;    // largest in-range completion of the call (NEG if none)
   int64_t cbase;      // origin of the cell grid (= first issue time)
-  uint32_t n_rest;    // cells k_cell_agg lists for k_cell_rest (grids off the bucket path)
-  uint32_t wctr;      // next unit of the fused channel stage
+  uint32_t wctr;      // next unit of the channel stage
 };
 
 // Workspace layout of one hbf_time_requests call.
@@ -131,9 +126,7 @@ struct Layout {
   size_t off_ctl, off_agg_cnt, off_agg_A, off_tin_L, off_tin_base;
   size_t off_totals, off_seg, off_dfnew, off_cfnew;
   size_t off_dd, off_ix, off_kr, off_lb;
-  size_t off_cagg, off_cgin;  // per (channel, time cell): aggregate, entering term
-  size_t off_wst;             // fused channel stage: published aggregate and inclusive term per cell
-  size_t off_nbl;             // cells k_cell_agg lists for k_cell_rest
+  size_t off_wst;             // channel stage: published aggregate and inclusive term per cell
   size_t off_iss;             // register blocking: issue times in die order (n int64)
   // vmem route (tiles of VM_TILE requests): per tile its burst summary, the
   // summary of everything before it, its route-clock pair and entering

@@ -29,9 +29,6 @@
 //                  decoupled look-back over earlier windows, and write
 //                  complete[] in request order (staged by index in LDS
 //                  where the window's requests cluster).
-//   k_cell_agg, k_cell_scan, k_cell_rest
-//                  the same stage as reduce, scan and reduce again, for
-//                  grids whose cells are too wide for the bucket merge.
 //   k_finalize     fail-closed error fill, or commit of the new clocks.
 //
 // A die emits at most one request per t_read_ns, so a time cell of width
@@ -59,7 +56,6 @@ __global__ void k_prologue(CallCtl *ctl) {
     ctl->max_dd = NEG;
     ctl->max_cpl = NEG;
     ctl->cbase = 0;
-    ctl->n_rest = 0;
     ctl->wctr = 0;
   }
 }
@@ -693,46 +689,7 @@ __global__ __launch_bounds__(SBLK) void k_die_scatter(
 
 // ------------------------------------------------------------------ channel stage
 
-// (dd, idx) lexicographic order; idx is unique.
-DEVI bool key_less(int64_t da, uint32_t ia, int64_t db, uint32_t ib) {
-  return da < db || (da == db && ia < ib);
-}
-
-// Run containing position p: the last d with rb[d] <= p.
-DEVI int run_of(const uint32_t *rb, int R, uint32_t p) {
-  int lo = 0, hi = R;  // rb[0] <= p < rb[R]
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (rb[mid] <= p) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
-
-constexpr int CAP_S = 256;     // requests per round of a streamed cell
-constexpr int SLOTS_MAX = 16;  // die runs per channel on the bucket path
-
-struct CellLds {
-  union {
-    struct {
-      uint64_t in[MCAP];                 // (dd - cell start) << 32 | index, in run order
-      uint8_t tbl[MAX_BUCKETS][SLOTS_MAX];  // 1 + position in its run of die d's request in bucket q
-    } f;
-    struct {
-      int64_t dd[2][CAP_S];
-      uint32_t ix[2][CAP_S];
-      uint8_t tg[2][CAP_S];
-    } s;
-  } u;
-  uint32_t rb[MAX_RUNS + 1]; // run offsets in the staging buffer
-  uint32_t lo[MAX_RUNS];     // run bounds: global positions in the die order
-  uint32_t hi[MAX_RUNS];
-  uint32_t cur[MAX_RUNS];
-  uint32_t take[MAX_RUNS];
-  uint32_t used[MAX_RUNS];
-  uint32_t safe;
-};
+constexpr int SLOTS_MAX = 16;  // die runs per channel on the bucket path; sorted requests per lane elsewhere
 
 // Sort keys of the bucket path are integers below 2^51 held in the mantissa
 // of a double in [1, 2) (exponent bits 0x3FF): there IEEE order is integer
@@ -768,154 +725,23 @@ DEVI void sort_slots(uint64_t (&a)[SL]) {
   }
 }
 
-// One wave streams a cell through the LDS in rounds of at most CAP_S
-// requests (cells that are too wide or too full for the bucket path).  Each
-// round loads at most CAP_S/R requests per run, ranks them (binary searches
-// in the other runs), and serves the prefix that no unloaded request can
-// precede.  gacc: running channel term; returns it after the cell.
-DEVI int64_t stream_cell(CellLds &S, const int64_t *DD, const uint32_t *IX, bool narrow, int64_t cstart,
-                         int R, int64_t gacc, int64_t rank0, int64_t xfer, bool emit, int64_t *complete,
-                         uint32_t n, uint32_t *errb) {
-  const uint32_t lane = lane_id();
-  if (lane < (uint32_t)R) S.cur[lane] = S.lo[lane];
-  wave_sync();
-  int64_t done = 0;
-  const uint32_t quota = CAP_S / R;
-  while (true) {
-    uint32_t rem = 0, take = 0;
-    if (lane < (uint32_t)R) rem = S.hi[lane] - S.cur[lane];
-    const uint32_t tot = wave_sum(rem);
-    if (tot == 0) break;
-    take = tot <= (uint32_t)CAP_S ? rem : min(rem, quota);
-    const uint32_t rbx = wave_excl_sum(take);
-    const uint32_t m = wave_sum(take);
-    if (lane < (uint32_t)R) {
-      S.rb[lane] = rbx;
-      S.take[lane] = take;
-      S.used[lane] = 0;
-    }
-    if (lane == 0) S.rb[R] = m;
-    wave_sync();
-    for (uint32_t p = lane; p < m; p += 64) {
-      const int d = run_of(S.rb, R, p);
-      const uint32_t src = S.cur[d] + (p - S.rb[d]);
-      if (narrow) {
-        const uint64_t x = reinterpret_cast<const uint64_t *>(DD)[src];
-        S.u.s.dd[0][p] = cstart + (int64_t)(x >> 32);
-        S.u.s.ix[0][p] = (uint32_t)x;
-      } else {
-        S.u.s.dd[0][p] = DD[src];
-        S.u.s.ix[0][p] = IX[src];
-      }
-      S.u.s.tg[0][p] = (uint8_t)d;
-    }
-    wave_sync();
-    // merged order: own index + requests of the other runs that precede
-    for (uint32_t p = lane; p < m; p += 64) {
-      const int d = S.u.s.tg[0][p];
-      const int64_t x = S.u.s.dd[0][p];
-      const uint32_t xi = S.u.s.ix[0][p];
-      uint32_t r = p - S.rb[d];
-      for (int d2 = 0; d2 < R; d2++) {
-        if (d2 == d) continue;
-        uint32_t a = S.rb[d2], b = S.rb[d2 + 1];
-        while (a < b) {
-          const uint32_t mid = (a + b) >> 1;
-          if (key_less(S.u.s.dd[0][mid], S.u.s.ix[0][mid], x, xi)) a = mid + 1;
-          else b = mid;
-        }
-        r += a - S.rb[d2];
-      }
-      S.u.s.dd[1][r] = x;
-      S.u.s.ix[1][r] = xi;
-      S.u.s.tg[1][r] = (uint8_t)d;
-    }
-    wave_sync();
-    // safe prefix: everything up to the smallest last-loaded request of a
-    // run that still has requests behind it
-    if (lane == 0) {
-      bool ok = false;
-      int64_t vd = 0;
-      uint32_t vi = 0;
-      for (int d = 0; d < R; d++) {
-        const uint32_t t = S.take[d];
-        if (t > 0 && t < S.hi[d] - S.cur[d]) {
-          const uint32_t q = S.rb[d] + t - 1;
-          if (!ok || key_less(S.u.s.dd[0][q], S.u.s.ix[0][q], vd, vi)) {
-            vd = S.u.s.dd[0][q];
-            vi = S.u.s.ix[0][q];
-            ok = true;
-          }
-        }
-      }
-      uint32_t safe = m;
-      if (ok) {
-        uint32_t a = 0, b = m;
-        while (a < b) {
-          const uint32_t mid = (a + b) >> 1;
-          if (!key_less(vd, vi, S.u.s.dd[1][mid], S.u.s.ix[1][mid])) a = mid + 1;
-          else b = mid;
-        }
-        safe = a;
-      }
-      S.safe = safe;
-    }
-    wave_sync();
-    const uint32_t safe = S.safe;
-    for (uint32_t base = 0; base < safe; base += 64) {
-      const uint32_t p = base + lane;
-      int64_t v = NEG;
-      if (p < safe) {
-        v = S.u.s.dd[1][p] - (rank0 + done + p) * xfer;
-        atomicAdd(&S.used[S.u.s.tg[1][p]], 1u);
-      }
-      const int64_t q = imax(gacc, wave_incl_max(v));
-      if (emit && p < safe) {
-        const int64_t cpl = (rank0 + done + p + 1) * xfer + q;
-        if (cpl >= TIME_LIMIT) *errb |= ERR_OVERFLOW;
-        const uint32_t ix = S.u.s.ix[1][p];
-        if (ix < n) complete[ix] = cpl;
-      }
-      gacc = imax(gacc, wave_max(v));
-    }
-    done += safe;
-    wave_sync();
-    if (lane < (uint32_t)R) S.cur[lane] += S.used[lane];
-    wave_sync();
-  }
-  return gacc;
-}
-
 // Channel stage.  With channel ranks k (1-based) and the channel free at f0
 // before the call, complete_k = k*xfer + max(f0, max_{i<=k} (dd_(i) - (i-1)*xfer)).
 // A cell knows its first rank from the cell table (the sum of its row), so
 // its aggregate is one number, M_j = max over its requests of
 // (dd - (rank-1)*xfer), and the term entering cell j is max(f0, M_j' for
-// j' < j).  On the bucket path k_cell_chan merges each cell once and finds
-// the entering term by a look-back over earlier windows.  Grids off the
-// bucket path run reduce, scan, reduce again:
-//   k_cell_agg   M_j of every cell;
-//   k_cell_scan  per channel, the running maximum of M_j seeded with f0;
-//   k_cell_rest  every cell again, now writing complete[] with its term.
-//
-// One wave per cell.  The bucket path (buckets of width 2^lg_tR <= tR hold
-// at most one request per die): lane q gathers the requests of bucket q --
-// die d's is at 1 + the byte the LDS table holds for (q, d) -- sorts them
-// in registers, and owns merged positions boff..boff+cnt-1 of the cell.
-// Cells that are too wide or too full stream through the LDS instead.
-
-// Cell of iteration `it` of this block: (window, channel) order,
-// grid-stride, so all blocks move along one common time front.
-DEVI bool cell_at(uint32_t it, uint32_t N, uint32_t C, uint32_t G, uint32_t &c, uint32_t &j) {
-  const uint64_t cell = (uint64_t)blockIdx.x + (uint64_t)it * gridDim.x;
-  if (cell >= N) return false;
-  j = (uint32_t)cell / C;
-  c = (uint32_t)cell - j * C;
-  return true;
-}
-
-// One pass over cell (c, j).  Returns M_j; with EMIT, writes instead the
-// completion of each of its requests given the entering term gin.
+// j' < j).  k_cell_chan orders each cell once, in registers, and finds the
+// entering term by a look-back over earlier windows.  Two ways to order a
+// cell, one wave each:
+//   bucket merge  cells of at most 64 buckets of width 2^lg_tR <= tR, which
+//                 hold at most one request per die: lane q gathers the
+//                 requests of bucket q, sorts them in registers and owns
+//                 merged positions boff..boff+cnt-1 (cell_merge);
+//   lane merge    every other grid (cells wider than 64 buckets, because
+//                 the stream is sparse, or more than 16 die queues per
+//                 channel): the runs are cut into pieces of up to 16
+//                 requests, one piece per lane, and merged by a bitonic
+//                 network across the lanes (cell_sort).
 // A cell's runs, lane d = die run d: die-order bounds [lo, hi) and the die
 // rank r0 of the first one.
 struct CellRuns {
@@ -955,203 +781,23 @@ DEVI void load_runs(const int64_t *__restrict__ DD, const CellRuns &cr, int R, u
   }
 }
 
-// Whether the cell grid allows the bucket path at all: buckets of width
-// 2^lg_tR, at most 64 of them per cell, packed 32-bit cell offsets, and at
-// most SL die runs per channel.  A cell then takes it if no run holds more
-// than 64 of its requests.
+// Whether the cell grid allows the bucket merge: buckets of width 2^lg_tR,
+// at most 64 of them per cell, packed 32-bit cell offsets, and at most SL
+// die runs per channel.
 template <int SL>
 DEVI bool grid_bucketable(const Geo &g, uint32_t shift) {
   return (shift - g.lg_tR <= 6) && shift <= 32 && g.lg_tR <= 20 && (int)g.Dk <= SL;
 }
 
-template <int SL, bool EMIT>
-DEVI int64_t cell_pass(CellLds &S, const int64_t *__restrict__ DD, const uint32_t *__restrict__ IX,
-                       const CellRuns &cr, const uint64_t (&xv)[SL], const Geo &g, uint32_t shift,
-                       int64_t cbase, uint32_t j, int64_t gin, int64_t *complete, uint32_t n,
-                       uint32_t *errb) {
-  const uint32_t lane = lane_id();
-  const uint32_t Dk = g.Dk;
-  const uint32_t lgt = g.lg_tR;
-  const bool bucketable = grid_bucketable<SL>(g, shift);
-  const int R = (int)Dk;
-  const int64_t xfer = g.xfer;
-  const int64_t cstart = cbase + ((int64_t)j << shift);
-  const uint32_t lo = cr.lo, hi = cr.hi, r0 = cr.r0;
-  const uint32_t len = hi - lo;
-  const uint32_t rbx = wave_excl_sum(len);
-  const uint32_t m = wave_sum(len);
-  const int64_t rank0 = wave_sum(r0);  // channel rank of the cell's first request
-  if (m == 0) return NEG;
-  if (lane < Dk) {
-    S.lo[lane] = lo;
-    S.hi[lane] = hi;
-    S.rb[lane] = rbx;
-  }
-  if (lane == 0) S.rb[R] = m;
-  wave_sync();
-  const uint32_t maxlen = wave_umax(lane < Dk ? len : 0u);
-  if (!(bucketable && maxlen <= 64)) {
-    if (EMIT) {
-      stream_cell(S, DD, IX, shift <= 32, cstart, R, gin, rank0, xfer, true, complete, n, errb);
-      return NEG;
-    }
-    return stream_cell(S, DD, IX, shift <= 32, cstart, R, NEG, rank0, xfer, false, complete, n, errb);
-  }
-  uint64_t slot[SL];
-  uint32_t cnt = 0;
-  // clear the bucket table (1 KB: 16 B per lane)
-  reinterpret_cast<uint4 *>(&S.u.f.tbl[0][0])[lane] = make_uint4(0, 0, 0, 0);
-  // the runs were loaded by load_runs.  Bucketable cells are at most 2^32 ns
-  // wide, so their entries are packed words (offset in the cell << 32 |
-  // index); staged as the bucket's sort key: offset in the bucket (< 2^20)
-  // << 31 | index.
-  wave_sync();
-  const uint64_t offmask = (uint64_t(1) << lgt) - 1;
-#pragma unroll
-  for (int d = 0; d < SL; d++) {
-    const uint32_t lend = __builtin_amdgcn_readlane(len, d);
-    const uint32_t rbd = __builtin_amdgcn_readlane(rbx, d);
-    if (d < R && lane < lend) {
-      const uint64_t rel = xv[d] >> 32;
-      S.u.f.in[rbd + lane] = KEY_ONE | (rel & offmask) << 31 | (xv[d] & 0xFFFFFFFFull);
-      S.u.f.tbl[rel >> lgt][d] = (uint8_t)(lane + 1);
-    }
-  }
-  wave_sync();
-  // lane q: gather, sort and count bucket q
-  {
-    const uint4 row = reinterpret_cast<const uint4 *>(&S.u.f.tbl[0][0])[lane];
-    const uint32_t rw[4] = {row.x, row.y, row.z, row.w};
-#pragma unroll
-    for (int d = 0; d < SL; d++) {
-      const uint32_t y = (rw[d >> 2] >> (8 * (d & 3))) & 0xFFu;
-      const uint32_t rbd = __builtin_amdgcn_readlane(rbx, d);
-      slot[d] = KEY_EMPTY;
-      if (y) {
-        slot[d] = S.u.f.in[rbd + y - 1];
-        cnt++;
-      }
-    }
-  }
-  sort_slots<SL>(slot);
-  const uint32_t boff = wave_excl_sum(cnt);
-  // Lindley prefix over the merged order, in registers: merged position p
-  // has value dd - (rank0 + p) * xfer, dd = cell start + bucket start + offset
-  const int64_t cst = cstart + ((int64_t)lane << lgt) - rank0 * xfer;
-  int64_t loc = NEG;
-#pragma unroll
-  for (int i = 0; i < SL; i++) {
-    if ((uint32_t)i < cnt) {
-      const int64_t v = cst + (int64_t)((slot[i] >> 31) & 0x1FFFFFu) - (int64_t)mul32(boff + i, (uint32_t)xfer);
-      loc = imax(loc, v);
-    }
-  }
-  if (!EMIT) return wave_max(loc);
-  int64_t carry = __shfl_up(wave_incl_max(loc), 1);
-  if (lane == 0) carry = NEG;
-  carry = imax(carry, gin);
-  const int64_t r0x = rank0 * xfer;
-#pragma unroll
-  for (int i = 0; i < SL; i++) {
-    if ((uint32_t)i < cnt) {
-      const int64_t v = cst + (int64_t)((slot[i] >> 31) & 0x1FFFFFu) - (int64_t)mul32(boff + i, (uint32_t)xfer);
-      carry = imax(carry, v);
-      const int64_t cpl = r0x + (int64_t)mul32(boff + i + 1, (uint32_t)xfer) + carry;
-      if (cpl >= TIME_LIMIT) *errb |= ERR_OVERFLOW;
-      const uint32_t ix = (uint32_t)slot[i] & 0x7FFFFFFFu;
-      if (ix < n) complete[ix] = cpl;
-    }
-  }
-  return NEG;
-}
-
-// The cell loop of both passes.  (Loading the next cell's runs while the
-// current one merges needs a second set of run registers: it halved the
-// occupancy of the aggregate pass and measured slower in the output pass.)
-template <int SL, typename Body>
-DEVI void cell_loop(const int64_t *__restrict__ DD, const uint32_t *__restrict__ LB,
-                    const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ totals, const Geo &g,
-                    uint32_t gmax, uint32_t N, uint32_t G, Body body) {
-  uint32_t c, j;
-  for (uint32_t it = 0; cell_at(it, N, g.C, G, c, j); it++) {
-    const CellRuns cr = cell_runs(LB, seg_start, totals, g.Dk, gmax, c, j);
-    uint64_t xv[SL];
-    load_runs<SL>(DD, cr, (int)g.Dk, xv);
-    body(c, j, cr, xv);
-    wave_sync();
-  }
-}
-
 constexpr uint32_t CMIN_NONE = 0xFFFFFFFFu;
 
-// Grids off the bucket path (cells too wide for 64 buckets, or more die
-// queues per channel than SL): M_j of every cell, which is listed for
-// k_cell_rest.  On the bucket path k_cell_chan does the whole stage and
-// this kernel returns at once.
-template <int SL>
-__global__ __launch_bounds__(64) void k_cell_agg(
-    const int64_t *__restrict__ DD, const uint32_t *__restrict__ IX, const uint32_t *__restrict__ LB,
-    const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ totals, Geo g,
-    CallCtl *ctl, int64_t *__restrict__ AGG, uint32_t *__restrict__ NBL, uint32_t gmax, uint32_t n) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  CellLds &S = *(CellLds *)smem;
-  if (agent_load32(&ctl->err)) return;
-  const uint32_t G = ctl->G, N = G * g.C, shift = ctl->shift;
-  if (grid_bucketable<SL>(g, shift)) return;
-  const int64_t cbase = ctl->cbase;
-  uint32_t errb = 0;
-  cell_loop<SL>(DD, LB, seg_start, totals, g, gmax, N, G,
-                [&](uint32_t c, uint32_t j, const CellRuns &cr, const uint64_t (&xv)[SL]) {
-                  const int64_t M = cell_pass<SL, false>(S, DD, IX, cr, xv, g, shift, cbase, j, NEG,
-                                                         nullptr, n, &errb);
-                  const uint32_t m = wave_sum(cr.hi - cr.lo);
-                  if (lane_id() == 0) {
-                    AGG[(size_t)c * gmax + j] = M;
-                    if (m > 0) NBL[atomicAdd(&ctl->n_rest, 1u)] = j * g.C + c;
-                  }
-                });
-  if (errb) atomicOr(&ctl->err, errb);
-}
-
-// Per channel: GIN[j] = max(f0, M_j' for j' < j); the channel clock after the
-// call is (its request count) * xfer + max(f0, every M_j).  One block per
-// channel, each thread a contiguous range of windows: fold, block scan, walk.
-__global__ __launch_bounds__(BLK) void k_cell_scan(const int64_t *__restrict__ AGG, int64_t *__restrict__ GIN,
-                                                   const uint32_t *__restrict__ totals, Geo g,
-                                                   CallCtl *ctl, const DevState *st,
-                                                   int64_t *__restrict__ cfnew, uint32_t gmax) {
-  __shared__ int64_t sh[WAVES];
-  if (agent_load32(&ctl->err)) return;
-  if (grid_bucketable<SLOTS_MAX>(g, ctl->shift)) return;  // the bucket path is k_cell_chan's
-  const uint32_t c = blockIdx.x, G = ctl->G;
-  const size_t row = (size_t)c * gmax;
-  const uint32_t per = (G + BLK - 1) / BLK;
-  const uint32_t ja = min(G, threadIdx.x * per), jb = min(G, ja + per);
-  int64_t m = NEG;
-  for (uint32_t j = ja; j < jb; j++) m = imax(m, AGG[row + j]);
-  const int64_t ex = block_excl_max<WAVES>(m, sh);
-  const int64_t f0 = st->chan_free[c];
-  int64_t carry = imax(f0, ex);
-  for (uint32_t j = ja; j < jb; j++) {
-    GIN[row + j] = carry;
-    carry = imax(carry, AGG[row + j]);
-  }
-  if (threadIdx.x == BLK - 1) {
-    uint64_t tot = 0;
-    for (uint32_t d = 0; d < g.Dk; d++) tot += totals[c * g.Dk + d];
-    const int64_t last = (int64_t)tot * g.xfer + imax(f0, imax(ex, m));
-    cfnew[c] = last;
-    // the channel's last completion of this call
-    if (tot) atomicMax((long long *)&ctl->max_cpl, (long long)last);
-  }
-}
-
-// ---- Fused channel stage (grids on the bucket path).  The work is cut into
-// units: a unit is one time window j and a group of up to CH_GROUP channels
-// (all of them when C <= CH_GROUP), and units are claimed in (window, group)
-// order from a counter of the call.  One 1,024-thread workgroup per unit:
-//   1. each wave merges two of the unit's cells (bucket path, kept in
-//      registers) and publishes each cell's term M_j;
+// ---- The stage's work is cut into units of up to 32 cells (16 with the lane
+// merge, whose network needs the registers of the second cell): one time
+// window of a group of 32 channels or, with fewer channels, as many windows
+// of all channels as make 32 cells; units are claimed in (window, group) order from
+// a counter of the call.  One 1,024-thread workgroup per unit:
+//   1. each wave orders its one or two cells (kept in registers) and
+//      publishes each cell's term M_j;
 //   2. per channel, the term entering the cell, max(f0, M_j' for j' < j),
 //      by a decoupled look-back over the earlier windows' published words:
 //      the nearest inclusive term plus the aggregates in between;
@@ -1162,8 +808,9 @@ __global__ __launch_bounds__(BLK) void k_cell_scan(const int64_t *__restrict__ A
 //      as a 32-bit offset from a base, and the band is written in index
 //      order (whole lines); completions outside the staged span, or whose
 //      offset does not fit, are stored directly.
-// A unit waits only for units claimed before it: their workgroups are
-// running and publish their aggregates without waiting, so every wait ends.
+// A unit waits only for its own waves and for units claimed before it: all
+// of them run and publish their aggregates without waiting, so every wait
+// ends.
 // The wait is bounded all the same; running past the bound fails the call
 // with ERR_INTERNAL instead of hanging.  The published words are single
 // 64-bit atomics that carry their own validity (0 = not yet), cleared by
@@ -1171,7 +818,6 @@ __global__ __launch_bounds__(BLK) void k_cell_scan(const int64_t *__restrict__ A
 // half-wave polling 32 consecutive windows of one channel reads two lines.
 constexpr int WIN_WAVES = 16;
 constexpr int WIN_THREADS = WIN_WAVES * 64;
-constexpr int CH_GROUP = 2 * WIN_WAVES;
 constexpr uint32_t WIN_SLOTS = 32768;
 constexpr uint32_t WIN_EMPTY = 0xFFFFFFFFu;
 constexpr uint32_t LOOKBACK_ROUNDS = 1u << 22;
@@ -1223,22 +869,22 @@ DEVI int64_t lane_i64(int64_t x, int l) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// The terms entering window j of two channels, one per half-wave (lanes
-// 0-31: channel ca, 32-63: channel cb; a channel >= C is skipped).  Lane s
+// The terms entering two cells, one per half-wave (lanes 0-31: window ja of
+// channel ca, 32-63: window jb of channel cb; a channel >= C is skipped).  Lane s
 // of a half inspects window base - s: its inclusive word, else its
 // aggregate.  A round ends at the nearest inclusive word (or before window
 // 0, where the term is the channel's clock f0) if no aggregate before it is
 // missing; otherwise the half folds what precedes the first missing one and
 // polls again from there.
-DEVI void look_back2(const uint64_t *WAGG, const uint64_t *WINC, uint32_t C, uint32_t gmax, uint32_t j,
-                     uint32_t ca, uint32_t cb, int64_t f0a, int64_t f0b, int64_t &ga, int64_t &gb,
+DEVI void look_back2(const uint64_t *WAGG, const uint64_t *WINC, uint32_t C, uint32_t gmax, uint32_t ja,
+                     uint32_t jb, uint32_t ca, uint32_t cb, int64_t f0a, int64_t f0b, int64_t &ga, int64_t &gb,
                      uint32_t *errb) {
   const uint32_t lane = lane_id(), s = lane & 31;
   const bool hi = lane >= 32;
   const uint32_t c = hi ? cb : ca;
   const int64_t f0 = hi ? f0b : f0a;
   int64_t acc0 = NEG, acc1 = NEG;
-  int64_t base0 = (int64_t)j - 1, base1 = (int64_t)j - 1;
+  int64_t base0 = (int64_t)ja - 1, base1 = (int64_t)jb - 1;
   bool done0 = ca >= C, done1 = cb >= C;
   uint32_t rounds = 0;
   while (!(done0 && done1)) {
@@ -1299,16 +945,18 @@ DEVI void look_back2(const uint64_t *WAGG, const uint64_t *WINC, uint32_t C, uin
   gb = acc1;
 }
 
-// A merged cell, held in registers: lane q owns bucket q's entries, sorted
-// (slot), their count and first merged position; plus the cell's size, its
-// smallest request index, the channel rank of its first request, and per
-// lane the maximum of dd - (rank0 + position) * xfer over its entries.
+// An ordered cell, held in registers: each lane owns cnt consecutive merged
+// positions from boff (slot, ascending); plus the cell's size, its smallest
+// request index, the channel rank of its first request, and per lane the
+// maximum of dd - (rank0 + position) * xfer over its entries.  big (uniform):
+// a cell ordered in several steps, whose slots are not kept.
 template <int SL>
 struct Merged {
   uint64_t slot[SL];
   uint32_t cnt, boff;
   uint32_t m, head;
   int64_t rank0, loc;
+  bool big;
 };
 
 // Merge one bucketable cell (lane q gathers bucket q's entries from the
@@ -1328,6 +976,7 @@ DEVI void cell_merge(uint8_t (*tbl)[SLOTS_MAX], const CellRuns &cr, const uint64
   M.head = CMIN_NONE;
   M.rank0 = 0;
   M.loc = NEG;
+  M.big = false;
 #pragma unroll
   for (int d = 0; d < SL; d++) M.slot[d] = KEY_EMPTY;
   if (M.m == 0) return;
@@ -1379,16 +1028,232 @@ DEVI void cell_merge(uint8_t (*tbl)[SLOTS_MAX], const CellRuns &cr, const uint64
   wave_sync();  // tbl is reused by the wave's next cell
 }
 
-// Completions of a merged cell given its entering term gin: staged in the
-// band when they fit, else stored directly.  mytop: staged span used.
+// ---- Lane merge.  A run of up to 16 * P requests sits on P = 64 / (die runs,
+// rounded up to a power of two) neighbouring lanes, 16 or fewer consecutive
+// requests each, so every group of P lanes is sorted from the start and
+// log2(64 / P) bitonic merges order the cell.  Keys: bit 62 set, offset from
+// a base time (< 2^30) << 31 | request index, below KEY_NONE; as doubles all
+// of them are finite and positive, so IEEE order is integer order here too.
+// A cell is merged with the fewest slots per lane (2, 4, 8 or 16) that hold
+// its longest run, and needs no search and no second pass: reducing every
+// such cell, scanning and ordering it again by binary searches in LDS took
+// 1,060 us of a 4 M-request call at 85 % channel load (32 channels x 16
+// dies; the whole call 1,156 us, now 176) and 2,770 us of a 3 M-request call
+// with 64 die queues per channel (2,890, now 245).
+constexpr uint64_t KEY_TOP = uint64_t(1) << 62;
+constexpr uint64_t KEY_NONE64 = uint64_t(3) << 61;
+constexpr uint32_t SUB_LG_MAX = 30;  // offsets of a lane-merge key
+
+// x of lane (l ^ M): DPP within rows of 16, LDS swizzle across rows of a
+// half, the half swap for the rest.
+template <int M>
+DEVI uint32_t lane_xor(uint32_t x) {
+  if constexpr (M == 1) return dpp32<0xB1, 0xF>(x, x);        // quad_perm [1,0,3,2]
+  else if constexpr (M == 2) return dpp32<0x4E, 0xF>(x, x);   // quad_perm [2,3,0,1]
+  else if constexpr (M == 3) return dpp32<0x1B, 0xF>(x, x);   // quad_perm [3,2,1,0]
+  else if constexpr (M == 7) return dpp32<0x141, 0xF>(x, x);  // row_half_mirror
+  else if constexpr (M == 4) return lane_xor<7>(lane_xor<3>(x));
+  else if constexpr (M == 15) return dpp32<0x140, 0xF>(x, x); // row_mirror
+  else if constexpr (M == 8) return dpp32<0x128, 0xF>(x, x);  // row_ror:8
+  else if constexpr (M == 16 || M == 31)
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (M << 10) | 0x1F);
+  else {  // 32, 63
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const uint32_t y = lane_id() < 32 ? r[1] : r[0];  // the other half's value
+    if constexpr (M == 32) return y;
+    else return lane_xor<31>(y);
+  }
+}
+template <int M>
+DEVI uint64_t lane_xor(uint64_t x) {
+  return (uint64_t)lane_xor<M>((uint32_t)(x >> 32)) << 32 | lane_xor<M>((uint32_t)x);
+}
+
+// Bitonic exchange across lanes l and l ^ L: the lower one keeps the smaller.
+template <int L, int SL>
+DEVI void cross_step(uint64_t (&a)[SL]) {
+  const bool lower = (lane_id() & L) == 0;
+#pragma unroll
+  for (int i = 0; i < SL; i++) {
+    const uint64_t y = lane_xor<L>(a[i]);
+    a[i] = ((a[i] < y) == lower) ? a[i] : y;
+  }
+}
+// Merge neighbouring sorted groups of L lanes into groups of 2 * L.
+template <int L, int SL>
+DEVI void lane_merge(uint64_t (&a)[SL]) {
+  const bool lower = (lane_id() & L) == 0;
+#pragma unroll
+  for (int i = 0; i < SL / 2; i++) {  // against the other group reversed
+    const uint64_t y = lane_xor<2 * L - 1>(a[SL - 1 - i]), z = lane_xor<2 * L - 1>(a[i]);
+    a[i] = ((a[i] < y) == lower) ? a[i] : y;
+    a[SL - 1 - i] = ((a[SL - 1 - i] < z) == lower) ? a[SL - 1 - i] : z;
+  }
+  if constexpr (L >= 32) cross_step<16, SL>(a);
+  if constexpr (L >= 16) cross_step<8, SL>(a);
+  if constexpr (L >= 8) cross_step<4, SL>(a);
+  if constexpr (L >= 4) cross_step<2, SL>(a);
+  if constexpr (L >= 2) cross_step<1, SL>(a);
+#pragma unroll
+  for (int s = SL / 2; s >= 1; s >>= 1) {
+#pragma unroll
+    for (int i = 0; i < SL; i++)
+      if (!(i & s)) cx_key(a[i], a[i + s]);
+  }
+}
+
+// The die-order entries of a call: packed words (cells at most 2^32 ns wide)
+// or die-done times and indices.
+struct DieOrder {
+  const int64_t *__restrict__ DD;
+  const uint32_t *__restrict__ IX;
+  bool narrow;
+  DEVI int64_t time(uint32_t at, int64_t cstart) const {
+    return narrow ? cstart + (int64_t)(reinterpret_cast<const uint64_t *>(DD)[at] >> 32) : DD[at];
+  }
+  DEVI uint32_t index(uint32_t at) const {
+    return narrow ? (uint32_t)reinterpret_cast<const uint64_t *>(DD)[at] : IX[at];
+  }
+};
+
+// Order at most 64 * SL requests: lane d holds run d's position `lo` and
+// length `len` (at most SL << lp), base time tb (>= cstart, every request
+// within 2^30 of it).
 template <int SL>
-DEVI void cell_emit(const Merged<SL> &M, const Geo &g, int64_t cstart, int64_t gin, uint32_t lo, int64_t wbase,
+DEVI void sort_take(const DieOrder &D, uint32_t lo, uint32_t len, uint32_t lp, int64_t cstart, int64_t tb,
+                    uint64_t (&slot)[SLOTS_MAX]) {
+  const uint32_t lane = lane_id();
+  const uint32_t d = lane >> lp, skip = (lane & ((1u << lp) - 1)) * SL;
+  const uint32_t at = __shfl(lo, (int)d) + skip, have = __shfl(len, (int)d);
+  const uint32_t cnt = have > skip ? have - skip : 0u;
+  uint64_t a[SL];
+  if (D.narrow) {
+    const uint64_t *DX = reinterpret_cast<const uint64_t *>(D.DD) + at;
+    const uint32_t sub = (uint32_t)(tb - cstart);
+#pragma unroll
+    for (int i = 0; i < SL; i++) a[i] = (uint32_t)i < cnt ? DX[i] : 0;
+#pragma unroll
+    for (int i = 0; i < SL; i++)
+      a[i] = (uint32_t)i < cnt
+                 ? (KEY_TOP | (uint64_t)((uint32_t)(a[i] >> 32) - sub) << 31 | (uint32_t)a[i])
+                 : KEY_NONE64;
+  } else {
+#pragma unroll
+    for (int i = 0; i < SL; i++) {
+      a[i] = KEY_NONE64;
+      if ((uint32_t)i < cnt) a[i] = KEY_TOP | (uint64_t)(D.DD[at + i] - tb) << 31 | D.IX[at + i];
+    }
+  }
+  if (lp == 0) lane_merge<1, SL>(a);
+  if (lp <= 1) lane_merge<2, SL>(a);
+  if (lp <= 2) lane_merge<4, SL>(a);
+  if (lp <= 3) lane_merge<8, SL>(a);
+  if (lp <= 4) lane_merge<16, SL>(a);
+  if (lp <= 5) lane_merge<32, SL>(a);
+#pragma unroll
+  for (int i = 0; i < SLOTS_MAX; i++) slot[i] = i < SL ? a[i < SL ? i : 0] : KEY_NONE64;
+}
+
+// Offset from the base time held by a slot.
+template <bool SORT>
+DEVI int64_t slot_off(uint64_t slot) {
+  return (int64_t)((slot >> 31) & (SORT ? 0x3FFFFFFFu : 0x1FFFFFu));
+}
+
+// Positions and Lindley terms of m ordered requests, per requests a lane.
+DEVI void sorted_terms(Merged<SLOTS_MAX> &M, uint32_t m, uint32_t per, int64_t tb, int64_t rank, int64_t xfer) {
+  M.boff = lane_id() * per;
+  M.cnt = m > M.boff ? min(m - M.boff, per) : 0u;
+  M.loc = NEG;
+  const int64_t cst = tb - rank * xfer;
+#pragma unroll
+  for (int i = 0; i < SLOTS_MAX; i++)
+    if ((uint32_t)i < M.cnt)
+      M.loc = imax(M.loc, cst + slot_off<true>(M.slot[i]) - (int64_t)mul32(M.boff + i, (uint32_t)xfer));
+}
+
+// The next requests of a cell that one step cannot hold: those within
+// 2^sub_lg (at most 2^30) of the earliest one left, at most the 64 * 16 that
+// a grid cell of minimum width can hold.  cur/hi: lane d's run; returns the
+// step's requests of the lane's run and its base time, or false at the end.
+DEVI bool big_step(const DieOrder &D, uint32_t cur, uint32_t hi, uint32_t lp, uint32_t sub_lg, int64_t cstart,
+                   int64_t &tb, uint32_t &cnt, uint32_t *errb) {
+  const uint32_t rem = hi - cur;
+  if (__ballot(rem != 0) == 0) return false;
+  // the wave's smallest time, by a maximum of 2^62 - time (0 where none)
+  tb = TIME_LIMIT - wave_max(rem ? TIME_LIMIT - D.time(cur, cstart) : 0);
+  const int64_t te = tb + (int64_t(1) << sub_lg);
+  uint32_t a = 0, b = min(rem, 64u);
+  while (a < b) {
+    const uint32_t mid = (a + b) >> 1;
+    if (D.time(cur + mid, cstart) < te) a = mid + 1;
+    else b = mid;
+  }
+  cnt = a;
+  if (cnt > (16u << lp)) {  // impossible: a die emits at most one request per tR
+    *errb |= ERR_INTERNAL;
+    cnt = 16u << lp;
+  }
+  return true;
+}
+
+// Order a cell by the lane merge.
+DEVI void cell_sort(const DieOrder &D, const CellRuns &cr, const Geo &g, uint32_t lp, uint32_t shift,
+                    uint32_t sub_lg, int64_t cstart, Merged<SLOTS_MAX> &M, uint32_t *errb) {
+  const uint32_t len = cr.hi - cr.lo;
+  M.m = wave_sum(len);
+  M.cnt = 0;
+  M.boff = 0;
+  M.head = CMIN_NONE;
+  M.rank0 = 0;
+  M.loc = NEG;
+  M.big = false;
+  if (M.m == 0) return;
+  M.rank0 = wave_sum(cr.r0);
+  const uint32_t longest = wave_umax(len);
+  M.head = ~wave_umax(len ? ~D.index(cr.lo) : 0u);  // a run's first entry has its smallest index
+  M.big = longest > (16u << lp) || shift > SUB_LG_MAX;
+  uint32_t cur = cr.lo, take = len, m = M.m;
+  int64_t tb = cstart, rank = M.rank0, term = NEG;
+  // one step, or as many as a big cell takes (only their terms are kept)
+  while (!M.big || big_step(D, cur, cr.hi, lp, sub_lg, cstart, tb, take, errb)) {
+    const uint32_t most = M.big ? wave_umax(take) : longest;
+    if (M.big) m = wave_sum(take);
+    uint32_t per;
+    if (most <= (2u << lp)) {
+      per = 2;
+      sort_take<2>(D, cur, take, lp, cstart, tb, M.slot);
+    } else if (most <= (4u << lp)) {
+      per = 4;
+      sort_take<4>(D, cur, take, lp, cstart, tb, M.slot);
+    } else if (most <= (8u << lp)) {
+      per = 8;
+      sort_take<8>(D, cur, take, lp, cstart, tb, M.slot);
+    } else {
+      per = 16;
+      sort_take<16>(D, cur, take, lp, cstart, tb, M.slot);
+    }
+    sorted_terms(M, m, per, tb, rank, g.xfer);
+    if (!M.big) return;
+    term = imax(term, wave_max(M.loc));
+    cur += take;
+    rank += m;
+  }
+  M.loc = term;
+  M.cnt = 0;
+}
+
+// Completions of an ordered cell given its entering term gin and the base
+// time of its slots (bucket merge: of bucket 0): staged in the band when they
+// fit, else stored directly.  mytop: staged span used.
+template <bool SORT, int SL>
+DEVI void cell_emit(const Merged<SL> &M, const Geo &g, int64_t tb, int64_t gin, uint32_t lo, int64_t wbase,
                     uint32_t *stage, int64_t *__restrict__ complete, uint32_t n, uint32_t *errb,
                     uint32_t &mytop) {
   if (M.m == 0) return;
   const uint32_t lane = lane_id();
   const int64_t xfer = g.xfer;
-  const int64_t cst = cstart + ((int64_t)lane << g.lg_tR) - M.rank0 * xfer;
+  const int64_t cst = tb + (SORT ? 0 : ((int64_t)lane << g.lg_tR)) - M.rank0 * xfer;
   int64_t carry = __shfl_up(wave_incl_max(M.loc), 1);
   if (lane == 0) carry = NEG;
   carry = imax(carry, gin);
@@ -1396,7 +1261,7 @@ DEVI void cell_emit(const Merged<SL> &M, const Geo &g, int64_t cstart, int64_t g
 #pragma unroll
   for (int i = 0; i < SL; i++) {
     if ((uint32_t)i < M.cnt) {
-      const int64_t v = cst + (int64_t)((M.slot[i] >> 31) & 0x1FFFFFu) - (int64_t)mul32(M.boff + i, (uint32_t)xfer);
+      const int64_t v = cst + slot_off<SORT>(M.slot[i]) - (int64_t)mul32(M.boff + i, (uint32_t)xfer);
       carry = imax(carry, v);
       const int64_t cpl = r0x + (int64_t)mul32(M.boff + i + 1, (uint32_t)xfer) + carry;
       if (cpl >= TIME_LIMIT) *errb |= ERR_OVERFLOW;
@@ -1415,26 +1280,56 @@ DEVI void cell_emit(const Merged<SL> &M, const Geo &g, int64_t cstart, int64_t g
   }
 }
 
+// Completions of a cell of the lane merge; a big cell takes its steps again,
+// now with the entering term.
+DEVI void sort_emit(const DieOrder &D, const CellRuns &cr, Merged<SLOTS_MAX> &M, const Geo &g, uint32_t lp,
+                    uint32_t sub_lg, int64_t cstart, int64_t gin, uint32_t lo, int64_t wbase, uint32_t *stage,
+                    int64_t *__restrict__ complete, uint32_t n, uint32_t *errb, uint32_t &mytop) {
+  uint32_t cur = cr.lo, take = 0;
+  int64_t tb = cstart;
+  while (!M.big || big_step(D, cur, cr.hi, lp, sub_lg, cstart, tb, take, errb)) {
+    if (M.big) {
+      M.m = wave_sum(take);
+      sort_take<16>(D, cur, take, lp, cstart, tb, M.slot);
+      sorted_terms(M, M.m, 16, tb, M.rank0, g.xfer);
+    }
+    cell_emit<true, SLOTS_MAX>(M, g, tb, gin, lo, wbase, stage, complete, n, errb, mytop);
+    if (!M.big) return;
+    gin = imax(gin, wave_max(M.loc));
+    cur += take;
+    M.rank0 += M.m;
+  }
+}
+
 // Requests of channel c in the call (lanes < Dk read one die queue each).
 DEVI uint32_t chan_total(const uint32_t *__restrict__ totals, uint32_t Dk, uint32_t c) {
   const uint32_t lane = lane_id();
   return wave_sum(lane < Dk ? totals[c * Dk + lane] : 0u);
 }
 
-template <int SL>
-__global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
-    const int64_t *__restrict__ DD, const uint32_t *__restrict__ LB, const uint32_t *__restrict__ seg_start,
-    const uint32_t *__restrict__ totals, Geo g, CallCtl *ctl, const DevState *st, uint64_t *WAGG, uint64_t *WINC,
-    int64_t *__restrict__ complete, int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  WinLds &S = *(WinLds *)smem;
-  if (agent_load32(&ctl->err)) return;
+// Units of the channel stage, cells ordered by the bucket merge or (SORT)
+// the lane merge.
+template <bool SORT, int SL>
+DEVI void chan_units(WinLds &S, const DieOrder &D, const uint32_t *__restrict__ LB,
+                     const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ totals, const Geo &g,
+                     CallCtl *ctl, const DevState *st, uint64_t *WAGG, uint64_t *WINC,
+                     int64_t *__restrict__ complete, int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n,
+                     uint32_t sub_lg) {
   const uint32_t G = ctl->G, shift = ctl->shift, C = g.C;
-  if (G == 0 || !grid_bucketable<SL>(g, shift)) return;
   const int64_t cbase = ctl->cbase, xfer = g.xfer;
-  const uint32_t t = threadIdx.x, w = t >> 6, lane = t & 63;
-  const uint32_t NG = (C + CH_GROUP - 1) / CH_GROUP;
-  const uint32_t U = G * NG;
+  const uint32_t t = threadIdx.x, lane = t & 63;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: the cells' bounds stay scalar
+  // cells of a unit: fewer where the call has too few to give every
+  // workgroup a full unit (1 M requests on 16 channels, 128 windows: 74 us a
+  // call with 16 or 8 cells a unit, 80 with 32)
+  uint32_t cells = SORT ? WIN_WAVES : 2 * WIN_WAVES;
+  while (cells > WIN_WAVES / 2 && (uint64_t)G * C <= (uint64_t)gridDim.x * (cells / 2)) cells >>= 1;
+  const uint32_t Cg = min(C, cells);                    // channels of a unit
+  const uint32_t NG = (C + cells - 1) / cells;
+  const uint32_t NW = cells / Cg;                       // windows of a unit (1 if there are several groups)
+  const uint32_t U = (G + NW - 1) / NW * NG;
+  uint32_t lp = 6;  // lane merge: log2 of the lanes of a run
+  while (lp > 0 && (64u >> lp) < g.Dk) lp--;
   for (uint32_t q = t; q < WIN_SLOTS; q += WIN_THREADS) S.stage[q] = WIN_EMPTY;
   uint32_t errb = 0;
   while (true) {
@@ -1442,48 +1337,64 @@ __global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
     __syncthreads();
     const uint32_t u = S.unit;
     if (u >= U) break;  // the same for the whole workgroup
-    const uint32_t j = u / NG, c0 = (u - j * NG) * CH_GROUP;
-    const int64_t cstart = cbase + ((int64_t)j << shift);
-    const uint32_t ca = c0 + w, cb = c0 + w + WIN_WAVES;
+    const uint32_t jw = u / NG, c0 = (u - jw * NG) * cells;
+    // the wave's cells (channel C: none)
+    uint32_t ca = C, cb = C, ja = 0, jb = 0;
+    {
+      const uint32_t qa = w / Cg, qb = (w + WIN_WAVES) / Cg;
+      ja = jw * NW + qa;
+      jb = jw * NW + qb;
+      if (w < cells && qa < NW && ja < G) ca = min(C, c0 + w - qa * Cg);
+      if (!SORT && w + WIN_WAVES < cells && qb < NW && jb < G) cb = min(C, c0 + w + WIN_WAVES - qb * Cg);
+    }
+    const int64_t sa = cbase + ((int64_t)ja << shift), sb = cbase + ((int64_t)jb << shift);
     Merged<SL> A, B;
     A.m = B.m = 0;
-    if (ca < C) {
-      const CellRuns cr = cell_runs(LB, seg_start, totals, g.Dk, gmax, ca, j);
-      uint64_t xv[SL];
-      load_runs<SL>(DD, cr, (int)g.Dk, xv);
-      cell_merge<SL>(S.tbl[w], cr, xv, g, cstart, A, &errb);
-    }
-    if (cb < C) {
-      const CellRuns cr = cell_runs(LB, seg_start, totals, g.Dk, gmax, cb, j);
-      uint64_t xv[SL];
-      load_runs<SL>(DD, cr, (int)g.Dk, xv);
-      cell_merge<SL>(S.tbl[w], cr, xv, g, cstart, B, &errb);
+    CellRuns ra = {0, 0, 0};
+    if constexpr (SORT) {
+      if (ca < C) {
+        ra = cell_runs(LB, seg_start, totals, g.Dk, gmax, ca, ja);
+        cell_sort(D, ra, g, lp, shift, sub_lg, sa, A, &errb);
+      }
+    } else {
+      if (ca < C) {
+        const CellRuns cr = cell_runs(LB, seg_start, totals, g.Dk, gmax, ca, ja);
+        uint64_t xv[SL];
+        load_runs<SL>(D.DD, cr, (int)g.Dk, xv);
+        cell_merge<SL>(S.tbl[w], cr, xv, g, sa, A, &errb);
+      }
+      if (cb < C) {
+        const CellRuns cr = cell_runs(LB, seg_start, totals, g.Dk, gmax, cb, jb);
+        uint64_t xv[SL];
+        load_runs<SL>(D.DD, cr, (int)g.Dk, xv);
+        cell_merge<SL>(S.tbl[w], cr, xv, g, sb, B, &errb);
+      }
     }
     const int64_t ma = A.m ? wave_max(A.loc) : NEG, mb = B.m ? wave_max(B.loc) : NEG;
     if (lane == 0) {
-      if (ca < C) agent_store64(&WAGG[(size_t)ca * gmax + j], enc_time(ma));
-      if (cb < C) agent_store64(&WAGG[(size_t)cb * gmax + j], enc_time(mb));
+      if (ca < C) agent_store64(&WAGG[(size_t)ca * gmax + ja], enc_time(ma));
+      if (cb < C) agent_store64(&WAGG[(size_t)cb * gmax + jb], enc_time(mb));
     }
     int64_t ga = NEG, gb = NEG;
-    look_back2(WAGG, WINC, C, gmax, j, ca, cb, ca < C ? st->chan_free[ca] : NEG, cb < C ? st->chan_free[cb] : NEG,
-               ga, gb, &errb);
+    look_back2(WAGG, WINC, C, gmax, ja, jb, ca, cb, ca < C ? st->chan_free[ca] : NEG,
+               cb < C ? st->chan_free[cb] : NEG, ga, gb, &errb);
     const int64_t ia = imax(ga, ma), ib = imax(gb, mb);
     if (lane == 0) {
-      if (ca < C) agent_store64(&WINC[(size_t)ca * gmax + j], enc_time(ia));
-      if (cb < C) agent_store64(&WINC[(size_t)cb * gmax + j], enc_time(ib));
+      if (ca < C) agent_store64(&WINC[(size_t)ca * gmax + ja], enc_time(ia));
+      if (cb < C) agent_store64(&WINC[(size_t)cb * gmax + jb], enc_time(ib));
     }
-    if (j == G - 1) {  // the channels' clocks after the call
-      const uint32_t ta = ca < C ? chan_total(totals, g.Dk, ca) : 0u;
-      const uint32_t tb = cb < C ? chan_total(totals, g.Dk, cb) : 0u;
+    if (ca < C && ja == G - 1) {  // the channel's clock after the call
+      const uint32_t ta = chan_total(totals, g.Dk, ca);
       if (lane == 0) {
-        if (ca < C) {
-          cfnew[ca] = (int64_t)ta * xfer + ia;
-          if (ta) atomicMax((long long *)&ctl->max_cpl, (long long)((int64_t)ta * xfer + ia));
-        }
-        if (cb < C) {
-          cfnew[cb] = (int64_t)tb * xfer + ib;
-          if (tb) atomicMax((long long *)&ctl->max_cpl, (long long)((int64_t)tb * xfer + ib));
-        }
+        cfnew[ca] = (int64_t)ta * xfer + ia;
+        if (ta) atomicMax((long long *)&ctl->max_cpl, (long long)((int64_t)ta * xfer + ia));
+      }
+    }
+    if (cb < C && jb == G - 1) {
+      const uint32_t tb = chan_total(totals, g.Dk, cb);
+      if (lane == 0) {
+        cfnew[cb] = (int64_t)tb * xfer + ib;
+        if (tb) atomicMax((long long *)&ctl->max_cpl, (long long)((int64_t)tb * xfer + ib));
       }
     }
     // band start (smallest index of the unit's requests) and completion base
@@ -1507,8 +1418,12 @@ __global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
     }
     if (lo != CMIN_NONE) {  // the same for the whole workgroup
       uint32_t top = 0;
-      cell_emit<SL>(A, g, cstart, ga, lo, wbase, S.stage, complete, n, &errb, top);
-      cell_emit<SL>(B, g, cstart, gb, lo, wbase, S.stage, complete, n, &errb, top);
+      if constexpr (SORT) {
+        sort_emit(D, ra, A, g, lp, sub_lg, sa, ga, lo, wbase, S.stage, complete, n, &errb, top);
+      } else {
+        cell_emit<false, SL>(A, g, sa, ga, lo, wbase, S.stage, complete, n, &errb, top);
+        cell_emit<false, SL>(B, g, sb, gb, lo, wbase, S.stage, complete, n, &errb, top);
+      }
       top = wave_umax(top);
       if (lane == 0 && top) atomicMax(&S.top, top);
       __syncthreads();
@@ -1527,32 +1442,26 @@ __global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
   if (errb) atomicOr(&ctl->err, errb);
 }
 
-// Grids off the bucket path: every cell k_cell_agg listed, one wave each,
-// streamed through the LDS with its entering term from k_cell_scan,
-// completions stored directly.
 template <int SL>
-__global__ __launch_bounds__(64) void k_cell_rest(
+__global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
+    const int64_t *__restrict__ DD, const uint32_t *__restrict__ LB, const uint32_t *__restrict__ seg_start,
+    const uint32_t *__restrict__ totals, Geo g, CallCtl *ctl, const DevState *st, uint64_t *WAGG, uint64_t *WINC,
+    int64_t *__restrict__ complete, int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (agent_load32(&ctl->err) || ctl->G == 0 || !grid_bucketable<SL>(g, ctl->shift)) return;
+  chan_units<false, SL>(*(WinLds *)smem, DieOrder{DD, nullptr, true}, LB, seg_start, totals, g, ctl, st, WAGG, WINC,
+                        complete, cfnew, gmax, n, 0);
+}
+
+__global__ __launch_bounds__(WIN_THREADS) void k_cell_sort(
     const int64_t *__restrict__ DD, const uint32_t *__restrict__ IX, const uint32_t *__restrict__ LB,
     const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ totals, Geo g, CallCtl *ctl,
-    const int64_t *__restrict__ GIN, const uint32_t *__restrict__ NBL, int64_t *__restrict__ complete,
-    uint32_t gmax, uint32_t n) {
+    const DevState *st, uint64_t *WAGG, uint64_t *WINC, int64_t *__restrict__ complete,
+    int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n, uint32_t sub_lg) {
   extern __shared__ __align__(16) unsigned char smem[];
-  CellLds &S = *(CellLds *)smem;
-  if (agent_load32(&ctl->err)) return;
-  const uint32_t nr = agent_load32(&ctl->n_rest);
-  const uint32_t shift = ctl->shift;
-  const int64_t cbase = ctl->cbase;
-  uint32_t errb = 0;
-  for (uint32_t i = blockIdx.x; i < nr; i += gridDim.x) {
-    const uint32_t id = NBL[i];
-    const uint32_t j = id / g.C, c = id - j * g.C;
-    const CellRuns cr = cell_runs(LB, seg_start, totals, g.Dk, gmax, c, j);
-    uint64_t xv[SL];
-    load_runs<SL>(DD, cr, (int)g.Dk, xv);
-    cell_pass<SL, true>(S, DD, IX, cr, xv, g, shift, cbase, j, GIN[(size_t)c * gmax + j], complete, n, &errb);
-    wave_sync();
-  }
-  if (errb) atomicOr(&ctl->err, errb);
+  if (agent_load32(&ctl->err) || ctl->G == 0 || grid_bucketable<SLOTS_MAX>(g, ctl->shift)) return;
+  chan_units<true, SLOTS_MAX>(*(WinLds *)smem, DieOrder{DD, IX, ctl->shift <= 32}, LB, seg_start, totals, g, ctl, st,
+                              WAGG, WINC, complete, cfnew, gmax, n, sub_lg);
 }
 
 // ------------------------------------------------------------------ k_finalize
@@ -1671,10 +1580,9 @@ __global__ __launch_bounds__(BLK) void k_fill(int64_t *__restrict__ p, int64_t n
 // ------------------------------------------------------------------ launchers
 
 const char *const kKernelNames[] = {"k_prologue",  "k_die_reduce", "k_tile_scan", "k_key_scan",
-                                    "k_die_scatter", "k_cell_chan", "k_cell_agg",  "k_cell_scan",
-                                    "k_cell_rest", "k_finalize",  "k_small"};
-const int kNumTimedKernels = 11;
-constexpr int SMALL_SLOT = 10;  // k_small's timing slot
+                                    "k_die_scatter", "k_cell_chan", "k_finalize", "k_small"};
+const int kNumTimedKernels = 8;
+constexpr int SMALL_SLOT = 7;  // k_small's timing slot
 
 static size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
@@ -1717,8 +1625,6 @@ hipError_t launch_time_requests(const Geo &g, const RangeTable &rt, const Layout
   uint32_t *IX = (uint32_t *)(ws + Lo.off_ix);
   uint32_t *KR = (uint32_t *)(ws + Lo.off_kr);
   uint32_t *LB = (uint32_t *)(ws + Lo.off_lb);
-  int64_t *AGG = (int64_t *)(ws + Lo.off_cagg);
-  int64_t *GIN = (int64_t *)(ws + Lo.off_cgin);
   uint64_t *WST = (uint64_t *)(ws + Lo.off_wst);
   const bool p2 = g.pow2 != 0;
   int evi = 0;
@@ -1781,78 +1687,23 @@ hipError_t launch_time_requests(const Geo &g, const RangeTable &rt, const Layout
     if ((e = launch_regblock(g, (const uint64_t *)DD, IX, (const int64_t *)(ws + Lo.off_iss), seg, totals, st, ctl,
                              complete, dfnew, cfnew, refresh, s)) != hipSuccess)
       return e;
-    mark();
-    mark();
-    mark();
   } else {
-    // channel stage.  On the bucket path (every grid but those with very
-    // wide cells or more than 16 die queues per channel) k_cell_chan does
-    // all of it; otherwise k_cell_agg -> k_cell_scan -> k_cell_rest.  Each
-    // kernel reads the grid the die stage chose and returns at once when
-    // the stage is the other one's.
-    int dev = 0, ncu = 256, per_cu = 0;
+    // channel stage: one 1,024-thread workgroup per CU (its LDS holds a
+    // unit's band)
+    int dev = 0, ncu = 256;
     hipGetDevice(&dev);
     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    const int sl = g.Dk <= 4 ? 4 : g.Dk <= 8 ? 8 : 16;
-    const uint32_t nn = (uint32_t)Lo.n;
     uint64_t *WAGG = WST, *WINC = WST + (size_t)Lo.gmax * g.C;
-    {  // one 1,024-thread workgroup per CU (its LDS holds a unit's band)
-      const dim3 gw((uint32_t)ncu), bw(WIN_THREADS);
-      const size_t lw = sizeof(WinLds);
-      if (sl == 4)
-        hipLaunchKernelGGL(k_cell_chan<4>, gw, bw, lw, s, DD, LB, seg, totals, g, ctl, st, WAGG, WINC, complete,
-                           cfnew, Lo.gmax, nn);
-      else if (sl == 8)
-        hipLaunchKernelGGL(k_cell_chan<8>, gw, bw, lw, s, DD, LB, seg, totals, g, ctl, st, WAGG, WINC, complete,
-                           cfnew, Lo.gmax, nn);
-      else
-        hipLaunchKernelGGL(k_cell_chan<16>, gw, bw, lw, s, DD, LB, seg, totals, g, ctl, st, WAGG, WINC, complete,
-                           cfnew, Lo.gmax, nn);
+    // (each returns at once when the grid is the other one's)
+    if (g.Dk <= SLOTS_MAX) {
+      hipLaunchKernelGGL(g.Dk <= 4 ? k_cell_chan<4> : g.Dk <= 8 ? k_cell_chan<8> : k_cell_chan<16>,
+                         dim3((uint32_t)ncu), dim3(WIN_THREADS), sizeof(WinLds), s, DD, LB, seg, totals, g, ctl, st,
+                         WAGG, WINC, complete, cfnew, Lo.gmax, (uint32_t)Lo.n);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    mark();
-    // off the bucket path: enough one-wave blocks to fill the chip, a
-    // multiple of the XCD count, and no more than there can be cells
-    const void *kfn = sl == 4 ? (const void *)k_cell_agg<4>
-                      : sl == 8 ? (const void *)k_cell_agg<8> : (const void *)k_cell_agg<16>;
-    hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, 64, sizeof(CellLds));
-    per_cu = per_cu < 1 ? 1 : (per_cu > 32 ? 32 : per_cu);
-    const uint64_t cells = (uint64_t)g.C * Lo.gmax;
-    auto grid_of = [&](int waves_per_cu) {
-      uint64_t blocks = (uint64_t)ncu * (uint64_t)waves_per_cu;
-      const uint64_t need = ((cells + NXCD - 1) / NXCD) * NXCD;
-      if (blocks > need) blocks = need;
-      blocks = (blocks / NXCD) * NXCD;
-      if (blocks < NXCD) blocks = NXCD;
-      return dim3((uint32_t)blocks);
-    };
-    const dim3 gr = grid_of(per_cu);
-    const dim3 bl(64);
-    const size_t lds = sizeof(CellLds);
-    uint32_t *NBL = (uint32_t *)(ws + Lo.off_nbl);
-    if (sl == 4)
-      hipLaunchKernelGGL(k_cell_agg<4>, gr, bl, lds, s, DD, IX, LB, seg, totals, g, ctl, AGG, NBL, Lo.gmax, nn);
-    else if (sl == 8)
-      hipLaunchKernelGGL(k_cell_agg<8>, gr, bl, lds, s, DD, IX, LB, seg, totals, g, ctl, AGG, NBL, Lo.gmax, nn);
-    else
-      hipLaunchKernelGGL(k_cell_agg<16>, gr, bl, lds, s, DD, IX, LB, seg, totals, g, ctl, AGG, NBL, Lo.gmax, nn);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    mark();
-    hipLaunchKernelGGL(k_cell_scan, dim3(g.C), dim3(BLK), 0, s, AGG, GIN, totals, g, ctl, st, cfnew, Lo.gmax);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    mark();
-    {
-      const dim3 gx = grid_of(4);
-      if (sl == 4)
-        hipLaunchKernelGGL(k_cell_rest<4>, gx, bl, lds, s, DD, IX, LB, seg, totals, g, ctl, GIN, NBL, complete,
-                           Lo.gmax, nn);
-      else if (sl == 8)
-        hipLaunchKernelGGL(k_cell_rest<8>, gx, bl, lds, s, DD, IX, LB, seg, totals, g, ctl, GIN, NBL, complete,
-                           Lo.gmax, nn);
-      else
-        hipLaunchKernelGGL(k_cell_rest<16>, gx, bl, lds, s, DD, IX, LB, seg, totals, g, ctl, GIN, NBL, complete,
-                           Lo.gmax, nn);
-    }
+    hipLaunchKernelGGL(k_cell_sort, dim3((uint32_t)ncu), dim3(WIN_THREADS), sizeof(WinLds), s, DD, IX, LB, seg,
+                       totals, g, ctl, st, WAGG, WINC, complete, cfnew, Lo.gmax, (uint32_t)Lo.n,
+                       Lo.s0 < SUB_LG_MAX ? Lo.s0 : SUB_LG_MAX);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark();
@@ -1960,7 +1811,8 @@ hipError_t set_lds_limits(uint32_t K) {
   for (const void *f : fc)
     if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c)) != hipSuccess) return e;
   if ((e = set_lds_small()) != hipSuccess) return e;
-  const void *fw[] = {(const void *)k_cell_chan<4>, (const void *)k_cell_chan<8>, (const void *)k_cell_chan<16>};
+  const void *fw[] = {(const void *)k_cell_chan<4>, (const void *)k_cell_chan<8>, (const void *)k_cell_chan<16>,
+                      (const void *)k_cell_sort};
   for (const void *f : fw)
     if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(WinLds))) != hipSuccess)
       return e;

@@ -420,7 +420,6 @@ __global__ void k_vm_prologue(CallCtl *ctl) {
     ctl->max_dd = NEG;
     ctl->max_cpl = NEG;
     ctl->cbase = 0;
-    ctl->n_rest = 0;
   }
 }
 
