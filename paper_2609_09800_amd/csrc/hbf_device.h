@@ -184,6 +184,106 @@ DEVI uint32_t wave_excl_sum(uint32_t v) { return wave_incl_sum(v) - v; }
 DEVI int64_t wave_max(int64_t x) { return lane63(wave_incl_max(x)); }
 DEVI uint32_t wave_umax(uint32_t x) { return lane63(wave_incl_umax(x)); }
 
+// ------------------------------------------------------------------ lane merge
+
+// Compare-exchange of two sort keys whose bit patterns are finite positive
+// doubles: IEEE order is integer order there, so one exact v_min_f64 /
+// v_max_f64 pair is the whole exchange.
+DEVI void cx_key(uint64_t &lo, uint64_t &hi) {
+  const double a = __builtin_bit_cast(double, lo), b = __builtin_bit_cast(double, hi);
+  double mn, mx;
+  asm("v_min_f64 %0, %1, %2" : "=v"(mn) : "v"(a), "v"(b));
+  asm("v_max_f64 %0, %1, %2" : "=v"(mx) : "v"(a), "v"(b));
+  lo = __builtin_bit_cast(uint64_t, mn);
+  hi = __builtin_bit_cast(uint64_t, mx);
+}
+
+// Order up to 64 * SL (SL <= 16) requests of one channel in registers.  A
+// run (one die queue's requests, ascending) of up to SL * P sits on P = 64 /
+// (die runs, rounded up to a power of two) neighbouring lanes, SL or fewer
+// consecutive requests each, so every group of P lanes is sorted from the
+// start and log2(64 / P) bitonic merges order the channel.  Keys: bit 62 set,
+// offset from a base time (< 2^30) << 31 | request index, below KEY_NONE64.
+constexpr uint64_t KEY_TOP = uint64_t(1) << 62;
+constexpr uint64_t KEY_NONE64 = uint64_t(3) << 61;
+constexpr int LANE_SLOTS = 16;  // requests per lane at most
+
+// log2 of the lanes of a run, for Dk <= 64 die runs
+DEVI uint32_t run_lanes_lg(uint32_t Dk) {
+  uint32_t lp = 6;
+  while (lp > 0 && (64u >> lp) < Dk) lp--;
+  return lp;
+}
+
+// x of lane (l ^ M): DPP within rows of 16, LDS swizzle across rows of a
+// half, the half swap for the rest.
+template <int M>
+DEVI uint32_t lane_xor(uint32_t x) {
+  if constexpr (M == 1) return dpp32<0xB1, 0xF>(x, x);        // quad_perm [1,0,3,2]
+  else if constexpr (M == 2) return dpp32<0x4E, 0xF>(x, x);   // quad_perm [2,3,0,1]
+  else if constexpr (M == 3) return dpp32<0x1B, 0xF>(x, x);   // quad_perm [3,2,1,0]
+  else if constexpr (M == 7) return dpp32<0x141, 0xF>(x, x);  // row_half_mirror
+  else if constexpr (M == 4) return lane_xor<7>(lane_xor<3>(x));
+  else if constexpr (M == 15) return dpp32<0x140, 0xF>(x, x); // row_mirror
+  else if constexpr (M == 8) return dpp32<0x128, 0xF>(x, x);  // row_ror:8
+  else if constexpr (M == 16 || M == 31)
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (M << 10) | 0x1F);
+  else {  // 32, 63
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const uint32_t y = lane_id() < 32 ? r[1] : r[0];  // the other half's value
+    if constexpr (M == 32) return y;
+    else return lane_xor<31>(y);
+  }
+}
+template <int M>
+DEVI uint64_t lane_xor(uint64_t x) {
+  return (uint64_t)lane_xor<M>((uint32_t)(x >> 32)) << 32 | lane_xor<M>((uint32_t)x);
+}
+
+// Bitonic exchange across lanes l and l ^ L: the lower one keeps the smaller.
+template <int L, int SL>
+DEVI void cross_step(uint64_t (&a)[SL]) {
+  const bool lower = (lane_id() & L) == 0;
+#pragma unroll
+  for (int i = 0; i < SL; i++) {
+    const uint64_t y = lane_xor<L>(a[i]);
+    a[i] = ((a[i] < y) == lower) ? a[i] : y;
+  }
+}
+// Merge neighbouring sorted groups of L lanes into groups of 2 * L.
+template <int L, int SL>
+DEVI void lane_merge(uint64_t (&a)[SL]) {
+  const bool lower = (lane_id() & L) == 0;
+#pragma unroll
+  for (int i = 0; i < SL / 2; i++) {  // against the other group reversed
+    const uint64_t y = lane_xor<2 * L - 1>(a[SL - 1 - i]), z = lane_xor<2 * L - 1>(a[i]);
+    a[i] = ((a[i] < y) == lower) ? a[i] : y;
+    a[SL - 1 - i] = ((a[SL - 1 - i] < z) == lower) ? a[SL - 1 - i] : z;
+  }
+  if constexpr (L >= 32) cross_step<16, SL>(a);
+  if constexpr (L >= 16) cross_step<8, SL>(a);
+  if constexpr (L >= 8) cross_step<4, SL>(a);
+  if constexpr (L >= 4) cross_step<2, SL>(a);
+  if constexpr (L >= 2) cross_step<1, SL>(a);
+#pragma unroll
+  for (int s = SL / 2; s >= 1; s >>= 1) {
+#pragma unroll
+    for (int i = 0; i < SL; i++)
+      if (!(i & s)) cx_key(a[i], a[i + s]);
+  }
+}
+
+// Merge the runs of 2^lp lanes each.
+template <int SL>
+DEVI void merge_runs(uint64_t (&a)[SL], uint32_t lp) {
+  if (lp == 0) lane_merge<1, SL>(a);
+  if (lp <= 1) lane_merge<2, SL>(a);
+  if (lp <= 2) lane_merge<4, SL>(a);
+  if (lp <= 3) lane_merge<8, SL>(a);
+  if (lp <= 4) lane_merge<16, SL>(a);
+  if (lp <= 5) lane_merge<32, SL>(a);
+}
+
 // ------------------------------------------------------------------ die-stage ranks
 
 // Stable rank of each item among this wave's items with the same key, in

@@ -689,22 +689,14 @@ __global__ __launch_bounds__(SBLK) void k_die_scatter(
 
 // ------------------------------------------------------------------ channel stage
 
-constexpr int SLOTS_MAX = 16;  // die runs per channel on the bucket path; sorted requests per lane elsewhere
+constexpr int SLOTS_MAX = 16;  // die runs per channel on the bucket path; requests per lane elsewhere
+static_assert(SLOTS_MAX == LANE_SLOTS, "both orders keep their slots in Merged");
 
 // Sort keys of the bucket path are integers below 2^51 held in the mantissa
 // of a double in [1, 2) (exponent bits 0x3FF): there IEEE order is integer
 // order, so one exact v_min_f64 / v_max_f64 pair is a whole compare-exchange.
 constexpr uint64_t KEY_ONE = uint64_t(0x3FF) << 52;
 constexpr uint64_t KEY_EMPTY = KEY_ONE | ((uint64_t(1) << 52) - 1);  // above every key
-
-DEVI void cx_key(uint64_t &lo, uint64_t &hi) {
-  const double a = __builtin_bit_cast(double, lo), b = __builtin_bit_cast(double, hi);
-  double mn, mx;
-  asm("v_min_f64 %0, %1, %2" : "=v"(mn) : "v"(a), "v"(b));
-  asm("v_max_f64 %0, %1, %2" : "=v"(mx) : "v"(a), "v"(b));
-  lo = __builtin_bit_cast(uint64_t, mn);
-  hi = __builtin_bit_cast(uint64_t, mx);
-}
 
 // Batcher's odd-even merge sort over SL registers (SL a power of two; 63
 // compare-exchanges for 16), ascending.
@@ -1028,79 +1020,14 @@ DEVI void cell_merge(uint8_t (*tbl)[SLOTS_MAX], const CellRuns &cr, const uint64
   wave_sync();  // tbl is reused by the wave's next cell
 }
 
-// ---- Lane merge.  A run of up to 16 * P requests sits on P = 64 / (die runs,
-// rounded up to a power of two) neighbouring lanes, 16 or fewer consecutive
-// requests each, so every group of P lanes is sorted from the start and
-// log2(64 / P) bitonic merges order the cell.  Keys: bit 62 set, offset from
-// a base time (< 2^30) << 31 | request index, below KEY_NONE; as doubles all
-// of them are finite and positive, so IEEE order is integer order here too.
+// ---- Cells of the lane merge.
 // A cell is merged with the fewest slots per lane (2, 4, 8 or 16) that hold
 // its longest run, and needs no search and no second pass: reducing every
 // such cell, scanning and ordering it again by binary searches in LDS took
 // 1,060 us of a 4 M-request call at 85 % channel load (32 channels x 16
 // dies; the whole call 1,156 us, now 176) and 2,770 us of a 3 M-request call
 // with 64 die queues per channel (2,890, now 245).
-constexpr uint64_t KEY_TOP = uint64_t(1) << 62;
-constexpr uint64_t KEY_NONE64 = uint64_t(3) << 61;
 constexpr uint32_t SUB_LG_MAX = 30;  // offsets of a lane-merge key
-
-// x of lane (l ^ M): DPP within rows of 16, LDS swizzle across rows of a
-// half, the half swap for the rest.
-template <int M>
-DEVI uint32_t lane_xor(uint32_t x) {
-  if constexpr (M == 1) return dpp32<0xB1, 0xF>(x, x);        // quad_perm [1,0,3,2]
-  else if constexpr (M == 2) return dpp32<0x4E, 0xF>(x, x);   // quad_perm [2,3,0,1]
-  else if constexpr (M == 3) return dpp32<0x1B, 0xF>(x, x);   // quad_perm [3,2,1,0]
-  else if constexpr (M == 7) return dpp32<0x141, 0xF>(x, x);  // row_half_mirror
-  else if constexpr (M == 4) return lane_xor<7>(lane_xor<3>(x));
-  else if constexpr (M == 15) return dpp32<0x140, 0xF>(x, x); // row_mirror
-  else if constexpr (M == 8) return dpp32<0x128, 0xF>(x, x);  // row_ror:8
-  else if constexpr (M == 16 || M == 31)
-    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (M << 10) | 0x1F);
-  else {  // 32, 63
-    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    const uint32_t y = lane_id() < 32 ? r[1] : r[0];  // the other half's value
-    if constexpr (M == 32) return y;
-    else return lane_xor<31>(y);
-  }
-}
-template <int M>
-DEVI uint64_t lane_xor(uint64_t x) {
-  return (uint64_t)lane_xor<M>((uint32_t)(x >> 32)) << 32 | lane_xor<M>((uint32_t)x);
-}
-
-// Bitonic exchange across lanes l and l ^ L: the lower one keeps the smaller.
-template <int L, int SL>
-DEVI void cross_step(uint64_t (&a)[SL]) {
-  const bool lower = (lane_id() & L) == 0;
-#pragma unroll
-  for (int i = 0; i < SL; i++) {
-    const uint64_t y = lane_xor<L>(a[i]);
-    a[i] = ((a[i] < y) == lower) ? a[i] : y;
-  }
-}
-// Merge neighbouring sorted groups of L lanes into groups of 2 * L.
-template <int L, int SL>
-DEVI void lane_merge(uint64_t (&a)[SL]) {
-  const bool lower = (lane_id() & L) == 0;
-#pragma unroll
-  for (int i = 0; i < SL / 2; i++) {  // against the other group reversed
-    const uint64_t y = lane_xor<2 * L - 1>(a[SL - 1 - i]), z = lane_xor<2 * L - 1>(a[i]);
-    a[i] = ((a[i] < y) == lower) ? a[i] : y;
-    a[SL - 1 - i] = ((a[SL - 1 - i] < z) == lower) ? a[SL - 1 - i] : z;
-  }
-  if constexpr (L >= 32) cross_step<16, SL>(a);
-  if constexpr (L >= 16) cross_step<8, SL>(a);
-  if constexpr (L >= 8) cross_step<4, SL>(a);
-  if constexpr (L >= 4) cross_step<2, SL>(a);
-  if constexpr (L >= 2) cross_step<1, SL>(a);
-#pragma unroll
-  for (int s = SL / 2; s >= 1; s >>= 1) {
-#pragma unroll
-    for (int i = 0; i < SL; i++)
-      if (!(i & s)) cx_key(a[i], a[i + s]);
-  }
-}
 
 // The die-order entries of a call: packed words (cells at most 2^32 ns wide)
 // or die-done times and indices.
@@ -1144,12 +1071,7 @@ DEVI void sort_take(const DieOrder &D, uint32_t lo, uint32_t len, uint32_t lp, i
       if ((uint32_t)i < cnt) a[i] = KEY_TOP | (uint64_t)(D.DD[at + i] - tb) << 31 | D.IX[at + i];
     }
   }
-  if (lp == 0) lane_merge<1, SL>(a);
-  if (lp <= 1) lane_merge<2, SL>(a);
-  if (lp <= 2) lane_merge<4, SL>(a);
-  if (lp <= 3) lane_merge<8, SL>(a);
-  if (lp <= 4) lane_merge<16, SL>(a);
-  if (lp <= 5) lane_merge<32, SL>(a);
+  merge_runs<SL>(a, lp);
 #pragma unroll
   for (int i = 0; i < SLOTS_MAX; i++) slot[i] = i < SL ? a[i < SL ? i : 0] : KEY_NONE64;
 }
@@ -1328,8 +1250,7 @@ DEVI void chan_units(WinLds &S, const DieOrder &D, const uint32_t *__restrict__ 
   const uint32_t NG = (C + cells - 1) / cells;
   const uint32_t NW = cells / Cg;                       // windows of a unit (1 if there are several groups)
   const uint32_t U = (G + NW - 1) / NW * NG;
-  uint32_t lp = 6;  // lane merge: log2 of the lanes of a run
-  while (lp > 0 && (64u >> lp) < g.Dk) lp--;
+  const uint32_t lp = run_lanes_lg(g.Dk);
   for (uint32_t q = t; q < WIN_SLOTS; q += WIN_THREADS) S.stage[q] = WIN_EMPTY;
   uint32_t errb = 0;
   while (true) {

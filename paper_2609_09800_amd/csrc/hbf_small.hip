@@ -1,23 +1,30 @@
 // Small calls in one launch (HBFSim, arXiv 2609.09800, Section "Design": the
 // online media model, a die-read queue then a channel-transfer queue, each
-// FCFS).  A call of at most one chunk (4,096 requests) is otherwise bound
-// by its dozen launches, not by its work.  Here one workgroup does it all:
-//   1. classify and validate, and rank each request among the chunk's
+// FCFS).  A call of a few thousand requests is otherwise bound by its
+// launches, not by its work.  Here one 1,024-thread workgroup does it all:
+//   1. classify and validate, and rank each request among the call's
 //      requests of its die queue (stable: index order);
-//   2. stage the chunk in die order (queue-major) and take the Lindley form
+//   2. stage the call in die order (queue-major) and take the Lindley form
 //      of each die queue as one segmented prefix maximum:
 //      die_done_r = (r+1)*tR + max(L, max over i <= r of issue_i - i*tR);
-//   3. place each request in its channel's service order: its rank there is
-//      the number of the channel's requests, over all of its die runs
-//      (each sorted by die-done), that come before it by (die-done, index),
-//      found by a binary search per run;
-//   4. the channel's Lindley form, again as one segmented prefix maximum:
-//      complete_r = (r+1)*xfer + max(F, max over i <= r of die_done_i - i*xfer);
-//   5. new clocks, or, on any error, HBF_TIME_ERROR everywhere and the clocks
+//   3. one wave per channel (or several, each a stretch of the channel's
+//      time) orders the channel's die runs by (die-done, index) in registers (the lane merge of hbf_device.h), takes the
+//      channel's Lindley form over the merged positions,
+//      complete_r = (r+1)*xfer + max(F, max over i <= r of die_done_i - i*xfer),
+//      and stores the completions; runs too long or too far apart for one
+//      merge are taken in several steps;
+//   4. new clocks, or, on any error, HBF_TIME_ERROR everywhere and the clocks
 //      left as they were.
 // It serves the plain two-stage model (no refresh quanta pending, no
-// register blocking, not the vmem route) with at most SMALL_K die queues, at
-// most SMALL_DK per channel.
+// register blocking, not the vmem route) where its LDS fits.  The call is a
+// chain of latencies on one CU (loads, ranks, two block scans, a merge): the
+// kernel takes 13 us at 512 requests and 14 at 1,536 on 16 channels x 8
+// dies, 23 at 4,096.  Searching each request's rank in every other run of
+// its channel by LDS reads took 60, 69 and 100 us.  A call that crowds one
+// of its channels serializes on that channel's wave, so one or two channels
+// share the workgroup's waves between them (4,096 requests on 1 x 16: 39 us
+// against 67 on one wave); from four channels on the second merge this
+// takes costs more than it gives (4 x 4: 36 us against 26).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,41 +35,38 @@ namespace hbf {
 
 namespace {
 
-DEVI size_t up16(size_t x) { return (x + 15) & ~size_t(15); }
+constexpr int SM_THREADS = 1024;
+constexpr int SM_WAVES = SM_THREADS / 64;
+constexpr int SM_SLOTS = 8;  // requests per lane of a merge at most
 
-// LDS: ranges | wcnt[DWAVES][K] u16 | tot[K] u16 | seg[K+1] u32 | cf[C] i64 |
-//      sdd[CHUNK] i64 | cdd[CHUNK] i64 | sidx, skey, cidx, cch [CHUNK] u16
+// LDS: ranges | wcnt[SM_WAVES][K] u16 | seg[K+1] u32 | cf[C] i64 | sdd[cap] i64 | sidx, skey [cap] u16,
+// cap = requests the workgroup holds
 struct SmallLayout {
-  size_t wcnt, tot, seg, cf, sdd, cdd, sidx, skey, cidx, cch, total;
+  size_t wcnt, seg, cf, sdd, sidx, skey, total;
 };
-__host__ __device__ inline SmallLayout small_layout(uint32_t K, uint32_t C) {
+__host__ __device__ inline SmallLayout small_layout(uint32_t K, uint32_t C, uint32_t cap) {
   SmallLayout L;
   size_t o = (sizeof(LdsRanges) + 15) & ~size_t(15);
-  L.wcnt = o; o += (size_t)DWAVES * K * 2;
-  L.tot = o;  o += (size_t)K * 2;
+  L.wcnt = o; o += (size_t)SM_WAVES * K * 2;
   o = (o + 15) & ~size_t(15);
   L.seg = o;  o += (size_t)(K + 1) * 4;
   o = (o + 15) & ~size_t(15);
   L.cf = o;   o += (size_t)C * 8;
-  L.sdd = o;  o += (size_t)CHUNK * 8;
-  L.cdd = o;  o += (size_t)CHUNK * 8;
-  L.sidx = o; o += (size_t)CHUNK * 2;
-  L.skey = o; o += (size_t)CHUNK * 2;
-  L.cidx = o; o += (size_t)CHUNK * 2;
-  L.cch = o;  o += (size_t)CHUNK * 2;
+  L.sdd = o;  o += (size_t)cap * 8;
+  L.sidx = o; o += (size_t)cap * 2;
+  L.skey = o; o += (size_t)cap * 2;
   L.total = o;
   return L;
 }
-
 
 // Stable rank of each item among this wave's items with the same key (item,
 // then lane order), and the wave's per-key counts in wcnt.  The lanes that
 // share a key are found with one ballot per key bit (a small call's keys
 // are few, so many lanes of a wave share one).
-DEVI void wave_rank_bits(const uint32_t *key, uint32_t *rank, uint16_t *wcnt, uint32_t nbits) {
-  const uint32_t lane = lane_id();
+template <int ITEMS>
+DEVI void wave_rank_bits(const uint32_t (&key)[ITEMS], uint32_t (&rank)[ITEMS], uint16_t *wcnt, uint32_t nbits) {
 #pragma unroll
-  for (int e = 0; e < DITEMS; e++) {
+  for (int e = 0; e < ITEMS; e++) {
     const uint32_t k = key[e];
     const bool valid = k != KEY_NONE;
     uint64_t mask = __ballot(valid);
@@ -84,96 +88,174 @@ DEVI void wave_rank_bits(const uint32_t *key, uint32_t *rank, uint16_t *wcnt, ui
   }
 }
 
+// One merge of a wave: the `take` (at most SL << lp) requests of each run
+// (lane d: run d) from staged position cur, all within 2^30 ns of tb; m in
+// all, channel ranks from `rank`, entering term `gin`.  Returns the term
+// after them and, with `emit`, stores their completions.
+template <int SL>
+DEVI int64_t small_merge(const int64_t *sdd, const uint16_t *sidx, uint32_t cur, uint32_t take, uint32_t lp,
+                         int64_t tb, uint32_t m, int64_t rank, int64_t xfer, int64_t gin, bool emit,
+                         int64_t *__restrict__ complete, uint32_t *errb) {
+  const uint32_t lane = lane_id();
+  const uint32_t d = lane >> lp, skip = (lane & ((1u << lp) - 1)) * SL;
+  const uint32_t at = __shfl(cur, (int)d) + skip, have = __shfl(take, (int)d);
+  const uint32_t cnt = have > skip ? have - skip : 0u;
+  uint64_t a[SL];
+#pragma unroll
+  for (int i = 0; i < SL; i++) {
+    a[i] = KEY_NONE64;
+    if ((uint32_t)i < cnt) a[i] = KEY_TOP | (uint64_t)(sdd[at + i] - tb) << 31 | sidx[at + i];
+  }
+  merge_runs<SL>(a, lp);
+  const uint32_t p0 = lane * SL, mine = m > p0 ? min(m - p0, (uint32_t)SL) : 0u;
+  const int64_t cst = tb - rank * xfer;
+  auto value = [&](int i) {  // of merged position p0 + i
+    return cst + (int64_t)((a[i] >> 31) & 0x3FFFFFFFu) - (int64_t)mul32(p0 + i, (uint32_t)xfer);
+  };
+  int64_t loc = NEG;
+#pragma unroll
+  for (int i = 0; i < SL; i++)
+    if ((uint32_t)i < mine) loc = imax(loc, value(i));
+  const int64_t inc = wave_incl_max(loc);
+  if (!emit) return imax(gin, lane63(inc));
+  int64_t carry = __shfl_up(inc, 1);
+  if (lane == 0) carry = NEG;
+  carry = imax(carry, gin);
+  const int64_t r0x = rank * xfer;
+#pragma unroll
+  for (int i = 0; i < SL; i++) {
+    if ((uint32_t)i < mine) {
+      carry = imax(carry, value(i));
+      const int64_t cpl = r0x + (int64_t)mul32(p0 + i + 1, (uint32_t)xfer) + carry;
+      if (cpl >= TIME_LIMIT) *errb |= ERR_OVERFLOW;
+      complete[(uint32_t)a[i] & 0x7FFFFFFFu] = cpl;
+    }
+  }
+  return imax(gin, lane63(inc));
+}
+
 }  // namespace
 
-template <bool POW2>
-__global__ __launch_bounds__(DBLK) void k_small(const uint64_t *__restrict__ addr, const int64_t *__restrict__ issue,
-                                               int64_t n, int64_t *__restrict__ complete, Geo g, RangeTable rt,
-                                               DevState *st, CallCtl *ctl) {
+// ITEMS: requests per thread; the call has at most ITEMS * 1,024.
+template <bool POW2, int ITEMS>
+__global__ __launch_bounds__(SM_THREADS) void k_small(const uint64_t *__restrict__ addr,
+                                                      const int64_t *__restrict__ issue, uint32_t n,
+                                                      int64_t *__restrict__ complete, Geo g, RangeTable rt,
+                                                      DevState *st, CallCtl *ctl) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ uint32_t shsum[DWAVES];
-  __shared__ SegMax shseg[DWAVES];
-  __shared__ uint32_t s_err, s_maxrun;
-  __shared__ int64_t s_max;
+  __shared__ uint32_t shsum[SM_WAVES];
+  __shared__ SegMax shseg[SM_WAVES];
+  __shared__ uint32_t s_err;
+  __shared__ int64_t s_max, s_term[SM_WAVES];
   const uint32_t K = g.K, Dk = g.Dk, C = g.C;
-  const SmallLayout SL = small_layout(K, C);
+  const SmallLayout SL = small_layout(K, C, ITEMS * SM_THREADS);
   LdsRanges *lr = (LdsRanges *)smem;
   uint16_t *wcnt = (uint16_t *)(smem + SL.wcnt);
-  uint16_t *tot = (uint16_t *)(smem + SL.tot);
   uint32_t *seg = (uint32_t *)(smem + SL.seg);
   int64_t *cf = (int64_t *)(smem + SL.cf);
   int64_t *sdd = (int64_t *)(smem + SL.sdd);
-  int64_t *cdd = (int64_t *)(smem + SL.cdd);
   uint16_t *sidx = (uint16_t *)(smem + SL.sidx);
   uint16_t *skey = (uint16_t *)(smem + SL.skey);
-  uint16_t *cidx = (uint16_t *)(smem + SL.cidx);
-  uint16_t *cch = (uint16_t *)(smem + SL.cch);
-  const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6;
+  const uint32_t t = threadIdx.x, lane = lane_id();
+  const uint32_t w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t nw = (n + 64 * ITEMS - 1) / (64 * ITEMS);  // waves with requests
   const int64_t tR = g.tR, xfer = g.xfer;
 
-  load_ranges(lr, rt);
-  for (uint32_t q = t; q < DWAVES * K; q += DBLK) wcnt[q] = 0;
+  // item e of wave w: requests (w * ITEMS + e) * 64 + lane
+  const uint32_t wb = w * 64 * ITEMS;
+  int64_t iss[ITEMS], prev[ITEMS];
+  uint64_t ad[ITEMS];
+#pragma unroll
+  for (int e = 0; e < ITEMS; e++) {
+    const uint32_t i = wb + e * 64 + lane;
+    iss[e] = i < n ? issue[i] : 0;
+    ad[e] = i < n ? addr[i] : 0;
+    prev[e] = lane == 0 && i > 0 && i < n ? issue[i - 1] : 0;
+  }
+  // (one range, the common case, needs no table in LDS)
+  if (rt.n != 1) load_ranges(lr, rt);
+  for (uint32_t q = t; q < nw * K; q += SM_THREADS) wcnt[q] = 0;
   if (t == 0) {
     s_err = 0;
-    s_maxrun = 0;
     s_max = NEG;
   }
   __syncthreads();
-  const RangeReg rr = range_reg(lr);
+  const RangeReg rr = {rt.n, rt.base[0], rt.bytes[0], rt.pbase[0]};
   uint32_t errb = 0;
 
-  // 1. classify, validate, rank within the die queue (item e of wave w:
-  //    requests w*512 + e*64 + lane)
-  const int64_t wb = (int64_t)w * 64 * DITEMS;
-  uint32_t key[DITEMS], rank[DITEMS];
-  int64_t iss[DITEMS];
+  // 1. classify, validate, rank within the die queue
+  uint32_t key[ITEMS], rank[ITEMS];
+  int64_t df[ITEMS];  // the queue's clock, loaded ahead of the run's head
 #pragma unroll
-  for (int e = 0; e < DITEMS; e++) {
-    const int64_t i = wb + e * 64 + lane;
+  for (int e = 0; e < ITEMS; e++) {
+    const uint32_t i = wb + e * 64 + lane;
     const bool v = i < n;
-    const int64_t x = v ? issue[i] : 0;
+    const int64_t x = iss[e];
+    int64_t before = dpp64<DPP_WAVE_SHR1, 0xF>(x, x);  // lane l - 1's issue time
+    if (lane == 0) before = i > 0 ? prev[e] : x;
     uint32_t k = KEY_NONE;
+    df[e] = NEG;
     if (v) {
       if (x < 0 || x >= ISSUE_LIMIT) errb |= ERR_RANGE_TIME;
-      if (i > 0 && x < issue[i - 1]) errb |= ERR_UNSORTED;
-      k = key_of<POW2>(g, lr, rr, addr[i]);
+      if (x < before) errb |= ERR_UNSORTED;
+      k = key_of<POW2>(g, lr, rr, ad[e]);
       if (k == KEY_NONE) complete[i] = x;  // native path: no modeled delay
+      else df[e] = st->die_free[k];
     }
     key[e] = k;
-    iss[e] = x;
   }
   uint32_t nbits = 0;
   while ((1u << nbits) < K) nbits++;
-  wave_rank_bits(key, rank, wcnt + w * K, nbits);
+  if (w < nw) wave_rank_bits<ITEMS>(key, rank, wcnt + w * K, nbits);
+  if (errb) atomicOr(&s_err, errb);
+  // the failure: every completion HBF_TIME_ERROR, the clocks as they were
+  auto fail = [&](uint32_t err) {
+    for (uint32_t i = t; i < n; i += SM_THREADS) complete[i] = HBF_TIME_ERROR;
+    if (t == 0) {
+      atomicOr(&st->sticky, err);
+      ctl->err = err;
+      ctl->n_in = 0;
+      ctl->max_cpl = NEG;
+    }
+  };
   __syncthreads();
-  cross_wave_offsets(wcnt, tot, K);
-  __syncthreads();
-  {  // each queue's run in die order
-    const uint32_t per = (K + DBLK - 1) / DBLK;
-    const uint32_t a0 = t * per, b0 = min(K, a0 + per);
+  if (s_err) {  // (the steps below rely on valid, ascending issue times)
+    fail(s_err);
+    return;
+  }
+  {  // each wave's offset among the waves; each queue's run in die order
+    const uint32_t per = (K + SM_THREADS - 1) / SM_THREADS;
+    const uint32_t a0 = min(K, t * per), b0 = min(K, a0 + per);
     uint32_t sum = 0;
-    for (uint32_t k = a0; k < b0; k++) sum += tot[k];
-    uint32_t ex;
-    const uint32_t all = block_excl_sum<DWAVES>(sum, &ex, shsum);
     for (uint32_t k = a0; k < b0; k++) {
+      uint32_t run = 0;
+      for (uint32_t v = 0; v < nw; v++) {
+        const uint32_t c = wcnt[v * K + k];
+        wcnt[v * K + k] = (uint16_t)run;
+        run += c;
+      }
+      seg[k] = run;
+      sum += run;
+    }
+    uint32_t ex;
+    const uint32_t all = block_excl_sum<SM_WAVES>(sum, &ex, shsum);
+    for (uint32_t k = a0; k < b0; k++) {
+      const uint32_t c = seg[k];
       seg[k] = ex;
-      ex += tot[k];
+      ex += c;
     }
     if (t == 0) seg[K] = all;
-    uint32_t longest = 0;
-    for (uint32_t k = a0; k < b0; k++) longest = max(longest, (uint32_t)tot[k]);
-    if (longest) atomicMax(&s_maxrun, longest);
   }
   __syncthreads();
   // 2. stage issue_r - r*tR in die order; a run's head also takes the die clock
 #pragma unroll
-  for (int e = 0; e < DITEMS; e++) {
+  for (int e = 0; e < ITEMS; e++) {
     const uint32_t k = key[e];
     if (k != KEY_NONE) {
       const uint32_t rc = wcnt[w * K + k] + rank[e];
       const uint32_t P = seg[k] + rc;
       int64_t v = iss[e] - (int64_t)rc * tR;
-      if (rc == 0) v = imax(v, st->die_free[k]);
+      if (rc == 0) v = imax(v, df[e]);
       sdd[P] = v;
       sidx[P] = (uint16_t)(wb + e * 64 + lane);
       skey[P] = (uint16_t)k;
@@ -181,151 +263,132 @@ __global__ __launch_bounds__(DBLK) void k_small(const uint64_t *__restrict__ add
   }
   __syncthreads();
   const uint32_t m = seg[K];
-  const uint32_t p0 = t * DITEMS;
   {
-    int64_t vals[DITEMS];
+    const uint32_t p0 = t * ITEMS;
+    int64_t vals[ITEMS];
+    uint32_t rk[ITEMS];
     SegMax agg = {0, NEG};
 #pragma unroll
-    for (int q = 0; q < DITEMS; q++) {
+    for (int q = 0; q < ITEMS; q++) {
       const uint32_t p = p0 + q;
       vals[q] = NEG;
+      rk[q] = 0;
       if (p < m) {
         vals[q] = sdd[p];
-        agg = seg_comb(agg, SegMax{p == seg[skey[p]], vals[q]});
+        rk[q] = p - seg[skey[p]];
+        agg = seg_comb(agg, SegMax{rk[q] == 0, vals[q]});
       }
     }
-    const SegMax ex = block_excl_segmax<DWAVES>(agg, shseg);
+    const SegMax ex = block_excl_segmax<SM_WAVES>(agg, shseg);
     int64_t run = ex.v;
 #pragma unroll
-    for (int q = 0; q < DITEMS; q++) {
+    for (int q = 0; q < ITEMS; q++) {
       const uint32_t p = p0 + q;
       if (p < m) {
-        const uint32_t r = p - seg[skey[p]];
-        run = r == 0 ? vals[q] : imax(run, vals[q]);
-        const int64_t dd = (int64_t)(r + 1) * tR + run;
+        run = rk[q] == 0 ? vals[q] : imax(run, vals[q]);
+        const int64_t dd = (int64_t)(rk[q] + 1) * tR + run;
         if (dd >= TIME_LIMIT) errb |= ERR_OVERFLOW;
         sdd[p] = dd;
       }
     }
   }
   __syncthreads();
-  // 3. channel service order.  A request's rank in its channel counts, in
-  // each die run of the channel, the entries before it (its own run: its
-  // position).  A thread's requests are consecutive in die order, mostly of
-  // one run, so their counts in another run only grow: the first is found by
-  // a binary search, the next ones by walking on from the previous count.
-  {
-    uint32_t top = 1;  // the largest power of two not above the longest run
-    while (2 * top <= CHUNK && 2 * top <= (uint32_t)s_maxrun) top *= 2;
-    uint32_t kq[DITEMS], r[DITEMS];
-    int64_t dq[DITEMS];
-    uint32_t iq[DITEMS];
-#pragma unroll
-    for (int q = 0; q < DITEMS; q++) {
-      const uint32_t p = p0 + q;
-      kq[q] = KEY_NONE;
-      r[q] = 0;
-      dq[q] = 0;
-      iq[q] = 0;
-      if (p < m) {
-        kq[q] = skey[p];
-        dq[q] = sdd[p];
-        iq[q] = sidx[p];
+  // 3. merge, channel completions, channel clocks: a wave per channel or,
+  // where there are fewer channels than waves, `parts` waves per channel,
+  // each taking one stretch of its time: they find their stretches' terms,
+  // then merge again with the terms entering them.
+  const uint32_t lp = run_lanes_lg(Dk);
+  const uint32_t most = (uint32_t)SM_SLOTS << lp;  // requests of a run per merge
+  const uint32_t parts = C <= 2 ? SM_WAVES / C : 1u;
+  for (uint32_t c0 = 0; c0 < C; c0 += SM_WAVES) {
+    const uint32_t c = c0 + w / parts, part = w % parts;  // (parts > 1: one round)
+    uint32_t lo = 0, hi = 0;
+    int64_t rank = 0, term = NEG;
+    if (c < C) {
+      if (lane < Dk) {
+        lo = seg[c * Dk + lane];
+        hi = seg[c * Dk + lane + 1];
       }
-    }
-    // entry j of the staged order comes before (d0, i0)
-    auto before = [&](uint32_t j, int64_t d0, uint32_t i0) {
-      const int64_t v = sdd[j];
-      const uint32_t sv = sidx[j];
-      return (v < d0) | ((v == d0) & (sv < i0));
-    };
-    for (uint32_t d = 0; d < Dk; d++) {
-      uint32_t prev_key = KEY_NONE, cnt = 0;
-#pragma unroll
-      for (int q = 0; q < DITEMS; q++) {
-        if (kq[q] != KEY_NONE) {
-          const uint32_t kk = (kq[q] / Dk) * Dk + d;
-          if (kk == kq[q]) {
-            r[q] += p0 + q - seg[kk];  // its own run: its position
-          } else {
-            const uint32_t lo = seg[kk], len = tot[kk];
-            if (kq[q] != prev_key) {  // the thread's first request of this run: binary search
-              cnt = 0;
-              for (uint32_t step = top; step > 0; step >>= 1) {
-                const uint32_t at = cnt + step;
-                if (at <= len && before(lo + at - 1, dq[q], iq[q])) cnt = at;
-              }
-            } else {
-              while (cnt < len && before(lo + cnt, dq[q], iq[q])) cnt++;
-            }
-            r[q] += cnt;
+      if (parts > 1) {
+        // stretches between equally spaced requests of the longest run
+        const uint32_t len = hi - lo, longest = wave_umax(len);
+        const uint32_t d = (uint32_t)__builtin_ctzll(__ballot(len == longest));
+        const uint32_t head = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)d);
+        auto first = [&](uint32_t j) {  // of the lane's requests at or after stretch j's start
+          if (j == 0) return lo;
+          if (j == parts) return hi;
+          const int64_t T = sdd[head + (uint32_t)((uint64_t)longest * j / parts)];
+          uint32_t a = lo, b = hi;
+          while (a < b) {
+            const uint32_t mid = (a + b) >> 1;
+            if (sdd[mid] < T) a = mid + 1;
+            else b = mid;
           }
-          prev_key = kq[q];
+          return a;
+        };
+        if (longest) {
+          const uint32_t a = first(part), b = first(part + 1);
+          rank = wave_sum(a - lo);
+          lo = a;
+          hi = b;
         }
       }
     }
-#pragma unroll
-    for (int q = 0; q < DITEMS; q++) {
-      if (kq[q] != KEY_NONE) {
-        const uint32_t c = kq[q] / Dk;
-        const uint32_t cp = seg[c * Dk] + r[q];
-        cdd[cp] = dq[q];
-        cidx[cp] = (uint16_t)iq[q];
-        cch[cp] = (uint16_t)c;
+    for (int pass = parts > 1 ? 0 : 1; pass < 2; pass++) {
+      const bool emit = pass == 1;
+      if (c < C && emit) {
+        term = st->chan_free[c];
+        for (uint32_t j = 0; parts > 1 && j < part; j++) term = imax(term, s_term[w - part + j]);
+      }
+      uint32_t cur = lo;
+      int64_t at = rank;
+      while (c < C && __ballot(hi != cur) != 0) {
+        const uint32_t rem = hi - cur;
+        // the earliest die-done left, by a maximum of 2^62 - time, and the
+        // first time this merge leaves out
+        const int64_t tb = TIME_LIMIT - wave_max(rem ? TIME_LIMIT - sdd[cur] : NEG);
+        int64_t te = tb + (int64_t(1) << 30);
+        if (rem > most) te = imin(te, sdd[cur + most]);
+        te = TIME_LIMIT - wave_max(TIME_LIMIT - te);
+        uint32_t take = min(rem, most);
+        if (rem && sdd[cur + take - 1] >= te) {  // (each run ascends)
+          uint32_t a = 0, b = take - 1;
+          while (a < b) {
+            const uint32_t mid = (a + b) >> 1;
+            if (sdd[cur + mid] < te) a = mid + 1;
+            else b = mid;
+          }
+          take = a;
+        }
+        const uint32_t longest = wave_umax(take), mm = wave_sum(take);
+        if (longest <= (2u << lp))
+          term = small_merge<2>(sdd, sidx, cur, take, lp, tb, mm, at, xfer, term, emit, complete, &errb);
+        else if (longest <= (4u << lp))
+          term = small_merge<4>(sdd, sidx, cur, take, lp, tb, mm, at, xfer, term, emit, complete, &errb);
+        else
+          term = small_merge<SM_SLOTS>(sdd, sidx, cur, take, lp, tb, mm, at, xfer, term, emit, complete, &errb);
+        cur += take;
+        at += mm;
+      }
+      if (!emit) {
+        if (lane == 0) s_term[w] = term;
+        __syncthreads();
+      } else if (c < C && part + 1 == parts && at > 0 && lane == 0) {
+        cf[c] = at * xfer + term;  // the channel's last completion
+        atomicMax((long long *)&s_max, (long long)cf[c]);
       }
     }
-  }
-  __syncthreads();
-  // 4. channel completions; a channel's head also takes the channel clock
-  {
-    int64_t vals[DITEMS];
-    SegMax agg = {0, NEG};
-#pragma unroll
-    for (int q = 0; q < DITEMS; q++) {
-      const uint32_t p = p0 + q;
-      vals[q] = NEG;
-      if (p < m) {
-        const uint32_t c = cch[p], h = seg[c * Dk];
-        int64_t v = cdd[p] - (int64_t)(p - h) * xfer;
-        if (p == h) v = imax(v, st->chan_free[c]);
-        vals[q] = v;
-        agg = seg_comb(agg, SegMax{p == h, v});
-      }
-    }
-    const SegMax ex = block_excl_segmax<DWAVES>(agg, shseg);
-    int64_t run = ex.v, mx = NEG;
-#pragma unroll
-    for (int q = 0; q < DITEMS; q++) {
-      const uint32_t p = p0 + q;
-      if (p < m) {
-        const uint32_t c = cch[p], h = seg[c * Dk];
-        run = p == h ? vals[q] : imax(run, vals[q]);
-        const int64_t cpl = (int64_t)(p - h + 1) * xfer + run;
-        if (cpl >= TIME_LIMIT) errb |= ERR_OVERFLOW;
-        complete[cidx[p]] = cpl;
-        mx = imax(mx, cpl);
-        if (p + 1 == seg[(c + 1) * Dk]) cf[c] = cpl;  // the channel's last
-      }
-    }
-    if (mx > NEG) atomicMax((long long *)&s_max, (long long)mx);
   }
   if (errb) atomicOr(&s_err, errb);
   __syncthreads();
-  // 5. clocks, or the failure
-  const uint32_t err = s_err;
-  if (err) {
-    for (int64_t i = t; i < n; i += DBLK) complete[i] = HBF_TIME_ERROR;
-    if (t == 0) {
-      atomicOr(&st->sticky, err);
-      ctl->err = err;
-      ctl->n_in = m;
-      ctl->max_cpl = NEG;
-    }
+  // 4. clocks, or the failure
+  if (s_err) {
+    fail(s_err);
     return;
   }
-  for (uint32_t k = t; k < K; k += DBLK)
-    if (tot[k]) st->die_free[k] = sdd[seg[k] + tot[k] - 1];
-  for (uint32_t c = t; c < C; c += DBLK)
+  for (uint32_t k = t; k < K; k += SM_THREADS)
+    if (seg[k + 1] > seg[k]) st->die_free[k] = sdd[seg[k + 1] - 1];
+  for (uint32_t c = t; c < C; c += SM_THREADS)
     if (seg[(c + 1) * Dk] > seg[c * Dk]) st->chan_free[c] = cf[c];
   if (t == 0) {
     ctl->err = 0;
@@ -334,29 +397,33 @@ __global__ __launch_bounds__(DBLK) void k_small(const uint64_t *__restrict__ add
   }
 }
 
-bool small_path_ok(const Geo &g, int64_t n, bool refresh) {
-  return !refresh && !g.reg_block && !g.vmem && n > 0 && n <= CHUNK && g.K <= SMALL_K && g.Dk <= SMALL_DK &&
-         small_layout(g.K, g.C).total <= SMALL_LDS_MAX;
-}
+// Requests per thread of a call of n requests.
+static int small_items(int64_t n) { return n <= 2 * SM_THREADS ? 2 : 4; }
 
-size_t lds_small(const Geo &g) { return small_layout(g.K, g.C).total; }
+bool small_path_ok(const Geo &g, int64_t n, bool refresh) {
+  return !refresh && !g.reg_block && !g.vmem && n > 0 && n <= SMALL_N &&
+         small_layout(g.K, g.C, small_items(n) * SM_THREADS).total <= SMALL_LDS_MAX;
+}
 
 hipError_t launch_small(const Geo &g, const RangeTable &rt, DevState *st, CallCtl *ctl, const uint64_t *addr,
                         const int64_t *issue, int64_t n, int64_t *complete, hipStream_t s) {
-  const size_t lds = lds_small(g);
-  if (g.pow2)
-    hipLaunchKernelGGL(k_small<true>, dim3(1), dim3(DBLK), lds, s, addr, issue, n, complete, g, rt, st, ctl);
-  else
-    hipLaunchKernelGGL(k_small<false>, dim3(1), dim3(DBLK), lds, s, addr, issue, n, complete, g, rt, st, ctl);
+  const int items = small_items(n);
+  const size_t lds = small_layout(g.K, g.C, items * SM_THREADS).total;
+  auto f = g.pow2 ? (items == 2 ? k_small<true, 2> : k_small<true, 4>)
+                  : (items == 2 ? k_small<false, 2> : k_small<false, 4>);
+  hipLaunchKernelGGL(f, dim3(1), dim3(SM_THREADS), lds, s, addr, issue, (uint32_t)n, complete, g, rt, st, ctl);
   return hipGetLastError();
 }
 
 // (the largest LDS any geometry on this path asks for)
 hipError_t set_lds_small() {
-  const int lds = SMALL_LDS_MAX;
-  hipError_t e = hipFuncSetAttribute((const void *)k_small<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void *)k_small<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  const void *f[] = {(const void *)k_small<true, 2>, (const void *)k_small<true, 4>, (const void *)k_small<false, 2>,
+                     (const void *)k_small<false, 4>};
+  for (const void *k : f) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SMALL_LDS_MAX);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace hbf

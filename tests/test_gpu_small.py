@@ -1,7 +1,6 @@
-"""Small calls (at most 4,096 requests, at most 512 die queues and 16 per
-channel) run as one workgroup; the HIP path against the reference model,
+"""Small calls (at most 4,096 requests) run as one workgroup; the HIP path against the reference model,
 bit for bit: completion times, status and the clocks left behind.  The
-cases reach the path's limits (4,096 requests, 512 queues, 16 per channel),
+cases reach the path's limits (4,096 requests, 2,048 queues, 64 per channel),
 long runs on one die (the block-wide scans), ties on die-done across the
 dies of a channel, idle resets, native requests, several ranges, calls that
 alternate with larger calls on the same clocks, and the error paths.
@@ -68,7 +67,6 @@ GEOMS = [
     ("4x4x2-pp", wl.geometry(4, 4, 2, t_read_ns=3000, bw=8_000_000_000, flags=1)),
     ("3x5x2-nonpow2", wl.geometry(3, 5, 2, t_read_ns=700, bw=5_000_000_000, page=12288)),
     ("1x1x1", wl.geometry(1, 1, 1, t_read_ns=50, bw=16384 * 10_000_000)),
-    # the path's limits: 16 die queues per channel, 512 die queues
     ("32x16x1-K512", wl.geometry(32, 16, 1, t_read_ns=3000, bw=8_000_000_000)),
     ("64x2x4-pp", wl.geometry(64, 2, 4, t_read_ns=2000, bw=8_000_000_000, flags=1)),
 ]
@@ -157,3 +155,26 @@ def test_small_call_errors(torch, case):
         state = (df, cf)
     run_both(torch, params, [(1 << 40, 1 << 30)], [(addr, issue), (addr, bad), (addr, issue + 10**7)], case,
              set_state=state)
+
+
+# every number of lanes per die run, one or two channels (several waves per
+# channel), more channels than waves, and 2,048 die queues
+MERGE_GEOMS = [(1, 1, 1, 0), (1, 16, 1, 0), (2, 9, 1, 0), (1, 17, 1, 0), (5, 33, 1, 0), (20, 3, 1, 0), (40, 8, 1, 0),
+               (2, 16, 4, 1), (32, 16, 4, 1), (1024, 2, 1, 0)]
+
+
+@pytest.mark.parametrize("geo", MERGE_GEOMS, ids=lambda g: "x".join(map(str, g)))
+@pytest.mark.parametrize("n", [1, 63, 1025, 2048, 2049, 4096])
+def test_channel_merges(torch, geo, n):
+    """Spread requests, then ones that crowd two dies (runs longer than one
+    merge takes) with gaps beyond the 2^30 ns one merge spans."""
+    C, D, P, flags = geo
+    params = wl.geometry(C, D, P, flags=flags)
+    rng = np.random.default_rng(n * 31 + C + D)
+    pages = rng.integers(0, 8192, n).astype(np.uint64)
+    crowd = np.where(rng.random(n) < 0.8, rng.integers(0, 2, n) * C, rng.integers(0, 8192, n)).astype(np.uint64)
+    t1 = np.cumsum(rng.integers(0, 600, n)).astype(np.int64)
+    t2 = t1 + (1 << 31) + np.cumsum(rng.random(n) < 0.002) * np.int64(3 << 29)
+    at = np.uint64(1 << 40)
+    run_both(torch, params, [(1 << 40, 8192 * 16384)],
+             [(at + pages * np.uint64(16384), t1), (at + crowd * np.uint64(16384), t2)], f"merges {geo} n={n}")
