@@ -19,15 +19,37 @@
 // Channels only meet through the layer's done time (its latest completion),
 // which sets the next layer's issue time.
 //
-//   k_lay_count  one workgroup per layer: each request's bucket (its die
-//                queue, or K for the native path), counts per (layer, bucket)
-//   k_lay_scan   one block: bucket offsets, layer-major; clears the
-//                per-(layer, channel) done words
-//   k_lay_place  one workgroup per layer: each request's index at its
+// In fact the layers do not wait for each other at all once no clock is
+// ahead of the first layer's issue time: layer l + 1 is issued after every
+// completion of layer l, so every die and channel it uses is idle again.
+// Every die then starts at t_l, request j of a die leaves it at t_l +
+// (j+1)*tR, the channel serves all requests j before any request j + 1, and
+// with N(j) = sum over its dies of min(j, m) the request of channel rank r
+// completes at
+//     t_l + (r+1)*xfer + max over i <= j of (i+1)*tR - N(i)*xfer .
+// N is concave, so the term is convex in i and its maximum is at i = 0 or j:
+// max(tR, (j+1)*tR - N(j)*xfer).  A layer's duration depends on its counts
+// alone, the issue times are a prefix sum, and all completions are
+// independent.
+//
+//   k_lay_count  one workgroup per tile of a layer: each request's bucket
+//                (its die queue, or K for the native path), counts
+//   k_lay_scan   one block per layer: bucket offsets, the layer's duration
+//                from an idle device; clears the layer's done words
+//   k_lay_place  one workgroup per tile: each request's index at its
 //                bucket's offset + its rank in the bucket (index order)
-//   k_lay_run    cooperative, one workgroup per channel, every layer in
-//                turn: the channel's completions, then one exchange of
-//                the layer's latest completion through the done words.
+//   k_lay_chain  one block: whether no clock is ahead of the first issue
+//                time; if so every layer's issue and done time and the
+//                clocks left behind
+//   k_lay_emit   then: issue times and completions, all layers at once, a
+//                thread per (channel, j): it orders the channel's requests j
+//                by index
+//   k_lay_run    otherwise: cooperative, one workgroup per channel, every
+//                layer in turn: the channel's completions, then one exchange
+//                of the layer's latest completion through the done words.
+// Two steps of 48 layers, 2.9 M requests on 16 channels x 8 dies: 100 us a
+// call (count 11, scan 6, place 29, chain 6, emit 14) against 918 with every
+// layer in turn, 8.8 us a layer on one CU per channel.
 // The result equals one hbf_time_requests call per layer on the persistent
 // model, with the same failure rules: a layer whose issue time is outside
 // [0, 2^61) or whose times reach 2^62 fails as a whole (completions
@@ -36,6 +58,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "hbf_device.h"
@@ -89,14 +112,30 @@ __global__ __launch_bounds__(LBLK) void k_lay_count(const uint64_t *__restrict__
   for (uint32_t k = threadIdx.x; k <= K; k += LBLK) CNT[(size_t)blockIdx.x * (K + 1) + k] = cnt[k];
 }
 
+// A layer's duration from an idle device (0 without in-range requests), its
+// issue time (k_lay_chain) and the most requests of one die queue.
+struct LayerSum {
+  int64_t dur, t;
+  uint32_t most, pad;
+};
+// What k_lay_chain decided: whether every layer finds an idle device, and
+// the first layer that fails (L if none).
+struct LayChain {
+  uint32_t idle, fail;
+};
+
 // One block per layer: the layer's bucket offsets (from the layer's start;
 // OFF[l][K+1] is the layer's end) and each of its tiles' offset in every
 // bucket; the layer's done words cleared.
 __global__ __launch_bounds__(LBLK) void k_lay_scan(const uint32_t *__restrict__ CNT, const int64_t *__restrict__ ls,
                                                    const uint32_t *__restrict__ tile0, uint32_t K,
                                                    uint32_t *__restrict__ OFF, uint32_t *__restrict__ TOFF,
-                                                   uint64_t *__restrict__ SLOT, uint32_t C) {
+                                                   uint64_t *__restrict__ SLOT, Geo g, LayerSum *__restrict__ LS) {
   __shared__ uint32_t sh[LWAVES];
+  __shared__ uint32_t cnt[MAX_KEYS];
+  __shared__ int64_t s_dur;
+  __shared__ uint32_t s_most;
+  const uint32_t C = g.C;
   const uint32_t l = blockIdx.x, KB = K + 1;
   const uint32_t f = tile0[l], e = tile0[l + 1];
   const uint32_t per = (KB + LBLK - 1) / LBLK;
@@ -109,11 +148,35 @@ __global__ __launch_bounds__(LBLK) void k_lay_scan(const uint32_t *__restrict__ 
   uint32_t o = (uint32_t)ls[l] + ex;
   for (uint32_t k = k0; k < k1; k++) {
     OFF[(size_t)l * (KB + 1) + k] = o;
+    const uint32_t o0 = o;
     for (uint32_t q = f; q < e; q++) {
       TOFF[(size_t)q * KB + k] = o;
       o += CNT[(size_t)q * KB + k];
     }
+    if (k < K) cnt[k] = o - o0;
   }
+  if (threadIdx.x == 0) {
+    s_dur = 0;
+    s_most = 0;
+  }
+  __syncthreads();
+  // from an idle device: the time from the layer's issue to its latest
+  // completion, and the requests of its busiest die queue
+  for (uint32_t c = threadIdx.x; c < C; c += LBLK) {
+    uint32_t all = 0, most = 0, n = 0;
+    for (uint32_t d = 0; d < g.Dk; d++) {
+      const uint32_t m = cnt[c * g.Dk + d];
+      all += m;
+      most = max(most, m);
+    }
+    if (all == 0) continue;
+    for (uint32_t d = 0; d < g.Dk; d++) n += min(most - 1, cnt[c * g.Dk + d]);
+    const int64_t dur = (int64_t)all * g.xfer + imax(g.tR, (int64_t)most * g.tR - (int64_t)n * g.xfer);
+    atomicMax((long long *)&s_dur, (long long)dur);
+    atomicMax(&s_most, most);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) LS[l] = LayerSum{s_dur, 0, s_most, 0};
   if (threadIdx.x == 0) OFF[(size_t)l * (KB + 1) + KB] = (uint32_t)ls[l + 1];
   for (uint32_t c = threadIdx.x; c < C; c += LBLK) SLOT[(size_t)l * C + c] = 0;
 }
@@ -189,6 +252,172 @@ DEVI int64_t floor_div(int64_t a, int64_t d) {
   return (a % d != 0 && a < 0) ? q - 1 : q;
 }
 
+// One block: the chain of issue times, and what it leaves behind.
+constexpr int CHBLK = 1024;
+__global__ __launch_bounds__(CHBLK) void k_lay_chain(const int64_t *__restrict__ ls, const uint32_t *__restrict__ OFF,
+                                                     LayerSum *__restrict__ LS, LayChain *__restrict__ ch, uint32_t L,
+                                                     int64_t t_start, int64_t compute_ns, int64_t *__restrict__ done,
+                                                     DevState *st, Geo g) {
+  __shared__ uint64_t wtot[CHBLK / 64];
+  __shared__ uint32_t s_late, s_fail, s_hit;
+  const uint32_t t = threadIdx.x, lane = lane_id(), w = t >> 6, K = g.K;
+  if (t == 0) {
+    s_late = 0;
+    s_fail = L;
+    s_hit = 0;
+  }
+  __syncthreads();
+  bool late = false;
+  for (uint32_t k = t; k < K; k += CHBLK) late |= st->die_free[k] > t_start;
+  for (uint32_t c = t; c < g.C; c += CHBLK) late |= st->chan_free[c] > t_start;
+  if (late) s_late = 1;
+  __syncthreads();
+  if (s_late) {  // the same for the whole block
+    if (t == 0) *ch = LayChain{0u, 0u};
+    return;
+  }
+  // issue times: an exclusive prefix sum of duration + compute time, each
+  // thread a contiguous share of the layers (sums wrap as the sequential
+  // additions do; a layer they carry out of range fails)
+  const uint32_t per = (L + CHBLK - 1) / CHBLK;
+  const uint32_t l0 = min(L, t * per), l1 = min(L, l0 + per);
+  uint64_t sum = 0;
+  for (uint32_t l = l0; l < l1; l++) sum += (uint64_t)LS[l].dur + (uint64_t)compute_ns;
+  uint64_t inc = sum;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t y = __shfl_up(inc, d);
+    if (lane >= (uint32_t)d) inc += y;
+  }
+  if (lane == 63) wtot[w] = inc;
+  __syncthreads();
+  uint64_t at = (uint64_t)t_start + inc - sum;
+  for (uint32_t v = 0; v < w; v++) at += wtot[v];
+  for (uint32_t l = l0; l < l1; l++) {
+    const int64_t tl = (int64_t)at;
+    LS[l].t = tl;
+    if (tl < 0 || (ls[l + 1] > ls[l] && tl >= ISSUE_LIMIT)) atomicMin(&s_fail, l);
+    at += (uint64_t)LS[l].dur + (uint64_t)compute_ns;
+  }
+  __syncthreads();
+  const uint32_t fail = s_fail;
+  for (uint32_t l = l0; l < l1; l++) {
+    if (l < fail) {
+      done[l] = LS[l].t + LS[l].dur;
+    } else {  // this layer failed, or one before it did
+      done[l] = HBF_TIME_ERROR;
+      if (l > fail) LS[l].t = HBF_TIME_ERROR + compute_ns;
+      if (ls[l + 1] > ls[l]) s_hit = 1;
+    }
+  }
+  __syncthreads();
+  if (t == 0) {
+    *ch = LayChain{1u, fail};
+    if (s_hit) atomicOr(&st->sticky, ERR_RANGE_TIME);
+  }
+  // the clocks: of the last layer before the failure that used each
+  const uint32_t KB = K + 1;
+  for (uint32_t k = t; k < K; k += CHBLK) {
+    for (uint32_t l = fail; l-- > 0;) {
+      const uint32_t *off = OFF + (size_t)l * (KB + 1);
+      const uint32_t m = off[k + 1] - off[k];
+      if (m) {
+        st->die_free[k] = LS[l].t + (int64_t)m * g.tR;
+        break;
+      }
+    }
+  }
+  for (uint32_t c = t; c < g.C; c += CHBLK) {
+    for (uint32_t l = fail; l-- > 0;) {
+      const uint32_t *off = OFF + (size_t)l * (KB + 1) + c * g.Dk;
+      const uint32_t all = off[g.Dk] - off[0];
+      if (!all) continue;
+      uint32_t most = 0, n = 0;
+      for (uint32_t d = 0; d < g.Dk; d++) most = max(most, off[d + 1] - off[d]);
+      for (uint32_t d = 0; d < g.Dk; d++) n += min(most - 1, off[d + 1] - off[d]);
+      st->chan_free[c] =
+          LS[l].t + (int64_t)all * g.xfer + imax(g.tR, (int64_t)most * g.tR - (int64_t)n * g.xfer);
+      break;
+    }
+  }
+}
+
+// Issue times and completions where every layer finds an idle device.  Block
+// (l, part) writes a share of layer l's issue times and native completions
+// and takes every parts-th group of EMJ request ranks j of all channels:
+// thread (channel, j) loads the channel's requests j, one per die, and ranks
+// them by index.  Consecutive j read consecutive list entries, and the
+// channels of a block complete whole lines of complete[] between them.
+// DT: die queues per channel held in registers (0: any number, read again
+// for each comparison).
+constexpr int EMBLK = 256;
+constexpr uint32_t EMJ = 16;
+template <int DT>
+__global__ __launch_bounds__(EMBLK) void k_lay_emit(const int64_t *__restrict__ ls, const uint32_t *__restrict__ OFF,
+                                                    const LayerSum *__restrict__ LS, const LayChain *__restrict__ ch,
+                                                    const uint32_t *__restrict__ LISTD, int64_t *__restrict__ issue,
+                                                    int64_t *__restrict__ complete, Geo g) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t *off = (uint32_t *)smem;  // [K + 2]
+  if (!ch->idle) return;
+  const uint32_t l = blockIdx.x, part = blockIdx.y, parts = gridDim.y, t = threadIdx.x;
+  const uint32_t K = g.K, Dk = g.Dk, C = g.C;
+  const int64_t la = ls[l], lb = ls[l + 1];
+  if (la == lb) return;
+  const int64_t tl = LS[l].t;
+  const bool fail = l >= ch->fail;
+  for (int64_t i = la + (int64_t)part * EMBLK + t; i < lb; i += (int64_t)parts * EMBLK) {
+    issue[i] = tl;
+    if (fail) complete[i] = HBF_TIME_ERROR;
+  }
+  if (fail) return;
+  const uint32_t *row = OFF + (size_t)l * (K + 2);
+  for (uint32_t k = t; k < K + 2; k += EMBLK) off[k] = row[k];
+  __syncthreads();
+  for (uint32_t q = off[K] + part * EMBLK + t; q < off[K + 1]; q += parts * EMBLK) complete[LISTD[q]] = tl;
+  const uint32_t most = LS[l].most;
+  const int64_t tR = g.tR, xfer = g.xfer;
+  for (uint32_t j0 = part * EMJ; j0 < most; j0 += parts * EMJ) {
+    for (uint32_t v = t; v < C * EMJ; v += EMBLK) {
+      const uint32_t j = j0 + (v & (EMJ - 1)), c = v / EMJ;
+      const uint32_t *o = off + c * Dk;
+      uint32_t n = 0;  // requests of the channel before its requests j
+      if constexpr (DT > 0) {
+        uint32_t ix[DT];
+#pragma unroll
+        for (int d = 0; d < DT; d++) {
+          ix[d] = 0xFFFFFFFFu;
+          if ((uint32_t)d < Dk) {
+            const uint32_t m = o[d + 1] - o[d];
+            n += min(j, m);
+            if (j < m) ix[d] = LISTD[o[d] + j];
+          }
+        }
+        const int64_t term = tl + imax(tR, (int64_t)(j + 1) * tR - (int64_t)n * xfer);
+#pragma unroll
+        for (int d = 0; d < DT; d++) {
+          if (ix[d] == 0xFFFFFFFFu) continue;
+          uint32_t r = n;
+#pragma unroll
+          for (int e = 0; e < DT; e++) r += ix[e] < ix[d] ? 1u : 0u;
+          complete[ix[d]] = term + (int64_t)(r + 1) * xfer;
+        }
+      } else {
+        for (uint32_t d = 0; d < Dk; d++) n += min(j, o[d + 1] - o[d]);
+        const int64_t term = tl + imax(tR, (int64_t)(j + 1) * tR - (int64_t)n * xfer);
+        for (uint32_t d = 0; d < Dk; d++) {
+          if (j >= o[d + 1] - o[d]) continue;
+          const uint32_t ix = LISTD[o[d] + j];
+          uint32_t r = n;
+          for (uint32_t e = 0; e < Dk; e++)
+            if (j < o[e + 1] - o[e] && LISTD[o[e] + j] < ix) r++;
+          complete[ix] = term + (int64_t)(r + 1) * xfer;
+        }
+      }
+    }
+  }
+}
+
 struct LayArgs {
   const int64_t *ls;
   const uint32_t *OFF, *LISTD;
@@ -197,6 +426,7 @@ struct LayArgs {
   uint64_t *SLOT;
   int64_t *issue, *complete, *done;
   DevState *st;
+  const LayChain *chain;
   Geo g;
   int64_t t_start, compute_ns;
   uint32_t L;
@@ -291,6 +521,7 @@ __global__ __launch_bounds__(RBLK) void k_lay_run(LayArgs A, uint32_t cap) {
   __shared__ int64_t s_last, s_chunk, s_lmax;
   __shared__ uint32_t s_err, s_any;
   __shared__ LayHdr hdr[2];
+  if (A.chain->idle) return;  // k_lay_emit did the call
   const Geo &g = A.g;
   const uint32_t Dk = g.Dk, C = g.C, K = g.K, KB = K + 1, c = blockIdx.x;
   const int64_t tR = g.tR, xfer = g.xfer;
@@ -472,7 +703,8 @@ static uint32_t n_tiles(const int64_t *ls, int L) {
 size_t layers_ws_bytes(const Geo &g, int64_t n, int L) {
   const size_t KB = g.K + 1, nt = (size_t)n / LAY_TILE + L + 1;
   return 256 * 16 + (size_t)(L + 1) * 8 + (size_t)(L + 1) * 4 + nt * sizeof(LayTile) + (size_t)n * (2 + 4 + 8 + 4) +
-         nt * KB * 4 * 2 + (size_t)L * (KB + 1) * 4 + (size_t)L * g.C * 8;
+         nt * KB * 4 * 2 + (size_t)L * (KB + 1) * 4 + (size_t)L * g.C * 8 + (size_t)L * sizeof(LayerSum) +
+         sizeof(LayChain);
 }
 
 hipError_t launch_layers(const Geo &g, const RangeTable &rt, char *ws, DevState *st, const uint64_t *addr,
@@ -518,6 +750,8 @@ hipError_t launch_layers(const Geo &g, const RangeTable &rt, char *ws, DevState 
   int64_t *RV = (int64_t *)take((size_t)n * 8);
   uint32_t *RI = (uint32_t *)take((size_t)n * 4);
   uint64_t *SLOT = (uint64_t *)take((size_t)L * g.C * 8);
+  LayerSum *LS = (LayerSum *)take((size_t)L * sizeof(LayerSum));
+  LayChain *chain = (LayChain *)take(sizeof(LayChain));
   if ((e = hipMemcpyAsync(d_up, up.data(), up.size(), hipMemcpyHostToDevice, s)) != hipSuccess) return e;
   if ((e = hipEventRecord(up_done, s)) != hipSuccess) return e;
   if (NT) {
@@ -528,13 +762,30 @@ hipError_t launch_layers(const Geo &g, const RangeTable &rt, char *ws, DevState 
                          CNT);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_lay_scan, dim3(L), dim3(LBLK), 0, s, CNT, ls, tile0, g.K, OFF, TOFF, SLOT, g.C);
+  hipLaunchKernelGGL(k_lay_scan, dim3(L), dim3(LBLK), 0, s, CNT, ls, tile0, g.K, OFF, TOFF, SLOT, g, LS);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (NT) {
     hipLaunchKernelGGL(k_lay_place, dim3(NT), dim3(LBLK), lds_lay_place(g.K), s, tiles, KEY, g.K, TOFF, LISTD);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
+  hipLaunchKernelGGL(k_lay_chain, dim3(1), dim3(CHBLK), 0, s, ls, OFF, LS, chain, (uint32_t)L, t_start, compute_ns,
+                     done, st, g);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (NT) {
+    // blocks per layer: about one per EMJ ranks of evenly spread requests
+    // (several die queues of a thread's channel give one block 16 x C x Dk)
+    int64_t most = 0;
+    for (int l = 0; l < L; l++) most = std::max(most, host_ls[l + 1] - host_ls[l]);
+    int64_t parts = most / ((int64_t)g.K * EMJ) + 1;
+    if (parts > 64) parts = 64;
+    const size_t lds = (size_t)(g.K + 2) * 4;
+    hipLaunchKernelGGL(g.Dk <= 4 ? k_lay_emit<4> : g.Dk <= 8 ? k_lay_emit<8> : g.Dk <= 16 ? k_lay_emit<16> : k_lay_emit<0>,
+                       dim3((uint32_t)L, (uint32_t)parts), dim3(EMBLK), lds, s, ls, OFF, LS, chain, LISTD, issue,
+                       complete, g);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   LayArgs A;
+  A.chain = chain;
   A.ls = ls;
   A.OFF = OFF;
   A.LISTD = LISTD;

@@ -180,3 +180,55 @@ def test_overflow_fails_the_layer(torch):
     gd, gc = m.get_state()
     od_, oc_ = o.state()
     assert np.array_equal(gd, od_) and np.array_equal(gc, oc_)
+
+
+@pytest.mark.parametrize("geo", [(3, 1, 1, 0), (2, 4, 1, 0), (5, 7, 1, 0), (16, 16, 1, 0), (1, 17, 1, 0), (2, 16, 4, 1),
+                                 (1024, 2, 1, 0)])
+@pytest.mark.parametrize("early", [False, True])
+def test_idle_and_busy_starts(torch, geo, early):
+    """Every layer finds an idle device (all layers at once), then a second
+    call whose first layer is issued before the clocks of some dies (layer
+    after layer) or after all of them.  Skewed layers: one die queue takes
+    most requests of some, others hold one request or none."""
+    from oracle import oracle
+    from paper_2609_09800_amd import hbf
+    C, D, P, flags = geo
+    say(f"closed loop: idle and busy starts {geo} early={early}")
+    params = wl.geometry(C, D, P, t_read_ns=700, flags=flags)
+    rng = np.random.default_rng(C + 10 * D + early)
+    m, o = hbf.Model(**params), oracle.OracleModel(**params)
+    assert m.register_range(1 << 40, 1 << 30)[0] == 0 and o.register_range(1 << 40, 1 << 30) == 0
+    t0 = 12345
+    for call in range(2):
+        sizes = np.array([0, 1, 4000, 17, 0, 2500, C, 3 * C * D * P + 1])
+        addr = []
+        for k, size in enumerate(sizes):
+            pg = rng.integers(-3, 1 << 16, size)
+            if k % 3 == 2:
+                pg = np.where(rng.random(size) < 0.8, C * rng.integers(0, 3, size) * D * P, pg)
+            addr.append(pg)
+        addr = ((1 << 40) + np.concatenate(addr).astype(np.int64) * 16384).astype(np.uint64)
+        ls = np.concatenate([[0], np.cumsum(sizes)])
+        a = torch.from_numpy(addr.view(np.int64)).cuda()
+        iss, cpl = torch.empty_like(a), torch.empty_like(a)
+        done = torch.empty(len(sizes), dtype=torch.int64, device="cuda")
+        assert m.time_layers(a, ls, t0, 300, iss, cpl, done) == 0
+        rc, oi, oc, od = o.time_layers(addr, ls, t0, 300)
+        assert m.get_status() == rc == 0
+        assert np.array_equal(iss.cpu().numpy(), oi) and np.array_equal(done.cpu().numpy(), od)
+        assert np.array_equal(cpl.cpu().numpy(), oc)
+        for x, y in zip(m.get_state(), o.state()):
+            assert np.array_equal(x, y)
+        t0 = int(od[0]) + 50 if early else int(od[-1])
+
+
+def test_issue_times_run_out_of_range(torch):
+    """The issue time passes 2^61 (a failing layer), also over empty layers;
+    the layers before keep their times and clocks."""
+    params = wl.geometry(4, 4, 2)
+    addr = ((1 << 40) + np.arange(60, dtype=np.int64) * 16384).astype(np.uint64)
+    for ls, t0, comp in [([0, 10, 20, 20, 45, 60], (1 << 61) - 40_000, 20_000),
+                         ([0, 10, 10, 10, 60], 5, (1 << 61) - 1),
+                         ([0, 0, 30, 60], (1 << 61) - 1, 0)]:
+        say(f"closed loop: out of range {ls}")
+        run_both(torch, params, [(1 << 40, 1 << 34)], addr, ls, t0, comp)
