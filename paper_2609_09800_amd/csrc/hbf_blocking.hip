@@ -100,7 +100,92 @@ constexpr int RSTRIDE = RING + 1;   // padded: lanes' rings start in different b
 constexpr int OUTB = 256;           // staged completions per write-out
 constexpr int QB = 128;             // staged quantum completions per write-out
 
-// One wave per channel (blockIdx.x); lane j = die queue c*Dk + j.
+// Steady rounds (see below) as one lane sees them: lane l takes die queue
+// l mod Dp (Dp: Dk rounded up to a power of two, at least 16) and every S-th
+// round (S = 64 / Dp), so a wave's batch covers `rounds` = S * FL rounds.
+constexpr uint32_t FL = 16;  // rounds per lane per batch
+constexpr uint32_t RW = 4;   // waves of a workgroup, one per SIMD (the channel loop needs its registers)
+struct SteadyData {
+  int64_t is[FL];
+  uint32_t ix[FL];
+};
+struct SteadyLane {
+  int64_t T;                    // of a round
+  int64_t c0;                   // the lane's die queue: its completion in the round before round 1
+  uint32_t a0, total, R, base;  // its admitted requests, requests, quanta and run
+  uint32_t S, sub, rounds;
+  bool on;
+  // die-order position of the queue's request of round j
+  __device__ __forceinline__ uint32_t pos(uint32_t j) const { return a0 + j - 2; }
+  __device__ __forceinline__ int64_t done(uint32_t j) const {
+    return c0 + (int64_t)j * T;
+  }
+  // The lane's rounds of the batch at j0: their requests, and the first one
+  // its die cannot keep (UINT32_MAX: none).
+  __device__ __forceinline__ uint32_t load(SteadyData &d, uint32_t j0, const int64_t *__restrict__ issue_do,
+                                           const uint32_t *__restrict__ ixs, uint32_t ixstride) const {
+    uint32_t bad = UINT32_MAX;
+    if (!on) return bad;
+#pragma unroll
+    for (uint32_t u = 0; u < FL; u++) {
+      const uint32_t q = pos(j0 + sub + S * u), at = q < total ? base + q : base;
+      d.is[u] = issue_do[at];
+      d.ix[u] = ixs[(size_t)at * ixstride];
+    }
+#pragma unroll
+    for (int u = (int)FL - 1; u >= 0; u--) {
+      const uint32_t j = j0 + sub + S * (uint32_t)u, q = pos(j);
+      const bool ok = j == 1 || (q < total && q >= R && d.is[u] <= done(j - 1));
+      if (!ok) bad = j;
+    }
+    return bad;
+  }
+  // Completions of its rounds up to `upto`.
+  __device__ __forceinline__ void store(const SteadyData &d, uint32_t j0, uint32_t upto,
+                                        int64_t *__restrict__ complete) const {
+    if (!on) return;
+#pragma unroll
+    for (uint32_t u = 0; u < FL; u++) {
+      const uint32_t j = j0 + sub + S * u;
+      if (j <= upto) complete[d.ix[u]] = done(j);
+    }
+  }
+};
+// From the die lanes' state (lane d: die queue d, in the stretch if `pend`)
+// to every lane's share.
+__device__ __forceinline__ SteadyLane steady_lane(uint32_t lane, uint32_t Dk, int64_t T, bool pend, uint32_t a0,
+                                                  int64_t c0, uint32_t total, uint32_t R, uint32_t base) {
+  SteadyLane s;
+  const uint32_t lgD = Dk <= 16 ? 4u : Dk <= 32 ? 5u : 6u;
+  const int dl = (int)(lane & ((1u << lgD) - 1));
+  s.T = T;
+  s.c0 = __shfl(c0, dl);
+  s.S = 64u >> lgD;
+  s.sub = lane >> lgD;
+  s.rounds = s.S * FL;
+  s.on = __shfl((int)(pend ? 1 : 0), dl) != 0;
+  s.a0 = (uint32_t)__shfl((int)a0, dl);
+  s.total = (uint32_t)__shfl((int)total, dl);
+  s.R = (uint32_t)__shfl((int)R, dl);
+  s.base = (uint32_t)__shfl((int)base, dl);
+  return s;
+}
+// Workgroup barrier for waves at different places of the program: each
+// arrival counts, whichever of the matching calls it comes from.
+__device__ __forceinline__ void block_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// One workgroup per channel (blockIdx.x).  Wave 0 runs the channel, its lane
+// j = die queue c*Dk + j; the other waves wait for long steady stretches and
+// take their share of each batch: a stretch of thousands of rounds is bound
+// by its batches' load latency.  1 M requests on 16 channels, about 8,000
+// rounds each: 725 us a call with one wave per channel and steady rounds
+// only where the channel is the bottleneck, 560 with four waves, 246 with
+// the die-bound rounds too (the last dies of each channel, which the general
+// loop took a page at a time).  Eight waves spill the loop.
 //   DDw / IX: die-ordered request indices (packed word's low half when the
 //   cell shift is <= 32, else IX); issue_do: their issue times; seg_start /
 //   totals: each die queue's run.  ref: refresh quanta pending (each die
@@ -109,7 +194,7 @@ constexpr int QB = 128;             // staged quantum completions per write-out
 // ROW: at most 16 die queues per channel, all in lanes 0-15 (one DPP row),
 // so the all-pairs comparisons of a round run on row rotations.
 template <bool ROW>
-__global__ __launch_bounds__(64) void k_regblock(const uint64_t *__restrict__ DDw, const uint32_t *__restrict__ IX,
+__global__ __launch_bounds__(64 * RW) void k_regblock(const uint64_t *__restrict__ DDw, const uint32_t *__restrict__ IX,
                                                  const int64_t *__restrict__ issue_do,
                                                  const uint32_t *__restrict__ seg_start,
                                                  const uint32_t *__restrict__ totals, Geo g, DevState *st,
@@ -121,11 +206,33 @@ __global__ __launch_bounds__(64) void k_regblock(const uint64_t *__restrict__ DD
   __shared__ int64_t out_cpl[OUTB];
   __shared__ uint32_t q_die[QB], q_rank[QB];
   __shared__ int64_t q_val[QB];
+  __shared__ SteadyLane s_steady[64];
+  __shared__ uint32_t s_round, s_bad;  // s_round 0: the channel is done
   if (__hip_atomic_load(&ctl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   const uint32_t c = blockIdx.x, lane = __lane_id(), Dk = g.Dk;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const bool narrow = ctl->shift <= 32;
+  // request indices: the low half of each packed die-order word, or IX
+  const uint32_t *ixs = narrow ? reinterpret_cast<const uint32_t *>(DDw) : IX;
+  const uint32_t ixstride = narrow ? 2u : 1u;
+  if (wave != 0) {  // batches of steady rounds until wave 0 says it is done
+    for (;;) {
+      block_sync();
+      const uint32_t j0 = s_round;
+      if (j0 == 0) return;
+      const SteadyLane sl = s_steady[lane];
+      const uint32_t mine = j0 + wave * sl.rounds;
+      SteadyData sd;
+      const uint32_t bad = wave_min32(sl.load(sd, mine, issue_do, ixs, ixstride));
+      if (lane == 0) atomicMin(&s_bad, bad);
+      block_sync();
+      const uint32_t all = s_bad;
+      sl.store(sd, mine, all == UINT32_MAX ? UINT32_MAX : all - 1, complete);
+      block_sync();
+    }
+  }
   const bool on = lane < Dk;
   const uint32_t k = c * Dk + (on ? lane : 0);
-  const bool narrow = ctl->shift <= 32;
   const int64_t tR = g.tR, tQ = g.tQ, xfer = g.xfer;
   const uint32_t total = on ? totals[k] : 0;
   const uint32_t base = on ? seg_start[k] : 0;
@@ -139,9 +246,6 @@ __global__ __launch_bounds__(64) void k_regblock(const uint64_t *__restrict__ DD
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  // request indices: the low half of each packed die-order word, or IX
-  const uint32_t *ixs = narrow ? reinterpret_cast<const uint32_t *>(DDw) : IX;
-  const uint32_t ixstride = narrow ? 2u : 1u;
   uint32_t loaded = 0;     // requests of this die queue written to the ring
   uint32_t admitted = 0;   // requests whose read has been scheduled
   uint32_t nix[CHUNK_R];   // in flight: requests loaded .. loaded + CHUNK_R - 1
@@ -339,67 +443,66 @@ __global__ __launch_bounds__(64) void k_regblock(const uint64_t *__restrict__ DD
       if (nq > QB - 64) flush_q();
     }
     if (nout > OUTB - 64) flush_out();
-    // Steady rounds.  If this round served every pending page back to back
-    // and every die re-read at once (its next request issued by then, no
-    // quantum claimed), the next round ranks the dies in the same order:
-    // each next page is ready tR after its predecessor left, and with
-    // P*xfer >= tR + xfer it is ready before the channel reaches it.  So
-    // in round j = 1, 2, ... the page of rank r completes at
-    // cf + ((j-1)*P + r + 1)*xfer, as long as every die's page of that round
+    // each die's next request must be in its ring before the next round
+    if (__ballot(on && admitted < total && loaded - admitted < 2)) top_up();
+    if (adm && admitted < total) {
+      const uint32_t sl = lane * RSTRIDE + admitted % RING;
+      nx_iss = ring_iss[sl];
+      nx_idx = ring_idx[sl];
+    }
+    // Steady rounds.  Let this round have served every pending page and
+    // every die have re-read at once (its next request issued by its page's
+    // completion, no quantum claimed), so that each next page is ready tR
+    // after its predecessor left.  Then the rounds repeat, in the same order
+    // and T later each time, in two cases: the channel is the bottleneck, T =
+    // P*xfer >= tR + xfer, and this round went back to back (the next pages
+    // are ready before the channel reaches them); or the dies are, T = tR +
+    // xfer > P*xfer, and the round's first page was no more than tR before
+    // its last (each next page then finds the channel free).  In round j =
+    // 1, 2, ... a die's page completes j*T after this round's, as long as it
     // was issued by its predecessor's completion and claims nothing.  Each
     // lane checks its own queue ahead, the shortest run decides, and those
     // rounds are written at once; the round after them is admitted as usual.
-    const bool steady = v == P && cm == 0 && (int64_t)P * xfer >= tR + xfer && !__ballot(pend && !adm) &&
-                        !__ballot(pend && (cpl != cfree - (int64_t)(P - 1 - r) * xfer || dd != cpl + tR));
+    const bool chan_bound = (int64_t)P * xfer >= tR + xfer;
+    const int64_t T = chan_bound ? (int64_t)P * xfer : tR + xfer;
+    const int64_t early = cfree - cpl;  // before the round's last completion
+    // (a stretch of one round is not worth a step: every die's request of
+    // round 2 is looked at first)
+    const bool steady = v == P && cm == 0 &&
+                        !__ballot(pend && !(adm && admitted < total && nx_iss <= cpl + T)) &&
+                        !__ballot(pend && ((chan_bound ? early != (int64_t)(P - 1 - r) * xfer : early > tR) ||
+                                           dd != cpl + tR));
     if (steady) {
-      constexpr uint32_t FL = 16, FMAX = 4096;  // rounds per lane per batch, rounds per step
-      const int64_t cf0 = cfree;
       const uint32_t a0 = admitted;             // the pending page is request a0 - 1 of the queue
-      // Every lane works here: lane l takes die queue l mod Dp (Dp: Dk
-      // rounded up to a power of two) and every S-th round (S = 64 / Dp),
-      // so a batch covers S*FL rounds.  Per batch: load each round's request
-      // (issue time, index), find the first round some die cannot keep,
-      // write the rounds before it.
-      const uint32_t lgD = Dk <= 16 ? 4u : Dk <= 32 ? 5u : 6u, S = 64u >> lgD;
-      const uint32_t dl = lane & ((1u << lgD) - 1), sub = lane >> lgD;
-      const bool pd = __shfl((int)(pend ? 1 : 0), (int)dl) != 0;
-      const uint32_t a0d = (uint32_t)__shfl((int)a0, (int)dl), rd = (uint32_t)__shfl((int)r, (int)dl);
-      const uint32_t td = (uint32_t)__shfl((int)total, (int)dl), Rd = (uint32_t)__shfl((int)R, (int)dl);
-      const uint32_t bd = (uint32_t)__shfl((int)base, (int)dl);
-      uint32_t m = 0;                           // rounds written (round 1: the pending pages)
-      for (uint32_t j0 = 1;; j0 += S * FL) {
-        uint32_t bad = UINT32_MAX;
-        int64_t is[FL];
-        uint32_t ix[FL];
-        if (pd) {
-#pragma unroll
-          for (uint32_t u = 0; u < FL; u++) {
-            const uint32_t pos = a0d + j0 + sub + S * u - 2, at = pos < td ? bd + pos : bd;
-            is[u] = issue_do[at];
-            ix[u] = ixs[(size_t)at * ixstride];
+      // Every lane works here (SteadyLane): per batch, load each round's
+      // request, find the first round some die cannot keep, write the rounds
+      // before it.  This wave takes the first batch; a stretch that outlasts
+      // it is taken by all the workgroup's waves, RW batches at a time.
+      const SteadyLane sl = steady_lane(lane, Dk, T, pend, a0, cpl, total, R, base);
+      SteadyData sd;
+      const uint32_t first = wave_min32(sl.load(sd, 1, issue_do, ixs, ixstride));
+      uint32_t m = first == UINT32_MAX ? sl.rounds : first - 1;  // rounds written (round 1: the pending pages)
+      sl.store(sd, 1, m, complete);
+      if (first == UINT32_MAX) {
+        s_steady[lane] = sl;
+        for (uint32_t j0 = 1 + sl.rounds;; j0 += RW * sl.rounds) {
+          if (lane == 0) {
+            s_round = j0;
+            s_bad = UINT32_MAX;
           }
-#pragma unroll
-          for (int u = (int)FL - 1; u >= 0; u--) {
-            const uint32_t j = j0 + sub + S * (uint32_t)u, pos = a0d + j - 2;
-            const bool ok = j == 1 || (pos < td && pos >= Rd &&
-                                       is[u] <= cf0 + ((int64_t)(j - 2) * P + rd + 1) * xfer);
-            if (!ok) bad = j;
-          }
+          block_sync();
+          const uint32_t mine = wave_min32(sl.load(sd, j0, issue_do, ixs, ixstride));
+          if (lane == 0) atomicMin(&s_bad, mine);
+          block_sync();
+          const uint32_t bad = s_bad;
+          m = bad == UINT32_MAX ? j0 + RW * sl.rounds - 1 : bad - 1;
+          sl.store(sd, j0, m, complete);
+          block_sync();  // s_bad has been read
+          if (bad != UINT32_MAX) break;
         }
-        const uint32_t fb = wave_min32(bad);
-        const uint32_t upto = fb == UINT32_MAX ? j0 + S * FL - 1 : fb - 1;
-        if (pd) {
-#pragma unroll
-          for (uint32_t u = 0; u < FL; u++) {
-            const uint32_t j = j0 + sub + S * u;
-            if (j <= upto) complete[ix[u]] = cf0 + ((int64_t)(j - 1) * P + rd + 1) * xfer;
-          }
-        }
-        m = upto;
-        if (fb != UINT32_MAX || m >= FMAX) break;
       }
-      const int64_t clm = cf0 + ((int64_t)(m - 1) * P + r + 1) * xfer;  // this lane's last completion
-      cfree = cf0 + (int64_t)m * P * xfer;
+      const int64_t clm = cpl + (int64_t)m * T;  // this lane's last completion
+      cfree += (int64_t)m * T;
       bool cl2 = false;
       if (pend) {
         if (clm >= TIME_LIMIT) err |= ERR_OVERFLOW;
@@ -438,16 +541,10 @@ __global__ __launch_bounds__(64) void k_regblock(const uint64_t *__restrict__ DD
         nx_iss = ring_iss[sl];
         nx_idx = ring_idx[sl];
       }
-      continue;
-    }
-    // each die's next request must be in its ring before the next round
-    if (__ballot(on && admitted < total && loaded - admitted < 2)) top_up();
-    if (adm && admitted < total) {
-      const uint32_t sl = lane * RSTRIDE + admitted % RING;
-      nx_iss = ring_iss[sl];
-      nx_idx = ring_idx[sl];
     }
   }
+  if (lane == 0) s_round = 0;
+  block_sync();  // the other waves end
   if (nout) flush_out();
   if (nq) flush_q();
   if (on && total) dfnew[k] = free_at;
@@ -465,7 +562,7 @@ __global__ __launch_bounds__(64) void k_regblock(const uint64_t *__restrict__ DD
 hipError_t launch_regblock(const Geo &g, const uint64_t *DDw, const uint32_t *IX, const int64_t *issue_do,
                            const uint32_t *seg_start, const uint32_t *totals, DevState *st, CallCtl *ctl,
                            int64_t *complete, int64_t *dfnew, int64_t *cfnew, bool ref, hipStream_t s) {
-  hipLaunchKernelGGL(g.Dk <= 16 ? k_regblock<true> : k_regblock<false>, dim3(g.C), dim3(64), 0, s, DDw, IX,
+  hipLaunchKernelGGL(g.Dk <= 16 ? k_regblock<true> : k_regblock<false>, dim3(g.C), dim3(64 * RW), 0, s, DDw, IX,
                      issue_do, seg_start, totals, g, st, ctl, complete, dfnew, cfnew, ref ? 1 : 0);
   return hipGetLastError();
 }

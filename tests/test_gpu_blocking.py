@@ -215,3 +215,26 @@ def test_steady_stretches_break_anywhere(torch, geo):
         issue = t0 + np.cumsum(steps)
         addr = (np.uint64(wl.RANGE_BASE) + pg.astype(np.uint64) * np.uint64(wl.PAGE))
         check_call(torch, g, o, addr, issue, f"steady stretches {geo} call {call}")
+
+
+@pytest.mark.parametrize("geo", [(1, 1, 1, 3000), (2, 4, 1, 30_000), (3, 5, 1, 9000), (1, 16, 1, 100_000),
+                                 (1, 48, 1, 200_000), (2, 8, 1, 2048 * 7), (2, 2, 1, 2048)])
+def test_die_bound_stretches(torch, geo):
+    """Backlogged dies that the channel keeps up with: rounds repeat every
+    tR + xfer (closed form while every die's next request is issued in time),
+    up to exactly as many dies as the channel can carry and, in the tail, one
+    die alone; a second call continues from the clocks left behind."""
+    C, D, P, tR = geo
+    params = wl.geometry(C, D, P, t_read_ns=tR, flags=BLOCK)
+    pages = C * D * P * 64
+    g, o = pair(params, [(wl.RANGE_BASE, pages * wl.PAGE)])
+    rng = np.random.default_rng(tR + D)
+    for call in range(2):
+        n = 9000
+        pg = rng.integers(0, pages, n)
+        hot = rng.random(n) < 0.3
+        pg[hot] = C * D * rng.integers(0, 4, int(hot.sum()))
+        steps = rng.integers(0, 2 * tR // (C * D) + 2, n)
+        steps[rng.choice(n, 20, replace=False)] = 40 * tR
+        addr = np.uint64(wl.RANGE_BASE) + pg.astype(np.uint64) * np.uint64(wl.PAGE)
+        check_call(torch, g, o, addr, (call << 40) + np.cumsum(steps).astype(np.int64), f"die-bound {geo} call {call}")
