@@ -36,7 +36,10 @@ Layout make_layout(const Geo &g, int64_t n) {
     L.total = o;
     return L;
   }
-  int64_t te = (n + TARGET_TILES - 1) / TARGET_TILES;
+  // (with more than 1,024 die queues the die passes' LDS leaves one block per
+  // CU, so half the tiles fill the chip, and the per-tile arrays halve)
+  const int64_t tiles = g.K > 1024 ? TARGET_TILES / 2 : TARGET_TILES;
+  int64_t te = (n + tiles - 1) / tiles;
   te = ((te + CHUNK - 1) / CHUNK) * CHUNK;
   if (te < CHUNK) te = CHUNK;
   L.tile_elems = te;
@@ -129,13 +132,13 @@ static int ensure_device(hbf_model *m) {
   for (int k = 0; k < MAX_KEYS; k++) host[0].die_free[k] = NEG;
   for (int c = 0; c < MAX_CHANNELS; c++) host[0].chan_free[c] = NEG;
   host[0].sticky = 0;
-  host[0].pad = 0;
+  host[0].call_err = 0;
   host[0].gemv_origin = 0;
   host[0].vfree = NEG;
   host[0].vlast = 0;
   host[0].vburst = 0;
   host[0].vhave = 0;
-  host[0].vpad = 0;
+  host[0].scan_ctr = 0;
   if (hipMemcpy(m->st, host.data(), sizeof(DevState), hipMemcpyHostToDevice) != hipSuccess) return HBF_EHIP;
   // (for the largest die-queue count: models of any size may follow)
   if (set_lds_limits(MAX_KEYS) != hipSuccess) return HBF_EHIP;

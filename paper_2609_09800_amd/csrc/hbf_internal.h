@@ -84,7 +84,7 @@ struct DevState {
   int64_t die_free[MAX_KEYS];     // NEG = idle
   int64_t chan_free[MAX_CHANNELS];
   uint32_t sticky;                // sticky error bits
-  uint32_t pad;
+  uint32_t call_err;              // errors of the call in progress, from pass 1 (zero between calls)
   uint32_t ref_pend[MAX_KEYS];
   uint32_t ref_head[MAX_KEYS];
   uint32_t ref_off[MAX_KEYS];
@@ -98,7 +98,7 @@ struct DevState {
   uint64_t vlast;
   int64_t vburst;
   uint32_t vhave;
-  uint32_t vpad;
+  uint32_t scan_ctr;              // finished blocks of the tile scan (zero between launches)
 };
 
 // Completion cell of a refresh quantum that has not been served.

@@ -18,8 +18,8 @@
 //                  native path, and per (tile, die queue) the count and the
 //                  departure of the tile's last request from an idle die.
 //   k_tile_scan    per die queue, compose the tiles in order -> each tile's
-//                  incoming die clock and rank offset; new die clocks.
-//   k_key_scan     die-queue segment offsets; the time-cell grid.
+//                  incoming die clock and rank offset; new die clocks; then
+//                  die-queue segment offsets and the time-cell grid.
 //   k_die_scatter  pass 2: exact die-done times, written in die-queue order
 //                  (an LDS-staged stable multisplit) plus, per (channel,
 //                  time cell, die), the first die rank in that cell.
@@ -45,21 +45,6 @@
 
 namespace hbf {
 
-// ------------------------------------------------------------------ k_prologue
-
-__global__ void k_prologue(CallCtl *ctl) {
-  if (threadIdx.x == 0) {
-    ctl->err = 0;
-    ctl->n_in = 0;
-    ctl->G = 0;
-    ctl->shift = 0;
-    ctl->max_dd = NEG;
-    ctl->max_cpl = NEG;
-    ctl->cbase = 0;
-    ctl->wctr = 0;
-  }
-}
-
 // ------------------------------------------------------------------ k_die_reduce
 
 
@@ -83,9 +68,8 @@ __global__ __launch_bounds__(DBLK) void k_die_reduce(const uint64_t *__restrict_
                                                     RangeTable rt, int64_t tile_elems,
                                                     uint32_t *__restrict__ agg_cnt,
                                                     int64_t *__restrict__ agg_A,
-                                                    uint32_t *__restrict__ KR, CallCtl *ctl,
-                                                    const uint32_t *__restrict__ tin_base,
-                                                    const DevState *st) {
+                                                    uint32_t *__restrict__ KR,
+                                                    const uint32_t *__restrict__ tin_base, DevState *st) {
   extern __shared__ __align__(16) unsigned char smem[];
   LdsRanges *lr = (LdsRanges *)smem;
   const uint32_t K = g.K;
@@ -214,7 +198,7 @@ __global__ __launch_bounds__(DBLK) void k_die_reduce(const uint64_t *__restrict_
       agg_A[row + k] = c ? (int64_t)c * tR + amax[li] : NEG;
     }
   }
-  if (errb) atomicOr(&ctl->err, errb);
+  if (errb) atomicOr(&st->call_err, errb);
 }
 
 // Count pass of the refresh path: per tile, the in-range requests of each
@@ -241,164 +225,197 @@ __global__ __launch_bounds__(DBLK) void k_die_count(const uint64_t *__restrict__
   for (uint32_t li = threadIdx.x; li < K; li += DBLK) agg_cnt[(size_t)blockIdx.x * K + lkey(g, li)] = cnt[li];
 }
 
-// Refresh path: per die queue, the call-wide rank of each tile's first
-// request (exclusive prefix over tiles) and the queue's total.  One wave
-// per die queue, lane = contiguous group of tiles.
-__global__ __launch_bounds__(BLK) void k_tile_count(const uint32_t *__restrict__ agg_cnt, uint32_t nt, uint32_t K,
-                                                    uint32_t *__restrict__ tin_base,
-                                                    uint32_t *__restrict__ totals) {
-  const uint32_t lane = lane_id();
-  const uint32_t k = blockIdx.x * WAVES + (threadIdx.x >> 6);
-  if (k >= K) return;  // whole wave
-  const uint32_t per = (nt + 63) / 64;
-  const uint32_t ta = min(nt, lane * per), tb = min(nt, ta + per);
-  uint32_t C = 0;
-  for (uint32_t t = ta; t < tb; t++) C += agg_cnt[(size_t)t * K + k];
-  uint32_t base = wave_excl_sum(C);
-  if (lane == 63) totals[k] = base + C;
-  for (uint32_t t = ta; t < tb; t++) {
-    tin_base[(size_t)t * K + k] = base;
-    base += agg_cnt[(size_t)t * K + k];
+// ------------------------------------------------------------------ tile scans
+
+// Per die queue, the tiles in order: what enters each tile.  A block takes
+// TQ consecutive die queues, thread (queue, group) a contiguous group of
+// tiles, so a row of threads reads consecutive words of a tile's row; the
+// group's values are loaded at once and kept, the groups are composed by lane
+// moves within a wave and through LDS across waves, and each thread walks its
+// group again.  Latency-bound: with one wave per queue, its lanes reading
+// their tiles a row apart and twice, this took 9 us for 128 queues x 245
+// tiles, 20 for 512 x 489 and 45 for 2,048 x 367 (and a launch of its own for
+// the grid below); now 8, 9 and 12 with the grid.
+//   TS_COUNT    refresh path, after the count pass: the call-wide rank of
+//               each tile's first request and the queue's total;
+//   TS_REFRESH  refresh path: the clock entering each tile from the
+//               global-form tile maxima M_t: L = svc_sum(base) + max(f0, max
+//               of M before);
+//   TS_PLAIN    both at once: composition of (A, count) segments in order,
+//               (A1, c1) then (A2, c2) = (max(A2, A1 + c2*tR), c1 + c2), A =
+//               NEG when empty; a clock L entering a segment leaves as
+//               max(A, L + c*tR).
+// The last block of TS_PLAIN and TS_REFRESH then sets up the call's control
+// block: die-queue segment starts, in-range count, time-cell grid.
+enum { TS_COUNT, TS_PLAIN, TS_REFRESH };
+constexpr int TSBLK = 1024;
+constexpr int TQ = 16;              // die queues per block
+constexpr int TG = TSBLK / TQ;      // tile groups per queue
+constexpr int TPER = (TARGET_TILES + TG - 1) / TG;  // tiles per group at most
+
+// Segment offsets and the time-cell grid, by one block; err: the call's
+// errors so far.  totals and dfnew come from blocks of the same launch.
+DEVI void key_scan(const uint32_t *totals, const int64_t *dfnew, uint32_t K, uint32_t *__restrict__ seg_start,
+                   const int64_t *__restrict__ issue, uint32_t gmax, uint32_t s0, uint32_t err, CallCtl *ctl) {
+  __shared__ uint32_t sh[TSBLK / 64];
+  __shared__ int64_t s_dd;
+  if (threadIdx.x == 0) s_dd = NEG;
+  __syncthreads();
+  const uint32_t per = (K + TSBLK - 1) / TSBLK;
+  const uint32_t a = min(K, threadIdx.x * per), b = min(K, a + per);
+  uint32_t sum = 0;
+  int64_t dd = NEG;  // the latest die-done time of the call
+  for (uint32_t k = a; k < b; k++) {
+    const uint32_t t = agent_load32(&totals[k]);
+    sum += t;
+    if (t) dd = imax(dd, (int64_t)agent_load64((const uint64_t *)&dfnew[k]));
+  }
+  uint32_t ex;
+  const uint32_t tot = block_excl_sum<TSBLK / 64>(sum, &ex, sh);
+  for (uint32_t k = a; k < b; k++) {
+    seg_start[k] = ex;
+    ex += agent_load32(&totals[k]);
+  }
+  dd = wave_max(dd);
+  if (lane_id() == 0) atomicMax((long long *)&s_dd, (long long)dd);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    CallCtl c = {err, tot, 0, 0, s_dd, NEG, 0, 0};
+    if (s_dd >= TIME_LIMIT) c.err |= ERR_OVERFLOW;
+    if (tot != 0) {
+      c.cbase = issue[0];
+      const int64_t span = s_dd - c.cbase + 1;  // > 0: every die-done > issue[0]
+      uint32_t sh2 = s0;
+      while (sh2 < 62 && ((span - 1) >> sh2) + 1 > (int64_t)gmax) sh2++;
+      c.shift = sh2;
+      c.G = (uint32_t)(((span - 1) >> sh2) + 1);
+    }
+    *ctl = c;
   }
 }
 
-// Refresh path: per die queue, the clock entering each tile from the
-// global-form tile maxima M_t:  L = svc_sum(base) + max(f0, max of M before).
-__global__ __launch_bounds__(BLK) void k_tile_scan_ref(const int64_t *__restrict__ agg_A, uint32_t nt, Geo g,
-                                                       const DevState *st, const uint32_t *__restrict__ tin_base,
-                                                       const uint32_t *__restrict__ totals,
-                                                       int64_t *__restrict__ tin_L,
-                                                       int64_t *__restrict__ dfnew, CallCtl *ctl) {
-  if (agent_load32(&ctl->err)) return;
-  const uint32_t lane = lane_id(), K = g.K;
-  const uint32_t k = blockIdx.x * WAVES + (threadIdx.x >> 6);
-  if (k >= K) return;  // whole wave
-  const uint32_t per = (nt + 63) / 64;
-  const uint32_t ta = min(nt, lane * per), tb = min(nt, ta + per);
-  int64_t M = NEG;
-  for (uint32_t t = ta; t < tb; t++) M = imax(M, agg_A[(size_t)t * K + k]);
-  const int64_t inc = wave_incl_max(M);
-  int64_t run = __shfl_up(inc, 1);
-  if (lane == 0) run = NEG;
-  const int64_t f0 = st->die_free[k];
-  const uint32_t R = st->ref_pend[k];
-  if (lane == 63) {
-    const uint32_t tot = totals[k];
-    if (tot) {
-      const int64_t Lend = svc_sum(tot, R, g.tR, g.tQ) + imax(f0, inc);
-      dfnew[k] = Lend;
-      atomicMax((long long *)&ctl->max_dd, (long long)Lend);
-      if (Lend >= TIME_LIMIT) atomicOr(&ctl->err, ERR_OVERFLOW);
+template <int MODE>
+__global__ __launch_bounds__(TSBLK) void k_tile_scan(const uint32_t *__restrict__ agg_cnt,
+                                                     const int64_t *__restrict__ agg_A, uint32_t nt, Geo g,
+                                                     DevState *st, int64_t *__restrict__ tin_L, uint32_t *tin_base,
+                                                     uint32_t *totals, int64_t *dfnew,
+                                                     uint32_t *__restrict__ seg_start,
+                                                     const int64_t *__restrict__ issue, uint32_t gmax, uint32_t s0,
+                                                     CallCtl *ctl) {
+  __shared__ int64_t wA[TSBLK / 64][TQ];
+  __shared__ uint32_t wC[TSBLK / 64][TQ];
+  __shared__ uint32_t s_last;
+  const uint32_t K = g.K, t = threadIdx.x, lane = lane_id(), w = t >> 6;
+  const int64_t tR = g.tR;
+  if (MODE != TS_COUNT) {
+    const uint32_t err = st->call_err;  // of pass 1; the same for every block
+    if (err) {
+      if (blockIdx.x == 0 && t == 0) *ctl = CallCtl{err, 0, 0, 0, NEG, NEG, 0, 0};
+      return;
     }
   }
-  for (uint32_t t = ta; t < tb; t++) {
-    tin_L[(size_t)t * K + k] = svc_sum(tin_base[(size_t)t * K + k], R, g.tR, g.tQ) + imax(f0, run);
-    run = imax(run, agg_A[(size_t)t * K + k]);
+  const uint32_t k = blockIdx.x * TQ + (t & (TQ - 1)), grp = t / TQ;
+  const bool on = k < K;
+  const uint32_t per = (nt + TG - 1) / TG;  // at most TPER
+  const uint32_t ta = min(nt, grp * per), tb = min(nt, ta + per);
+  uint32_t c[TPER];
+  int64_t v[TPER];
+#pragma unroll
+  for (int q = 0; q < TPER; q++) {
+    const bool in = on && ta + q < tb;
+    const size_t at = in ? (size_t)(ta + q) * K + k : 0;
+    c[q] = in && MODE != TS_REFRESH ? agg_cnt[at] : 0u;
+    v[q] = in && MODE != TS_COUNT ? agg_A[at] : NEG;
   }
-}
-
-// Per die queue, compose the tiles in order.  One wave per die queue, lane g
-// holding a contiguous group of tiles: each lane folds its group, a wave
-// scan composes the groups, and each lane walks its group again writing the
-// clock and rank entering every tile.  Composition of (A, count) segments in
-// order: (A1, c1) then (A2, c2) = (max(A2, A1 + c2*tR), c1 + c2), A = NEG
-// when empty; a clock L entering a segment leaves as max(A, L + c*tR).
-__global__ __launch_bounds__(BLK) void k_tile_scan(const uint32_t *__restrict__ agg_cnt,
-                                                   const int64_t *__restrict__ agg_A, uint32_t nt,
-                                                   uint32_t K, int64_t tR, const DevState *st,
-                                                   int64_t *__restrict__ tin_L,
-                                                   uint32_t *__restrict__ tin_base,
-                                                   uint32_t *__restrict__ totals,
-                                                   int64_t *__restrict__ dfnew, CallCtl *ctl) {
-  if (agent_load32(&ctl->err)) return;
-  const uint32_t lane = lane_id();
-  const uint32_t k = blockIdx.x * WAVES + (threadIdx.x >> 6);
-  if (k >= K) return;  // whole wave
-  const uint32_t per = (nt + 63) / 64;
-  const uint32_t ta = min(nt, lane * per), tb = min(nt, ta + per);
+  int64_t f0 = NEG;
+  uint32_t R = 0;
+  if (MODE != TS_COUNT && on) f0 = st->die_free[k];
+  if (MODE == TS_REFRESH && on) R = st->ref_pend[k];
+  // the group's (A, C); a tile without requests of k leaves A as it is
   int64_t A = NEG;
   uint32_t C = 0;
-  for (uint32_t t = ta; t < tb; t++) {
-    const uint32_t c = agg_cnt[(size_t)t * K + k];
-    if (c) {
-      A = imax(agg_A[(size_t)t * K + k], A + (int64_t)c * tR);
-      C += c;
-    }
-  }
-  // inclusive scan over the lanes' groups
-  int64_t iA = A;
-  uint32_t iC = C;
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int64_t pA = __shfl_up(iA, d);
-    const uint32_t pC = __shfl_up(iC, d);
-    if (lane >= (uint32_t)d) {
-      iA = imax(iA, pA + (int64_t)iC * tR);
-      iC += pC;
+  for (int q = 0; q < TPER; q++) {
+    if (MODE == TS_REFRESH) {
+      A = imax(A, v[q]);
+    } else if (c[q]) {
+      if (MODE == TS_PLAIN) A = imax(v[q], A + (int64_t)c[q] * tR);
+      C += c[q];
     }
   }
-  int64_t xA = __shfl_up(iA, 1);
-  uint32_t xC = __shfl_up(iC, 1);
-  if (lane == 0) {
+  const int64_t tS = MODE == TS_PLAIN ? tR : 0;
+  // inclusive over the wave's groups of the same queue (16 lanes apart)
+#pragma unroll
+  for (int d = TQ; d < 64; d <<= 1) {
+    const int64_t pA = __shfl_up(A, d);
+    const uint32_t pC = __shfl_up(C, d);
+    if (lane >= (uint32_t)d) {
+      A = imax(A, pA + (int64_t)C * tS);
+      C += pC;
+    }
+  }
+  if (lane >= 64 - TQ) {
+    wA[w][lane & (TQ - 1)] = A;
+    wC[w][lane & (TQ - 1)] = C;
+  }
+  int64_t xA = __shfl_up(A, TQ);  // exclusive within the wave
+  uint32_t xC = __shfl_up(C, TQ);
+  if (lane < TQ) {
     xA = NEG;
     xC = 0;
   }
-  const int64_t f0 = st->die_free[k];
-  int64_t L = imax(xA, f0 + (int64_t)xC * tR);  // clock entering the lane's group
-  uint32_t base = xC;
-  if (lane == 63) {
-    const int64_t Lend = imax(iA, f0 + (int64_t)iC * tR);
-    totals[k] = iC;
-    dfnew[k] = Lend;
-    if (iC) {
-      atomicMax((long long *)&ctl->max_dd, (long long)Lend);
-      if (Lend >= TIME_LIMIT) atomicOr(&ctl->err, ERR_OVERFLOW);
+  __syncthreads();
+  int64_t pA = NEG;
+  uint32_t pC = 0;
+  for (uint32_t q = 0; q < w; q++) {
+    const uint32_t cq = wC[q][t & (TQ - 1)];
+    pA = imax(wA[q][t & (TQ - 1)], pA + (int64_t)cq * tS);
+    pC += cq;
+  }
+  const int64_t bA = imax(xA, pA + (int64_t)xC * tS);  // before the thread's group
+  const uint32_t bC = pC + xC;
+  if (on && t >= TSBLK - TQ) {  // the last group: the queue as a whole
+    const int64_t eA = imax(A, pA + (int64_t)C * tS);
+    const uint32_t eC = pC + C;
+    uint32_t tot = eC;
+    if (MODE == TS_REFRESH) tot = totals[k];
+    else agent_store32(&totals[k], tot);
+    if (MODE != TS_COUNT) {
+      const int64_t end = MODE == TS_PLAIN ? imax(eA, f0 + (int64_t)tot * tR)
+                                           : svc_sum(tot, R, tR, g.tQ) + imax(f0, eA);
+      agent_store64((uint64_t *)&dfnew[k], (uint64_t)end);
     }
   }
-  for (uint32_t t = ta; t < tb; t++) {
-    tin_L[(size_t)t * K + k] = L;
-    tin_base[(size_t)t * K + k] = base;
-    const uint32_t c = agg_cnt[(size_t)t * K + k];
-    if (c) L = imax(agg_A[(size_t)t * K + k], L + (int64_t)c * tR);
-    base += c;
-  }
-}
-
-// ------------------------------------------------------------------ k_key_scan
-
-// One block: die-queue segment starts, in-range count, time-cell grid.
-__global__ __launch_bounds__(BLK) void k_key_scan(const uint32_t *__restrict__ totals, uint32_t K,
-                                                  uint32_t *__restrict__ seg_start,
-                                                  const int64_t *__restrict__ issue, uint32_t gmax,
-                                                  uint32_t s0, CallCtl *ctl) {
-  __shared__ uint32_t sh[WAVES];
-  if (agent_load32(&ctl->err)) return;
-  const uint32_t per = (K + BLK - 1) / BLK;
-  const uint32_t a = threadIdx.x * per, b = min(K, a + per);
-  uint32_t s = 0;
-  for (uint32_t k = a; k < b; k++) s += totals[k];
-  uint32_t ex;
-  uint32_t tot = block_excl_sum<WAVES>(s, &ex, sh);
-  for (uint32_t k = a; k < b; k++) {
-    seg_start[k] = ex;
-    ex += totals[k];
-  }
-  if (threadIdx.x == 0) {
-    ctl->n_in = tot;
-    if (tot == 0) {
-      ctl->G = 0;
-      ctl->shift = 0;
-      ctl->cbase = 0;
-    } else {
-      const int64_t cbase = issue[0];
-      const int64_t span = ctl->max_dd - cbase + 1;  // > 0: every die-done > issue[0]
-      uint32_t sh2 = s0;
-      while (sh2 < 62 && ((span - 1) >> sh2) + 1 > (int64_t)gmax) sh2++;
-      ctl->cbase = cbase;
-      ctl->shift = sh2;
-      ctl->G = (uint32_t)(((span - 1) >> sh2) + 1);
+  if (on) {
+    int64_t L = MODE == TS_PLAIN ? imax(bA, f0 + (int64_t)bC * tR) : imax(f0, bA);
+    uint32_t base = bC;
+#pragma unroll
+    for (int q = 0; q < TPER; q++) {
+      if (ta + q >= tb) break;
+      const size_t at = (size_t)(ta + q) * K + k;
+      if (MODE == TS_REFRESH) {
+        tin_L[at] = svc_sum(tin_base[at], R, tR, g.tQ) + L;
+        L = imax(L, v[q]);
+        continue;
+      }
+      tin_base[at] = base;
+      base += c[q];
+      if (MODE == TS_PLAIN) {
+        tin_L[at] = L;
+        if (c[q]) L = imax(v[q], L + (int64_t)c[q] * tR);
+      }
     }
   }
+  if (MODE == TS_COUNT) return;
+  // the block that finishes last goes on (totals and dfnew were stored past
+  // the caches above; each wave's stores have left it before the count)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (t == 0) s_last = atomicAdd(&st->scan_ctr, 1u) == gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  if (t == 0) st->scan_ctr = 0;
+  key_scan(totals, dfnew, K, seg_start, issue, gmax, s0, 0, ctl);
 }
 
 // ------------------------------------------------------------------ k_die_scatter
@@ -838,13 +855,6 @@ DEVI int64_t wave_min(int64_t x) { return -wave_max(-x); }
 // published value lies in [NEG, 2^62)).
 DEVI uint64_t enc_time(int64_t x) { return (uint64_t)x + (uint64_t(1) << 62); }
 DEVI int64_t dec_time(uint64_t w) { return (int64_t)(w - (uint64_t(1) << 62)); }
-DEVI uint64_t agent_load64(const uint64_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-DEVI void agent_store64(uint64_t *p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Inclusive maximum within each half (32 lanes) of the wave: lanes 31 and
 // 63 end up holding the two halves' maxima.
 DEVI int64_t half_incl_max(int64_t x) {
@@ -1363,27 +1373,32 @@ DEVI void chan_units(WinLds &S, const DieOrder &D, const uint32_t *__restrict__ 
   if (errb) atomicOr(&ctl->err, errb);
 }
 
-template <int SL>
+// SL: die runs per channel of the bucket merge; WHAT: the grids this kernel
+// takes (it returns at once on others).  One kernel for both costs the bucket
+// merge 17 spilled registers, 6.28 ms against 6.03 on 2^28 requests; two
+// kernels cost a launch, 4 us.
+constexpr int GRID_BUCKET = 1, GRID_LANE = 2;
+template <int SL, int WHAT>
 __global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
-    const int64_t *__restrict__ DD, const uint32_t *__restrict__ LB, const uint32_t *__restrict__ seg_start,
-    const uint32_t *__restrict__ totals, Geo g, CallCtl *ctl, const DevState *st, uint64_t *WAGG, uint64_t *WINC,
-    int64_t *__restrict__ complete, int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  if (agent_load32(&ctl->err) || ctl->G == 0 || !grid_bucketable<SL>(g, ctl->shift)) return;
-  chan_units<false, SL>(*(WinLds *)smem, DieOrder{DD, nullptr, true}, LB, seg_start, totals, g, ctl, st, WAGG, WINC,
-                        complete, cfnew, gmax, n, 0);
-}
-
-__global__ __launch_bounds__(WIN_THREADS) void k_cell_sort(
     const int64_t *__restrict__ DD, const uint32_t *__restrict__ IX, const uint32_t *__restrict__ LB,
     const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ totals, Geo g, CallCtl *ctl,
     const DevState *st, uint64_t *WAGG, uint64_t *WINC, int64_t *__restrict__ complete,
     int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n, uint32_t sub_lg) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (agent_load32(&ctl->err) || ctl->G == 0 || grid_bucketable<SLOTS_MAX>(g, ctl->shift)) return;
-  chan_units<true, SLOTS_MAX>(*(WinLds *)smem, DieOrder{DD, IX, ctl->shift <= 32}, LB, seg_start, totals, g, ctl, st,
-                              WAGG, WINC, complete, cfnew, gmax, n, sub_lg);
+  if (agent_load32(&ctl->err) || ctl->G == 0) return;
+  WinLds &S = *(WinLds *)smem;
+  const DieOrder D = {DD, IX, ctl->shift <= 32};
+  const bool bucket = grid_bucketable<SL>(g, ctl->shift);
+  if constexpr ((WHAT & GRID_BUCKET) != 0)
+    if (bucket)
+      chan_units<false, SL>(S, D, LB, seg_start, totals, g, ctl, st, WAGG, WINC, complete, cfnew, gmax, n, sub_lg);
+  if constexpr ((WHAT & GRID_LANE) != 0)
+    if (!bucket)
+      chan_units<true, SLOTS_MAX>(S, D, LB, seg_start, totals, g, ctl, st, WAGG, WINC, complete, cfnew, gmax, n,
+                                  sub_lg);
 }
+// Calls of at least this many requests take a kernel per kind of grid.
+constexpr int64_t CHAN_SPLIT = int64_t(1) << 22;
 
 // ------------------------------------------------------------------ k_finalize
 
@@ -1397,7 +1412,10 @@ __global__ __launch_bounds__(BLK) void k_finalize(int64_t *__restrict__ complete
   if (err) {
     for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK)
       complete[i] = HBF_TIME_ERROR;
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&st->sticky, err);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      atomicOr(&st->sticky, err);
+      st->call_err = 0;
+    }
     return;
   }
   if (blockIdx.x != 0) return;
@@ -1500,10 +1518,10 @@ __global__ __launch_bounds__(BLK) void k_fill(int64_t *__restrict__ p, int64_t n
 
 // ------------------------------------------------------------------ launchers
 
-const char *const kKernelNames[] = {"k_prologue",  "k_die_reduce", "k_tile_scan", "k_key_scan",
-                                    "k_die_scatter", "k_cell_chan", "k_finalize", "k_small"};
-const int kNumTimedKernels = 8;
-constexpr int SMALL_SLOT = 7;  // k_small's timing slot
+const char *const kKernelNames[] = {"k_die_reduce", "k_tile_scan", "k_die_scatter", "k_cell_chan",
+                                    "k_finalize", "k_small"};
+const int kNumTimedKernels = 6;
+constexpr int SMALL_SLOT = 5;  // k_small's timing slot
 
 static size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
@@ -1554,10 +1572,14 @@ hipError_t launch_time_requests(const Geo &g, const RangeTable &rt, const Layout
   };
   hipError_t e;
   mark();
-  hipLaunchKernelGGL(k_prologue, dim3(1), dim3(64), 0, s, ctl);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  mark();
-  const dim3 key_waves((g.K + WAVES - 1) / WAVES);
+  // (the call's control block is set up by the tile scan; errors before it
+  // go to the model's call_err, which is zero between calls)
+  const dim3 tq((g.K + TQ - 1) / TQ);
+  auto tile_scan = [&](auto kfn) {
+    hipLaunchKernelGGL(kfn, tq, dim3(TSBLK), 0, s, agg_cnt, agg_A, Lo.nt, g, st, tin_L, tin_base, totals, dfnew, seg,
+                       issue, Lo.gmax, Lo.s0, ctl);
+    return hipGetLastError();
+  };
   if (refresh) {
     // count pass and per-tile rank bases first (timed with pass 1)
     const size_t lds = lds_die_count(g.K);
@@ -1568,28 +1590,18 @@ hipError_t launch_time_requests(const Geo &g, const RangeTable &rt, const Layout
       hipLaunchKernelGGL(k_die_count<false>, dim3(Lo.nt), dim3(DBLK), lds, s, addr, Lo.n, g, rt,
                          Lo.tile_elems, agg_cnt);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tile_count, key_waves, dim3(BLK), 0, s, agg_cnt, Lo.nt, g.K, tin_base, totals);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = tile_scan(k_tile_scan<TS_COUNT>)) != hipSuccess) return e;
   }
   {
     const size_t lds = lds_die_reduce(g.K);
     auto kfn = p2 ? (refresh ? k_die_reduce<true, true> : k_die_reduce<true, false>)
                   : (refresh ? k_die_reduce<false, true> : k_die_reduce<false, false>);
     hipLaunchKernelGGL(kfn, dim3(Lo.nt), dim3(DBLK), lds, s, addr, issue, Lo.n, complete, g, rt, Lo.tile_elems,
-                       agg_cnt, agg_A, KR, ctl, tin_base, st);
+                       agg_cnt, agg_A, KR, tin_base, st);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark();
-  if (refresh)
-    hipLaunchKernelGGL(k_tile_scan_ref, key_waves, dim3(BLK), 0, s, agg_A, Lo.nt, g, st, tin_base, totals, tin_L,
-                       dfnew, ctl);
-  else
-    hipLaunchKernelGGL(k_tile_scan, key_waves, dim3(BLK), 0, s, agg_cnt, agg_A, Lo.nt, g.K, g.tR, st, tin_L,
-                       tin_base, totals, dfnew, ctl);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  mark();
-  hipLaunchKernelGGL(k_key_scan, dim3(1), dim3(BLK), 0, s, totals, g.K, seg, issue, Lo.gmax, Lo.s0, ctl);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = refresh ? tile_scan(k_tile_scan<TS_REFRESH>) : tile_scan(k_tile_scan<TS_PLAIN>)) != hipSuccess) return e;
   mark();
   {
     const size_t lds = lds_die_scatter(g.K);
@@ -1615,22 +1627,29 @@ hipError_t launch_time_requests(const Geo &g, const RangeTable &rt, const Layout
     hipGetDevice(&dev);
     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     uint64_t *WAGG = WST, *WINC = WST + (size_t)Lo.gmax * g.C;
-    // (each returns at once when the grid is the other one's)
-    if (g.Dk <= SLOTS_MAX) {
-      hipLaunchKernelGGL(g.Dk <= 4 ? k_cell_chan<4> : g.Dk <= 8 ? k_cell_chan<8> : k_cell_chan<16>,
-                         dim3((uint32_t)ncu), dim3(WIN_THREADS), sizeof(WinLds), s, DD, LB, seg, totals, g, ctl, st,
-                         WAGG, WINC, complete, cfnew, Lo.gmax, (uint32_t)Lo.n);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+    auto chan = [&](auto kfn) {
+      hipLaunchKernelGGL(kfn, dim3((uint32_t)ncu), dim3(WIN_THREADS), sizeof(WinLds), s, DD, IX, LB, seg, totals, g,
+                         ctl, st, WAGG, WINC, complete, cfnew, Lo.gmax, (uint32_t)Lo.n,
+                         Lo.s0 < SUB_LG_MAX ? Lo.s0 : SUB_LG_MAX);
+      return hipGetLastError();
+    };
+    constexpr int BOTH = GRID_BUCKET | GRID_LANE;
+    if (g.Dk > SLOTS_MAX) {
+      e = chan(k_cell_chan<SLOTS_MAX, GRID_LANE>);
+    } else if (Lo.n < CHAN_SPLIT) {
+      e = chan(g.Dk <= 4 ? k_cell_chan<4, BOTH> : g.Dk <= 8 ? k_cell_chan<8, BOTH> : k_cell_chan<16, BOTH>);
+    } else {
+      e = chan(g.Dk <= 4   ? k_cell_chan<4, GRID_BUCKET>
+               : g.Dk <= 8 ? k_cell_chan<8, GRID_BUCKET> : k_cell_chan<16, GRID_BUCKET>);
+      if (e == hipSuccess) e = chan(k_cell_chan<SLOTS_MAX, GRID_LANE>);
     }
-    hipLaunchKernelGGL(k_cell_sort, dim3((uint32_t)ncu), dim3(WIN_THREADS), sizeof(WinLds), s, DD, IX, LB, seg,
-                       totals, g, ctl, st, WAGG, WINC, complete, cfnew, Lo.gmax, (uint32_t)Lo.n,
-                       Lo.s0 < SUB_LG_MAX ? Lo.s0 : SUB_LG_MAX);
+    if (e != hipSuccess) return e;
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark();
   {
-    int64_t blocks = (Lo.n + BLK - 1) / BLK;
-    if (blocks > 4096) blocks = 4096;
+    int64_t blocks = (Lo.n + BLK - 1) / BLK;  // (only a failed call needs more than one)
+    if (blocks > 256) blocks = 256;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(k_finalize, dim3((uint32_t)blocks), dim3(BLK), 0, s, complete, Lo.n, ctl, st, dfnew,
                        totals, cfnew, g.K, g.C);
@@ -1732,8 +1751,11 @@ hipError_t set_lds_limits(uint32_t K) {
   for (const void *f : fc)
     if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c)) != hipSuccess) return e;
   if ((e = set_lds_small()) != hipSuccess) return e;
-  const void *fw[] = {(const void *)k_cell_chan<4>, (const void *)k_cell_chan<8>, (const void *)k_cell_chan<16>,
-                      (const void *)k_cell_sort};
+  constexpr int BOTH = GRID_BUCKET | GRID_LANE;
+  const void *fw[] = {(const void *)k_cell_chan<4, BOTH>,        (const void *)k_cell_chan<8, BOTH>,
+                      (const void *)k_cell_chan<16, BOTH>,       (const void *)k_cell_chan<4, GRID_BUCKET>,
+                      (const void *)k_cell_chan<8, GRID_BUCKET>, (const void *)k_cell_chan<16, GRID_BUCKET>,
+                      (const void *)k_cell_chan<16, GRID_LANE>};
   for (const void *f : fw)
     if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(WinLds))) != hipSuccess)
       return e;
