@@ -364,7 +364,7 @@ typedef struct hbf_cache *hbf_cache_t;  /* opaque, owned by the library */
 /* Create an empty cache (allocates frames*12 bytes of device memory for up
  * to 63 frames, range_pages*8 + frames*2 bytes above; caches of 64 frames
  * or more over at most 2^26 range pages also hold the chunk state below,
- * range_pages*24 bytes and about 3.1 MiB;
+ * range_pages*16 bytes and 3.1 MiB or range_pages*6 bytes, at most 24 MiB;
  * synchronous). */
 int hbf_cache_create(uint32_t frames, uint32_t prefetch_pages, uint64_t range_pages, hbf_cache_t *out);
 void hbf_cache_destroy(hbf_cache_t cache);
@@ -384,16 +384,18 @@ int hbf_cache_access(hbf_cache_t cache, const uint64_t *dev_pages, int64_t n, ui
                      uint64_t *dev_pf_page, int64_t *dev_pf_src, int64_t pf_cap, int64_t *dev_counts,
                      void *stream);
 
-/* Accesses served together (default: frames/16 clamped to [16384, 262144]
- * for caches with chunk state, else 0).  A call is
- * cut into chunks of that many accesses.  Each chunk is first solved in
- * parallel as if nothing were evicted: an access faults only as the first
- * access of a page not resident when the chunk began, unless an earlier
- * fault at most prefetch_pages below it inserted the page.  That answer
- * is kept only if every hit and every prefetch candidate it found resident
- * is still within the last `frames` insertions at that moment, which makes
- * it exactly the FIFO answer.  Otherwise the chunk is served one access
- * after another.  The results do not depend on the chunk length.
+/* Accesses served together.  A call is cut into chunks.  Each is first
+ * solved in parallel as if nothing were evicted: an access faults only as
+ * the first access of a page not resident when the chunk began, unless an
+ * earlier fault at most prefetch_pages below it inserted the page.  That
+ * answer holds up to the first hit, or prefetch candidate found resident,
+ * that is no longer within the last `frames` insertions at that moment; so
+ * far it is exactly the FIFO answer and is kept, and the next chunk begins
+ * there (or, where hardly anything was kept, after a stretch served one
+ * access after another).  The chunk lengths follow from what was kept until
+ * a length is set here, and are that one from then on; get_chunk reports
+ * frames/16 clamped to [16384, 262144] for a cache with chunk state before,
+ * 0 for others.  The results do not depend on the chunk length.
  * 0 <= accesses <= 262144; a nonzero value needs chunk state (HBF_EINVAL
  * otherwise).  Host only. */
 int hbf_cache_set_chunk(hbf_cache_t cache, uint32_t accesses);
@@ -403,10 +405,9 @@ int hbf_cache_get_chunk(hbf_cache_t cache, uint32_t *accesses);
  * prefetch depths): configuration b has host_frames[b] frames and
  * host_prefetch[b] prefetch pages, starts empty, and serves all of
  * dev_pages[0..n).  dev_counts: int64[n_cfg][5], the five counters of
- * each.  1 <= n_cfg <= 65535.  Caches that have a default chunk length
- * (see hbf_cache_set_chunk) are served chunk by chunk with the smallest of
- * those lengths.  Allocates the caches' state for the call (about
- * range_pages*32 bytes per cache of 64 frames or more over at most 2^26
+ * each.  1 <= n_cfg <= 65535.  Caches that have chunk state
+ * are served chunk by chunk (see hbf_cache_set_chunk).  Allocates the
+ * caches' state for the call (about range_pages*30 bytes per cache of 64 frames or more over at most 2^26
  * range pages, range_pages*8 for larger ranges, frames*12 below 64 frames;
  * HBF_ENOMEM if that does not fit) and synchronises `stream` before
  * returning; returns HBF_EINVAL if some page was >= range_pages (counts

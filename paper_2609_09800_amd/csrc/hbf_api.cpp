@@ -620,9 +620,13 @@ struct hbf_cache {
   int64_t *status = nullptr;   // [0] status, [1] prefetch reads of the call
   int *dids = nullptr;
   uint32_t lmax = 0;           // chunk state allocated for chunks of up to lmax accesses
-  uint32_t chunk = 0;          // accesses per chunk; 0 = the sequential run alone
-  uint32_t epoch = 0;          // last chunk tag used
+  uint32_t chunk = 0;          // accesses per chunk as reported; 0 = the sequential run alone
+  bool asked = false;          // the caller set the chunk length
 };
+
+// status, the call's prefetch reads, then the barriers of the chunked solve;
+// zeroed by every call
+constexpr int64_t CACHE_STATUS_WORDS = 2 + CHUNK_GROUPS / 2;
 
 static bool cache_params_ok(uint32_t F, uint32_t d, uint64_t R) {
   return F >= 1 && F < (1u << 31) && d < F && d <= CACHE_MAX_PREFETCH && R >= 1 && R <= (uint64_t)N_LIMIT;
@@ -658,7 +662,7 @@ static int cache_alloc(const uint32_t *F, const uint32_t *d, const uint32_t *lma
     coff[b] = o;
     if (lmax[b]) {
       const size_t L = lmax[b];
-      o = up256(o + R * 8 * 3);           // at, lt, tt
+      o = up256(o + R * 8 * 2);           // at, tt
       o = up256(o + (L + 1) * 8);         // S
       o = up256(o + (L / 1024 + 1) * 8);  // bs
       o = up256(o + L * 4);               // seg
@@ -672,7 +676,7 @@ static int cache_alloc(const uint32_t *F, const uint32_t *d, const uint32_t *lma
   const size_t occfg = o;
   o = up256(o + sizeof(ChunkCfg) * n);
   const size_t ost = o;
-  o = up256(o + 16);
+  o = up256(o + CACHE_STATUS_WORDS * 8);
   void *p = nullptr;
   if (hipMalloc(&p, o) != hipSuccess) return HBF_ENOMEM;
   char *base = (char *)p;
@@ -702,9 +706,8 @@ static int cache_alloc(const uint32_t *F, const uint32_t *d, const uint32_t *lma
       const size_t L = lmax[b];
       q = coff[b];
       ccfg[b].at = (uint64_t *)(base + q);
-      ccfg[b].lt = ccfg[b].at + R;
-      ccfg[b].tt = ccfg[b].lt + R;
-      q = up256(q + R * 8 * 3);
+      ccfg[b].tt = ccfg[b].at + R;
+      q = up256(q + R * 8 * 2);
       ccfg[b].S = (uint64_t *)(base + q);
       q = up256(q + (L + 1) * 8);
       ccfg[b].bs = (uint64_t *)(base + q);
@@ -740,27 +743,6 @@ static int cache_alloc(const uint32_t *F, const uint32_t *d, const uint32_t *lma
   return HBF_OK;
 }
 
-// Serve pages[0..n) on the chunked caches ids[0..n_chunk): chunk after chunk,
-// each solved in parallel and checked, the sequential run for those that
-// fail; then the prefetched pages still pending.  *epoch: the last tag used.
-static bool run_chunks(const CacheCfg *dcfg, const ChunkCfg *dccfg, const int *ids, int n_chunk, uint32_t max_f,
-                       uint32_t max_d, uint64_t R, const uint64_t *pages, int64_t n, uint32_t chunk,
-                       uint32_t *epoch, uint8_t *hit, uint64_t *pf_page, int64_t *pf_src, int64_t pf_cap,
-                       int64_t *status, int64_t *n_pf, hipStream_t s) {
-  for (int64_t c0 = 0; c0 < n; c0 += chunk) {
-    if (*epoch >= 0xFFFFFF00u) {  // tags about to repeat: clear them
-      if (launch_chunk_clear(dccfg, ids, n_chunk, R, s) != hipSuccess) return false;
-      *epoch = 0;
-    }
-    ++*epoch;
-    const int64_t L = n - c0 < (int64_t)chunk ? n - c0 : (int64_t)chunk;
-    if (launch_cache_chunk(dcfg, dccfg, ids, n_chunk, max_f, max_d, R, pages, c0, L, *epoch, hit, pf_page, pf_src,
-                           pf_cap, status, n_pf, s) != hipSuccess)
-      return false;
-  }
-  return launch_cache_pending(dcfg, ids, n_chunk, max_f, status, s) == hipSuccess;
-}
-
 extern "C" {
 
 int hbf_cache_create(uint32_t frames, uint32_t prefetch_pages, uint64_t range_pages, hbf_cache_t *out) {
@@ -770,7 +752,7 @@ int hbf_cache_create(uint32_t frames, uint32_t prefetch_pages, uint64_t range_pa
   c->F = frames;
   c->d = prefetch_pages;
   c->R = range_pages;
-  c->lmax = frames > CACHE_LDS_MAX && range_pages <= CHUNK_MAX_R ? CHUNK_MAX : 0;
+  c->lmax = frames > CACHE_LDS_MAX && range_pages <= CHUNK_MAX_R ? std::max(CHUNK_MAX, chunk_limit(range_pages)) : 0;
   c->chunk = chunk_default(frames, range_pages);
   CacheAlloc al;
   int rc = cache_alloc(&c->F, &c->d, &c->lmax, 1, c->R, &al);
@@ -807,8 +789,9 @@ int hbf_cache_reset(hbf_cache_t c, void *stream) {
 }
 
 int hbf_cache_set_chunk(hbf_cache_t c, uint32_t accesses) {
-  if (!c || (accesses && (!c->dccfg || accesses > c->lmax))) return HBF_EINVAL;
+  if (!c || (accesses && (!c->dccfg || accesses > CHUNK_MAX))) return HBF_EINVAL;
   c->chunk = accesses;
+  c->asked = true;
   return HBF_OK;
 }
 
@@ -823,11 +806,13 @@ int hbf_cache_access(hbf_cache_t c, const uint64_t *pages, int64_t n, uint8_t *h
   if (!c || !counts || n < 0 || n > N_LIMIT || (n > 0 && (!pages || !hit))) return HBF_EINVAL;
   if ((pf_page == nullptr) != (pf_src == nullptr) || pf_cap < 0) return HBF_EINVAL;
   const hipStream_t s = (hipStream_t)stream;
-  if (launch_fill(c->status, 2, 0, s) != hipSuccess) return HBF_EHIP;
+  if (launch_fill(c->status, CACHE_STATUS_WORDS, 0, s) != hipSuccess) return HBF_EHIP;
   if (n > 0 && c->chunk) {
     if (launch_cache_check(pages, n, c->R, c->status, s) != hipSuccess ||
-        !run_chunks(c->dcfg, c->dccfg, c->dids, 1, c->F, c->d, c->R, pages, n, c->chunk, &c->epoch, hit, pf_page,
-                    pf_src, pf_page ? pf_cap : 0, c->status, c->status + 1, s))
+        launch_cache_chunks(c->dcfg, c->dccfg, c->dids, 1, c->R, pages, n, c->asked ? c->chunk : 0, hit, pf_page,
+                            pf_src, pf_page ? pf_cap : 0, c->status, c->status + 1, (uint32_t *)(c->status + 2),
+                            s) != hipSuccess ||
+        launch_cache_pending(c->dcfg, c->dids, 1, c->F, c->status, s) != hipSuccess)
       return HBF_EHIP;
   } else if (n > 0 && launch_cache_run(c->dcfg, c->dids, 1, c->F <= CACHE_LDS_MAX, c->F, c->R, pages, n, hit,
                                        pf_page, pf_src, pf_page ? pf_cap : 0, c->status, c->status + 1,
@@ -842,32 +827,25 @@ int hbf_cache_sweep(const uint32_t *frames, const uint32_t *prefetch, int n_cfg,
                     const uint64_t *pages, int64_t n, int64_t *counts, void *stream) {
   if (!frames || !prefetch || n_cfg < 1 || n_cfg > 65535 || !counts || n < 0 || n > N_LIMIT || (n > 0 && !pages))
     return HBF_EINVAL;
-  uint32_t max_f = 0, chunk = 0;
+  uint32_t max_f = 0;
   std::vector<uint32_t> lmax(n_cfg, 0);
   for (int b = 0; b < n_cfg; b++) {
     if (!cache_params_ok(frames[b], prefetch[b], range_pages)) return HBF_EINVAL;
     max_f = std::max(max_f, frames[b]);
-    const uint32_t cd = chunk_default(frames[b], range_pages);
-    if (cd) chunk = chunk ? std::min(chunk, cd) : cd;
+    if (chunk_default(frames[b], range_pages)) lmax[b] = chunk_limit(range_pages);
   }
-  // the chunked caches share one chunk length: the smallest of their defaults
-  for (int b = 0; b < n_cfg; b++)
-    if (chunk_default(frames[b], range_pages)) lmax[b] = chunk;
   CacheAlloc al;
   int rc = cache_alloc(frames, prefetch, lmax.data(), n_cfg, range_pages, &al);
   if (rc) return rc;
   const hipStream_t s = (hipStream_t)stream;
-  uint32_t max_lds = 0, max_seq = 0, max_chunk = 0, max_dchunk = 0;
+  uint32_t max_lds = 0, max_seq = 0, max_chunk = 0;
   for (int b = 0; b < n_cfg; b++) {
     if (frames[b] <= CACHE_LDS_MAX) max_lds = std::max(max_lds, frames[b]);
     else if (!lmax[b]) max_seq = std::max(max_seq, frames[b]);
-    else {
-      max_chunk = std::max(max_chunk, frames[b]);
-      max_dchunk = std::max(max_dchunk, prefetch[b]);
-    }
+    else max_chunk = std::max(max_chunk, frames[b]);
   }
   const int *ids_seq = al.dids + al.n_lds, *ids_chunk = al.dids + al.n_lds + al.n_seq;
-  bool ok = launch_fill(al.status, 2, 0, s) == hipSuccess &&
+  bool ok = launch_fill(al.status, CACHE_STATUS_WORDS, 0, s) == hipSuccess &&
             launch_cache_clear(al.dcfg, n_cfg, range_pages, max_f, s) == hipSuccess;
   if (ok && al.n_chunk) ok = launch_chunk_clear(al.dccfg, ids_chunk, al.n_chunk, range_pages, s) == hipSuccess;
   // the LDS-resident caches, the sequential device-memory ones, then the
@@ -879,10 +857,10 @@ int hbf_cache_sweep(const uint32_t *frames, const uint32_t *prefetch, int n_cfg,
     ok = launch_cache_run(al.dcfg, ids_seq, al.n_seq, false, max_seq, range_pages, pages, n, nullptr, nullptr,
                           nullptr, 0, al.status, nullptr, s) == hipSuccess;
   if (ok && n > 0 && al.n_chunk > 0) {
-    uint32_t epoch = 0;
     ok = (al.n_lds + al.n_seq > 0 || launch_cache_check(pages, n, range_pages, al.status, s) == hipSuccess) &&
-         run_chunks(al.dcfg, al.dccfg, ids_chunk, al.n_chunk, max_chunk, max_dchunk, range_pages, pages, n, chunk,
-                    &epoch, nullptr, nullptr, nullptr, 0, al.status, nullptr, s);
+         launch_cache_chunks(al.dcfg, al.dccfg, ids_chunk, al.n_chunk, range_pages, pages, n, 0, nullptr, nullptr,
+                             nullptr, 0, al.status, nullptr, (uint32_t *)(al.status + 2), s) == hipSuccess &&
+         launch_cache_pending(al.dcfg, ids_chunk, al.n_chunk, max_chunk, al.status, s) == hipSuccess;
   }
   ok = ok && launch_cache_report(al.dcfg, n_cfg, nullptr, al.status, counts, 5, s) == hipSuccess;
   // the temporary state is freed once the sweep has run

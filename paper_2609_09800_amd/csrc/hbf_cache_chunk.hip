@@ -16,16 +16,33 @@
 //    it was not resident when the chunk began.  A fault's insertions are
 //    numbered in page order after those of every earlier fault (a prefix
 //    sum over the chunk's accesses).
-// The answer is the true one iff every residency decision it took holds
-// under FIFO: each page's last hit, and each prefetch candidate found
-// resident, must still lie within the last F insertions at that moment.
-// The check runs on the device; a chunk that passes is committed (hit
-// flags, frame flags, evictions of prefetched pages never hit, counters),
-// one that fails is undone and served by the sequential wave.  Nothing
+// The answer is the true one as long as every residency decision it took
+// holds under FIFO: each hit's page, and each prefetch candidate found
+// resident, must lie within the last F insertions at that moment.  Up to the
+// first access whose decision fails the two processes insert the same pages
+// in the same order, so the accesses before it are committed (hit flags,
+// frame flags, evictions of prefetched pages never hit, counters), the
+// insertions from it on are undone, and the next chunk begins there.  Nothing
 // scales with the range: per-page state is tagged with the chunk's epoch.
+//
+// One cooperative launch serves a whole call: a group of workgroups per
+// cache, with a barrier of the group between the steps of a chunk.  Chunks
+// are as long as their checks let them be: doubled while they pass, cut to
+// twice what was committed when one does not, and where next to nothing is,
+// one wave takes a stretch access by access.  What bounds a chunk is the chain
+// of its eight steps -- a barrier of 256 workgroups is 9 us, of one workgroup
+// nothing -- and the longest segment of its walk.  1.94 M accesses of the MoE
+// stream, prefetch 7 (seven launches a chunk of 110 K accesses before, and a
+// chunk that failed its check served access by access):
+//   frames 1.77 M  1,596 -> 500 us      frames 300 K   8,360 -> 720 us
+//   frames 1.0 M  27,900 -> 2,330 us    frames 4,000   9,180 -> 620 us
+// and 64 accesses 57 -> 47 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
+#include "hbf_cache_run.h"
 #include "hbf_internal.h"
 
 namespace hbf {
@@ -33,13 +50,6 @@ namespace hbf {
 namespace {
 
 constexpr uint32_t NONE32 = 0xFFFFFFFFu;
-
-template <typename T>
-using gptr = __attribute__((address_space(1))) T *;
-template <typename T>
-__device__ __forceinline__ T ldr(const T *p) {
-  return __hip_atomic_load((gptr<const T>)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ uint32_t rdl(uint32_t v, uint32_t l) {
@@ -63,72 +73,243 @@ __device__ __forceinline__ int64_t wave_sum(int64_t v) {
 }
 
 struct Tags {
-  uint64_t a, t;  // first access (~epoch), last access and insertion time (epoch)
+  uint64_t a, t;  // first access (~epoch), insertion time (epoch)
   __device__ explicit Tags(uint32_t epoch) : a((uint64_t)(~epoch) << 32), t((uint64_t)epoch << 32) {}
 };
 constexpr uint64_t HI = 0xFFFFFFFF00000000ull;
 
-}  // namespace
 
-// Tags of the chunk's first and last access per page; counts cleared.
-__global__ __launch_bounds__(256) void k_chunk_tag(const CacheCfg *__restrict__ cfgs, const ChunkCfg *__restrict__ ccs,
-                                                   const int *ids, const uint64_t *__restrict__ pages, int64_t L,
-                                                   uint32_t epoch, const int64_t *status, const int64_t *n_pf) {
-  if (ldr(status)) return;
-  const int id = ids[blockIdx.y];
-  const ChunkCfg cc = ccs[id];
-  const Tags tg(epoch);
-  for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < L; j += (int64_t)gridDim.x * 256) {
-    const uint64_t p = pages[j];
-    atomicMin((unsigned long long *)&cc.at[p], (unsigned long long)(tg.a | (uint64_t)j));
-    atomicMax((unsigned long long *)&cc.lt[p], (unsigned long long)(tg.t | (uint64_t)j));
-    cc.S[j] = 0;
+constexpr int CBLK = 1024;          // threads per workgroup
+constexpr int CWAVES = CBLK / 64;
+constexpr int64_t SCAN = CBLK;      // accesses per piece of the prefix sum, one per thread
+constexpr uint32_t SPIN_MAX = 1u << 24;
+// A chunk of which fewer accesses than this are committed costs more than
+// taking them one after another (about 0.1 us each).
+constexpr uint32_t SEQ_TRY = 1024;
+// A chunk most of whose candidates lie within d pages of one first accessed
+// later (7 of 16; half of them is the most there can be) is a scattered
+// working set seen for the first time.  Its segments are long, and their
+// groups of 64 pages cost 5 us each in turn; an eighth of it has short ones,
+// and makes most of the rest resident: 200,000 accesses to 50,000 pages,
+// prefetch 7, 4.3 ms whole and 0.61 ms so.  With fewer such candidates
+// than this the chunk is taken as it is.
+constexpr uint32_t DENSE_MIN = 4096;
+constexpr uint32_t SEQ_MIN = 4096, SEQ_MAX = 1u << 17;
+
+// The workgroups of one group: this one's number, how many, and their
+// barrier (a counter that only grows, zero at the launch).
+struct Group {
+  uint32_t b, nb;
+  uint32_t *bar;
+  uint32_t target;
+  int64_t *status;
+  // Every store of the group before is visible to every load after.  False
+  // (bounded wait, never expected) ends the kernel with HBF_EINTERNAL.
+  __device__ bool sync() {
+    __shared__ uint32_t s_ok;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    target += nb;
+    if (nb == 1) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // atomics went past the L1
+      return true;
+    }
+    if (threadIdx.x == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t spin = 0;
+      while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target && ++spin < SPIN_MAX)
+        __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      s_ok = spin < SPIN_MAX;
+      if (!s_ok) st(status, (int64_t)HBF_EINTERNAL);
+    }
+    __syncthreads();
+    const bool ok = s_ok != 0;
+    return ok;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  // the group's threads over [0, n)
+  __device__ int64_t first() const { return (int64_t)b * CBLK + threadIdx.x; }
+  __device__ int64_t step() const { return (int64_t)nb * CBLK; }
+};
+
+// Tags of the chunk's first access per page; counts cleared.
+__device__ __forceinline__ void chunk_tag(const Group &gr, const ChunkCfg &cc, const uint64_t *__restrict__ pages,
+                                          int64_t L, uint32_t epoch, const Tags &tg) {
+  for (int64_t j = gr.first(); j < L; j += gr.step()) {
+    atomicMin((unsigned long long *)&cc.at[pages[j]], (unsigned long long)(tg.a | (uint64_t)j));
+    cc.S[j] = 0;
+    if (j % SCAN == 0) cc.bs[j / SCAN] = 0;
+  }
+  if (gr.b == 0 && threadIdx.x == 0) {
     cc.S[L] = 0;
     cc.ctl->nseg = 0;
-    cc.ctl->valid = 1;
+    cc.ctl->loose[epoch & 1] = 0;  // (the other one may still be read)
+    cc.ctl->good = (uint32_t)L;
     cc.ctl->lost_old = 0;
-    cc.ctl->I0 = ldr(&cfgs[id].ctl->ins);
-    cfgs[id].ctl->pend = 0;  // recounted once the call's chunks have run
-    cc.ctl->npf0 = (id == ids[0] && n_pf) ? ldr(n_pf) : 0;
   }
 }
 
-// Segment starts: candidates with no candidate among the d pages below.
-__global__ __launch_bounds__(256) void k_chunk_starts(const CacheCfg *__restrict__ cfgs,
-                                                      const ChunkCfg *__restrict__ ccs, const int *ids,
-                                                      const uint64_t *__restrict__ pages, int64_t L, uint32_t epoch,
-                                                      const int64_t *status) {
-  if (ldr(status)) return;
-  const int id = ids[blockIdx.y];
-  const CacheCfg c = cfgs[id];
-  const ChunkCfg cc = ccs[id];
-  const Tags tg(epoch);
-  const int64_t lim = ldr(&cc.ctl->I0) - (int64_t)c.F;  // resident at the start iff pins >= lim
-  const int64_t span = ((L + 255) / 256) * 256;
-  for (int64_t j0 = (int64_t)blockIdx.x * 256; j0 < span; j0 += (int64_t)gridDim.x * 256) {
-    const int64_t j = j0 + threadIdx.x;
-    bool start = false;
-    uint64_t q_start = 0;
+// Access j is a fault of `cnt` insertions: its word of the prefix sums
+// (insertions << 32 | faults).
+__device__ __forceinline__ void set_fault(const ChunkCfg &cc, uint32_t j, uint32_t cnt) {
+  cc.S[j] = ((uint64_t)cnt << 32) | 1u;
+}
+
+// A run: accesses j0, j0 + 1, ... to candidate pages q0, q0 + 1, ... (a
+// scan).  If no candidate lies within d pages below q0, its faults are every
+// (d + 1)-th access, so the walk can begin again at any multiple of d + 1
+// pages into it.  It does every split_pages(d) pages (a multiple of a wave's
+// 64 as well), up to SPLIT_MAX of them, each entry an own segment: a segment
+// holds its first page (26 bits) and its split's number.  Without them a
+// chunk waits for its longest scan, 1.1 us per 64 pages.
+constexpr uint32_t SPLIT_SHIFT = 26, SPLIT_MAX = 14;
+static_assert(CHUNK_MAX_R <= uint64_t(1) << SPLIT_SHIFT && SPLIT_MAX < 64, "a segment entry is one word");
+__device__ __forceinline__ uint32_t split_pages(uint32_t d) {
+  uint32_t p = 64, m = d + 1;  // lcm(64, d + 1)
+  while (p % m) p += 64;
+  return p * ((511 + p) / p);
+}
+
+// Segment starts: candidates with no candidate among the d pages below (not
+// resident at the chunk's start: pins < lim), and the splits of runs.  Each
+// workgroup takes consecutive pieces of CBLK accesses; a run entering its
+// first is followed back as far as its splits reach.  Without prefetch every candidate is a
+// fault of its own and nothing is left to walk.
+__device__ __forceinline__ void chunk_starts(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+                                             const uint64_t *__restrict__ pages, int64_t L, uint64_t R, int64_t lim,
+                                             uint32_t epoch, const Tags &tg) {
+  __shared__ int s_brk[CWAVES];
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6, d = c.d;
+  auto candidate = [&](int64_t j, uint64_t p) { return cc.at[p] == (tg.a | (uint64_t)j) && c.pins[p] < lim; };
+  if (d == 0) {
+    for (int64_t j = gr.first(); j < L; j += gr.step()) {
+      const uint64_t p = pages[j];
+      const bool f = candidate(j, p);
+      const uint64_t m = __ballot(f);
+      if (f) {
+        cc.tt[p] = tg.t | (uint64_t)j;
+        cc.S[j] = (uint64_t(1) << 32) | 1u;
+        if (lane == ctz64(m))  // (a wave's accesses lie in one piece)
+          atomicAdd((unsigned long long *)&cc.bs[j / SCAN], (unsigned long long)(((uint64_t(1) << 32) | 1u) * popc(m)));
+      }
+    }
+    return;
+  }
+  // first access of the nearest candidate among the d pages below p (NONE32: none)
+  auto before = [&](uint64_t p) {
+    const uint32_t m = (uint32_t)min((uint64_t)d, p);
+    for (uint32_t k0 = 1; k0 <= m; k0 += 4) {
+      uint64_t a[4];
+      int64_t x[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++) {
+        const uint64_t q = p - min(k0 + u, m);
+        a[u] = cc.at[q];
+        x[u] = c.pins[q];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++)
+        if ((a[u] & HI) == tg.a && x[u] < lim) return (uint32_t)a[u];
+    }
+    return NONE32;
+  };
+  auto is_start = [&](uint64_t p) { return before(p) == NONE32; };
+  // A segment start with no candidate among the d pages above either is a
+  // segment of its own: resolved here, a lane each, where scattered accesses
+  // would keep a wave each busy (10,000 of them 430 -> 133 us).
+  auto alone = [&](uint64_t p, uint32_t j) {
+    const uint32_t m = (uint32_t)min((uint64_t)d, R - 1 - p);
+    uint64_t ins = 1;  // pages of p .. p + d not resident
+    for (uint32_t k0 = 1; k0 <= m; k0 += 4) {
+      uint64_t a[4];
+      int64_t x[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++) {
+        const uint64_t q = p + min(k0 + u, m);
+        a[u] = cc.at[q];
+        x[u] = c.pins[q];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++) {
+        if (k0 + u > m || x[u] >= lim) continue;
+        if ((a[u] & HI) == tg.a) return false;
+        ins |= uint64_t(1) << (k0 + u);
+      }
+    }
+    uint32_t cnt = 0;
+    for (; ins; ins &= ins - 1) cc.tt[p + ctz64(ins)] = tg.t | (uint64_t)cnt++ << 24 | j;
+    set_fault(cc, j, cnt);
+    return true;
+  };
+  // whether access j goes on from access j - 1 in a run
+  auto linked = [&](int64_t j) {
+    if (j <= 0 || j >= L) return false;
+    const uint64_t p = pages[j], p1 = pages[j - 1];
+    return p == p1 + 1 && candidate(j, p) && candidate(j - 1, p1);
+  };
+  // the last access of this piece's at or before the thread's that does not
+  // go on from its predecessor (-1: none); all: the piece's last one
+  auto last_break = [&](int64_t j, bool brk, int &all) {
+    int x = brk ? (int)j : -1;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= (uint32_t)o) x = max(x, y);
+    }
+    if (lane == 63) s_brk[w] = x;
+    __syncthreads();
+    all = -1;
+    for (int i = 0; i < CWAVES; i++) {
+      if (i < (int)w) x = max(x, s_brk[i]);
+      all = max(all, s_brk[i]);
+    }
+    __syncthreads();
+    return x;
+  };
+  const uint32_t W = split_pages(d);
+  const uint32_t splits = min(SPLIT_MAX, (uint32_t)(7 * CBLK) / W);  // a run is followed back 7 pieces
+  const int64_t per = ((L + CBLK - 1) / CBLK + gr.nb - 1) / gr.nb * CBLK;
+  const int64_t a0 = (int64_t)gr.b * per, a1 = min(L, a0 + per);
+  int in = -1;  // start of the run that the piece's first access goes on from (-1: not known)
+  for (int64_t c0 = a0; c0 < a1; c0 += CBLK) {
+    const int64_t j = c0 + threadIdx.x;
+    const bool lk = linked(j);
+    int all = -1;
+    int run = last_break(j, !lk, all);
+    if (c0 == a0 && __syncthreads_or(threadIdx.x == 0 && lk)) {
+      int back = -1;
+      for (int64_t b0 = c0 - CBLK; b0 >= 0 && b0 >= c0 - 7 * CBLK && back < 0; b0 -= CBLK)
+        last_break(b0 + threadIdx.x, !linked(b0 + threadIdx.x), back);
+      in = back;
+    }
+    if (run < 0) run = in;
+    if (all >= 0) in = all;  // for the next piece
+    bool start = false, loose = false, late = false;
+    uint32_t entry = 0;
     if (j < L) {
       const uint64_t p = pages[j];
-      if (cc.at[p] == (tg.a | (uint64_t)j) && c.pins[p] < lim) {
-        start = true;
-        for (uint32_t k = 1; k <= c.d && k <= p; k++) {
-          const uint64_t q = p - k;
-          if ((cc.at[q] & HI) == tg.a && c.pins[q] < lim) {
-            start = false;
-            break;
-          }
+      if (lk) {
+        const uint32_t o = run < 0 ? 1u : (uint32_t)((int)j - run);  // pages into the run
+        if (o % W == 0 && o / W <= splits && is_start(pages[run])) {
+          start = true;
+          entry = (uint32_t)p | (o / W) << SPLIT_SHIFT;
         }
+      } else if (candidate(j, p)) {
+        const uint32_t b = before(p);
+        loose = true;
+        start = b == NONE32 && !alone(p, (uint32_t)j);
+        entry = (uint32_t)p;
+        late = b != NONE32 && b > (uint32_t)j;
       }
-      if (start) q_start = p;
     }
-    const uint32_t k = wave_append(&cc.ctl->nseg, start);  // every lane of the wave, converged
-    if (start && k < cc.Lmax) cc.seg[k] = (uint32_t)q_start;
+    const uint64_t um = __ballot(loose), lm = __ballot(late);
+    if (um && lane == 0)
+      atomicAdd((unsigned long long *)&cc.ctl->loose[epoch & 1], (unsigned long long)popc(lm) << 32 | popc(um));
+    const uint32_t k = wave_append(&cc.ctl->nseg, start);
+    if (start && k < cc.Lmax) cc.seg[k] = entry;
   }
 }
+}  // namespace
 
 // One wave per segment: faults, insertion times, per-fault insertion
 // counts and each insertion's rank within its fault, all written as plain
@@ -140,7 +321,7 @@ struct Walk {
   uint32_t pa;      // previous group: this lane's first-access time
   uint64_t open;    // previous group: faults whose windows reach this group
   uint32_t pcnt;    // previous group: insertions so far of this lane's open fault
-  uint32_t lastA;   // the largest first-access time among the segment's candidates so far
+  uint32_t lastA;   // previous group: the largest first-access time among its candidates
   bool hasA;
 };
 
@@ -164,6 +345,34 @@ __device__ __forceinline__ bool walk_group(Walk &w, uint64_t base, uint64_t at_c
   const bool nonres = inR && pin_c < lim;
   const bool cand = a != NONE32 && nonres;
   const uint64_t cm = __ballot(cand);
+  const uint32_t af0 = rdl(a, 0);
+  if (cm == ~0ull && !__ballot(a != af0 + lane) && popc(w.open) <= 1 && !(w.hasA && w.lastA >= af0) &&
+      base + 64 < R && base - w.lastc <= d) {
+    // a scan's middle: every (d + 1)-th page is a fault, beginning after the
+    // window of the one that reaches in
+    const uint32_t m = d + 1;
+    uint32_t x = 0, g = 0, ag = 0, c0 = 0;
+    if (w.open) {
+      g = ctz64(w.open);
+      x = g + m - 64;
+      ag = rdl(w.pa, g);
+      c0 = rdl(w.pcnt, g);
+    }
+    const uint32_t q = (((lane - x) & 0xFFu) * (65536u / m + 1)) >> 16;  // (lane - x) / m from lane x on
+    const uint32_t f = x + q * m;
+    const bool in = lane >= x;
+    if (x && lane == g) set_fault(cc, w.pa, c0 + x);
+    const bool flt = in && lane == f, whole = lane + d < 64;
+    if (flt && whole) set_fault(cc, a, m);
+    cc.tt[r] = tg.t | ((uint64_t)(in ? lane - f : c0 + lane) << 24) | (in ? af0 + f : ag);
+    w.open = __ballot(flt && !whole);
+    w.pa = a;
+    w.pcnt = 64 - lane;
+    w.lastc = base + 63;
+    w.lastA = af0 + 63;
+    w.hasA = true;
+    return false;
+  }
   // the segment continues while candidates are at most d pages apart
   const uint64_t below = cm & lt;
   const uint64_t prevpos = below ? base + 63 - (uint64_t)__builtin_clzll(below) : w.lastc;
@@ -172,7 +381,8 @@ __device__ __forceinline__ bool walk_group(Walk &w, uint64_t base, uint64_t at_c
   if (segc) w.lastc = base + 63 - (uint64_t)__builtin_clzll(segc);
   const bool in_ext = inR && r <= w.lastc + d;
   const bool last = !(w.lastc + d >= base + 64 && base + 64 < R);
-  // do the segment's candidates so far have increasing first-access times?
+  // do the candidates of this group and the one before it (none further away
+  // matters, d < 64) have increasing first-access times?
   const bool sc = (segc >> lane) & 1;
   const uint64_t sbelow = segc & lt;
   const uint32_t apl = (uint32_t)__shfl((int)a, sbelow ? 63 - __builtin_clzll(sbelow) : lane);
@@ -217,25 +427,19 @@ __device__ __forceinline__ bool walk_group(Walk &w, uint64_t base, uint64_t at_c
     for (uint64_t m = w.open; m; m &= m - 1) {
       const uint32_t g = ctz64(m);
       const uint32_t ag = rdl(w.pa, g);
-      rem &= ~__ballot(lane + 64 - g <= d && ag < a);
+      const bool near = lane + 64 - g <= d;
+      rem &= ~__ballot(near && ag < a);
+      if (near) tau = ag < tau ? ag : tau;
     }
     while (rem) {
       const uint32_t f = ctz64(rem);
       fm |= 1ull << f;
       const uint32_t af = rdl(a, f);
       rem &= ~(1ull << f);
-      rem &= ~__ballot(lane > f && lane - f <= d && af < a);
-    }
-    // insertion time: the earliest fault whose window holds this page
-    for (uint64_t m = w.open; m; m &= m - 1) {
-      const uint32_t g = ctz64(m);
-      const uint32_t ag = rdl(w.pa, g);
-      if (lane + 64 - g <= d) tau = ag < tau ? ag : tau;
-    }
-    for (uint64_t m = fm; m; m &= m - 1) {
-      const uint32_t f = ctz64(m);
-      const uint32_t af = rdl(a, f);
-      if (lane >= f && lane - f <= d) tau = af < tau ? af : tau;
+      const bool near = lane >= f && lane - f <= d;
+      rem &= ~__ballot(near && af < a);
+      // insertion time: the earliest fault whose window holds this page
+      if (near) tau = af < tau ? af : tau;
     }
     ins = in_ext && tau != NONE32 && nonres;
     for (uint64_t m = w.open; m; m &= m - 1) {  // windows that end in this group
@@ -264,7 +468,7 @@ __device__ __forceinline__ bool walk_group(Walk &w, uint64_t base, uint64_t at_c
       }
     }
   }
-  // the largest first-access time among the segment's candidates
+  // the largest first-access time among the group's candidates
   if (segc) {
     uint32_t mx = sc ? a : 0;
     if (mono) {
@@ -276,12 +480,12 @@ __device__ __forceinline__ bool walk_group(Walk &w, uint64_t base, uint64_t at_c
       }
       mx = rdl(mx, 0);
     }
-    w.lastA = w.hasA && w.lastA > mx ? w.lastA : mx;
+    w.lastA = mx;
     w.hasA = true;
   }
   // per-fault counts (packed: insertions << 32 | 1) and the page words
-  if (fin_prev) cc.S[w.pa] = ((uint64_t)ncnt << 32) | 1u;
-  if (fin_cur) cc.S[a] = ((uint64_t)cnt << 32) | 1u;
+  if (fin_prev) set_fault(cc, w.pa, ncnt);
+  if (fin_cur) set_fault(cc, a, cnt);
   if (ins) cc.tt[r] = tg.t | ((uint64_t)rank << 24) | tau;
   w.pa = a;
   w.open = nopen;
@@ -290,27 +494,26 @@ __device__ __forceinline__ bool walk_group(Walk &w, uint64_t base, uint64_t at_c
 }
 }  // namespace
 
-__global__ __launch_bounds__(256) void k_chunk_walk(const CacheCfg *__restrict__ cfgs, const ChunkCfg *__restrict__ ccs,
-                                                    const int *ids, uint64_t R, uint32_t epoch,
-                                                    const int64_t *status) {
-  if (ldr(status)) return;
-  const int id = ids[blockIdx.y];
-  const CacheCfg c = cfgs[id];
-  const ChunkCfg cc = ccs[id];
-  const Tags tg(epoch);
+namespace {
+__device__ __forceinline__ void chunk_walk(const Group &gr, const CacheCfg &c, const ChunkCfg &cc, uint64_t R,
+                                           int64_t lim, const Tags &tg) {
   const uint32_t lane = lane_id(), d = c.d;
-  const int64_t lim = ldr(&cc.ctl->I0) - (int64_t)c.F;
-  const uint32_t nseg_all = ldr(&cc.ctl->nseg);
+  const uint32_t nseg_all = ld(&cc.ctl->nseg);
   const uint32_t nseg = nseg_all < cc.Lmax ? nseg_all : cc.Lmax;
+  const uint32_t W = split_pages(d), splits = min(SPLIT_MAX, (uint32_t)(7 * CBLK) / W);
   // page state, loaded unconditionally (addresses clamped into the range;
   // lanes past the end are masked when the group is resolved)
   const gptr<const uint64_t> atg = (gptr<const uint64_t>)cc.at;
   const gptr<const int64_t> ping = (gptr<const int64_t>)c.pins;
   auto at_of = [&](uint64_t base) { return atg[base + lane < R ? base + lane : R - 1]; };
   auto pin_of = [&](uint64_t base) { return ping[base + lane < R ? base + lane : R - 1]; };
-  for (uint32_t si = blockIdx.x * 4 + threadIdx.x / 64; si < nseg; si += gridDim.x * 4) {
-    const uint64_t s = ldr(&cc.seg[si]);
+  // (consecutive segments to different workgroups)
+  for (uint32_t si = threadIdx.x / 64 * gr.nb + gr.b; si < nseg; si += gr.nb * CWAVES) {
+    const uint32_t entry = ld(&cc.seg[si]), split = entry >> SPLIT_SHIFT;
+    const uint64_t s = entry & ((1u << SPLIT_SHIFT) - 1);
     Walk w{s, NONE32, 0, 0, 0, false};
+    uint32_t as = 0;                 // first access of page s
+    bool run = split < splits;       // pages s .. so far are a run, which the next split may take on
     // the next four groups in flight
     uint64_t a0 = at_of(s), a1 = at_of(s + 64), a2 = at_of(s + 128), a3 = at_of(s + 192);
     int64_t p0 = pin_of(s), p1 = pin_of(s + 64), p2 = pin_of(s + 128), p3 = pin_of(s + 192);
@@ -325,219 +528,359 @@ __global__ __launch_bounds__(256) void k_chunk_walk(const CacheCfg *__restrict__
       p2 = p3;
       a3 = at_of(base + 256);
       p3 = pin_of(base + 256);
-      if (walk_group(w, base, at_c, pin_c, R, d, lim, tg, cc)) break;
+      const bool end = walk_group(w, base, at_c, pin_c, R, d, lim, tg, cc);
+      if (end) break;
+      if (run) {
+        if (base == s) as = rdl((uint32_t)at_c, 0);
+        const uint32_t o = (uint32_t)(base - s);
+        run = !__ballot(!((at_c & HI) == tg.a && pin_c < lim && (uint32_t)at_c == as + o + lane));
+        // (the split's page is the first of the next group)
+        if (run && o + 64 == W) {
+          if (__ballot(lane == 0 && (a0 & HI) == tg.a && p0 < lim && (uint32_t)a0 == as + W)) break;
+          run = false;
+        }
+      }
     }
   }
 }
 
-// Exclusive scan of the packed per-access counts in two launches: the sum
-// of each 1,024 accesses, then each block's scan offset by the sums before it.
-namespace {
-__device__ __forceinline__ uint64_t block_sum_1024(uint64_t v, uint64_t *part) {
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  if (lane_id() == 0) part[threadIdx.x >> 6] = v;
-  __syncthreads();
-  uint64_t t = 0;
-  for (int w = 0; w < 16; w++) t += part[w];
-  return t;
-}
-}  // namespace
-
-__global__ __launch_bounds__(1024) void k_chunk_bsum(const ChunkCfg *__restrict__ ccs, const int *ids, int64_t L,
-                                                     const int64_t *status) {
-  __shared__ uint64_t part[16];
-  if (ldr(status)) return;
-  const ChunkCfg cc = ccs[ids[blockIdx.y]];
-  const int64_t j = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-  const uint64_t t = block_sum_1024(j < L ? cc.S[j] : 0, part);
-  if (threadIdx.x == 0) cc.bs[blockIdx.x] = t;
+// The sum of each piece's counts.  (Added up by atomics where the faults are
+// found, a walk's loads wait behind them: a scan took 0.83 us and not 0.65
+// per 64 pages.)
+__device__ __forceinline__ void chunk_sums(const Group &gr, const ChunkCfg &cc, int64_t L) {
+  __shared__ uint64_t part[CWAVES];
+  for (int64_t q = gr.b; q * SCAN < L; q += gr.nb) {
+    const int64_t j = q * SCAN + threadIdx.x;
+    uint64_t v = j < L ? cc.S[j] : 0;
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if (lane_id() == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint64_t t = 0;
+      for (int w = 0; w < CWAVES; w++) t += part[w];
+      cc.bs[q] = t;
+    }
+    __syncthreads();
+  }
 }
 
-namespace {
 // The page word of r, if the fault at access A inserted it: its rank, else -1.
 __device__ __forceinline__ int owned_rank(uint64_t v, const Tags &tg, uint32_t A) {
   return (v & (HI | 0xFFFFFFull)) == (tg.t | A) ? (int)((v >> 24) & 63u) : -1;
 }
-}  // namespace
 
-// Second scan pass: each block's exclusive scan offset by the sums before
-// it; then each fault in the block (an access j whose page word names j
+// The d + 1 pages of each fault of a wave, one per lane: as many whole faults
+// at a time as 64 lanes hold, so that a fault costs a latency or two and not
+// d + 1 of them.  load(in, src, k), then body(in, src, k, what load gave): the
+// lane (if `in`) has page k of lane src's fault; all lanes call it together.
+template <typename Load, typename Body>
+__device__ __forceinline__ void fault_pages(bool fault, uint32_t d, Load load, Body body) {
+  __shared__ uint8_t s_lane[CWAVES][64];
+  const uint64_t fm = __ballot(fault);
+  if (!fm) return;
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6, nf = popc(fm);
+  const uint32_t m = d + 1, at_once = 64 / m, own = lane / m, k = lane - own * m;
+  if (fault) s_lane[w][popc(fm & ((1ull << lane) - 1))] = (uint8_t)lane;
+  wave_lds_order();
+  auto has = [&](uint32_t f) { return own < at_once && f + own < nf; };
+  auto src = [&](uint32_t f) { return (int)s_lane[w][has(f) ? f + own : 0]; };
+  for (uint32_t f = 0; f < nf; f += 2 * at_once) {  // two rounds' loads in flight
+    const uint32_t f2 = f + at_once;
+    const auto x = load(has(f), src(f), k), y = load(has(f2), src(f2), k);
+    body(has(f), src(f), k, x);
+    if (f2 < nf) body(has(f2), src(f2), k, y);
+  }
+  wave_lds_order();
+}
+
+// Exclusive scan of the packed per-access counts: each piece's own, offset by
+// the sums of the pieces before it; then each fault in the piece (an access j whose page word names j
 // itself, rank 0) numbers its insertions: I0 + insertions before j + rank.
-__global__ __launch_bounds__(1024) void k_chunk_scan(const CacheCfg *__restrict__ cfgs,
-                                                     const ChunkCfg *__restrict__ ccs, const int *ids,
-                                                     const uint64_t *__restrict__ pages, int64_t L, uint64_t R,
-                                                     uint32_t epoch, const int64_t *status) {
-  __shared__ uint64_t part[16];
-  __shared__ uint64_t s_pre;
-  if (ldr(status)) return;
-  const int id = ids[blockIdx.y];
-  const CacheCfg c = cfgs[id];
-  const ChunkCfg cc = ccs[id];
-  const Tags tg(epoch);
+__device__ __forceinline__ void chunk_scan(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+                                           const uint64_t *__restrict__ pages, int64_t L, uint64_t R, int64_t I0,
+                                           const Tags &tg) {
+  __shared__ uint64_t part[CWAVES], before[CWAVES];
   const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
-  if (w == 0) {  // the sums of the blocks before this one
+  uint64_t pre = 0;  // the sums of the pieces before q
+  int64_t done = 0;  // pieces in it
+  for (int64_t q = gr.b; q * SCAN < L; q += gr.nb) {
     uint64_t p = 0;
-    for (uint32_t i = lane; i < blockIdx.x; i += 64) p += cc.bs[i];
+    for (int64_t i = done + threadIdx.x; i < q; i += CBLK) p += cc.bs[i];
     for (int o = 32; o >= 1; o >>= 1) p += __shfl_xor(p, o);
-    if (lane == 0) s_pre = p;
-  }
-  const int64_t j = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-  const uint64_t v = j < L ? cc.S[j] : 0;
-  uint64_t x = v;  // inclusive scan within the wave
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t y = __shfl_up(x, o);
-    if (lane >= (uint32_t)o) x += y;
-  }
-  if (lane == 63) part[w] = x;
-  __syncthreads();
-  uint64_t off = s_pre;
-  for (uint32_t i = 0; i < w; i++) off += part[i];
-  if (j >= L) return;
-  const uint64_t sj = off + x - v;
-  cc.S[j] = sj;
-  if (j == L - 1) cc.S[L] = off + x;
-  if (v == 0) return;  // not a fault
-  const uint64_t p = pages[j];
-  const int64_t x0 = ldr(&cc.ctl->I0) + (int64_t)(sj >> 32);
-  for (uint32_t k = 0; k <= c.d && p + k < R; k++) {
-    const int rk = owned_rank(cc.tt[p + k], tg, (uint32_t)j);
-    if (rk >= 0) c.pins[p + k] = x0 + rk;
+    if (lane == 0) before[w] = p;
+    const int64_t j = q * SCAN + threadIdx.x;
+    const uint64_t v = j < L ? cc.S[j] : 0;
+    uint64_t x = v;  // inclusive scan within the wave
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint64_t y = __shfl_up(x, o);
+      if (lane >= (uint32_t)o) x += y;
+    }
+    if (lane == 63) part[w] = x;
+    __syncthreads();
+    for (int i = 0; i < CWAVES; i++) pre += before[i];
+    uint64_t off = pre;
+    for (uint32_t i = 0; i < w; i++) off += part[i];
+    __syncthreads();
+    done = q;
+    const uint64_t sj = off + x - v;
+    if (j < L) cc.S[j] = sj;
+    if (j == L - 1) cc.S[L] = off + x;
+    const bool fault = v != 0;
+    const uint64_t pg = fault ? pages[j] : 0;
+    const int64_t x0 = I0 + (int64_t)(sj >> 32);
+    auto load = [&](bool in, int src, uint32_t k) {
+      const uint64_t r = __shfl(pg, src) + k;
+      return in && r < R ? cc.tt[r] : 0;
+    };
+    fault_pages(fault, c.d, load, [&](bool, int src, uint32_t k, uint64_t t) {
+      const uint64_t r = __shfl(pg, src) + k;
+      const uint32_t jf = (uint32_t)__shfl((int)j, src);
+      const int64_t xf = __shfl(x0, src);
+      const int rk = owned_rank(t, tg, jf);
+      if (rk >= 0) c.pins[r] = xf + rk;
+    });
   }
 }
 
-// The check: every page's last hit, and every prefetch candidate found
-// resident, lies within the last F insertions at that moment.  Also, read
-// before anything changes: frames filled before the chunk and evicted
-// within it that hold a prefetched page never hit (a page resident at the
-// start and accessed in the chunk was hit before its eviction).
-__global__ __launch_bounds__(256) void k_chunk_check(const CacheCfg *__restrict__ cfgs,
-                                                     const ChunkCfg *__restrict__ ccs, const int *ids,
-                                                     const uint64_t *__restrict__ pages, int64_t L, uint64_t R,
-                                                     uint32_t epoch, const int64_t *status) {
-  if (ldr(status)) return;
-  const int id = ids[blockIdx.y];
-  const CacheCfg c = cfgs[id];
-  const ChunkCfg cc = ccs[id];
-  const Tags tg(epoch);
-  const int64_t I0 = ldr(&cc.ctl->I0), F = c.F;
-  const int64_t I1 = I0 + (int64_t)(ldr(&cc.S[L]) >> 32);
-  const uint32_t nblk_a = (uint32_t)((L + 255) / 256);
-  bool bad = false;
+// The check: the first access whose decision does not hold -- a hit on a
+// page, or a fault that found a prefetch candidate resident, not within the
+// last F insertions at that moment -- into ctl->good.
+__device__ __forceinline__ void chunk_check(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+                                            const uint64_t *__restrict__ pages, int64_t L, uint64_t R, int64_t I0,
+                                            const Tags &tg) {
+  uint32_t bad = NONE32;
+  const uint32_t lane = lane_id(), base = lane / (c.d + 1) * (c.d + 1);
+  const int64_t span = (L + 63) / 64 * 64;
+  for (int64_t j = gr.first(); j < span; j += gr.step()) {  // whole waves stay together
+    const uint64_t p = j < L ? pages[j] : 0;
+    const int64_t low = j < L ? I0 + (int64_t)(cc.S[j] >> 32) - (int64_t)c.F : 0;  // resident at j: pins >= low
+    const bool fault = j < L && cc.tt[p] == (tg.t | (uint64_t)j);
+    if (j < L && !fault && c.pins[p] < low) bad = min(bad, (uint32_t)j);
+    if (c.d == 0) continue;
+    struct Word {
+      uint64_t t;
+      int64_t x;
+    };
+    auto load = [&](bool in, int src, uint32_t k) {
+      const uint64_t r = __shfl(p, src) + k;
+      in = in && r < R;
+      return Word{in ? cc.tt[r] : 0, in ? c.pins[r] : INT64_MAX};  // (past the range: never a failure)
+    };
+    fault_pages(fault, c.d, load, [&](bool in, int src, uint32_t, Word v) {
+      const uint32_t jf = (uint32_t)__shfl((int)j, src);
+      const int64_t lf = __shfl(low, src), x = v.x;
+      const bool own = in && owned_rank(v.t, tg, jf) >= 0;
+      // the fault's insertions before this candidate
+      const uint64_t before = __ballot(own) & ((1ull << lane) - 1) & ~((1ull << base) - 1);
+      if (in && !own && x < lf + (int64_t)popc(before)) bad = min(bad, jf);
+    });
+  }
+  for (int o = 32; o >= 1; o >>= 1) bad = min(bad, (uint32_t)__shfl_xor((int)bad, o));
+  if (lane_id() == 0 && bad != NONE32) atomicMin(&cc.ctl->good, bad);
+}
+
+// Frames filled before the chunk and evicted by its first T accesses that
+// hold a prefetched page never hit (read before any flag changes; a page
+// resident at the start and accessed was hit before its eviction).
+__device__ __forceinline__ void chunk_lost(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+                                           const uint64_t *__restrict__ pages, int64_t T, int64_t I0, int64_t I1,
+                                           const Tags &tg) {
+  const int64_t F = c.F;
+  const int64_t ylo = I0 - F > 0 ? I0 - F : 0, yhi = I1 - F < I0 ? I1 - F : I0;
+  if (yhi <= ylo) return;  // nothing of before is evicted
   int64_t lost = 0;
-  if (blockIdx.x < nblk_a) {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j < L) {
-      const uint64_t p = pages[j];
-      const bool fault = cc.tt[p] == (tg.t | (uint64_t)j);
-      if (cc.lt[p] == (tg.t | (uint64_t)j) && !fault)  // the page's last access, a hit
-        bad = c.pins[p] < I0 + (int64_t)(cc.S[j] >> 32) - F;
-      if (fault) {  // the candidates this fault found resident
-        const int64_t at_fault = I0 + (int64_t)(cc.S[j] >> 32) - F;
-        int64_t before = 1;
-        for (uint32_t k = 1; k <= c.d && p + k < R; k++) {
-          const uint64_t q = p + k;
-          if (owned_rank(cc.tt[q], tg, (uint32_t)j) >= 0) {
-            before++;
-          } else if (c.pins[q] < at_fault + before) {
-            bad = true;
-            break;
-          }
-        }
-      } else if (cc.at[p] == (tg.a | (uint64_t)j)) {
-        const int64_t x = c.pins[p];
-        if (x >= I0 - F && x < I0 && x < I1 - F) {
-          const uint64_t fr = (uint64_t)x % (uint64_t)F;
-          lost -= (c.fpf[fr] && !c.fhit[fr]) ? 1 : 0;
-        }
-      }
-    }
-  } else {
-    const int64_t ylo = I0 - F > 0 ? I0 - F : 0, yhi = I1 - F < I0 ? I1 - F : I0;
-    for (int64_t y = ylo + (int64_t)(blockIdx.x - nblk_a) * 256 + threadIdx.x; y < yhi;
-         y += (int64_t)(gridDim.x - nblk_a) * 256) {
-      const uint64_t fr = (uint64_t)y % (uint64_t)F;
-      lost += (c.fpf[fr] && !c.fhit[fr]) ? 1 : 0;
+  for (int64_t j = gr.first(); j < T; j += gr.step()) {
+    const uint64_t p = pages[j];
+    if (cc.at[p] != (tg.a | (uint64_t)j)) continue;
+    const int64_t x = c.pins[p];
+    if (x >= ylo && x < yhi) {
+      const uint64_t fr = (uint64_t)x % (uint64_t)F;
+      lost -= (c.fpf[fr] && !c.fhit[fr]) ? 1 : 0;
     }
   }
-  if (__ballot(bad) && lane_id() == 0) cc.ctl->valid = 0;
+  for (int64_t y = ylo + gr.first(); y < yhi; y += gr.step()) {
+    const uint64_t fr = (uint64_t)y % (uint64_t)F;
+    lost += (c.fpf[fr] && !c.fhit[fr]) ? 1 : 0;
+  }
   lost = wave_sum(lost);
   if (lane_id() == 0 && lost) atomicAdd((unsigned long long *)&cc.ctl->lost_old, (unsigned long long)lost);
 }
 
-// Commit, per access (checked chunks): hit flags; a hit on a page resident
-// at the start marks its frame; each fault's insertions still resident set
-// their frame flags, those evicted within the chunk count as unused when
-// prefetched and never hit, prefetch outputs; then the counters.  A chunk
-// that failed its check is undone instead, so that the sequential run
-// starts from the chunk's initial state (a page not resident at the start
-// stays so).  The frames written here are distinct: they hold the last F
-// insertions.
-__global__ __launch_bounds__(256) void k_chunk_commit(const CacheCfg *__restrict__ cfgs,
-                                                      const ChunkCfg *__restrict__ ccs, const int *ids,
-                                                      const uint64_t *__restrict__ pages, int64_t c0, int64_t L,
-                                                      uint64_t R, uint32_t epoch, uint8_t *hit, uint64_t *pf_page,
-                                                      int64_t *pf_src, int64_t pf_cap, const int64_t *status,
-                                                      int64_t *n_pf) {
-  if (ldr(status)) return;
-  const int id = ids[blockIdx.y];
-  const CacheCfg c = cfgs[id];
-  const ChunkCfg cc = ccs[id];
-  const Tags tg(epoch);
-  const bool ok = ldr(&cc.ctl->valid) != 0;
-  const uint64_t tot = ldr(&cc.S[L]);
-  const int64_t I0 = ldr(&cc.ctl->I0), F = c.F, nf = (uint32_t)tot, M = (int64_t)(tot >> 32), I1 = I0 + M;
-  const bool keep_pf = pf_page && id == ids[0];
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// Commit of the first T accesses: hit flags; a hit on a page resident at the
+// start marks its frame; each fault's insertions still resident set their
+// frame flags, those evicted meanwhile count as unused when prefetched and
+// never hit, prefetch outputs; then the counters.  The insertions of later
+// faults are undone (a page not resident at the start stays so).  The frames
+// written here are distinct: they hold the last F insertions.
+__device__ __forceinline__ void chunk_commit(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+                                             const uint64_t *__restrict__ pages, int64_t c0, int64_t L, int64_t T,
+                                             uint64_t R, int64_t I0, int64_t npf0, const Tags &tg, uint8_t *hit,
+                                             uint64_t *pf_page, int64_t *pf_src, int64_t pf_cap, int64_t *n_pf) {
+  const uint64_t tot = ld(&cc.S[T]);
+  const int64_t F = c.F, nf = (uint32_t)tot, M = (int64_t)(tot >> 32), I1 = I0 + M;
   int64_t lost = 0;
-  if (j < L) {
-    const uint64_t p = pages[j];
-    const bool fault = cc.tt[p] == (tg.t | (uint64_t)j);
+  const int64_t span = (L + 63) / 64 * 64;
+  for (int64_t j = gr.first(); j < span; j += gr.step()) {  // whole waves stay together
+    const uint64_t p = j < L ? pages[j] : 0;
+    const bool fault = j < L && cc.tt[p] == (tg.t | (uint64_t)j), ok = j < T;
     if (ok && hit) hit[c0 + j] = fault ? 0 : 1;
     if (ok && !fault && cc.at[p] == (tg.a | (uint64_t)j)) {
       const int64_t x = c.pins[p];
       if (x >= I1 - F && x < I0) c.fhit[(uint64_t)x % (uint64_t)F] = 1;
     }
-    if (fault) {
-      const uint64_t sj = cc.S[j];
-      const int64_t pf_before = ldr(&cc.ctl->npf0) + (int64_t)(sj >> 32) - (int64_t)(uint32_t)sj;
-      for (uint32_t k = 0; k <= c.d && p + k < R; k++) {
-        const uint64_t r = p + k;
-        const int rk = owned_rank(cc.tt[r], tg, (uint32_t)j);
-        if (rk < 0) continue;
-        if (!ok) {
-          c.pins[r] = PINS_NEVER;
-          continue;
-        }
-        const int64_t x = c.pins[r];
-        const uint64_t l = cc.lt[r];
-        const bool used = (l & HI) == tg.t && (uint32_t)l > (uint32_t)j;
-        if (x >= I1 - F) {
-          const uint64_t fr = (uint64_t)x % (uint64_t)F;
-          c.fpf[fr] = rk > 0 ? 1 : 0;
-          c.fhit[fr] = used ? 1 : 0;
-        } else {
-          lost += (rk > 0 && !used) ? 1 : 0;
-        }
-        if (keep_pf && rk > 0) {
-          const int64_t q = pf_before + rk - 1;
-          if (q >= 0 && q < pf_cap) {
-            pf_page[q] = r;
-            pf_src[q] = c0 + j;
-          }
-        }
+    const uint64_t sj = fault ? cc.S[j] : 0;
+    const int64_t pf0 = npf0 + (int64_t)(sj >> 32) - (int64_t)(uint32_t)sj - 1;  // prefetch reads before, less 1
+    struct Word {
+      uint64_t t, a;
+      int64_t x;
+    };
+    auto load = [&](bool in, int src, uint32_t k) {
+      const uint64_t r = __shfl(p, src) + k;
+      in = in && r < R;
+      return Word{in ? cc.tt[r] : 0, in ? cc.at[r] : 0, in ? c.pins[r] : 0};
+    };
+    fault_pages(fault, c.d, load, [&](bool, int src, uint32_t k, Word v) {
+      const uint64_t r = __shfl(p, src) + k;
+      const uint32_t jf = (uint32_t)__shfl((int)j, src);
+      const int64_t q = __shfl(pf0, src);
+      const int rk = owned_rank(v.t, tg, jf);
+      if (rk < 0) return;
+      if ((int64_t)jf >= T) {
+        c.pins[r] = PINS_NEVER;
+        return;
       }
-    }
+      // (a prefetched page is hit from its first access on)
+      const bool used = rk > 0 && (v.a & HI) == tg.a && (int64_t)(uint32_t)v.a < T;
+      const int64_t x = v.x;
+      if (x >= I1 - F) {
+        const uint64_t fr = (uint64_t)x % (uint64_t)F;
+        c.fpf[fr] = rk > 0 ? 1 : 0;
+        c.fhit[fr] = used ? 1 : 0;
+      } else {
+        lost += (rk > 0 && !used) ? 1 : 0;
+      }
+      if (pf_page && rk > 0 && q + rk < pf_cap) {
+        pf_page[q + rk] = r;
+        pf_src[q + rk] = c0 + (int64_t)jf;
+      }
+    });
   }
   lost = wave_sum(lost);
-  if (lane_id() == 0 && lost) atomicAdd((unsigned long long *)&c.ctl->count[4], (unsigned long long)lost);
-  if (ok && blockIdx.x == 0 && threadIdx.x == 0) {
-    c.ctl->count[0] += L - nf;
+  if (gr.b == 0 && threadIdx.x == 0) {
+    lost += ld(&cc.ctl->lost_old);
+    c.ctl->count[0] += T - nf;
     c.ctl->count[1] += nf;
     c.ctl->count[2] += M - nf;
-    atomicAdd((unsigned long long *)&c.ctl->count[4], (unsigned long long)ldr(&cc.ctl->lost_old));
     c.ctl->ins = I1;
     c.ctl->head = (uint32_t)((uint64_t)I1 % (uint64_t)F);
-    if (keep_pf && n_pf) *n_pf = ldr(&cc.ctl->npf0) + M - nf;
+    c.ctl->pend = 0;
+    if (n_pf) *n_pf = npf0 + M - nf;
+  }
+  if (lane_id() == 0 && lost) atomicAdd((unsigned long long *)&c.ctl->count[4], (unsigned long long)lost);
+}
+
+__device__ __forceinline__ void chunk_clear(const Group &gr, const ChunkCfg &cc, uint64_t R) {
+  for (uint64_t q = (uint64_t)gr.first(); q < R; q += (uint64_t)gr.step()) {
+    cc.at[q] = ~0ull;
+    cc.tt[q] = 0;
+  }
+}
+}  // namespace
+
+struct ChunkRun {
+  const CacheCfg *cfgs;
+  const ChunkCfg *ccs;
+  const int *ids;
+  int n_ids;
+  uint32_t groups;
+  uint64_t R;
+  const uint64_t *pages;
+  int64_t n;
+  uint32_t chunk;  // accesses per chunk, 0: as many as pass
+  uint8_t *hit;
+  uint64_t *pf_page;
+  int64_t *pf_src;
+  int64_t pf_cap;
+  int64_t *status, *n_pf;
+  uint32_t *bars;  // one per group
+};
+
+__global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
+  __shared__ RunLds S;
+  if (ld(A.status)) return;  // a page outside the range: nothing changes
+  const uint32_t nb = gridDim.x / A.groups, grp = blockIdx.x / nb;
+  if (grp >= A.groups) return;
+  Group gr = {blockIdx.x - grp * nb, nb, A.bars + grp, 0, A.status};
+  for (int ci = (int)grp; ci < A.n_ids; ci += (int)A.groups) {
+    const int id = A.ids[ci];
+    const CacheCfg c = A.cfgs[id];
+    const ChunkCfg cc = A.ccs[id];
+    const bool first = ci == 0;
+    uint64_t *pf_page = first ? A.pf_page : nullptr;
+    int64_t *n_pf = first ? A.n_pf : nullptr;
+    uint8_t *hit = A.hit;  // (a single cache's)
+    const uint32_t most = A.chunk ? A.chunk : cc.Lmax;
+    uint32_t len = A.chunk ? A.chunk : min(cc.Lmax, CHUNK_FIRST), seq = SEQ_MIN;
+    uint32_t epoch = ld(&cc.ctl->epoch);
+    int64_t pos = 0;
+    while (pos < A.n) {  // (all of it the same on every workgroup of the group)
+      if (epoch >= 0xFFFFFF00u) {  // tags about to repeat
+        chunk_clear(gr, cc, A.R);
+        epoch = 0;
+        if (!gr.sync()) return;
+      }
+      const Tags tg(++epoch);
+      const uint64_t *pages = A.pages + pos;
+      const int64_t L = A.n - pos < (int64_t)len ? A.n - pos : (int64_t)len;
+      const int64_t I0 = ld(&c.ctl->ins), lim = I0 - (int64_t)c.F, npf0 = n_pf ? ld(n_pf) : 0;
+      chunk_tag(gr, cc, pages, L, epoch, tg);
+      if (!gr.sync()) return;
+      chunk_starts(gr, c, cc, pages, L, A.R, lim, epoch, tg);
+      if (!gr.sync()) return;
+      if (!A.chunk) {
+        const uint64_t lw = ld(&cc.ctl->loose[epoch & 1]);
+        const uint32_t loose = (uint32_t)lw, late = (uint32_t)(lw >> 32);
+        if (loose >= DENSE_MIN && late > loose / 16 * 7) {
+          len = (uint32_t)(L / 8);  // begin again with less
+          continue;
+        }
+      }
+      if (c.d > 0) {
+        chunk_walk(gr, c, cc, A.R, lim, tg);
+        if (!gr.sync()) return;
+        chunk_sums(gr, cc, L);
+        if (!gr.sync()) return;
+      }
+      chunk_scan(gr, c, cc, pages, L, A.R, I0, tg);
+      if (!gr.sync()) return;
+      chunk_check(gr, c, cc, pages, L, A.R, I0, tg);
+      if (!gr.sync()) return;
+      const int64_t T = ld(&cc.ctl->good);
+      const int64_t I1 = I0 + (int64_t)(ld(&cc.S[T]) >> 32);
+      if (I1 > (int64_t)c.F && I0 > 0) {  // frames of before are evicted
+        chunk_lost(gr, c, cc, pages, T, I0, I1, tg);
+        if (!gr.sync()) return;
+      }
+      chunk_commit(gr, c, cc, pages, pos, L, T, A.R, I0, npf0, tg, hit, pf_page, A.pf_src, A.pf_cap, n_pf);
+      pos += T;
+      if (pos >= A.n) break;  // nothing of this cache is read again
+      if (!gr.sync()) return;
+      if (T == L) {
+        len = min(len > most / 2 ? most : len * 2, most);
+        seq = SEQ_MIN;
+        continue;
+      }
+      len = (uint32_t)min((int64_t)most, max((int64_t)2 * T, (int64_t)SEQ_TRY));
+      if (T >= SEQ_TRY) continue;
+      const int64_t m = A.n - pos < (int64_t)seq ? A.n - pos : (int64_t)seq;
+      if (gr.b == 0 && threadIdx.x < 64)
+        cache_run_wave(c, S, A.R, A.pages + pos, m, hit ? hit + pos : nullptr, pf_page, A.pf_src, A.pf_cap, n_pf, pos);
+      if (!gr.sync()) return;
+      pos += m;
+      seq = min(seq * 2, SEQ_MAX);
+      len = min(most, CHUNK_MIN);
+    }
+    if (gr.b == 0 && threadIdx.x == 0) cc.ctl->epoch = epoch;
   }
 }
 
@@ -545,9 +888,9 @@ __global__ __launch_bounds__(256) void k_chunk_clear(const ChunkCfg *__restrict_
   const ChunkCfg cc = ccs[ids[blockIdx.y]];
   for (uint64_t q = (uint64_t)blockIdx.x * 256 + threadIdx.x; q < R; q += (uint64_t)gridDim.x * 256) {
     cc.at[q] = ~0ull;
-    cc.lt[q] = 0;
     cc.tt[q] = 0;
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) cc.ctl->epoch = 0;
 }
 
 hipError_t launch_chunk_clear(const ChunkCfg *dev_ccfgs, const int *cfg_ids, int n_cfg, uint64_t R, hipStream_t s) {
@@ -557,30 +900,41 @@ hipError_t launch_chunk_clear(const ChunkCfg *dev_ccfgs, const int *cfg_ids, int
   return hipGetLastError();
 }
 
-hipError_t launch_cache_chunk(const CacheCfg *cfgs, const ChunkCfg *ccs, const int *ids, int n_cfg, uint32_t max_f,
-                              uint32_t max_d, uint64_t R, const uint64_t *pages, int64_t c0, int64_t L,
-                              uint32_t epoch, uint8_t *hit, uint64_t *pf_page, int64_t *pf_src, int64_t pf_cap,
-                              int64_t *status, int64_t *n_pf, hipStream_t s) {
-  (void)max_f;
-  (void)max_d;
-  const uint64_t *pg = pages + c0;
-  const uint32_t nb = (uint32_t)((L + 255) / 256);
-  const uint32_t nsb = (uint32_t)((L + 1023) / 1024);
-  const uint32_t walk = nb < 1024 ? nb : 1024;  // 4 waves per block, one segment each at a time
-  const uint32_t nev = 256;                     // blocks over the evictions of earlier frames
-  hipLaunchKernelGGL(k_chunk_tag, dim3(nb, n_cfg), dim3(256), 0, s, cfgs, ccs, ids, pg, L, epoch, status, n_pf);
-  hipLaunchKernelGGL(k_chunk_starts, dim3(nb, n_cfg), dim3(256), 0, s, cfgs, ccs, ids, pg, L, epoch, status);
-  hipLaunchKernelGGL(k_chunk_walk, dim3(walk, n_cfg), dim3(256), 0, s, cfgs, ccs, ids, R, epoch, status);
-  hipLaunchKernelGGL(k_chunk_bsum, dim3(nsb, n_cfg), dim3(1024), 0, s, ccs, ids, L, status);
-  hipLaunchKernelGGL(k_chunk_scan, dim3(nsb, n_cfg), dim3(1024), 0, s, cfgs, ccs, ids, pg, L, R, epoch, status);
-  hipLaunchKernelGGL(k_chunk_check, dim3(nb + nev, n_cfg), dim3(256), 0, s, cfgs, ccs, ids, pg, L, R, epoch,
-                     status);
-  hipLaunchKernelGGL(k_chunk_commit, dim3(nb, n_cfg), dim3(256), 0, s, cfgs, ccs, ids, pg, c0, L, R, epoch, hit,
-                     pf_page, pf_src, pf_cap, status, n_pf);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_cache_seq(cfgs, ccs, ids, n_cfg, R, pg, L, c0, hit ? hit + c0 : nullptr, pf_page, pf_src, pf_cap,
-                          status, n_pf, s);
+// A workgroup for each 1,024 accesses, above 64 of them for each 2,048:
+// a scattered fault wants waves, a barrier costs more the more workgroups meet.
+// 221 K accesses of a scan 154 us at one per 1,024, 125 at one per 2,048;
+// 10 K scattered ones 258 us at one per 2,048, 133 at one per 1,024.
+static int64_t chunk_share(int64_t n) {
+  return std::max((n + 2 * CBLK - 1) / (2 * CBLK), std::min((n + CBLK - 1) / CBLK, (int64_t)64));
+}
+// Workgroups of k_chunk_run resident at once (0: no cooperative launches).
+static int chunk_blocks() {
+  int dev = 0, coop = 0, ncu = 0, per = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void *)k_chunk_run, CBLK, 0) != hipSuccess)
+    return 0;
+  return per > 0 ? ncu : 0;  // one per CU: a barrier's cost grows with the workgroups
+}
+
+hipError_t launch_cache_chunks(const CacheCfg *cfgs, const ChunkCfg *ccs, const int *ids, int n_cfg, uint64_t R,
+                               const uint64_t *pages, int64_t n, uint32_t chunk, uint8_t *hit, uint64_t *pf_page,
+                               int64_t *pf_src, int64_t pf_cap, int64_t *status, int64_t *n_pf, uint32_t *bars,
+                               hipStream_t s) {
+  int blocks = chunk_blocks();
+  if (blocks <= 0) return hipErrorNotSupported;
+  ChunkRun A = {cfgs, ccs, ids, n_cfg, 0, R, pages, n, chunk, hit, pf_page, pf_src, pf_cap, status, n_pf, bars};
+  // no more workgroups than a short call has work for
+  const int64_t use = chunk_share(n) * n_cfg;
+  if (use < blocks) blocks = (int)use;
+  A.groups = (uint32_t)std::min(std::min(n_cfg, blocks), CHUNK_GROUPS);
+  if (blocks == 1) {  // no one to wait for
+    hipLaunchKernelGGL(k_chunk_run, dim3(1), dim3(CBLK), 0, s, A);
+    return hipGetLastError();
+  }
+  void *args[] = {&A};
+  return hipLaunchCooperativeKernel((const void *)k_chunk_run, dim3((uint32_t)blocks), dim3(CBLK), args, 0, s);
 }
 
 }  // namespace hbf

@@ -217,26 +217,31 @@ struct CacheCfg {
 constexpr int64_t PINS_NEVER = INT64_MIN / 4;
 // Chunked solve of a device-memory cache (hbf_cache_chunk.hip).  Per page
 // (R entries each, tagged with the chunk's epoch in the high 32 bits): the
-// chunk's first access (tag ~epoch, kept by atomicMin), its last access,
-// and, for a page inserted by the chunk, the time of the fault that
-// inserted it (bits 0-23) and its rank among that fault's insertions (bits
-// 24-29).  Per chunk: the per-access insertion/fault counts and their
-// exclusive scan (S, Lmax + 1 entries), the sums per 1,024 accesses and
-// the segment starts.
+// chunk's first access (tag ~epoch, kept by atomicMin) and, for a page
+// inserted by the chunk, the time of the fault that inserted it (bits 0-23)
+// and its rank among that fault's insertions (bits 24-29).  Per chunk: the
+// per-access insertion/fault counts and their exclusive scan (S, Lmax + 1
+// entries), the sums per 1,024 accesses and the segment starts.
 struct ChunkCtl {
-  uint32_t nseg, valid;
-  int64_t I0, npf0;  // insertions and prefetch outputs before the chunk
+  uint32_t nseg;
+  uint32_t good;     // accesses of the chunk before the first decision that does not hold
+  uint32_t epoch;    // last chunk tag used
+  uint32_t pad;
+  uint64_t loose[2];  // candidates outside runs (low word), those near one accessed later (high); odd or even tag
   int64_t lost_old;  // frames filled before the chunk, evicted within it holding a prefetched page never hit
 };
 struct ChunkCfg {
-  uint64_t *at, *lt, *tt;
+  uint64_t *at, *tt;
   uint64_t *S;
   uint64_t *bs;
   uint32_t *seg;
   ChunkCtl *ctl;
   uint32_t Lmax;
 };
-constexpr uint32_t CHUNK_MAX = 1u << 18;          // accesses per chunk
+constexpr uint32_t CHUNK_MAX = 1u << 18;          // accesses per chunk that a caller can ask for
+constexpr uint32_t CHUNK_LIMIT = 1u << 21;        // accesses per chunk (24 bits of a page's word hold a time)
+constexpr uint32_t CHUNK_FIRST = 1u << 20;        // accesses of a call's first chunk
+constexpr int CHUNK_GROUPS = 256;                 // caches served at the same time
 constexpr uint64_t CHUNK_MAX_R = uint64_t(1) << 26;  // range pages with per-page chunk state
 constexpr uint32_t CHUNK_MIN = 16384;            // default accesses per chunk, at least
 
@@ -247,14 +252,19 @@ constexpr uint32_t CACHE_MAX_PREFETCH = 63;  // one fault's candidates fit one w
 // round of 64 accesses without prefetch then never evicts a page it
 // inserted, and one fault's insertion offsets, at most 63, stay below F).
 constexpr uint32_t CACHE_LDS_MAX = 63;
-// Default accesses per chunk for F frames (0: sequential only).  A chunk
-// whose check fails costs its sequential run plus a few launches, so the
-// default is long; F/16 above the minimum keeps a large cache's chunks from
-// turning over its whole window.
+// Accesses per chunk that hbf_cache_get_chunk reports for a new cache of F
+// frames (0: sequential only); unless a length is asked for, chunks are as
+// long as their checks let them be, up to chunk_limit.
 inline uint32_t chunk_default(uint32_t F, uint64_t R) {
   if (F <= CACHE_LDS_MAX || R > CHUNK_MAX_R) return 0;
   uint32_t c = F / 16;
   return c < CHUNK_MIN ? CHUNK_MIN : (c > CHUNK_MAX ? CHUNK_MAX : c);
+}
+// Accesses a chunk's state holds over R pages: the state per access stays
+// below the state per page.
+inline uint32_t chunk_limit(uint64_t R) {
+  const uint64_t c = R / 2;
+  return (uint32_t)(c < CHUNK_MIN ? CHUNK_MIN : (c > CHUNK_LIMIT ? CHUNK_LIMIT : c));
 }
 hipError_t launch_cache_clear(CacheCfg *dev_cfgs, int n_cfg, uint64_t R, uint32_t max_f, hipStream_t s);
 // cfg_ids: the caches to run (device, n_cfg entries); every one of them has
@@ -263,22 +273,15 @@ hipError_t launch_cache_clear(CacheCfg *dev_cfgs, int n_cfg, uint64_t R, uint32_
 hipError_t launch_cache_run(const CacheCfg *dev_cfgs, const int *cfg_ids, int n_cfg, bool lds, uint32_t max_f,
                             uint64_t R, const uint64_t *pages, int64_t n, uint8_t *hit, uint64_t *pf_page,
                             int64_t *pf_src, int64_t pf_cap, int64_t *status, int64_t *n_pf_out, hipStream_t s);
-// The sequential device-memory run alone (no page check, no pending count):
-// caches whose chunk check passed (ccfgs[id].ctl->valid) are skipped; the
-// prefetch outputs continue from *n_pf_out and name access i_base + i.
-hipError_t launch_cache_seq(const CacheCfg *dev_cfgs, const ChunkCfg *dev_ccfgs, const int *cfg_ids, int n_cfg,
-                            uint64_t R, const uint64_t *pages, int64_t n, int64_t i_base, uint8_t *hit,
-                            uint64_t *pf_page, int64_t *pf_src, int64_t pf_cap, const int64_t *status,
-                            int64_t *n_pf_out, hipStream_t s);
 hipError_t cache_set_lds_limit();
-// One chunk pages[c0 .. c0 + L) of the caches ids[0..n_cfg) (all with chunk
-// state, L <= their Lmax): parallel solve, check, commit or undo, then the
-// sequential run for the caches whose check failed.  epoch: nonzero, new
-// for every chunk since the tags were cleared.
-hipError_t launch_cache_chunk(const CacheCfg *dev_cfgs, const ChunkCfg *dev_ccfgs, const int *cfg_ids, int n_cfg,
-                              uint32_t max_f, uint32_t max_d, uint64_t R, const uint64_t *pages, int64_t c0,
-                              int64_t L, uint32_t epoch, uint8_t *hit, uint64_t *pf_page, int64_t *pf_src,
-                              int64_t pf_cap, int64_t *status, int64_t *n_pf, hipStream_t s);
+// Serve pages[0..n) on the caches ids[0..n_cfg) (all with chunk state): one
+// cooperative launch.  chunk: accesses per chunk (0: as many as pass their
+// check).  hit (n entries), pf_*, n_pf: the first cache's, or null.  bars:
+// CHUNK_GROUPS words, zero.  hipErrorNotSupported without cooperative launches.
+hipError_t launch_cache_chunks(const CacheCfg *dev_cfgs, const ChunkCfg *dev_ccfgs, const int *cfg_ids, int n_cfg,
+                               uint64_t R, const uint64_t *pages, int64_t n, uint32_t chunk, uint8_t *hit,
+                               uint64_t *pf_page, int64_t *pf_src, int64_t pf_cap, int64_t *status, int64_t *n_pf,
+                               uint32_t *bars, hipStream_t s);
 hipError_t launch_cache_check(const uint64_t *pages, int64_t n, uint64_t R, int64_t *status, hipStream_t s);
 hipError_t launch_cache_pending(const CacheCfg *dev_cfgs, const int *cfg_ids, int n_cfg, uint32_t max_f,
                                 const int64_t *status, hipStream_t s);

@@ -1,8 +1,9 @@
 """Chunked solve of the frame cache (Sections D5, D6; FIFO and next-page
 prefetch as read in include/hbf.h), HIP path against the reference model
 through the C ABI.  Each chunk is solved in parallel as if nothing were
-evicted, checked on the device, and committed or served one access after
-another; the results must not depend on the chunk length.  Cases: chunk
+evicted, checked on the device, and committed as far as the check holds
+(stretches where hardly any of it does are served one access after another);
+the results must not depend on the chunk length.  Cases: chunk
 lengths from 1 to the whole call, caches small enough that most chunks fail
 their check and large enough that all pass, every prefetch depth class,
 calls that continue one cache across chunk boundaries, the prefetch outputs
@@ -246,3 +247,86 @@ def test_random_chunked_caches(torch, seed):
     s = np.asarray(streams(rng, kind, n, R), dtype=np.int64)
     cuts = np.sort(rng.integers(0, n, 2))
     run_both(torch, F, d, R, [s[:cuts[0]], s[cuts[0]:cuts[1]], s[cuts[1]:]], chunk, f"random{seed}-{kind}")
+
+
+def auto_stream(rng, kind, n, R, d):
+    if kind == "scans":        # runs over many splits, some read again in pieces
+        out, have = [], 0
+        while have < n:
+            a = int(rng.integers(0, R - 1))
+            m = min(int(rng.integers(1, 9000)), R - a)
+            run = a + np.arange(m)
+            k = int(rng.integers(0, 4))
+            if k == 0:         # a jump back inside the run
+                c = int(rng.integers(0, m))
+                run = np.concatenate([run[:c], run[:c // 2], run[c:]])
+            elif k == 1:       # two halves in turns: no run at all
+                h = m // 2
+                run = np.stack([run[:h], run[h:2 * h]], 1).reshape(-1)
+            out.append(run)
+            have += run.size
+        return np.concatenate(out)[:n]
+    if kind == "scattered":    # a working set seen for the first time
+        return rng.integers(0, R, n)
+    # single faults whose windows just meet, overlap or stay apart
+    return rng.permutation(np.minimum(np.cumsum(rng.integers(max(d - 1, 1), d + 3, n)) % R, R - 1))
+
+
+@pytest.mark.parametrize("d", [0, 1, 2, 6, 7, 31, 62, 63])
+@pytest.mark.parametrize("kind", ["scans", "scattered", "spaced"])
+def test_lengths_by_themselves(torch, kind, d):
+    """Chunk lengths left to the solve, over caches whose checks pass, fail
+    halfway and fail at once; calls of one workgroup and of many."""
+    from oracle import oracle
+    from paper_2609_09800_amd import hbf
+    rng = np.random.default_rng(7000 + d)
+    R = 30011
+    for F in (64, 700, 9000, 26000, 31000):
+        say(f"automatic lengths {kind} d={d} F={F}")
+        g = hbf.Cache(F, d, R)
+        o = oracle.OracleCache(F, d, R)
+        for n in (1, 63, 1024, 1025, 50000):
+            p = np.ascontiguousarray(auto_stream(rng, kind, n, R, d), dtype=np.int64)
+            cap = n * (d + 1)
+            hit = torch.empty(n, dtype=torch.uint8, device="cuda")
+            cnt = torch.zeros(8, dtype=torch.int64, device="cuda")
+            pp, ps = (torch.full((cap,), -1, dtype=torch.int64, device="cuda") for _ in range(2))
+            assert g.access(torch.from_numpy(p).cuda(), hit, cnt, pp, ps) == 0
+            _, wh, wp, ws = o.access(p, pf_cap=cap)
+            c = cnt.cpu().numpy()
+            m = int(c[5])
+            assert c[6] == 0 and np.array_equal(c[:5], o.counts()), (n, c, o.counts())
+            assert np.array_equal(hit.cpu().numpy(), wh), n
+            assert m == len(wp) and np.array_equal(pp.cpu().numpy()[:m], wp) and np.array_equal(ps.cpu().numpy()[:m], ws)
+        g.close()
+
+
+@pytest.mark.parametrize("n", [500, 40000])
+def test_captured_calls(torch, n):
+    """A captured call replayed several times, other work between: each replay
+    goes on from the cache the last one left."""
+    from oracle import oracle
+    from paper_2609_09800_amd import hbf
+    rng = np.random.default_rng(5)
+    F, d, R = 9000, 7, 30011
+    g = hbf.Cache(F, d, R)
+    o = oracle.OracleCache(F, d, R)
+    pd = torch.zeros(n, dtype=torch.int64, device="cuda")
+    hit = torch.empty(n, dtype=torch.uint8, device="cuda")
+    cnt = torch.zeros(8, dtype=torch.int64, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        assert g.access(pd, hit, cnt, stream=side) == 0
+    for r in range(4):
+        say(f"replay {r} n={n}")
+        p = np.ascontiguousarray(auto_stream(rng, "scans", n, R, d), dtype=np.int64)
+        pd.copy_(torch.from_numpy(p))
+        graph.replay()
+        torch.cuda.synchronize()
+        _, wh, _, _ = o.access(p, pf_cap=0)
+        assert np.array_equal(hit.cpu().numpy(), wh)
+        assert np.array_equal(cnt.cpu().numpy()[:5], o.counts())
+        (hit.float() * 2).sum().item()
+    g.close()
