@@ -36,6 +36,7 @@
 
 namespace hbf {
 
+constexpr int GEMV_PAGE = 16384;  // bytes of the pages page_vec takes
 constexpr int GEMV_MAXV = 8;  // 16-byte weight vectors held per lane
 // Longest wait of a workgroup for the call's origin (never reached: workgroup
 // 0 publishes it as soon as it starts); past it the call fails.
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(256) void k_gemv_measured(int64_t *__restrict__ mea
 
 // ------------------------------------------------------------------ page bodies
 
-// General shape: one page of R = page_bytes / (2K) rows by one 256-thread
+// Any other shape (pages of other sizes): one page of R = page_bytes / (2K) rows by one 256-thread
 // workgroup.  Wave w takes rows w, w+4, ...; lane l takes the 16-byte
 // vectors l, l+64, ... of each row (VPL = K/512 of them).  `wait` runs
 // between the page's loads and its first use.
@@ -240,58 +241,86 @@ __device__ __forceinline__ void butterfly(float *val, int lane) {
   }
 }
 
-// The expert shape of the MoE workloads (K = 2048, 16 KiB pages of 4 rows)
-// at batch B <= BB, BB = 1, 2, 4, 8 or 16 (rows b >= B are zero and not
-// written).  Thread t of the page's workgroup holds the 16-byte column slice
-// t of all 4 rows and of every activation row, so each activation vector is
-// read once per workgroup (not once per row) and feeds 4 dot products.  The
-// activations are loaded right after the page, before the wait.  The 4*BB
-// partial sums of a lane are reduced across the wave by a transposing
-// butterfly (63 exchanges for 64 values instead of 6 per value, all in
-// registers), then across the 4 waves through LDS.  (Workgroups of 2 or 4
-// pages, sharing one activation load, measured slower at every batch: fewer
-// workgroups in flight.)
-template <int BB, bool PAD, typename Wait>
-__device__ __forceinline__ void page_k2048(int q, const uint16_t *__restrict__ W, int N,
-                                           const uint16_t *__restrict__ X, int B_, float *__restrict__ Y,
-                                           float (*red)[64], Wait wait) {
-  constexpr int K = 2048, R = 4, V = R * BB;
-  constexpr int LGV = V == 4 ? 2 : V == 8 ? 3 : V == 16 ? 4 : V == 32 ? 5 : 6;
+// A 16 KiB page of K = 512, 1024, 2048 or 4096 columns, BB = 1, 2, 4, 8
+// or 16 activation rows at a time (PAD: rows past the batch are zero and not
+// written; MANY: a larger batch, BB rows after BB rows).  Thread t of the
+// page's workgroup holds four 16-byte vectors of it, always of the same
+// column slices: for K = 2048 slice t of all 4 rows; for fewer columns the
+// workgroup is 2 or 4 groups of waves, group g with rows g, g + G, ...; for
+// K = 4096 the thread has CP = 2 slices of 2 rows.  So an
+// activation vector is read once per workgroup or group (not once per row)
+// and feeds RT dot products.  The activations are loaded right after the
+// page, before the wait.  A lane's RT*BB partial sums are reduced across the
+// wave by a transposing butterfly (63 exchanges for 64 values instead of 6
+// per value, all in registers), then across the group's waves through LDS.
+// (Workgroups of 2 or 4 pages, sharing one activation load, measured slower
+// at every batch: fewer workgroups in flight.)
+template <int K, int BB, bool PAD, bool MANY, typename Wait>
+__device__ __forceinline__ void page_vec(int q, const uint16_t *__restrict__ W, int N,
+                                         const uint16_t *__restrict__ X, int B_, float *__restrict__ Y,
+                                         float (*red)[64], Wait wait) {
+  constexpr int T = K >= 2048 ? 256 : K / 8;                 // threads across a row
+  constexpr int G = 256 / T, GW = 4 / G;                     // row groups, waves of one
+  constexpr int CP = K > 2048 ? K / 2048 : 1, RT = 4 / CP;   // slices and rows of a thread
+  constexpr int R = G * RT, V = RT * BB;
+  constexpr int LGV = V == 1 ? 0 : V == 2 ? 1 : V == 4 ? 2 : V == 8 ? 3 : V == 16 ? 4 : V == 32 ? 5 : 6;
+  static_assert(V <= 64 && R * K * 2 == GEMV_PAGE, "a page is four vectors a thread");
   const int row0 = q * R;
   const int e = row0 / N;
   const int nb = row0 - e * N;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int g = t / T, c = t % T;
 
   // ---- issue: every load of this page, then the activations
-  uint4 v[R];
+  uint4 v[RT][CP];
 #pragma unroll
-  for (int r = 0; r < R; r++) v[r] = *(const uint4 *)(W + (size_t)(row0 + r) * K + (size_t)t * 8);
-  const int B = PAD ? B_ : BB;  // the batch (PAD: B_ < BB rows, the rest zero)
-  const uint16_t *xe = X + (size_t)e * B * K + (size_t)t * 8;
-  uint4 xv[BB];
+  for (int r = 0; r < RT; r++)
 #pragma unroll
-  for (int b = 0; b < BB; b++) xv[b] = b < B ? *(const uint4 *)(xe + (size_t)b * K) : make_uint4(0, 0, 0, 0);
+    for (int p = 0; p < CP; p++)
+      v[r][p] = *(const uint4 *)(W + (size_t)(row0 + r * G + g) * K + (size_t)(p * 256 + c) * 8);
+  const int B = PAD || MANY ? B_ : BB;
+  const uint16_t *xe = X + (size_t)e * B * K + (size_t)c * 8;
+  uint4 xv[BB][CP];
+  auto load = [&](int b0) {
+#pragma unroll
+    for (int b = 0; b < BB; b++)
+#pragma unroll
+      for (int p = 0; p < CP; p++)
+        xv[b][p] = !PAD || b0 + b < B ? *(const uint4 *)(xe + (size_t)(b0 + b) * K + (size_t)p * 2048)
+                                      : make_uint4(0, 0, 0, 0);
+  };
+  load(0);
 
   // ---- consumption point
   wait();
 
   // ---- consume: value index r*BB + b
-  float val[V];
+  for (int b0 = 0;;) {
+    float val[V];
 #pragma unroll
-  for (int b = 0; b < BB; b++)
+    for (int b = 0; b < BB; b++)
 #pragma unroll
-    for (int r = 0; r < R; r++) val[r * BB + b] = dot8(v[r], xv[b]);
-  butterfly<V, 0>(val, lane);
-  red[w][lane] = val[0];
-  __syncthreads();
-  // the lane holding value index i has i's bits in its top log2(V) bits
-  if (t < V) {
-    const int src = t << (6 - LGV);
-    const float sum = red[0][src] + red[1][src] + red[2][src] + red[3][src];
-    const int r = t / BB, b = t - r * BB;
-    if (b < B) Y[((size_t)e * B + b) * N + nb + r] = sum;
+      for (int r = 0; r < RT; r++) {
+        val[r * BB + b] = dot8(v[r][0], xv[b][0]);
+#pragma unroll
+        for (int p = 1; p < CP; p++) val[r * BB + b] += dot8(v[r][p], xv[b][p]);
+      }
+    butterfly<V, 0>(val, lane);
+    red[w][lane] = val[0];
+    __syncthreads();
+    // the lane holding value index i has i's bits in its top log2(V) bits
+    if (t < V * G) {
+      const int og = t / V, i = t % V, src = i << (6 - LGV);
+      float sum = red[og * GW][src];
+#pragma unroll
+      for (int u = 1; u < GW; u++) sum += red[og * GW + u][src];
+      const int r = i / BB * G + og, b = b0 + i % BB;
+      if (!PAD || b < B) Y[((size_t)e * B + b) * N + nb + r] = sum;
+    }
+    if (MANY && (b0 += BB) < B) load(b0);
+    __syncthreads();  // red is reused
+    if (!MANY || b0 >= B) break;
   }
-  __syncthreads();  // red is reused by the workgroup's next page
 }
 
 // ------------------------------------------------------------------ matrix cores
@@ -420,12 +449,12 @@ __global__ __launch_bounds__(256) void k_gemv_general(const uint16_t *__restrict
   page_general(blockIdx.x, W, K, N, R, X, B, Y, [] {});
 }
 
-template <int BB, bool PAD>
-__global__ __launch_bounds__(256) void k_gemv_k2048(const uint16_t *__restrict__ W, int N,
-                                                    const uint16_t *__restrict__ X, int B_,
-                                                    float *__restrict__ Y) {
+template <int K, int BB, bool PAD, bool MANY>
+__global__ __launch_bounds__(256) void k_gemv_vec(const uint16_t *__restrict__ W, int N,
+                                                  const uint16_t *__restrict__ X, int B_,
+                                                  float *__restrict__ Y) {
   __shared__ float red[4][64];
-  page_k2048<BB, PAD>(blockIdx.x, W, N, X, B_, Y, red, [] {});
+  page_vec<K, BB, PAD, MANY>(blockIdx.x, W, N, X, B_, Y, red, [] {});
 }
 
 // With delays: persistent workgroups.  Workgroup g owns pages g + i*G
@@ -491,17 +520,55 @@ __global__ __launch_bounds__(256) void k_gemv_general_timed(const uint16_t *__re
               [&](int q, auto wait) { page_general(q, W, K, N, R, X, B, Y, wait); });
 }
 
-template <int BB, bool PAD>
-__global__ __launch_bounds__(256) void k_gemv_k2048_timed(const uint16_t *__restrict__ W, int N,
-                                                          const uint16_t *__restrict__ X, int B_,
-                                                          float *__restrict__ Y, int npages,
-                                                          const int64_t *__restrict__ pi,
-                                                          const int64_t *__restrict__ pc,
-                                                          int64_t *__restrict__ meas, int64_t tick_ps,
-                                                          DevState *st) {
+template <int K, int BB, bool PAD, bool MANY>
+__global__ __launch_bounds__(256) void k_gemv_vec_timed(const uint16_t *__restrict__ W, int N,
+                                                        const uint16_t *__restrict__ X, int B_,
+                                                        float *__restrict__ Y, int npages,
+                                                        const int64_t *__restrict__ pi,
+                                                        const int64_t *__restrict__ pc,
+                                                        int64_t *__restrict__ meas, int64_t tick_ps,
+                                                        DevState *st) {
   __shared__ float red[4][64];
   timed_pages(npages, pi, pc, meas, tick_ps, st,
-              [&](int q, auto wait) { page_k2048<BB, PAD>(q, W, N, X, B_, Y, red, wait); });
+              [&](int q, auto wait) { page_vec<K, BB, PAD, MANY>(q, W, N, X, B_, Y, red, wait); });
+}
+
+using GemvFn = void (*)(const uint16_t *, int, const uint16_t *, int, float *);
+using GemvTimedFn = void (*)(const uint16_t *, int, const uint16_t *, int, float *, int, const int64_t *,
+                             const int64_t *, int64_t *, int64_t, DevState *);
+struct GemvKernels {
+  GemvFn plain;
+  GemvTimedFn timed;
+};
+template <int K, int BB, bool PAD, bool MANY>
+static GemvKernels vec_kernels() {
+  return {k_gemv_vec<K, BB, PAD, MANY>, k_gemv_vec_timed<K, BB, PAD, MANY>};
+}
+// Batches 1, 2, 4, 8 (and 16 on K = 2048) exactly, others padded to the next
+// of those; above, 8 rows at a time, the page's
+// vectors kept.  Per call without / with (zero) delays on 8 x [768 x K],
+// against page_general, which reads an activation row again for each of a
+// wave's rows and reduces each output by itself, in us:
+//   K =  512   batch 1   4.8 ->  2.8   7.2 ->  4.8   batch 24  37 ->  6.3   41 ->  8.4
+//   K = 1024   batch 4   9.8 ->  3.4  12.3 ->  5.5   batch 24  40 ->  8.3   41 -> 10.3
+//   K = 2048                                         batch 24  52 -> 13.9   90 -> 16.3
+//   K = 4096   batch 4  34.7 -> 10.4  45.8 -> 12.9   batch 24 160 -> 29.9  228 -> 33.8
+// The error against 64 bits is that of before (6.2e-8 to 8.4e-8); the matrix
+// cores, which would be faster on batches above 16, have 1.3e-7 and more, so
+// they take no further batch.
+template <int K>
+static GemvKernels vec_for(int B) {
+  if (B == 1) return vec_kernels<K, 1, false, false>();
+  if (B == 2) return vec_kernels<K, 2, false, false>();
+  if (B == 4) return vec_kernels<K, 4, false, false>();
+  if (B == 8) return vec_kernels<K, 8, false, false>();
+  if (B < 4) return vec_kernels<K, 4, true, false>();
+  if (B < 8) return vec_kernels<K, 8, true, false>();
+  if constexpr (K == 2048) {
+    if (B == 16) return vec_kernels<K, 16, false, false>();
+    if (B < 16) return vec_kernels<K, 16, true, false>();
+  }
+  return B % 8 ? vec_kernels<K, 8, true, true>() : vec_kernels<K, 8, false, true>();
 }
 
 // Persistent grid of a timed kernel: as many workgroups as the GPU holds at
@@ -548,24 +615,23 @@ hipError_t launch_gemv(const uint16_t *W, int E, int K, int N, int page_bytes, c
       hipLaunchKernelGGL(k_gemv_mfma<4>, dim3(tiles), dim3(256), 0, s, W, K, N, X, B, Y);
     return hipGetLastError();
   }
-  if (K == 2048 && R == 4 && B >= 1 && B <= 16) {
+  const bool vec = page_bytes == GEMV_PAGE && B >= 1;
+  const GemvKernels f = !vec        ? GemvKernels{nullptr, nullptr}
+                        : K == 512  ? vec_for<512>(B)
+                        : K == 1024 ? vec_for<1024>(B)
+                        : K == 2048 ? vec_for<2048>(B)
+                        : K == 4096 ? vec_for<4096>(B)
+                                    : GemvKernels{nullptr, nullptr};
+  if (f.plain) {
     if (!timed) {
-      auto kfn = B == 1 ? k_gemv_k2048<1, false> : B == 2 ? k_gemv_k2048<2, false>
-               : B == 4 ? k_gemv_k2048<4, false> : B == 8 ? k_gemv_k2048<8, false>
-               : B == 16 ? k_gemv_k2048<16, false> : B < 4 ? k_gemv_k2048<4, true>
-               : B < 8 ? k_gemv_k2048<8, true> : k_gemv_k2048<16, true>;
-      hipLaunchKernelGGL(kfn, dim3((uint32_t)pages), dim3(256), 0, s, W, N, X, B, Y);
+      hipLaunchKernelGGL(f.plain, dim3((uint32_t)pages), dim3(256), 0, s, W, N, X, B, Y);
       return hipGetLastError();
     }
-    auto kfn = B == 1 ? k_gemv_k2048_timed<1, false> : B == 2 ? k_gemv_k2048_timed<2, false>
-             : B == 4 ? k_gemv_k2048_timed<4, false> : B == 8 ? k_gemv_k2048_timed<8, false>
-             : B == 16 ? k_gemv_k2048_timed<16, false> : B < 4 ? k_gemv_k2048_timed<4, true>
-             : B < 8 ? k_gemv_k2048_timed<8, true> : k_gemv_k2048_timed<16, true>;
     uint32_t grid = 0;
-    hipError_t e = timed_grid((const void *)kfn, ncu, pages, &grid);
+    hipError_t e = timed_grid((const void *)f.timed, ncu, pages, &grid);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_gemv_origin, dim3(1), dim3(64), 0, s, st);
-    hipLaunchKernelGGL(kfn, dim3(grid), dim3(256), 0, s, W, N, X, B, Y, (int)pages, pi, pc, meas, tick_ps, st);
+    hipLaunchKernelGGL(f.timed, dim3(grid), dim3(256), 0, s, W, N, X, B, Y, (int)pages, pi, pc, meas, tick_ps, st);
     return finish_measured(meas, pages, tick_ps, st, s);
   }
   if (!timed) {

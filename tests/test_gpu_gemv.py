@@ -56,8 +56,8 @@ def rel_l2(y, ref):
 @pytest.mark.parametrize("batch", [1, 2, 3, 4, 5, 8, 12, 16, 17])
 def test_gemv_with_modeled_delays(torch, batch):
     """Config 4: 8 experts x [768 x 2048] bf16, delays from the config-3 model
-    (batches up to 16 take the K = 2048 kernel, padded to 1, 2, 4, 8 or 16
-    rows; batch 17 the general one)."""
+    (batches up to 16 padded to 1, 2, 4, 8 or 16 rows; batch 17 8 rows at a
+    time)."""
     from oracle import oracle
     from paper_2609_09800_amd import hbf
     say(f"gemv config4 batch={batch}")
@@ -94,7 +94,7 @@ def test_gemv_with_modeled_delays(torch, batch):
 
 @pytest.mark.parametrize("K,N,batch", [(512, 64, 3), (4096, 32, 2), (1024, 48, 16)])
 def test_gemv_other_shapes_with_delays(torch, K, N, batch):
-    """The general kernel (16, 2 or 8 rows per 16 KiB page) with a delay per
+    """Other column counts (16, 2 or 8 rows per 16 KiB page) with a delay per
     page: every consumer waits at least its page's delay, and the product is
     right."""
     from oracle import oracle
@@ -118,6 +118,42 @@ def test_gemv_other_shapes_with_delays(torch, K, N, batch):
     got = meas.cpu().numpy()
     assert np.all(got >= req)
     assert abs(got.mean() - req.mean()) / req.mean() <= 0.01
+
+
+@pytest.mark.parametrize("delays", [False, True])
+@pytest.mark.parametrize("K,page", [(512, PAGE), (1024, PAGE), (2048, PAGE), (4096, PAGE), (1024, 8192), (4096, 32768),
+                                    (1536, 12288)])
+def test_gemv_page_kernels(torch, K, page, delays):
+    """Every page kernel: each column count of the 16 KiB pages and other page
+    sizes, batches at the edges of the rows taken at a time.  Any order of
+    summing K exact products in fp32 is within K 2^-24 of their magnitudes'
+    sum."""
+    from paper_2609_09800_amd import hbf
+    N = page // (2 * K) * 7
+    params = dict(wl.geometry(16, 8, 4), page_bytes=page)
+    for batch in (1, 2, 3, 4, 7, 8, 9, 15, 16, 17, 24, 63, 64):
+        say(f"gemv page kernel K={K} page={page} batch={batch} delays={delays}")
+        W, X = wl.config4_operands(seed=K + batch, batch=batch, experts=2, K=K, N=N)
+        raw = torch.empty(W.nbytes + page, dtype=torch.uint8, device="cuda")
+        off = (-raw.data_ptr()) % page
+        Wd = raw[off:off + W.nbytes].view(torch.int16).view(W.shape)
+        Wd.copy_(torch.from_numpy(W.view(np.int16)))
+        Xd = torch.from_numpy(X.view(np.int16)).cuda()
+        Y = torch.full((2, batch, N), float("nan"), dtype=torch.float32, device="cuda")
+        m = hbf.Model(**params)
+        assert m.register_range(Wd.data_ptr(), W.nbytes)[0] == 0
+        pages = W.nbytes // page
+        times = []
+        if delays:
+            rng = np.random.default_rng(batch)
+            times = [torch.zeros(pages, dtype=torch.int64, device="cuda"),
+                     torch.from_numpy(rng.integers(0, 3, pages).astype(np.int64) * 1500).cuda()]
+        assert m.gemv_instrumented(Wd, Xd, Y, *times) == 0
+        assert m.get_status() == 0
+        w, x = ((v.astype(np.uint32) << 16).view(np.float32).astype(np.float64) for v in (W.view(np.uint16), X.view(np.uint16)))
+        ref = np.matmul(x, w.transpose(0, 2, 1))
+        room = K * 2.0 ** -24 * np.matmul(np.abs(x), np.abs(w).transpose(0, 2, 1))
+        assert (np.abs(Y.cpu().numpy() - ref) <= room).all(), batch
 
 
 def test_gemv_without_delays(torch):
