@@ -201,7 +201,7 @@ int hbf_time_requests(hbf_model_t model, const uint64_t *dev_addr, const int64_t
  * earlier call that launches work creates it, e.g. hbf_model_reset);
  * HBF_ENOWORKSPACE if hbf_workspace_bytes(model, n) exceeds
  * HBF_NOALLOC_SCRATCH_BYTES (up to about 4 M requests on the 16 x 8 x 4
- * geometry, 2.9 M with 2,048 die queues). */
+ * geometry, 3.3 M with 2,048 die queues). */
 #define HBF_NOALLOC_SCRATCH_BYTES (64ull << 20)
 int hbf_time_requests_noalloc(hbf_model_t model, const uint64_t *dev_addr, const int64_t *dev_issue_ns,
                               int64_t n, int64_t *dev_complete_ns, void *stream);
