@@ -555,7 +555,7 @@ __global__ __launch_bounds__(64 * RW) void k_regblock(const uint64_t *__restrict
   if (__ballot(err != 0)) {
     uint32_t e = err;
     for (int d = 32; d >= 1; d >>= 1) e |= (uint32_t)__shfl_xor((int)e, d);
-    if (lane == 0) atomicOr(&ctl->err, e);
+    if (lane == 0) atomicOr(&ctl->late, e);
   }
 }
 

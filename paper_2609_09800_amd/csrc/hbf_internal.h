@@ -104,7 +104,9 @@ struct DevState {
 // Completion cell of a refresh quantum that has not been served.
 constexpr int64_t REFRESH_PENDING = -1;
 
-// Per-call control block (in the workspace).
+// Per-call control block (in the workspace).  The waves of a workgroup read
+// `err` one by one and leave the call on it, so no kernel that does so may
+// write it: what the channel stage finds goes to `late`, and k_finalize adds it.
 struct CallCtl {
   uint32_t err;       // per-call error bits
   uint32_t n_in;      // in-range requests
@@ -114,6 +116,7 @@ struct CallCtl {
   int64_t max_cpl;    // largest in-range completion of the call (NEG if none)
   int64_t cbase;      // origin of the cell grid (= first issue time)
   uint32_t wctr;      // next unit of the channel stage
+  uint32_t late;      // error bits found by the channel stage
 };
 
 // Workspace layout of one hbf_time_requests call.

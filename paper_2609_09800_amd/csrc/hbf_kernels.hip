@@ -280,7 +280,7 @@ DEVI void key_scan(const uint32_t *totals, const int64_t *dfnew, uint32_t K, uin
   if (lane_id() == 0) atomicMax((long long *)&s_dd, (long long)dd);
   __syncthreads();
   if (threadIdx.x == 0) {
-    CallCtl c = {err, tot, 0, 0, s_dd, NEG, 0, 0};
+    CallCtl c = {err, tot, 0, 0, s_dd, NEG, 0, 0, 0};
     if (s_dd >= TIME_LIMIT) c.err |= ERR_OVERFLOW;
     if (tot != 0) {
       c.cbase = issue[0];
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(TSBLK) void k_tile_scan(const uint32_t *__restrict_
   if (MODE != TS_COUNT) {
     const uint32_t err = st->call_err;  // of pass 1; the same for every block
     if (err) {
-      if (blockIdx.x == 0 && t == 0) *ctl = CallCtl{err, 0, 0, 0, NEG, NEG, 0, 0};
+      if (blockIdx.x == 0 && t == 0) *ctl = CallCtl{err, 0, 0, 0, NEG, NEG, 0, 0, 0};
       return;
     }
   }
@@ -1408,11 +1408,12 @@ __global__ __launch_bounds__(BLK) void k_finalize(int64_t *__restrict__ complete
                                                   const uint32_t *__restrict__ totals,
                                                   const int64_t *__restrict__ cfnew, uint32_t K,
                                                   uint32_t C) {
-  const uint32_t err = agent_load32(&ctl->err);
+  const uint32_t late = agent_load32(&ctl->late), err = agent_load32(&ctl->err) | late;
   if (err) {
     for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK)
       complete[i] = HBF_TIME_ERROR;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+      ctl->err = err;  // (`late` decides the same for workgroups that read this one)
       atomicOr(&st->sticky, err);
       st->call_err = 0;
     }

@@ -238,3 +238,22 @@ def test_die_bound_stretches(torch, geo):
         steps[rng.choice(n, 20, replace=False)] = 40 * tR
         addr = np.uint64(wl.RANGE_BASE) + pg.astype(np.uint64) * np.uint64(wl.PAGE)
         check_call(torch, g, o, addr, (call << 40) + np.cumsum(steps).astype(np.int64), f"die-bound {geo} call {call}")
+
+
+def test_overflow_on_one_of_many_channels(torch):
+    """One channel's clock next to 2^62, on 1,024 channels (more workgroups
+    than run at once, so many start after that channel has failed): the call
+    fails as a whole, the clocks stay, and the next call is right."""
+    params = wl.geometry(1024, 2, 1, flags=BLOCK)
+    g, o = pair(params, [(wl.RANGE_BASE, 1 << 30)])
+    rng = np.random.default_rng(77)
+    pages = rng.integers(0, (1 << 30) // wl.PAGE, 40000)
+    issue = np.sort(rng.integers(0, 100_000, pages.size))
+    die = np.full(2048, -(1 << 63), dtype=np.int64)
+    chan = np.full(1024, -(1 << 63), dtype=np.int64)
+    chan[3] = (1 << 62) - 2000
+    assert g.set_state(die, chan) == 0 and o.set_state(die, chan) == 0
+    addr = np.uint64(wl.RANGE_BASE) + pages.astype(np.uint64) * np.uint64(wl.PAGE)
+    check_call(torch, g, o, addr, issue, "one channel overflows")
+    rest = pages % 1024 != 3
+    check_call(torch, g, o, addr[rest], issue[rest], "the others go on")

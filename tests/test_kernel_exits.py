@@ -1,0 +1,26 @@
+"""Kernels whose workgroups meet at barriers must leave a call as whole
+workgroups.  Their waves read the control block's error word one by one, so
+no workgroup of the same launch may write it: a late workgroup would
+otherwise split, and the waves that stay would work from LDS that nobody
+filled.  (Read from the source: a split depends on timing and cannot be shown
+by running the kernels.)"""
+import os
+import re
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_09800_amd", "csrc")
+
+
+def body(src, name):
+    """Source text of the function `name`, up to the brace in column 0 that ends it."""
+    at = re.search(r"\b%s\(" % name, src).start()
+    return src[at:src.index("\n}\n", at)]
+
+
+@pytest.mark.parametrize("file,exits,works", [("hbf_blocking.hip", "k_regblock", "k_regblock")])
+def test_the_word_a_workgroup_leaves_on_is_not_written(file, exits, works):
+    src = open(os.path.join(CSRC, file)).read()
+    assert re.search(r"if \(.*ctl->err.*\) return;", body(src, exits))
+    text = re.sub(r"//[^\n]*", "", body(src, exits) + body(src, works))
+    assert not re.search(r"\batomic[A-Z]\w*\(&ctl->err\b|ctl->err\s*\|?=[^=]", text)
