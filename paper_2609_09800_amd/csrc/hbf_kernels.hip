@@ -1370,7 +1370,7 @@ DEVI void chan_units(WinLds &S, const DieOrder &D, const uint32_t *__restrict__ 
     }
     __syncthreads();
   }
-  if (errb) atomicOr(&ctl->err, errb);
+  if (errb) atomicOr(&ctl->late, errb);
 }
 
 // SL: die runs per channel of the bucket merge; WHAT: the grids this kernel

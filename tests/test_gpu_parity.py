@@ -240,6 +240,24 @@ def test_time_domain_overflow_and_resume(torch):
     run_both(torch, params, [(1 << 40, 1 << 30)], [(addr, issue)], "resume", set_state=(df, cf))
 
 
+@pytest.mark.parametrize("geo,n", [((64, 4, 1), 20_000), ((64, 32, 1), 20_000), ((16, 8, 1), (1 << 22) + 1)])
+def test_overflow_in_the_channel_stage(torch, geo, n):
+    """One channel's clock next to 2^62: found while the channel stage runs
+    (bucket merge, lane merge, and both in kernels of their own); the call
+    fails as a whole, the clocks stay, and the next call is right."""
+    params = wl.geometry(*geo, t_read_ns=3000)
+    ranges = [(1 << 40, 1 << 36)]
+    rng = np.random.default_rng(n)
+    pages = rng.integers(0, (1 << 36) // 16384, n)
+    issue = np.sort(rng.integers(0, 40 * n, n))
+    addr = np.uint64(1 << 40) + pages.astype(np.uint64) * np.uint64(16384)
+    cf = np.full(geo[0], I64MIN, dtype=np.int64)
+    cf[5] = (1 << 62) - 2000
+    rest = pages % geo[0] != 5
+    run_both(torch, params, ranges, [(addr, issue), (addr[rest], issue[rest])], "channel overflow",
+             set_state=(np.full(geo[0] * geo[1], I64MIN, dtype=np.int64), cf))
+
+
 def test_reset_restores_idle(torch):
     params = wl.geometry(4, 4, 1)
     w = wl.random_stream(8, 9_000, params, 1024, 100.0)

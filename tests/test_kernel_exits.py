@@ -18,7 +18,10 @@ def body(src, name):
     return src[at:src.index("\n}\n", at)]
 
 
-@pytest.mark.parametrize("file,exits,works", [("hbf_blocking.hip", "k_regblock", "k_regblock")])
+@pytest.mark.parametrize("file,exits,works", [
+    ("hbf_blocking.hip", "k_regblock", "k_regblock"),
+    ("hbf_kernels.hip", "k_cell_chan", "chan_units"),
+])
 def test_the_word_a_workgroup_leaves_on_is_not_written(file, exits, works):
     src = open(os.path.join(CSRC, file)).read()
     assert re.search(r"if \(.*ctl->err.*\) return;", body(src, exits))
