@@ -43,6 +43,7 @@
 #include <algorithm>
 
 #include "hbf_cache_run.h"
+#include "hbf_group.h"
 #include "hbf_internal.h"
 
 namespace hbf {
@@ -118,7 +119,8 @@ struct Group {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       uint32_t spin = 0;
-      while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target && ++spin < SPIN_MAX)
+      while (!counter_reached(__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), target) &&
+             ++spin < SPIN_MAX)
         __builtin_amdgcn_s_sleep(1);
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       s_ok = spin < SPIN_MAX;
