@@ -809,7 +809,12 @@ struct ChunkRun {
 
 __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
   __shared__ RunLds S;
-  if (ld(A.status)) return;  // a page outside the range: nothing changes
+  // A page outside the range: nothing changes.  (One thread reads the word
+  // for all: a barrier that runs out writes it during the launch.)
+  __shared__ uint32_t s_go;
+  if (threadIdx.x == 0) s_go = ld(A.status) == 0;
+  __syncthreads();
+  if (!s_go) return;
   const uint32_t nb = gridDim.x / A.groups, grp = blockIdx.x / nb;
   if (grp >= A.groups) return;
   Group gr = {blockIdx.x - grp * nb, nb, A.bars + grp, 0, A.status};

@@ -27,3 +27,12 @@ def test_the_word_a_workgroup_leaves_on_is_not_written(file, exits, works):
     assert re.search(r"if \(.*ctl->err.*\) return;", body(src, exits))
     text = re.sub(r"//[^\n]*", "", body(src, exits) + body(src, works))
     assert not re.search(r"\batomic[A-Z]\w*\(&ctl->err\b|ctl->err\s*\|?=[^=]", text)
+
+
+def test_the_cache_kernel_reads_its_status_once_per_workgroup():
+    """Barriers that run out write the status word during the launch."""
+    src = open(os.path.join(CSRC, "hbf_cache_chunk.hip")).read()
+    text = re.sub(r"//[^\n]*", "", body(src, "k_chunk_run"))
+    assert "st(status," in src
+    reads = re.findall(r"[^;]*ld\(A\.status\)[^;]*;", text)
+    assert len(reads) == 1 and "if (threadIdx.x == 0)" in reads[0]
