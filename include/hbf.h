@@ -379,7 +379,10 @@ int hbf_cache_reset(hbf_cache_t cache, void *stream);
  * hits, faults, prefetch reads, prefetched pages used, prefetched pages
  * evicted unused, all since the last reset; [5] prefetch reads issued by
  * this call; [6] 0, or HBF_EINVAL if some page was >= range_pages (then
- * nothing changed and dev_hit is not written); [7] 0.  Asynchronous. */
+ * nothing changed and dev_hit is not written), or HBF_EINTERNAL if a bounded
+ * wait inside the call ran out (never expected; the cache was left part-way
+ * through a chunk and the call's outputs mean nothing: reset it before the
+ * next call); [7] 0.  Asynchronous. */
 int hbf_cache_access(hbf_cache_t cache, const uint64_t *dev_pages, int64_t n, uint8_t *dev_hit,
                      uint64_t *dev_pf_page, int64_t *dev_pf_src, int64_t pf_cap, int64_t *dev_counts,
                      void *stream);
@@ -411,7 +414,8 @@ int hbf_cache_get_chunk(hbf_cache_t cache, uint32_t *accesses);
  * range pages, range_pages*8 for larger ranges, frames*12 below 64 frames;
  * HBF_ENOMEM if that does not fit) and synchronises `stream` before
  * returning; returns HBF_EINVAL if some page was >= range_pages (counts
- * then all zero). */
+ * then all zero), HBF_EINTERNAL if a bounded wait ran out (never expected;
+ * counts then mean nothing). */
 int hbf_cache_sweep(const uint32_t *host_frames, const uint32_t *host_prefetch, int n_cfg, uint64_t range_pages,
                     const uint64_t *dev_pages, int64_t n, int64_t *dev_counts, void *stream);
 

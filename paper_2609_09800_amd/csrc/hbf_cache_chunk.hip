@@ -830,20 +830,27 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
     uint32_t len = A.chunk ? A.chunk : min(cc.Lmax, CHUNK_FIRST), seq = SEQ_MIN;
     uint32_t epoch = ld(&cc.ctl->epoch);
     int64_t pos = 0;
+    // A barrier of the chunk.  Where it runs out the call ends, and later ones
+    // begin past every tag in use (workgroups are at most one chunk apart).
+    auto meet = [&]() {
+      if (gr.sync()) return true;
+      if (threadIdx.x == 0) atomicMax(&cc.ctl->epoch, epoch + 2);
+      return false;
+    };
     while (pos < A.n) {  // (all of it the same on every workgroup of the group)
       if (epoch >= 0xFFFFFF00u) {  // tags about to repeat
         chunk_clear(gr, cc, A.R);
         epoch = 0;
-        if (!gr.sync()) return;
+        if (!meet()) return;
       }
       const Tags tg(++epoch);
       const uint64_t *pages = A.pages + pos;
       const int64_t L = A.n - pos < (int64_t)len ? A.n - pos : (int64_t)len;
       const int64_t I0 = ld(&c.ctl->ins), lim = I0 - (int64_t)c.F, npf0 = n_pf ? ld(n_pf) : 0;
       chunk_tag(gr, cc, pages, L, epoch, tg);
-      if (!gr.sync()) return;
+      if (!meet()) return;
       chunk_starts(gr, c, cc, pages, L, A.R, lim, epoch, tg);
-      if (!gr.sync()) return;
+      if (!meet()) return;
       if (!A.chunk) {
         const uint64_t lw = ld(&cc.ctl->loose[epoch & 1]);
         const uint32_t loose = (uint32_t)lw, late = (uint32_t)(lw >> 32);
@@ -854,24 +861,24 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
       }
       if (c.d > 0) {
         chunk_walk(gr, c, cc, A.R, lim, tg);
-        if (!gr.sync()) return;
+        if (!meet()) return;
         chunk_sums(gr, cc, L);
-        if (!gr.sync()) return;
+        if (!meet()) return;
       }
       chunk_scan(gr, c, cc, pages, L, A.R, I0, tg);
-      if (!gr.sync()) return;
+      if (!meet()) return;
       chunk_check(gr, c, cc, pages, L, A.R, I0, tg);
-      if (!gr.sync()) return;
+      if (!meet()) return;
       const int64_t T = ld(&cc.ctl->good);
       const int64_t I1 = I0 + (int64_t)(ld(&cc.S[T]) >> 32);
       if (I1 > (int64_t)c.F && I0 > 0) {  // frames of before are evicted
         chunk_lost(gr, c, cc, pages, T, I0, I1, tg);
-        if (!gr.sync()) return;
+        if (!meet()) return;
       }
       chunk_commit(gr, c, cc, pages, pos, L, T, A.R, I0, npf0, tg, hit, pf_page, A.pf_src, A.pf_cap, n_pf);
       pos += T;
       if (pos >= A.n) break;  // nothing of this cache is read again
-      if (!gr.sync()) return;
+      if (!meet()) return;
       if (T == L) {
         len = min(len > most / 2 ? most : len * 2, most);
         seq = SEQ_MIN;
@@ -882,7 +889,7 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
       const int64_t m = A.n - pos < (int64_t)seq ? A.n - pos : (int64_t)seq;
       if (gr.b == 0 && threadIdx.x < 64)
         cache_run_wave(c, S, A.R, A.pages + pos, m, hit ? hit + pos : nullptr, pf_page, A.pf_src, A.pf_cap, n_pf, pos);
-      if (!gr.sync()) return;
+      if (!meet()) return;
       pos += m;
       seq = min(seq * 2, SEQ_MAX);
       len = min(most, CHUNK_MIN);

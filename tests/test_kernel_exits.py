@@ -36,3 +36,13 @@ def test_the_cache_kernel_reads_its_status_once_per_workgroup():
     assert "st(status," in src
     reads = re.findall(r"[^;]*ld\(A\.status\)[^;]*;", text)
     assert len(reads) == 1 and "if (threadIdx.x == 0)" in reads[0]
+
+
+def test_a_cache_call_that_runs_out_leaves_its_tags_behind():
+    """Page words are told apart by the chunk's tag, which a reset does not
+    clear: a call that ends at a barrier must not let the next one use its
+    tags again, so every barrier of k_chunk_run passes the last tag on."""
+    src = open(os.path.join(CSRC, "hbf_cache_chunk.hip")).read()
+    text = re.sub(r"//[^\n]*", "", body(src, "k_chunk_run"))
+    assert text.count("gr.sync()") == 1
+    assert re.search(r"if \(gr\.sync\(\)\) return true;\s*if \(threadIdx\.x == 0\) atomicMax\(&cc\.ctl->epoch, epoch \+ 2\);", text)
