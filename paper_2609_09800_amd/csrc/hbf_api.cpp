@@ -624,9 +624,10 @@ struct hbf_cache {
   bool asked = false;          // the caller set the chunk length
 };
 
-// status, the call's prefetch reads, then the barriers of the chunked solve;
-// zeroed by every call
-constexpr int64_t CACHE_STATUS_WORDS = 2 + CHUNK_GROUPS / 2;
+// status, the call's prefetch reads, then (in the next line) the words of the
+// chunked solve's groups; zeroed by every call
+constexpr int64_t CACHE_GROUP_AT = 16;
+constexpr int64_t cache_status_words(int groups) { return CACHE_GROUP_AT + groups * (int64_t)(sizeof(GroupWords) / 8); }
 
 static bool cache_params_ok(uint32_t F, uint32_t d, uint64_t R) {
   return F >= 1 && F < (1u << 31) && d < F && d <= CACHE_MAX_PREFETCH && R >= 1 && R <= (uint64_t)N_LIMIT;
@@ -676,7 +677,7 @@ static int cache_alloc(const uint32_t *F, const uint32_t *d, const uint32_t *lma
   const size_t occfg = o;
   o = up256(o + sizeof(ChunkCfg) * n);
   const size_t ost = o;
-  o = up256(o + CACHE_STATUS_WORDS * 8);
+  o = up256(o + cache_status_words(std::min(n, CHUNK_GROUPS)) * 8);
   void *p = nullptr;
   if (hipMalloc(&p, o) != hipSuccess) return HBF_ENOMEM;
   char *base = (char *)p;
@@ -806,12 +807,12 @@ int hbf_cache_access(hbf_cache_t c, const uint64_t *pages, int64_t n, uint8_t *h
   if (!c || !counts || n < 0 || n > N_LIMIT || (n > 0 && (!pages || !hit))) return HBF_EINVAL;
   if ((pf_page == nullptr) != (pf_src == nullptr) || pf_cap < 0) return HBF_EINVAL;
   const hipStream_t s = (hipStream_t)stream;
-  if (launch_fill(c->status, CACHE_STATUS_WORDS, 0, s) != hipSuccess) return HBF_EHIP;
+  if (launch_fill(c->status, cache_status_words(1), 0, s) != hipSuccess) return HBF_EHIP;
   if (n > 0 && c->chunk) {
     if (launch_cache_check(pages, n, c->R, c->status, s) != hipSuccess ||
         launch_cache_chunks(c->dcfg, c->dccfg, c->dids, 1, c->R, pages, n, c->asked ? c->chunk : 0, hit, pf_page,
-                            pf_src, pf_page ? pf_cap : 0, c->status, c->status + 1, (uint32_t *)(c->status + 2),
-                            s) != hipSuccess ||
+                            pf_src, pf_page ? pf_cap : 0, c->status, c->status + 1,
+                            (GroupWords *)(c->status + CACHE_GROUP_AT), s) != hipSuccess ||
         launch_cache_pending(c->dcfg, c->dids, 1, c->F, c->status, s) != hipSuccess)
       return HBF_EHIP;
   } else if (n > 0 && launch_cache_run(c->dcfg, c->dids, 1, c->F <= CACHE_LDS_MAX, c->F, c->R, pages, n, hit,
@@ -845,7 +846,7 @@ int hbf_cache_sweep(const uint32_t *frames, const uint32_t *prefetch, int n_cfg,
     else max_chunk = std::max(max_chunk, frames[b]);
   }
   const int *ids_seq = al.dids + al.n_lds, *ids_chunk = al.dids + al.n_lds + al.n_seq;
-  bool ok = launch_fill(al.status, CACHE_STATUS_WORDS, 0, s) == hipSuccess &&
+  bool ok = launch_fill(al.status, cache_status_words(std::min(n_cfg, CHUNK_GROUPS)), 0, s) == hipSuccess &&
             launch_cache_clear(al.dcfg, n_cfg, range_pages, max_f, s) == hipSuccess;
   if (ok && al.n_chunk) ok = launch_chunk_clear(al.dccfg, ids_chunk, al.n_chunk, range_pages, s) == hipSuccess;
   // the LDS-resident caches, the sequential device-memory ones, then the
@@ -859,7 +860,8 @@ int hbf_cache_sweep(const uint32_t *frames, const uint32_t *prefetch, int n_cfg,
   if (ok && n > 0 && al.n_chunk > 0) {
     ok = (al.n_lds + al.n_seq > 0 || launch_cache_check(pages, n, range_pages, al.status, s) == hipSuccess) &&
          launch_cache_chunks(al.dcfg, al.dccfg, ids_chunk, al.n_chunk, range_pages, pages, n, 0, nullptr, nullptr,
-                             nullptr, 0, al.status, nullptr, (uint32_t *)(al.status + 2), s) == hipSuccess &&
+                             nullptr, 0, al.status, nullptr, (GroupWords *)(al.status + CACHE_GROUP_AT),
+                             s) == hipSuccess &&
          launch_cache_pending(al.dcfg, ids_chunk, al.n_chunk, max_chunk, al.status, s) == hipSuccess;
   }
   ok = ok && launch_cache_report(al.dcfg, n_cfg, nullptr, al.status, counts, 5, s) == hipSuccess;

@@ -25,8 +25,11 @@
 // insertions from it on are undone, and the next chunk begins there.  Nothing
 // scales with the range: per-page state is tagged with the chunk's epoch.
 //
-// One cooperative launch serves a whole call: a group of workgroups per
-// cache, with a barrier of the group between the steps of a chunk.  Chunks
+// One launch serves a whole call: a group of workgroups per cache, with a
+// barrier of the group between the steps of a chunk.  Nothing relies on all of
+// them running at once (a captured call may be replayed beside another, and
+// kernels of other streams hold CUs): a group is whoever has started when it
+// closes (group_join).  Chunks
 // are as long as their checks let them be: doubled while they pass, cut to
 // twice what was committed when one does not, and where next to nothing is,
 // one wave takes a stretch access by access.  What bounds a chunk is the chain
@@ -97,13 +100,47 @@ constexpr uint32_t SEQ_TRY = 1024;
 constexpr uint32_t DENSE_MIN = 4096;
 constexpr uint32_t SEQ_MIN = 4096, SEQ_MAX = 1u << 17;
 
-// The workgroups of one group: this one's number, how many, and their
-// barrier (a counter that only grows, zero at the launch).
+// How long a group waits for its workgroups to start, in ticks of 10 ns: 100 us
+// (starting 256 of them takes 10 or so), and, since fewer members take longer,
+// 1 ns more for each access.
+constexpr uint64_t PATIENCE = 10000, PATIENCE_PER = 10;
+
+// One group as one of its workgroups sees it: its number, the members, and
+// their barrier (a counter that only grows, zero at the launch).
 struct Group {
   uint32_t b, nb;
-  uint32_t *bar;
+  GroupWords *words;
   uint32_t target;
   int64_t *status;
+  // Of at most `want` workgroups (group_join); false: this one is not a member.
+  __device__ bool join(uint32_t want, uint64_t patience) {
+    struct Words {
+      GroupWords *w;
+      uint64_t from, patience;
+      __device__ uint32_t arrive() { return atomicAdd(&w->arrived, 1u); }
+      __device__ uint32_t close() { return atomicOr(&w->arrived, GROUP_CLOSED); }
+      __device__ uint32_t count() { return ld(&w->members); }
+      __device__ void set_count(uint32_t n) { st(&w->members, n); }
+      __device__ bool wait() {
+        __builtin_amdgcn_s_sleep(1);
+        return __builtin_amdgcn_s_memrealtime() - from < patience;
+      }
+    };
+    __shared__ Member s_m;
+    if (want > 1) {
+      if (threadIdx.x == 0) {
+        Words w = {words, __builtin_amdgcn_s_memrealtime(), patience};
+        s_m = group_join(w, want);
+      }
+      __syncthreads();
+      b = s_m.id;
+      nb = s_m.count;
+    } else {
+      b = 0;
+      nb = 1;
+    }
+    return nb != 0;
+  }
   // Every store of the group before is visible to every load after.  False
   // (bounded wait, never expected) ends the kernel with HBF_EINTERNAL.
   __device__ bool sync() {
@@ -117,6 +154,7 @@ struct Group {
     }
     if (threadIdx.x == 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      uint32_t *bar = &words->bar;
       __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       uint32_t spin = 0;
       while (!counter_reached(__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), target) &&
@@ -804,7 +842,7 @@ struct ChunkRun {
   int64_t *pf_src;
   int64_t pf_cap;
   int64_t *status, *n_pf;
-  uint32_t *bars;  // one per group
+  GroupWords *words;  // one entry per group
 };
 
 __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
@@ -815,9 +853,10 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
   if (threadIdx.x == 0) s_go = ld(A.status) == 0;
   __syncthreads();
   if (!s_go) return;
-  const uint32_t nb = gridDim.x / A.groups, grp = blockIdx.x / nb;
+  const uint32_t want = gridDim.x / A.groups, grp = blockIdx.x / want;
   if (grp >= A.groups) return;
-  Group gr = {blockIdx.x - grp * nb, nb, A.bars + grp, 0, A.status};
+  Group gr = {0, 0, A.words + grp, 0, A.status};
+  if (!gr.join(want, PATIENCE + (uint64_t)A.n / PATIENCE_PER)) return;
   for (int ci = (int)grp; ci < A.n_ids; ci += (int)A.groups) {
     const int id = A.ids[ci];
     const CacheCfg c = A.cfgs[id];
@@ -921,34 +960,24 @@ hipError_t launch_chunk_clear(const ChunkCfg *dev_ccfgs, const int *cfg_ids, int
 static int64_t chunk_share(int64_t n) {
   return std::max((n + 2 * CBLK - 1) / (2 * CBLK), std::min((n + CBLK - 1) / CBLK, (int64_t)64));
 }
-// Workgroups of k_chunk_run resident at once (0: no cooperative launches).
-static int chunk_blocks() {
-  int dev = 0, coop = 0, ncu = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void *)k_chunk_run, CBLK, 0) != hipSuccess)
-    return 0;
-  return per > 0 ? ncu : 0;  // one per CU: a barrier's cost grows with the workgroups
-}
 
 hipError_t launch_cache_chunks(const CacheCfg *cfgs, const ChunkCfg *ccs, const int *ids, int n_cfg, uint64_t R,
                                const uint64_t *pages, int64_t n, uint32_t chunk, uint8_t *hit, uint64_t *pf_page,
-                               int64_t *pf_src, int64_t pf_cap, int64_t *status, int64_t *n_pf, uint32_t *bars,
+                               int64_t *pf_src, int64_t pf_cap, int64_t *status, int64_t *n_pf, GroupWords *words,
                                hipStream_t s) {
-  int blocks = chunk_blocks();
-  if (blocks <= 0) return hipErrorNotSupported;
-  ChunkRun A = {cfgs, ccs, ids, n_cfg, 0, R, pages, n, chunk, hit, pf_page, pf_src, pf_cap, status, n_pf, bars};
+  // one workgroup per CU: a barrier's cost grows with them
+  int dev = 0, blocks = 0;
+  hipError_t e;
+  if ((e = hipGetDevice(&dev)) != hipSuccess ||
+      (e = hipDeviceGetAttribute(&blocks, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
+    return e;
+  ChunkRun A = {cfgs, ccs, ids, n_cfg, 0, R, pages, n, chunk, hit, pf_page, pf_src, pf_cap, status, n_pf, words};
   // no more workgroups than a short call has work for
   const int64_t use = chunk_share(n) * n_cfg;
   if (use < blocks) blocks = (int)use;
   A.groups = (uint32_t)std::min(std::min(n_cfg, blocks), CHUNK_GROUPS);
-  if (blocks == 1) {  // no one to wait for
-    hipLaunchKernelGGL(k_chunk_run, dim3(1), dim3(CBLK), 0, s, A);
-    return hipGetLastError();
-  }
-  void *args[] = {&A};
-  return hipLaunchCooperativeKernel((const void *)k_chunk_run, dim3((uint32_t)blocks), dim3(CBLK), args, 0, s);
+  hipLaunchKernelGGL(k_chunk_run, dim3((uint32_t)blocks), dim3(CBLK), 0, s, A);
+  return hipGetLastError();
 }
 
 }  // namespace hbf

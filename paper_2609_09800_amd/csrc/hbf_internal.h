@@ -241,6 +241,12 @@ struct ChunkCfg {
   ChunkCtl *ctl;
   uint32_t Lmax;
 };
+// The words by which the workgroups of one group meet, each in a line of its own.
+struct GroupWords {
+  uint32_t bar, pad0[31];      // arrivals at barriers
+  uint32_t arrived, pad1[31];  // workgroups that have started (group_join)
+  uint32_t members, pad2[31];
+};
 constexpr uint32_t CHUNK_MAX = 1u << 18;          // accesses per chunk that a caller can ask for
 constexpr uint32_t CHUNK_LIMIT = 1u << 21;        // accesses per chunk (24 bits of a page's word hold a time)
 constexpr uint32_t CHUNK_FIRST = 1u << 20;        // accesses of a call's first chunk
@@ -278,13 +284,13 @@ hipError_t launch_cache_run(const CacheCfg *dev_cfgs, const int *cfg_ids, int n_
                             int64_t *pf_src, int64_t pf_cap, int64_t *status, int64_t *n_pf_out, hipStream_t s);
 hipError_t cache_set_lds_limit();
 // Serve pages[0..n) on the caches ids[0..n_cfg) (all with chunk state): one
-// cooperative launch.  chunk: accesses per chunk (0: as many as pass their
-// check).  hit (n entries), pf_*, n_pf: the first cache's, or null.  bars:
-// CHUNK_GROUPS words, zero.  hipErrorNotSupported without cooperative launches.
+// launch.  chunk: accesses per chunk (0: as many as pass their check).  hit (n
+// entries), pf_*, n_pf: the first cache's, or null.  groups: one entry per
+// cache, at most CHUNK_GROUPS of them, zero.
 hipError_t launch_cache_chunks(const CacheCfg *dev_cfgs, const ChunkCfg *dev_ccfgs, const int *cfg_ids, int n_cfg,
                                uint64_t R, const uint64_t *pages, int64_t n, uint32_t chunk, uint8_t *hit,
                                uint64_t *pf_page, int64_t *pf_src, int64_t pf_cap, int64_t *status, int64_t *n_pf,
-                               uint32_t *bars, hipStream_t s);
+                               GroupWords *groups, hipStream_t s);
 hipError_t launch_cache_check(const uint64_t *pages, int64_t n, uint64_t R, int64_t *status, hipStream_t s);
 hipError_t launch_cache_pending(const CacheCfg *dev_cfgs, const int *cfg_ids, int n_cfg, uint32_t max_f,
                                 const int64_t *status, hipStream_t s);

@@ -330,3 +330,51 @@ def test_captured_calls(torch, n):
         assert np.array_equal(cnt.cpu().numpy()[:5], o.counts())
         (hit.float() * 2).sum().item()
     g.close()
+
+
+@pytest.mark.parametrize("captured", [True, False])
+def test_calls_side_by_side(torch, captured):
+    """Calls of two caches on two streams at the same time, captured and
+    replayed or launched, with another stream's kernels between them: no call
+    waits for workgroups that the others leave no room for."""
+    from oracle import oracle
+    from paper_2609_09800_amd import hbf
+    rng = np.random.default_rng(6)
+    F, d, R, n = 9000, 7, 600011, 300000
+    caches = [hbf.Cache(F, d, R) for _ in range(2)]
+    models = [oracle.OracleCache(F, d, R) for _ in range(2)]
+    streams_ = [torch.cuda.Stream() for _ in range(3)]
+    pd = [torch.zeros(n, dtype=torch.int64, device="cuda") for _ in range(2)]
+    hit = [torch.empty(n, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    cnt = [torch.zeros(8, dtype=torch.int64, device="cuda") for _ in range(2)]
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    graphs = []
+    if captured:
+        for i in range(2):
+            graphs.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(graphs[i], stream=streams_[i]):
+                assert caches[i].access(pd[i], hit[i], cnt[i], stream=streams_[i]) == 0
+    for r in range(5):
+        say(f"side by side captured={captured} round {r}")
+        pages = [np.ascontiguousarray(auto_stream(rng, k, n, R, d), dtype=np.int64) for k in ("scans", "spaced")]
+        for i in range(2):
+            pd[i].copy_(torch.from_numpy(pages[i]))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(streams_[2]):
+            for _ in range(4):
+                busy @ busy
+        for i in range(2):
+            with torch.cuda.stream(streams_[i]):
+                if captured:
+                    graphs[i].replay()
+                else:
+                    assert caches[i].access(pd[i], hit[i], cnt[i], stream=streams_[i]) == 0
+        torch.cuda.synchronize()
+        for i in range(2):
+            _, wh, _, _ = models[i].access(pages[i], pf_cap=0)
+            c = cnt[i].cpu().numpy()
+            assert c[6] == 0 and np.array_equal(c[:5], models[i].counts())
+            assert np.array_equal(hit[i].cpu().numpy(), wh)
+    for c in caches:
+        c.close()
