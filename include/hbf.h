@@ -395,10 +395,11 @@ int hbf_cache_access(hbf_cache_t cache, const uint64_t *dev_pages, int64_t n, ui
  * that is no longer within the last `frames` insertions at that moment; so
  * far it is exactly the FIFO answer and is kept, and the next chunk begins
  * there (or, where hardly anything was kept, after a stretch served one
- * access after another).  The chunk lengths follow from what was kept until
- * a length is set here, and are that one from then on; get_chunk reports
- * frames/16 clamped to [16384, 262144] for a cache with chunk state before,
- * 0 for others.  The results do not depend on the chunk length.
+ * access after another).  The chunk lengths follow from what was kept; a
+ * cache with chunk state reports that as frames/16 clamped to [16384,
+ * 262144], others report 0.  Setting another length fixes it, setting the
+ * one first reported goes back to lengths that follow from what was kept,
+ * 0 serves one access after another.  The results do not depend on it.
  * 0 <= accesses <= 262144; a nonzero value needs chunk state (HBF_EINVAL
  * otherwise).  Host only. */
 int hbf_cache_set_chunk(hbf_cache_t cache, uint32_t accesses);

@@ -620,8 +620,7 @@ struct hbf_cache {
   int64_t *status = nullptr;   // [0] status, [1] prefetch reads of the call
   int *dids = nullptr;
   uint32_t lmax = 0;           // chunk state allocated for chunks of up to lmax accesses
-  uint32_t chunk = 0;          // accesses per chunk as reported; 0 = the sequential run alone
-  bool asked = false;          // the caller set the chunk length
+  uint32_t chunk = 0;          // accesses per chunk as reported or set; 0 = the sequential run alone
 };
 
 // status, the call's prefetch reads, then (in the next line) the words of the
@@ -792,7 +791,6 @@ int hbf_cache_reset(hbf_cache_t c, void *stream) {
 int hbf_cache_set_chunk(hbf_cache_t c, uint32_t accesses) {
   if (!c || (accesses && (!c->dccfg || accesses > CHUNK_MAX))) return HBF_EINVAL;
   c->chunk = accesses;
-  c->asked = true;
   return HBF_OK;
 }
 
@@ -810,7 +808,7 @@ int hbf_cache_access(hbf_cache_t c, const uint64_t *pages, int64_t n, uint8_t *h
   if (launch_fill(c->status, cache_status_words(1), 0, s) != hipSuccess) return HBF_EHIP;
   if (n > 0 && c->chunk) {
     if (launch_cache_check(pages, n, c->R, c->status, s) != hipSuccess ||
-        launch_cache_chunks(c->dcfg, c->dccfg, c->dids, 1, c->R, pages, n, c->asked ? c->chunk : 0, hit, pf_page,
+        launch_cache_chunks(c->dcfg, c->dccfg, c->dids, 1, c->R, pages, n, chunk_asked(c->chunk, c->F, c->R), hit, pf_page,
                             pf_src, pf_page ? pf_cap : 0, c->status, c->status + 1,
                             (GroupWords *)(c->status + CACHE_GROUP_AT), s) != hipSuccess ||
         launch_cache_pending(c->dcfg, c->dids, 1, c->F, c->status, s) != hipSuccess)

@@ -269,6 +269,12 @@ inline uint32_t chunk_default(uint32_t F, uint64_t R) {
   uint32_t c = F / 16;
   return c < CHUNK_MIN ? CHUNK_MIN : (c > CHUNK_MAX ? CHUNK_MAX : c);
 }
+// The length a cache whose setting is `accesses` (not 0) asks of the chunked
+// solve: that one, or 0 (as long as the checks allow) where it is the one
+// reported for a new cache, so that putting a saved setting back is no change.
+inline uint32_t chunk_asked(uint32_t accesses, uint32_t F, uint64_t R) {
+  return accesses == chunk_default(F, R) ? 0 : accesses;
+}
 // Accesses a chunk's state holds over R pages: the state per access stays
 // below the state per page.
 inline uint32_t chunk_limit(uint64_t R) {
