@@ -38,6 +38,7 @@ namespace {
 constexpr int SM_THREADS = 1024;
 constexpr int SM_WAVES = SM_THREADS / 64;
 constexpr int SM_SLOTS = 8;  // requests per lane of a merge at most
+constexpr uint32_t SM_SHARE = 4 * SM_WAVES;  // channels above which several share a wave
 
 // LDS: ranges | wcnt[SM_WAVES][K] u16 | seg[K+1] u32 | cf[C] i64 | sdd[cap] i64 | sidx, skey [cap] u16,
 // cap = requests the workgroup holds
@@ -134,10 +135,59 @@ DEVI int64_t small_merge(const int64_t *sdd, const uint16_t *sidx, uint32_t cur,
   return imax(gin, lane63(inc));
 }
 
+// Several channels at once, 2^lw lanes each: a run has 2^lr of them, and the
+// lane holds `len` (at most SL) of its requests from staged position `at`.  The
+// group merges and completes its channel of m requests (0: none) as small_merge
+// does with 64 lanes.  cfree: the channel's clock; returns its term after the
+// call (on every lane).
+template <int SL>
+DEVI int64_t group_merge(const int64_t *sdd, const uint16_t *sidx, uint32_t at, uint32_t len, uint32_t lr,
+                         uint32_t lw, int64_t tb, uint32_t m, int64_t xfer, int64_t cfree,
+                         int64_t *__restrict__ complete, uint32_t *errb) {
+  const uint32_t lane = lane_id(), W = 1u << lw, sub = lane & (W - 1);
+  uint64_t a[SL];
+#pragma unroll
+  for (int i = 0; i < SL; i++) {
+    a[i] = KEY_NONE64;
+    if ((uint32_t)i < len) a[i] = KEY_TOP | (uint64_t)(sdd[at + i] - tb) << 31 | sidx[at + i];
+  }
+  if (lr <= 0 && lw >= 1) lane_merge<1, SL>(a);
+  if (lr <= 1 && lw >= 2) lane_merge<2, SL>(a);
+  if (lr <= 2 && lw >= 3) lane_merge<4, SL>(a);
+  if (lr <= 3 && lw >= 4) lane_merge<8, SL>(a);
+  if (lr <= 4 && lw >= 5) lane_merge<16, SL>(a);
+  if (lr <= 5 && lw >= 6) lane_merge<32, SL>(a);
+  const uint32_t p0 = sub * SL, mine = m > p0 ? min(m - p0, (uint32_t)SL) : 0u;
+  auto value = [&](int i) {  // of merged position p0 + i
+    return tb + (int64_t)((a[i] >> 31) & 0x3FFFFFFFu) - (int64_t)mul32(p0 + i, (uint32_t)xfer);
+  };
+  int64_t inc = NEG;
+#pragma unroll
+  for (int i = 0; i < SL; i++)
+    if ((uint32_t)i < mine) inc = imax(inc, value(i));
+  for (uint32_t o = 1; o < W; o <<= 1) {
+    const int64_t y = __shfl_up(inc, o);
+    if (sub >= o) inc = imax(inc, y);
+  }
+  int64_t carry = __shfl_up(inc, 1);
+  carry = sub ? imax(carry, cfree) : cfree;
+#pragma unroll
+  for (int i = 0; i < SL; i++) {
+    if ((uint32_t)i < mine) {
+      carry = imax(carry, value(i));
+      const int64_t cpl = (int64_t)mul32(p0 + i + 1, (uint32_t)xfer) + carry;
+      if (cpl >= TIME_LIMIT) *errb |= ERR_OVERFLOW;
+      complete[(uint32_t)a[i] & 0x7FFFFFFFu] = cpl;
+    }
+  }
+  return imax(cfree, __shfl(inc, (int)(lane | (W - 1))));
+}
+
 }  // namespace
 
-// ITEMS: requests per thread; the call has at most ITEMS * 1,024.
-template <bool POW2, int ITEMS>
+// ITEMS: requests per thread; the call has at most ITEMS * 1,024.  SHARE: more
+// than SM_SHARE channels.
+template <bool POW2, int ITEMS, bool SHARE>
 __global__ __launch_bounds__(SM_THREADS) void k_small(const uint64_t *__restrict__ addr,
                                                       const int64_t *__restrict__ issue, uint32_t n,
                                                       int64_t *__restrict__ complete, Geo g, RangeTable rt,
@@ -299,9 +349,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_small(const uint64_t *__restrict
   // then merge again with the terms entering them.
   const uint32_t lp = run_lanes_lg(Dk);
   const uint32_t most = (uint32_t)SM_SLOTS << lp;  // requests of a run per merge
-  const uint32_t parts = C <= 2 ? SM_WAVES / C : 1u;
-  for (uint32_t c0 = 0; c0 < C; c0 += SM_WAVES) {
-    const uint32_t c = c0 + w / parts, part = w % parts;  // (parts > 1: one round)
+  const uint32_t parts = !SHARE && C <= 2 ? SM_WAVES / C : 1u;
+  // one channel (or, with `parts` above 1, the wave's stretch of it)
+  auto channel = [&](uint32_t c, uint32_t part) {
     uint32_t lo = 0, hi = 0;
     int64_t rank = 0, term = NEG;
     if (c < C) {
@@ -378,6 +428,46 @@ __global__ __launch_bounds__(SM_THREADS) void k_small(const uint64_t *__restrict
         atomicMax((long long *)&s_max, (long long)cf[c]);
       }
     }
+  };
+  if constexpr (SHARE) {
+    // Many channels: 2^(lp - lr) of them share a wave, each run on 2^lr lanes,
+    // enough for twice the mean run.  A channel with a longer run, or with
+    // requests 2^30 ns after its first, follows by itself.  2,048 requests on
+    // 512 x 1: SHARE_US one by one.
+    uint32_t lr = 0;
+    while (lr < lp && (uint64_t)K * SM_SLOTS << lr < 2 * (uint64_t)m) lr++;
+    const uint32_t lw = 6 - lp + lr, hold = (uint32_t)SM_SLOTS << lr;
+    const uint32_t d = (lane & ((1u << lw) - 1)) >> lr, skip = (lane & ((1u << lr) - 1)) * SM_SLOTS;
+    for (uint32_t c0 = w << (6 - lw); c0 < C; c0 += SM_WAVES << (6 - lw)) {
+      const uint32_t c = c0 + (lane >> lw);
+      const bool on = c < C && d < Dk;
+      const uint32_t lo = on ? seg[c * Dk + d] : 0u, all = on ? seg[c * Dk + d + 1] - lo : 0u;
+      if (__ballot(all != 0) == 0) continue;
+      int64_t tb = all ? sdd[lo] : TIME_LIMIT;
+      for (uint32_t o = 1u << lr; o < (1u << lw); o <<= 1) tb = imin(tb, __shfl_xor(tb, o));
+      const uint64_t over = __ballot(all > hold || (all && sdd[lo + all - 1] - tb >= (int64_t(1) << 30)));
+      const uint64_t group = (lw == 6 ? ~uint64_t(0) : (uint64_t(1) << (1u << lw)) - 1) << (lane >> lw << lw);
+      const bool alone = (over & group) != 0;
+      uint32_t len = alone || all <= skip ? 0u : min(all - skip, (uint32_t)SM_SLOTS), mm = len;
+      for (uint32_t o = 1; o < (1u << lw); o <<= 1) mm += (uint32_t)__shfl_xor((int)mm, o);
+      const uint32_t longest = wave_umax(len);
+      if (longest) {
+        const int64_t cfree = c < C ? st->chan_free[c] : NEG;
+        const int64_t term = group_merge<SM_SLOTS>(sdd, sidx, lo + skip, len, lr, lw, tb, mm, xfer, cfree, complete,
+                                                   &errb);
+        if (mm && (lane & ((1u << lw) - 1)) == 0) {
+          cf[c] = mm * xfer + term;  // the channel's last completion
+          atomicMax((long long *)&s_max, (long long)cf[c]);
+        }
+      }
+      for (uint64_t rest = __ballot(alone); rest;) {
+        const uint32_t q = (uint32_t)__builtin_ctzll(rest) >> lw;
+        channel(c0 + q, 0);
+        rest &= ~((lw == 6 ? ~uint64_t(0) : (uint64_t(1) << (1u << lw)) - 1) << (q << lw));
+      }
+    }
+  } else {
+    for (uint32_t c0 = 0; c0 < C; c0 += SM_WAVES) channel(c0 + w / parts, w % parts);  // (parts > 1: one round)
   }
   if (errb) atomicOr(&s_err, errb);
   __syncthreads();
@@ -409,16 +499,21 @@ hipError_t launch_small(const Geo &g, const RangeTable &rt, DevState *st, CallCt
                         const int64_t *issue, int64_t n, int64_t *complete, hipStream_t s) {
   const int items = small_items(n);
   const size_t lds = small_layout(g.K, g.C, items * SM_THREADS).total;
-  auto f = g.pow2 ? (items == 2 ? k_small<true, 2> : k_small<true, 4>)
-                  : (items == 2 ? k_small<false, 2> : k_small<false, 4>);
+  auto pick = [&](auto two, auto four) { return items == 2 ? two : four; };
+  auto f = g.C > SM_SHARE ? (g.pow2 ? pick(k_small<true, 2, true>, k_small<true, 4, true>)
+                                              : pick(k_small<false, 2, true>, k_small<false, 4, true>))
+                                    : (g.pow2 ? pick(k_small<true, 2, false>, k_small<true, 4, false>)
+                                              : pick(k_small<false, 2, false>, k_small<false, 4, false>));
   hipLaunchKernelGGL(f, dim3(1), dim3(SM_THREADS), lds, s, addr, issue, (uint32_t)n, complete, g, rt, st, ctl);
   return hipGetLastError();
 }
 
 // (the largest LDS any geometry on this path asks for)
 hipError_t set_lds_small() {
-  const void *f[] = {(const void *)k_small<true, 2>, (const void *)k_small<true, 4>, (const void *)k_small<false, 2>,
-                     (const void *)k_small<false, 4>};
+  const void *f[] = {(const void *)k_small<true, 2, false>,  (const void *)k_small<true, 4, false>,
+                     (const void *)k_small<false, 2, false>, (const void *)k_small<false, 4, false>,
+                     (const void *)k_small<true, 2, true>,   (const void *)k_small<true, 4, true>,
+                     (const void *)k_small<false, 2, true>,  (const void *)k_small<false, 4, true>};
   for (const void *k : f) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SMALL_LDS_MAX);
     if (e != hipSuccess) return e;

@@ -160,7 +160,7 @@ def test_small_call_errors(torch, case):
 # every number of lanes per die run, one or two channels (several waves per
 # channel), more channels than waves, and 2,048 die queues
 MERGE_GEOMS = [(1, 1, 1, 0), (1, 16, 1, 0), (2, 9, 1, 0), (1, 17, 1, 0), (5, 33, 1, 0), (20, 3, 1, 0), (40, 8, 1, 0),
-               (2, 16, 4, 1), (32, 16, 4, 1), (1024, 2, 1, 0)]
+               (2, 16, 4, 1), (32, 16, 4, 1), (1024, 2, 1, 0), (512, 1, 1, 0), (100, 5, 1, 0), (65, 31, 1, 0)]
 
 
 @pytest.mark.parametrize("geo", MERGE_GEOMS, ids=lambda g: "x".join(map(str, g)))
