@@ -1054,13 +1054,27 @@ struct DieOrder {
 };
 
 // Order at most 64 * SL requests: lane d holds run d's position `lo` and
-// length `len` (at most SL << lp), base time tb (>= cstart, every request
-// within 2^30 of it).
+// length `len`, base time tb (>= cstart, every request within 2^30 of it).
+// Each run takes 2^lp neighbouring lanes (len at most SL << lp) or, with
+// `pieces`, as many lanes as it needs (lp 0, run_pieces<SL>(len) at most 64).
+template <int SL>
+DEVI uint32_t run_pieces(uint32_t len) { return (len + SL - 1) / SL; }
 template <int SL>
 DEVI void sort_take(const DieOrder &D, uint32_t lo, uint32_t len, uint32_t lp, int64_t cstart, int64_t tb,
-                    uint64_t (&slot)[SLOTS_MAX]) {
+                    uint64_t (&slot)[SLOTS_MAX], bool pieces = false) {
   const uint32_t lane = lane_id();
-  const uint32_t d = lane >> lp, skip = (lane & ((1u << lp) - 1)) * SL;
+  uint32_t d = lane >> lp, skip = (lane & ((1u << lp) - 1)) * SL;
+  if (pieces) {  // the lane's run: the first whose pieces end past the lane
+    const uint32_t end = wave_incl_sum(run_pieces<SL>(len));
+    uint32_t a = 0, b = 63;
+    for (int step = 0; step < 6; step++) {
+      const uint32_t mid = (a + b) >> 1;
+      if ((uint32_t)__shfl((int)end, (int)mid) > lane) b = mid;
+      else a = mid + 1;
+    }
+    d = a;
+    skip = (lane - ((uint32_t)__shfl((int)end, (int)d) - run_pieces<SL>((uint32_t)__shfl((int)len, (int)d)))) * SL;
+  }
   const uint32_t at = __shfl(lo, (int)d) + skip, have = __shfl(len, (int)d);
   const uint32_t cnt = have > skip ? have - skip : 0u;
   uint64_t a[SL];
@@ -1104,34 +1118,38 @@ DEVI void sorted_terms(Merged<SLOTS_MAX> &M, uint32_t m, uint32_t per, int64_t t
       M.loc = imax(M.loc, cst + slot_off<true>(M.slot[i]) - (int64_t)mul32(M.boff + i, (uint32_t)xfer));
 }
 
-// The next requests of a cell that one step cannot hold: those within
-// 2^sub_lg (at most 2^30) of the earliest one left, at most the 64 * 16 that
-// a grid cell of minimum width can hold.  cur/hi: lane d's run; returns the
-// step's requests of the lane's run and its base time, or false at the end.
-DEVI bool big_step(const DieOrder &D, uint32_t cur, uint32_t hi, uint32_t lp, uint32_t sub_lg, int64_t cstart,
-                   int64_t &tb, uint32_t &cnt, uint32_t *errb) {
-  const uint32_t rem = hi - cur;
+// The next requests of a cell that one step cannot hold: up to the first one
+// that the longest runs' lanes or the keys' offsets (2^30 from the earliest
+// left) leave out.  cur/hi: lane d's run; returns the step's requests of the
+// lane's run and its base time, or false at the end.  (One hot die queue in a
+// sparse stream makes its cells big; steps of a fixed 2^15 ns then took them
+// nearly a request at a time, 2.8 ms for 300,000 requests on 64 queues a
+// channel.)
+DEVI bool big_step(const DieOrder &D, uint32_t cur, uint32_t hi, uint32_t lp, int64_t cstart, int64_t &tb,
+                   uint32_t &cnt) {
+  const uint32_t rem = hi - cur, most = 16u << lp;
   if (__ballot(rem != 0) == 0) return false;
   // the wave's smallest time, by a maximum of 2^62 - time (0 where none)
   tb = TIME_LIMIT - wave_max(rem ? TIME_LIMIT - D.time(cur, cstart) : 0);
-  const int64_t te = tb + (int64_t(1) << sub_lg);
-  uint32_t a = 0, b = min(rem, 64u);
-  while (a < b) {
-    const uint32_t mid = (a + b) >> 1;
-    if (D.time(cur + mid, cstart) < te) a = mid + 1;
-    else b = mid;
-  }
-  cnt = a;
-  if (cnt > (16u << lp)) {  // impossible: a die emits at most one request per tR
-    *errb |= ERR_INTERNAL;
-    cnt = 16u << lp;
+  int64_t te = tb + (int64_t(1) << SUB_LG_MAX);
+  if (rem > most) te = imin(te, D.time(cur + most, cstart));
+  te = TIME_LIMIT - wave_max(TIME_LIMIT - te);
+  cnt = min(rem, most);
+  if (cnt && D.time(cur + cnt - 1, cstart) >= te) {  // (each run ascends)
+    uint32_t a = 0, b = cnt - 1;
+    while (a < b) {
+      const uint32_t mid = (a + b) >> 1;
+      if (D.time(cur + mid, cstart) < te) a = mid + 1;
+      else b = mid;
+    }
+    cnt = a;
   }
   return true;
 }
 
 // Order a cell by the lane merge.
 DEVI void cell_sort(const DieOrder &D, const CellRuns &cr, const Geo &g, uint32_t lp, uint32_t shift,
-                    uint32_t sub_lg, int64_t cstart, Merged<SLOTS_MAX> &M, uint32_t *errb) {
+                    int64_t cstart, Merged<SLOTS_MAX> &M) {
   const uint32_t len = cr.hi - cr.lo;
   M.m = wave_sum(len);
   M.cnt = 0;
@@ -1145,10 +1163,28 @@ DEVI void cell_sort(const DieOrder &D, const CellRuns &cr, const Geo &g, uint32_
   const uint32_t longest = wave_umax(len);
   M.head = ~wave_umax(len ? ~D.index(cr.lo) : 0u);  // a run's first entry has its smallest index
   M.big = longest > (16u << lp) || shift > SUB_LG_MAX;
+  // A run or two longer than their lanes, in a cell whose requests fit the
+  // wave: the lanes are dealt out by need (one hot die queue in a sparse
+  // stream; 9,000 requests on 8 x 64 queues 188 -> HOT_US us)
+  if (M.big && shift <= SUB_LG_MAX) {
+    uint32_t per = 0;
+    if (wave_sum(run_pieces<4>(len)) <= 64) {
+      per = 4;
+      sort_take<4>(D, cr.lo, len, 0, cstart, cstart, M.slot, true);
+    } else if (wave_sum(run_pieces<16>(len)) <= 64) {
+      per = 16;
+      sort_take<16>(D, cr.lo, len, 0, cstart, cstart, M.slot, true);
+    }
+    if (per) {
+      M.big = false;
+      sorted_terms(M, M.m, per, cstart, M.rank0, g.xfer);
+      return;
+    }
+  }
   uint32_t cur = cr.lo, take = len, m = M.m;
   int64_t tb = cstart, rank = M.rank0, term = NEG;
   // one step, or as many as a big cell takes (only their terms are kept)
-  while (!M.big || big_step(D, cur, cr.hi, lp, sub_lg, cstart, tb, take, errb)) {
+  while (!M.big || big_step(D, cur, cr.hi, lp, cstart, tb, take)) {
     const uint32_t most = M.big ? wave_umax(take) : longest;
     if (M.big) m = wave_sum(take);
     uint32_t per;
@@ -1215,11 +1251,11 @@ DEVI void cell_emit(const Merged<SL> &M, const Geo &g, int64_t tb, int64_t gin, 
 // Completions of a cell of the lane merge; a big cell takes its steps again,
 // now with the entering term.
 DEVI void sort_emit(const DieOrder &D, const CellRuns &cr, Merged<SLOTS_MAX> &M, const Geo &g, uint32_t lp,
-                    uint32_t sub_lg, int64_t cstart, int64_t gin, uint32_t lo, int64_t wbase, uint32_t *stage,
+                    int64_t cstart, int64_t gin, uint32_t lo, int64_t wbase, uint32_t *stage,
                     int64_t *__restrict__ complete, uint32_t n, uint32_t *errb, uint32_t &mytop) {
   uint32_t cur = cr.lo, take = 0;
   int64_t tb = cstart;
-  while (!M.big || big_step(D, cur, cr.hi, lp, sub_lg, cstart, tb, take, errb)) {
+  while (!M.big || big_step(D, cur, cr.hi, lp, cstart, tb, take)) {
     if (M.big) {
       M.m = wave_sum(take);
       sort_take<16>(D, cur, take, lp, cstart, tb, M.slot);
@@ -1245,8 +1281,7 @@ template <bool SORT, int SL>
 DEVI void chan_units(WinLds &S, const DieOrder &D, const uint32_t *__restrict__ LB,
                      const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ totals, const Geo &g,
                      CallCtl *ctl, const DevState *st, uint64_t *WAGG, uint64_t *WINC,
-                     int64_t *__restrict__ complete, int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n,
-                     uint32_t sub_lg) {
+                     int64_t *__restrict__ complete, int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n) {
   const uint32_t G = ctl->G, shift = ctl->shift, C = g.C;
   const int64_t cbase = ctl->cbase, xfer = g.xfer;
   const uint32_t t = threadIdx.x, lane = t & 63;
@@ -1285,7 +1320,7 @@ DEVI void chan_units(WinLds &S, const DieOrder &D, const uint32_t *__restrict__ 
     if constexpr (SORT) {
       if (ca < C) {
         ra = cell_runs(LB, seg_start, totals, g.Dk, gmax, ca, ja);
-        cell_sort(D, ra, g, lp, shift, sub_lg, sa, A, &errb);
+        cell_sort(D, ra, g, lp, shift, sa, A);
       }
     } else {
       if (ca < C) {
@@ -1350,7 +1385,7 @@ DEVI void chan_units(WinLds &S, const DieOrder &D, const uint32_t *__restrict__ 
     if (lo != CMIN_NONE) {  // the same for the whole workgroup
       uint32_t top = 0;
       if constexpr (SORT) {
-        sort_emit(D, ra, A, g, lp, sub_lg, sa, ga, lo, wbase, S.stage, complete, n, &errb, top);
+        sort_emit(D, ra, A, g, lp, sa, ga, lo, wbase, S.stage, complete, n, &errb, top);
       } else {
         cell_emit<false, SL>(A, g, sa, ga, lo, wbase, S.stage, complete, n, &errb, top);
         cell_emit<false, SL>(B, g, sb, gb, lo, wbase, S.stage, complete, n, &errb, top);
@@ -1383,7 +1418,7 @@ __global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
     const int64_t *__restrict__ DD, const uint32_t *__restrict__ IX, const uint32_t *__restrict__ LB,
     const uint32_t *__restrict__ seg_start, const uint32_t *__restrict__ totals, Geo g, CallCtl *ctl,
     const DevState *st, uint64_t *WAGG, uint64_t *WINC, int64_t *__restrict__ complete,
-    int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n, uint32_t sub_lg) {
+    int64_t *__restrict__ cfnew, uint32_t gmax, uint32_t n) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (agent_load32(&ctl->err) || ctl->G == 0) return;
   WinLds &S = *(WinLds *)smem;
@@ -1391,11 +1426,10 @@ __global__ __launch_bounds__(WIN_THREADS) void k_cell_chan(
   const bool bucket = grid_bucketable<SL>(g, ctl->shift);
   if constexpr ((WHAT & GRID_BUCKET) != 0)
     if (bucket)
-      chan_units<false, SL>(S, D, LB, seg_start, totals, g, ctl, st, WAGG, WINC, complete, cfnew, gmax, n, sub_lg);
+      chan_units<false, SL>(S, D, LB, seg_start, totals, g, ctl, st, WAGG, WINC, complete, cfnew, gmax, n);
   if constexpr ((WHAT & GRID_LANE) != 0)
     if (!bucket)
-      chan_units<true, SLOTS_MAX>(S, D, LB, seg_start, totals, g, ctl, st, WAGG, WINC, complete, cfnew, gmax, n,
-                                  sub_lg);
+      chan_units<true, SLOTS_MAX>(S, D, LB, seg_start, totals, g, ctl, st, WAGG, WINC, complete, cfnew, gmax, n);
 }
 // Calls of at least this many requests take a kernel per kind of grid.
 constexpr int64_t CHAN_SPLIT = int64_t(1) << 22;
@@ -1630,8 +1664,7 @@ hipError_t launch_time_requests(const Geo &g, const RangeTable &rt, const Layout
     uint64_t *WAGG = WST, *WINC = WST + (size_t)Lo.gmax * g.C;
     auto chan = [&](auto kfn) {
       hipLaunchKernelGGL(kfn, dim3((uint32_t)ncu), dim3(WIN_THREADS), sizeof(WinLds), s, DD, IX, LB, seg, totals, g,
-                         ctl, st, WAGG, WINC, complete, cfnew, Lo.gmax, (uint32_t)Lo.n,
-                         Lo.s0 < SUB_LG_MAX ? Lo.s0 : SUB_LG_MAX);
+                         ctl, st, WAGG, WINC, complete, cfnew, Lo.gmax, (uint32_t)Lo.n);
       return hipGetLastError();
     };
     constexpr int BOTH = GRID_BUCKET | GRID_LANE;

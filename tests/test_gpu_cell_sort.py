@@ -48,6 +48,26 @@ def test_lane_merge_crowded_cells(torch, geo, quiet):  # noqa: F811
              f"crowded {geo} quiet {quiet}")
 
 
+@pytest.mark.parametrize("geo", [(8, 64, 1, 3000, 0), (4, 16, 1, 3000, 0), (2, 3, 1, 3000, 0)],
+                         ids=lambda g: "x".join(map(str, g)))
+def test_lane_merge_hot_queues_in_a_sparse_stream(torch, geo):  # noqa: F811
+    """Wide cells that a few crowded die queues make too big for one step:
+    steps end at the queues' lanes, at the cell's end, and with ties across
+    dies at the step's end."""
+    C, D, P, tR, flags = geo
+    params = wl.geometry(C, D, P, t_read_ns=tR, flags=flags)
+    rng = np.random.default_rng(C)
+    n = 30_000
+    issue = np.sort(rng.integers(0, n * 40_000 // C, n))
+    issue[10_000:14_000] = issue[10_000]          # simultaneous: ties on every die
+    page = rng.integers(0, 1 << 14, n)
+    hot = rng.random(n) < 0.3
+    page[hot] = page[hot] // (C * D) * (C * D) + C * rng.integers(0, 2, int(hot.sum()))
+    addr = np.uint64(1 << 40) + page.astype(np.uint64) * np.uint64(16384)
+    run_both(torch, params, [(1 << 40, 16384 << 15)], [(addr, issue), (addr[:9_000], issue[:9_000] + issue[-1])],
+             f"hot queues {geo}")
+
+
 def test_lane_merge_long_reads(torch):  # noqa: F811
     """tR near its limit: a cell's minimum width exceeds 2^30 ns."""
     params = wl.geometry(2, 3, 1, t_read_ns=(1 << 29) - 7)
