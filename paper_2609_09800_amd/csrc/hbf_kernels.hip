@@ -1165,7 +1165,8 @@ DEVI void cell_sort(const DieOrder &D, const CellRuns &cr, const Geo &g, uint32_
   M.big = longest > (16u << lp) || shift > SUB_LG_MAX;
   // A run or two longer than their lanes, in a cell whose requests fit the
   // wave: the lanes are dealt out by need (one hot die queue in a sparse
-  // stream; 9,000 requests on 8 x 64 queues 188 -> HOT_US us)
+  // stream; a call of 9,000 requests on 8 x 64
+  // queues 188 -> 63 us)
   if (M.big && shift <= SUB_LG_MAX) {
     uint32_t per = 0;
     if (wave_sum(run_pieces<4>(len)) <= 64) {

@@ -7,9 +7,10 @@
 //   2. stage the call in die order (queue-major) and take the Lindley form
 //      of each die queue as one segmented prefix maximum:
 //      die_done_r = (r+1)*tR + max(L, max over i <= r of issue_i - i*tR);
-//   3. one wave per channel (or several, each a stretch of the channel's
-//      time) orders the channel's die runs by (die-done, index) in registers (the lane merge of hbf_device.h), takes the
-//      channel's Lindley form over the merged positions,
+//   3. one wave per channel (several on one or two channels, each a stretch of
+//      the channel's time; a share of a wave on more than 64) orders the
+//      channel's die runs by (die-done, index) in registers (the lane merge of
+//      hbf_device.h), takes the channel's Lindley form over the merged positions,
 //      complete_r = (r+1)*xfer + max(F, max over i <= r of die_done_i - i*xfer),
 //      and stores the completions; runs too long or too far apart for one
 //      merge are taken in several steps;
