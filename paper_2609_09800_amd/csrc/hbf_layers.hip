@@ -43,7 +43,8 @@
 //                clocks left behind
 //   k_lay_emit   then: issue times and completions, all layers at once, a
 //                thread per (channel, j): it orders the channel's requests j
-//                by index
+//                by index (k_lay_emit_wave on more than 16 die queues per
+//                channel: a lane per die queue)
 //   k_lay_run    otherwise: cooperative, one workgroup per channel, every
 //                layer in turn: the channel's completions, then one exchange
 //                of the layer's latest completion through the done words.
@@ -344,76 +345,190 @@ __global__ __launch_bounds__(CHBLK) void k_lay_chain(const int64_t *__restrict__
 
 // Issue times and completions where every layer finds an idle device.  Block
 // (l, part) writes a share of layer l's issue times and native completions
-// and takes every parts-th group of EMJ request ranks j of all channels:
-// thread (channel, j) loads the channel's requests j, one per die, and ranks
-// them by index.  Consecutive j read consecutive list entries, and the
-// channels of a block complete whole lines of complete[] between them.
-// DT: die queues per channel held in registers (0: any number, read again
-// for each comparison).
+// and takes its share of the layer's tiles, `unit` request ranks j of one
+// channel each.  A tile loads the channel's requests j, one per die queue,
+// and ranks them by index.  Consecutive j read consecutive list entries, and
+// tiles of the same j go to neighbouring channels, which complete whole lines
+// of complete[] between them.  That order has a tile for every channel up to
+// the busiest queue's last rank; where at least three quarters of those must
+// be empty (one die queue takes most of the layer) the tiles are numbered
+// channel by channel instead and found by a search (96 layers of 30,000
+// requests of one die queue on 256 x 8: 220 us a call; 22,300 with every
+// channel looked at for every rank, 9,000 with every layer in turn).
+constexpr uint32_t EMJ = 16, EMQ = 4;  // ranks of a tile of k_lay_emit, of k_lay_emit_wave
+struct EmitLayer {
+  uint32_t *off, *tp;  // LDS [K + 2], [C + 1]
+  uint32_t C, lg_C, count, unit;  // lg_C: 32 if C is no power of two
+  int64_t t;  // the layer's issue time
+  bool skewed;
+  // tile v's channel and first rank; false: there is none
+  DEVI bool tile(uint32_t v, uint32_t &c, uint32_t &j) const {
+    if (v >= count) return false;
+    if (skewed) {
+      uint32_t a = 0, b = C;  // the last channel with tp <= v (empty ones have no tile)
+      while (b - a > 1) {
+        const uint32_t mid = (a + b) >> 1;
+        if (tp[mid] <= v) a = mid;
+        else b = mid;
+      }
+      c = a;
+      j = (v - tp[a]) * unit;
+    } else {
+      const uint32_t q = lg_C < 32 ? v >> lg_C : v / C;
+      c = v - q * C;
+      j = q * unit;
+    }
+    return true;
+  }
+};
+// What a workgroup of layer l = blockIdx.x does first: its share of the
+// layer's issue times and native completions, the layer's offsets into LDS.
+// False: nothing else to do.
+DEVI bool emit_layer(const int64_t *__restrict__ ls, const uint32_t *__restrict__ OFF, const LayerSum *__restrict__ LS,
+                     const LayChain *__restrict__ ch, const uint32_t *__restrict__ LISTD, int64_t *__restrict__ issue,
+                     int64_t *__restrict__ complete, const Geo &g, uint32_t unit, uint32_t *lds, EmitLayer &E) {
+  const uint32_t l = blockIdx.x, part = blockIdx.y, parts = gridDim.y, t = threadIdx.x, nt = blockDim.x, K = g.K;
+  const LayChain chain = *ch;
+  const LayerSum S = LS[l];
+  const int64_t la = ls[l], lb = ls[l + 1];
+  if (!chain.idle || la == lb) return false;
+  const int64_t tl = S.t;
+  const bool fail = l >= chain.fail;
+  for (int64_t i = la + (int64_t)part * nt + t; i < lb; i += (int64_t)parts * nt) {
+    issue[i] = tl;
+    if (fail) complete[i] = HBF_TIME_ERROR;
+  }
+  if (fail) return false;
+  E.off = lds;
+  E.tp = lds + K + 2;
+  E.C = g.C;
+  E.lg_C = g.pow2 ? g.lg_C : 32;
+  E.unit = unit;
+  E.t = tl;
+  const uint32_t *row = OFF + (size_t)l * (K + 2);
+  for (uint32_t k = t; k < K + 2; k += nt) E.off[k] = row[k];
+  // (below 2^29: most <= 2^22; unit 16 and C <= 1,024, or unit 4 and C <= 2,048 / 17)
+  E.count = (S.most + unit - 1) / unit * g.C;
+  // each channel but for its last tile has a request in each of the tile's ranks
+  E.skewed = E.count / 4 > (row[K] - row[0]) / unit + g.C;
+  __syncthreads();
+  if (E.skewed) {  // the channels' first tiles
+    if (t < 64) {
+      uint32_t sum = 0;
+      for (uint32_t c0 = 0; c0 < g.C; c0 += 64) {
+        const uint32_t c = c0 + t;
+        uint32_t m = 0;
+        for (uint32_t d = 0; c < g.C && d < g.Dk; d++) m = max(m, E.off[c * g.Dk + d + 1] - E.off[c * g.Dk + d]);
+        const uint32_t inc = wave_incl_sum((m + unit - 1) / unit);
+        if (c < g.C) E.tp[c + 1] = sum + inc;
+        sum += lane63(inc);
+      }
+      if (t == 0) E.tp[0] = 0;
+    }
+    __syncthreads();
+    E.count = E.tp[g.C];
+  }
+  for (uint32_t q = E.off[K] + part * nt + t; q < E.off[K + 1]; q += parts * nt) complete[LISTD[q]] = tl;
+  return true;
+}
+
+// Up to 16 die queues per channel (DT, all in a thread's registers): a thread
+// per rank.
 constexpr int EMBLK = 256;
-constexpr uint32_t EMJ = 16;
 template <int DT>
 __global__ __launch_bounds__(EMBLK) void k_lay_emit(const int64_t *__restrict__ ls, const uint32_t *__restrict__ OFF,
                                                     const LayerSum *__restrict__ LS, const LayChain *__restrict__ ch,
                                                     const uint32_t *__restrict__ LISTD, int64_t *__restrict__ issue,
                                                     int64_t *__restrict__ complete, Geo g) {
   extern __shared__ __align__(16) unsigned char smem[];
-  uint32_t *off = (uint32_t *)smem;  // [K + 2]
-  if (!ch->idle) return;
-  const uint32_t l = blockIdx.x, part = blockIdx.y, parts = gridDim.y, t = threadIdx.x;
-  const uint32_t K = g.K, Dk = g.Dk, C = g.C;
-  const int64_t la = ls[l], lb = ls[l + 1];
-  if (la == lb) return;
-  const int64_t tl = LS[l].t;
-  const bool fail = l >= ch->fail;
-  for (int64_t i = la + (int64_t)part * EMBLK + t; i < lb; i += (int64_t)parts * EMBLK) {
-    issue[i] = tl;
-    if (fail) complete[i] = HBF_TIME_ERROR;
-  }
-  if (fail) return;
-  const uint32_t *row = OFF + (size_t)l * (K + 2);
-  for (uint32_t k = t; k < K + 2; k += EMBLK) off[k] = row[k];
-  __syncthreads();
-  for (uint32_t q = off[K] + part * EMBLK + t; q < off[K + 1]; q += parts * EMBLK) complete[LISTD[q]] = tl;
-  const uint32_t most = LS[l].most;
-  const int64_t tR = g.tR, xfer = g.xfer;
-  for (uint32_t j0 = part * EMJ; j0 < most; j0 += parts * EMJ) {
-    for (uint32_t v = t; v < C * EMJ; v += EMBLK) {
-      const uint32_t j = j0 + (v & (EMJ - 1)), c = v / EMJ;
-      const uint32_t *o = off + c * Dk;
-      uint32_t n = 0;  // requests of the channel before its requests j
-      if constexpr (DT > 0) {
-        uint32_t ix[DT];
+  EmitLayer E;
+  if (!emit_layer(ls, OFF, LS, ch, LISTD, issue, complete, g, EMJ, (uint32_t *)smem, E)) return;
+  const uint32_t Dk = g.Dk, t = threadIdx.x;
+  const int64_t tl = E.t, tR = g.tR, xfer = g.xfer;
+  for (uint32_t v0 = blockIdx.y * (EMBLK / EMJ); v0 < E.count; v0 += gridDim.y * (EMBLK / EMJ)) {
+    uint32_t c, j;
+    if (!E.tile(v0 + t / EMJ, c, j)) continue;
+    j += t % EMJ;
+    const uint32_t *o = E.off + c * Dk;
+    uint32_t n = 0;  // requests of the channel before its requests j
+    uint32_t ix[DT];
 #pragma unroll
-        for (int d = 0; d < DT; d++) {
-          ix[d] = 0xFFFFFFFFu;
-          if ((uint32_t)d < Dk) {
-            const uint32_t m = o[d + 1] - o[d];
-            n += min(j, m);
-            if (j < m) ix[d] = LISTD[o[d] + j];
-          }
-        }
-        const int64_t term = tl + imax(tR, (int64_t)(j + 1) * tR - (int64_t)n * xfer);
-#pragma unroll
-        for (int d = 0; d < DT; d++) {
-          if (ix[d] == 0xFFFFFFFFu) continue;
-          uint32_t r = n;
-#pragma unroll
-          for (int e = 0; e < DT; e++) r += ix[e] < ix[d] ? 1u : 0u;
-          complete[ix[d]] = term + (int64_t)(r + 1) * xfer;
-        }
-      } else {
-        for (uint32_t d = 0; d < Dk; d++) n += min(j, o[d + 1] - o[d]);
-        const int64_t term = tl + imax(tR, (int64_t)(j + 1) * tR - (int64_t)n * xfer);
-        for (uint32_t d = 0; d < Dk; d++) {
-          if (j >= o[d + 1] - o[d]) continue;
-          const uint32_t ix = LISTD[o[d] + j];
-          uint32_t r = n;
-          for (uint32_t e = 0; e < Dk; e++)
-            if (j < o[e + 1] - o[e] && LISTD[o[e] + j] < ix) r++;
-          complete[ix] = term + (int64_t)(r + 1) * xfer;
-        }
+    for (int d = 0; d < DT; d++) {
+      ix[d] = 0xFFFFFFFFu;
+      if ((uint32_t)d < Dk) {
+        const uint32_t m = o[d + 1] - o[d];
+        n += min(j, m);
+        if (j < m) ix[d] = LISTD[o[d] + j];
       }
+    }
+    const int64_t term = tl + imax(tR, (int64_t)(j + 1) * tR - (int64_t)n * xfer);
+#pragma unroll
+    for (int d = 0; d < DT; d++) {
+      if (ix[d] == 0xFFFFFFFFu) continue;
+      uint32_t r = n;
+#pragma unroll
+      for (int e = 0; e < DT; e++) r += ix[e] < ix[d] ? 1u : 0u;
+      complete[ix[d]] = term + (int64_t)(r + 1) * xfer;
+    }
+  }
+}
+
+// On 17 to 64 die queues per channel: W = 32 or 64 lanes take a tile, a lane
+// per die queue, its EMQ ranks' loads in flight together, and order each
+// rank's requests among the lanes.
+// 96 layers of 30,000 requests on 32 x 64: 210 us a call, k_lay_emit's way,
+// with the channel's entries read again for every comparison, 1,970, and
+// every layer in turn 1,650; one layer of 1 M 314, 2,080 and 670.
+constexpr int EWBLK = 1024;
+template <int W>
+__global__ __launch_bounds__(EWBLK) void k_lay_emit_wave(const int64_t *__restrict__ ls,
+                                                         const uint32_t *__restrict__ OFF,
+                                                         const LayerSum *__restrict__ LS,
+                                                         const LayChain *__restrict__ ch,
+                                                         const uint32_t *__restrict__ LISTD,
+                                                         int64_t *__restrict__ issue, int64_t *__restrict__ complete,
+                                                         Geo g) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  EmitLayer E;
+  if (!emit_layer(ls, OFF, LS, ch, LISTD, issue, complete, g, EMQ, (uint32_t *)smem, E)) return;
+  const uint32_t Dk = g.Dk, lane = lane_id(), d = lane & (W - 1), per = blockDim.x / W;
+  const int64_t tl = E.t, tR = g.tR, xfer = g.xfer;
+  const uint64_t group = W == 64 ? ~uint64_t(0) : uint64_t(0xFFFFFFFFu) << (lane & 32);
+  for (uint32_t v0 = blockIdx.y * per; v0 < E.count; v0 += gridDim.y * per) {
+    uint32_t c = 0, j0 = 0;
+    const bool on = E.tile(v0 + threadIdx.x / W, c, j0) && d < Dk;
+    const uint32_t o = on ? E.off[c * Dk + d] : 0u, m = on ? E.off[c * Dk + d + 1] - o : 0u;
+    if (!__ballot(j0 < m)) continue;  // (a wave stays together)
+    uint32_t ix[EMQ];
+#pragma unroll
+    for (uint32_t u = 0; u < EMQ; u++) ix[u] = j0 + u < m ? LISTD[o + j0 + u] : 0xFFFFFFFFu;
+    uint32_t n = min(j0, m);  // requests of the channel before its requests j0
+#pragma unroll
+    for (int x = 1; x < W; x <<= 1) n += (uint32_t)__shfl_xor((int)n, x);
+#pragma unroll
+    for (uint32_t u = 0; u < EMQ; u++) {
+      const uint32_t j = j0 + u;
+      const uint64_t have = __ballot(j < m);
+      if (!have) break;
+      uint32_t r = n;
+      auto count = [&](int e) {  // the tile's lane e
+        uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)ix[u], e);
+        if constexpr (W == 32) {
+          const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)ix[u], e + 32);
+          y = lane < 32 ? y : hi;
+        }
+        r += y < ix[u] ? 1u : 0u;
+      };
+      const uint64_t any = W == 64 ? have : (have | have >> 32) & 0xFFFFFFFFu;
+      if ((uint32_t)__popcll(any) * 4 <= Dk) {  // few die queues reach this rank
+        for (uint64_t mm = any; mm; mm &= mm - 1) count((int)__builtin_ctzll(mm));
+      } else {
+#pragma unroll 8
+        for (uint32_t e = 0; e < Dk; e++) count((int)e);
+      }
+      if (j < m)
+        complete[ix[u]] = tl + imax(tR, (int64_t)(j + 1) * tR - (int64_t)n * xfer) + (int64_t)(r + 1) * xfer;
+      n += (uint32_t)__popcll(have & group);
     }
   }
 }
@@ -752,6 +867,7 @@ hipError_t launch_layers(const Geo &g, const RangeTable &rt, char *ws, DevState 
   uint64_t *SLOT = (uint64_t *)take((size_t)L * g.C * 8);
   LayerSum *LS = (LayerSum *)take((size_t)L * sizeof(LayerSum));
   LayChain *chain = (LayChain *)take(sizeof(LayChain));
+  const bool wave = g.Dk > 16;  // k_lay_emit_wave
   if ((e = hipMemcpyAsync(d_up, up.data(), up.size(), hipMemcpyHostToDevice, s)) != hipSuccess) return e;
   if ((e = hipEventRecord(up_done, s)) != hipSuccess) return e;
   if (NT) {
@@ -772,16 +888,21 @@ hipError_t launch_layers(const Geo &g, const RangeTable &rt, char *ws, DevState 
                      done, st, g);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (NT) {
-    // blocks per layer: about one per EMJ ranks of evenly spread requests
-    // (several die queues of a thread's channel give one block 16 x C x Dk)
+    // blocks per layer: enough to take a tile per thread group of evenly spread
+    // requests; small layers' waves in blocks of 256 threads (20,000 layers
+    // of 64 requests on 32 x 64: 1,410 us with 1,024, 990 with 256)
     int64_t most = 0;
     for (int l = 0; l < L; l++) most = std::max(most, host_ls[l + 1] - host_ls[l]);
-    int64_t parts = most / ((int64_t)g.K * EMJ) + 1;
-    if (parts > 64) parts = 64;
-    const size_t lds = (size_t)(g.K + 2) * 4;
-    hipLaunchKernelGGL(g.Dk <= 4 ? k_lay_emit<4> : g.Dk <= 8 ? k_lay_emit<8> : g.Dk <= 16 ? k_lay_emit<16> : k_lay_emit<0>,
-                       dim3((uint32_t)L, (uint32_t)parts), dim3(EMBLK), lds, s, ls, OFF, LS, chain, LISTD, issue,
-                       complete, g);
+    const int threads = wave ? (most <= 1024 ? 256 : EWBLK) : EMBLK;
+    const int64_t at_once = wave ? threads / (g.Dk <= 32 ? 32 : 64) : threads / (int)EMJ;
+    const int64_t parts = std::min(most / ((int64_t)g.Dk * (wave ? EMQ : EMJ) * at_once) + 1, (int64_t)256);
+    hipLaunchKernelGGL(g.Dk <= 4    ? k_lay_emit<4>
+                       : g.Dk <= 8  ? k_lay_emit<8>
+                       : g.Dk <= 16 ? k_lay_emit<16>
+                       : g.Dk <= 32 ? k_lay_emit_wave<32>
+                                    : k_lay_emit_wave<64>,
+                       dim3((uint32_t)L, (uint32_t)parts), dim3(threads), (size_t)(g.K + 2 + g.C + 1) * 4, s, ls, OFF,
+                       LS, chain, LISTD, issue, complete, g);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   LayArgs A;

@@ -232,3 +232,20 @@ def test_issue_times_run_out_of_range(torch):
                          ([0, 0, 30, 60], (1 << 61) - 1, 0)]:
         say(f"closed loop: out of range {ls}")
         run_both(torch, params, [(1 << 40, 1 << 34)], addr, ls, t0, comp)
+
+
+@pytest.mark.parametrize("geo", [(16, 16, 1, 0), (256, 8, 1, 0), (5, 7, 3, 1), (6, 16, 2, 1), (32, 16, 4, 1)])
+@pytest.mark.parametrize("most", [1000, 5000])  # (largest layers of up to 1,024 requests run in smaller blocks)
+def test_skewed_layers(torch, geo, most):
+    """Layers that one die queue or one channel takes, beside evenly spread
+    ones, up to and above 16 and 32 die queues per channel: every way of
+    dealing an idle device's layers out."""
+    C, D, P, flags = geo
+    say(f"closed loop: skewed layers {geo} most={most}")
+    params = wl.geometry(C, D, P, flags=flags)
+    rng = np.random.default_rng(C + D + most)
+    sizes = [most, most, most, 1, most // 2, 0, most - 3]
+    step = [1, C * D * P, C, 1, C * D * P, 1, C]
+    addr = np.concatenate([rng.integers(-1, 2000, s) * k for s, k in zip(sizes, step)])
+    addr = ((1 << 40) + addr.astype(np.int64) * 16384).astype(np.uint64)
+    run_both(torch, params, [(1 << 40, 1 << 40)], addr, np.concatenate([[0], np.cumsum(sizes)]), 7, 100)
