@@ -316,30 +316,45 @@ __global__ __launch_bounds__(CHBLK) void k_lay_chain(const int64_t *__restrict__
     *ch = LayChain{1u, fail};
     if (s_hit) atomicOr(&st->sticky, ERR_RANGE_TIME);
   }
-  // the clocks: of the last layer before the failure that used each
+  // the clocks: of the last layer before the failure that used each.  Most are
+  // used by the last one; looking further back takes 16 layers at a time, their
+  // loads in flight together (a queue that no layer uses is looked for in all
+  // of them: 20,000 layers on 4 of 128 queues, 11.3 -> 1.8 ms a call).
   const uint32_t KB = K + 1;
-  for (uint32_t k = t; k < K; k += CHBLK) {
-    for (uint32_t l = fail; l-- > 0;) {
+  auto last_use = [&](uint32_t a, uint32_t b) {  // layer + 1 of the last requests of queues a..b-1, or 0
+    auto used = [&](uint32_t l) {
       const uint32_t *off = OFF + (size_t)l * (KB + 1);
-      const uint32_t m = off[k + 1] - off[k];
-      if (m) {
-        st->die_free[k] = LS[l].t + (int64_t)m * g.tR;
-        break;
-      }
+      return off[b] != off[a];
+    };
+    if (fail == 0 || used(fail - 1)) return fail;
+    for (uint32_t hi = fail - 1; hi > 0; hi -= min(hi, 16u)) {
+      uint32_t at = 0;
+      bool u[16];
+#pragma unroll
+      for (uint32_t i = 0; i < 16; i++) u[i] = used(hi - min(hi, i + 1));
+#pragma unroll
+      for (uint32_t i = 16; i-- > 0;)
+        if (u[i]) at = hi - min(hi, i + 1) + 1;
+      if (at) return at;
     }
+    return 0u;
+  };
+  for (uint32_t k = t; k < K; k += CHBLK) {
+    const uint32_t l = last_use(k, k + 1);
+    if (l == 0) continue;
+    const uint32_t *off = OFF + (size_t)(l - 1) * (KB + 1);
+    st->die_free[k] = LS[l - 1].t + (int64_t)(off[k + 1] - off[k]) * g.tR;
   }
   for (uint32_t c = t; c < g.C; c += CHBLK) {
-    for (uint32_t l = fail; l-- > 0;) {
-      const uint32_t *off = OFF + (size_t)l * (KB + 1) + c * g.Dk;
-      const uint32_t all = off[g.Dk] - off[0];
-      if (!all) continue;
-      uint32_t most = 0, n = 0;
-      for (uint32_t d = 0; d < g.Dk; d++) most = max(most, off[d + 1] - off[d]);
-      for (uint32_t d = 0; d < g.Dk; d++) n += min(most - 1, off[d + 1] - off[d]);
-      st->chan_free[c] =
-          LS[l].t + (int64_t)all * g.xfer + imax(g.tR, (int64_t)most * g.tR - (int64_t)n * g.xfer);
-      break;
-    }
+    const uint32_t l = last_use(c * g.Dk, (c + 1) * g.Dk);
+    if (l == 0) continue;
+    const uint32_t *off = OFF + (size_t)(l - 1) * (KB + 1) + c * g.Dk;
+    const uint32_t all = off[g.Dk] - off[0];
+    uint32_t most = 0, n = 0;
+    for (uint32_t d = 0; d < g.Dk; d++) most = max(most, off[d + 1] - off[d]);
+    for (uint32_t d = 0; d < g.Dk; d++) n += min(most - 1, off[d + 1] - off[d]);
+    st->chan_free[c] =
+        LS[l - 1].t + (int64_t)all * g.xfer + imax(g.tR, (int64_t)most * g.tR - (int64_t)n * g.xfer);
   }
 }
 

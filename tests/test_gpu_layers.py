@@ -249,3 +249,16 @@ def test_skewed_layers(torch, geo, most):
     addr = np.concatenate([rng.integers(-1, 2000, s) * k for s, k in zip(sizes, step)])
     addr = ((1 << 40) + addr.astype(np.int64) * 16384).astype(np.uint64)
     run_both(torch, params, [(1 << 40, 1 << 40)], addr, np.concatenate([[0], np.cumsum(sizes)]), 7, 100)
+
+
+@pytest.mark.parametrize("L", [1, 2, 16, 17, 18, 33, 70])
+def test_clocks_of_layers_long_ago(torch, L):
+    """Die queue q is last used by layer q (mod L + 1; one of them by none):
+    each clock is the one that layer left, however far back."""
+    say(f"closed loop: clocks of layers long ago L={L}")
+    params = wl.geometry(4, 9, 1)
+    q = np.arange(36)
+    pages = [np.concatenate([q[q % (L + 1) == l], q[q % (L + 1) == l]]) for l in range(L)]
+    addr = ((1 << 40) + np.concatenate(pages).astype(np.int64) * 16384).astype(np.uint64)
+    ls = np.concatenate([[0], np.cumsum([p.size for p in pages])])
+    run_both(torch, params, [(1 << 40, 1 << 30)], addr, ls, 5, 10)
