@@ -55,7 +55,15 @@ namespace {
 
 constexpr uint32_t NONE32 = 0xFFFFFFFFu;
 
-__device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
+// The thread's number, hidden from the compiler: what the steps derive from it
+// would otherwise all be kept through a call's chunks (68 registers spilled, a
+// third of the time of a call that runs access by access).
+__device__ __forceinline__ uint32_t thread_id() {
+  uint32_t t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ uint32_t lane_id() { return thread_id() & 63; }
 __device__ __forceinline__ uint32_t rdl(uint32_t v, uint32_t l) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
 }
@@ -91,13 +99,14 @@ constexpr uint32_t SPIN_MAX = 1u << 24;
 // taking them one after another (about 0.1 us each).
 constexpr uint32_t SEQ_TRY = 1024;
 // A chunk most of whose candidates lie within d pages of one first accessed
-// later (7 of 16; half of them is the most there can be) is a scattered
-// working set seen for the first time.  Its segments are long, and their
-// groups of 64 pages cost 5 us each in turn; an eighth of it has short ones,
-// and makes most of the rest resident: 200,000 accesses to 50,000 pages,
-// prefetch 7, 4.3 ms whole and 0.61 ms so.  With fewer such candidates
-// than this the chunk is taken as it is.
-constexpr uint32_t DENSE_MIN = 4096;
+// later (7 of 16; half of them is the most there can be), more than DENSE_SEG
+// of them a segment, is a scattered working set seen for the first time.  The
+// groups of 64 pages of its segments cost 5 us each in turn; an eighth of it
+// has short ones, and makes most of the rest resident: 200,000 accesses to
+// 50,000 pages, prefetch 7, 4.3 ms whole and 0.61 ms so; 30,000 accesses,
+// whose segments are short, 300 us so and 136 whole.  With fewer such candidates than
+// DENSE_MIN the chunk is taken as it is.
+constexpr uint32_t DENSE_MIN = 4096, DENSE_SEG = 512;
 constexpr uint32_t SEQ_MIN = 4096, SEQ_MAX = 1u << 17;
 
 // How long a group waits for its workgroups to start, in ticks of 10 ns: 100 us
@@ -128,7 +137,7 @@ struct Group {
     };
     __shared__ Member s_m;
     if (want > 1) {
-      if (threadIdx.x == 0) {
+      if (thread_id() == 0) {
         Words w = {words, __builtin_amdgcn_s_memrealtime(), patience};
         s_m = group_join(w, want);
       }
@@ -152,7 +161,7 @@ struct Group {
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // atomics went past the L1
       return true;
     }
-    if (threadIdx.x == 0) {
+    if (thread_id() == 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       uint32_t *bar = &words->bar;
       __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -168,8 +177,12 @@ struct Group {
     const bool ok = s_ok != 0;
     return ok;
   }
-  // the group's threads over [0, n)
-  __device__ int64_t first() const { return (int64_t)b * CBLK + threadIdx.x; }
+  // The group's threads over [0, n); consecutive waves' shares go to different
+  // workgroups, since the faults, which cost, are often all in the first few.
+  __device__ int64_t first() const {
+    const uint32_t t = thread_id();
+    return (int64_t)(t / 64 * nb + b) * 64 + (t & 63);
+  }
   __device__ int64_t step() const { return (int64_t)nb * CBLK; }
 };
 
@@ -181,10 +194,10 @@ __device__ __forceinline__ void chunk_tag(const Group &gr, const ChunkCfg &cc, c
     cc.S[j] = 0;
     if (j % SCAN == 0) cc.bs[j / SCAN] = 0;
   }
-  if (gr.b == 0 && threadIdx.x == 0) {
+  if (gr.b == 0 && thread_id() == 0) {
     cc.S[L] = 0;
-    cc.ctl->nseg = 0;
-    cc.ctl->loose[epoch & 1] = 0;  // (the other one may still be read)
+    cc.ctl->nseg[epoch & 1] = 0;  // (the other ones may still be read)
+    cc.ctl->loose[epoch & 1] = 0;
     cc.ctl->good = (uint32_t)L;
     cc.ctl->lost_old = 0;
   }
@@ -194,6 +207,84 @@ __device__ __forceinline__ void chunk_tag(const Group &gr, const ChunkCfg &cc, c
 // (insertions << 32 | faults).
 __device__ __forceinline__ void set_fault(const ChunkCfg &cc, uint32_t j, uint32_t cnt) {
   cc.S[j] = ((uint64_t)cnt << 32) | 1u;
+}
+
+// The page word of r, if the fault at access A inserted it: its rank, else -1.
+__device__ __forceinline__ int owned_rank(uint64_t v, const Tags &tg, uint32_t A) {
+  return (v & (HI | 0xFFFFFFull)) == (tg.t | A) ? (int)((v >> 24) & 63u) : -1;
+}
+
+// The d + 1 pages from each of some of a workgroup's accesses on, one per lane,
+// as many accesses at a time as a wave's lanes hold.  Access i of them has page
+// q[i], index j[i], x[i]; load(in, i, k), then body(in, i, k, what load gave):
+// the lane (if `in`) has page k of access i; a wave's lanes call it together.
+// Returns the thread's i; out[i] holds what body left there, `none` if nothing.
+// Each wave takes its own, or (SHARE_D pages or more) all waves share them
+// out: few of them often have them all, and one access is a round (64
+// scattered ones at depth 63, one wave's: 183 -> 57 us a call; at depth 7
+// sharing gains 12 of 62 there, but its barriers cost runs 5 us of 68).
+constexpr uint32_t SHARE_D = 16;
+struct PageLds {
+  uint64_t q[CBLK];
+  int64_t x[CBLK];
+  uint32_t j[CBLK], out[CBLK];
+  uint32_t n[CWAVES];
+};
+template <typename Load, typename Body>
+__device__ __forceinline__ uint32_t access_pages(PageLds &P, uint32_t d, bool mine, uint64_t q, uint32_t j, int64_t x,
+                                                 uint32_t none, Load load, Body body) {
+  constexpr uint32_t FLY = 2;  // rounds whose loads are in flight (4: the same)
+  const uint64_t am = __ballot(mine);
+  const uint32_t lane = lane_id(), w = thread_id() >> 6;
+  const uint32_t m = d + 1, at_once = 64 / m, own = lane / m, k = lane - own * m;
+  const bool share = d >= SHARE_D;  // (the same for the whole workgroup)
+  uint32_t at = popc(am & ((1ull << lane) - 1)), all = popc(am);
+  uint32_t from = w * 64, step = at_once;
+  if (share) {
+    if (lane == 0) P.n[w] = all;
+    __syncthreads();
+    all = 0;
+    for (uint32_t i = 0; i < CWAVES; i++) {
+      if (i < w) at += P.n[i];
+      all += P.n[i];
+    }
+    from = w * at_once;
+    step = at_once * CWAVES;
+  } else {
+    at += from;
+    all += from;
+  }
+  if (mine) {
+    P.q[at] = q;
+    P.x[at] = x;
+    P.j[at] = j;
+    P.out[at] = none;
+  }
+  if (share) __syncthreads();
+  else wave_lds_order();
+  for (uint32_t f = from; f < all; f += FLY * step) {
+    decltype(load(false, 0u, 0u)) v[FLY];
+#pragma unroll
+    for (uint32_t u = 0; u < FLY; u++) {
+      const uint32_t i = f + u * step + own;
+      const bool in = own < at_once && i < all;
+      v[u] = load(in, in ? i : 0u, k);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < FLY; u++) {
+      const uint32_t i = f + u * step + own;
+      const bool in = own < at_once && i < all;
+      if (f + u * step < all) body(in, in ? i : 0u, k, v[u]);
+    }
+  }
+  if (share) __syncthreads();
+  else wave_lds_order();
+  return at;
+}
+// The lanes that have the same access as this one there.
+__device__ __forceinline__ uint64_t access_lanes(uint32_t d) {
+  const uint32_t m = d + 1;
+  return (m == 64 ? ~0ull : (1ull << m) - 1) << (lane_id() / m * m);
 }
 
 // A run: accesses j0, j0 + 1, ... to candidate pages q0, q0 + 1, ... (a
@@ -216,11 +307,11 @@ __device__ __forceinline__ uint32_t split_pages(uint32_t d) {
 // workgroup takes consecutive pieces of CBLK accesses; a run entering its
 // first is followed back as far as its splits reach.  Without prefetch every candidate is a
 // fault of its own and nothing is left to walk.
-__device__ __forceinline__ void chunk_starts(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+__device__ __forceinline__ void chunk_starts(const Group &gr, PageLds &P, const CacheCfg &c, const ChunkCfg &cc,
                                              const uint64_t *__restrict__ pages, int64_t L, uint64_t R, int64_t lim,
                                              uint32_t epoch, const Tags &tg) {
   __shared__ int s_brk[CWAVES];
-  const uint32_t lane = lane_id(), w = threadIdx.x >> 6, d = c.d;
+  const uint32_t lane = lane_id(), w = thread_id() >> 6, d = c.d;
   auto candidate = [&](int64_t j, uint64_t p) { return cc.at[p] == (tg.a | (uint64_t)j) && c.pins[p] < lim; };
   if (d == 0) {
     for (int64_t j = gr.first(); j < L; j += gr.step()) {
@@ -236,51 +327,45 @@ __device__ __forceinline__ void chunk_starts(const Group &gr, const CacheCfg &c,
     }
     return;
   }
-  // first access of the nearest candidate among the d pages below p (NONE32: none)
-  auto before = [&](uint64_t p) {
-    const uint32_t m = (uint32_t)min((uint64_t)d, p);
-    for (uint32_t k0 = 1; k0 <= m; k0 += 4) {
-      uint64_t a[4];
-      int64_t x[4];
-#pragma unroll
-      for (uint32_t u = 0; u < 4; u++) {
-        const uint64_t q = p - min(k0 + u, m);
-        a[u] = cc.at[q];
-        x[u] = c.pins[q];
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < 4; u++)
-        if ((a[u] & HI) == tg.a && x[u] < lim) return (uint32_t)a[u];
-    }
-    return NONE32;
+  const uint64_t group = access_lanes(d);
+  // of page q (of those threads that ask): the first access of the nearest
+  // candidate among the d pages below (NONE32: none)
+  struct Word {
+    uint64_t a;
+    int64_t x;
   };
-  auto is_start = [&](uint64_t p) { return before(p) == NONE32; };
+  auto before = [&](bool ask, uint64_t q) {
+    auto load = [&](bool in, uint32_t i, uint32_t k) {
+      const uint64_t r = P.q[i] - k;
+      in = in && k > 0 && r < R;  // (wraps below page 0)
+      return Word{in ? cc.at[r] : 0, in ? c.pins[r] : INT64_MAX};
+    };
+    const uint32_t i = access_pages(P, d, ask, q, 0, 0, NONE32, load, [&](bool in, uint32_t i, uint32_t, Word v) {
+      const uint64_t m = __ballot(in && (v.a & HI) == tg.a && v.x < lim) & group;
+      if (m && lane == ctz64(m)) P.out[i] = (uint32_t)v.a;
+    });
+    return ask ? P.out[i] : NONE32;
+  };
   // A segment start with no candidate among the d pages above either is a
-  // segment of its own: resolved here, a lane each, where scattered accesses
-  // would keep a wave each busy (10,000 of them 430 -> 133 us).
-  auto alone = [&](uint64_t p, uint32_t j) {
-    const uint32_t m = (uint32_t)min((uint64_t)d, R - 1 - p);
-    uint64_t ins = 1;  // pages of p .. p + d not resident
-    for (uint32_t k0 = 1; k0 <= m; k0 += 4) {
-      uint64_t a[4];
-      int64_t x[4];
-#pragma unroll
-      for (uint32_t u = 0; u < 4; u++) {
-        const uint64_t q = p + min(k0 + u, m);
-        a[u] = cc.at[q];
-        x[u] = c.pins[q];
+  // segment of its own: resolved here (page q, access j), where scattered
+  // accesses would keep a wave each busy.  Whether it is one.
+  auto alone = [&](bool ask, uint64_t q, uint32_t j) {
+    auto load = [&](bool in, uint32_t i, uint32_t k) {
+      const uint64_t r = P.q[i] + k;
+      in = in && r < R;
+      return Word{in && k > 0 ? cc.at[r] : 0, in ? c.pins[r] : INT64_MAX};
+    };
+    const uint32_t i = access_pages(P, d, ask, q, j, 0, 0, load, [&](bool in, uint32_t i, uint32_t k, Word v) {
+      const bool ins = in && v.x < lim;  // not resident
+      const uint64_t im = __ballot(ins) & group, cm = __ballot(ins && (v.a & HI) == tg.a) & group;
+      if (cm || !ins) return;
+      cc.tt[P.q[i] + k] = tg.t | (uint64_t)popc(im & ((1ull << lane) - 1)) << 24 | P.j[i];
+      if (k == 0) {
+        set_fault(cc, P.j[i], popc(im));
+        P.out[i] = 1;
       }
-#pragma unroll
-      for (uint32_t u = 0; u < 4; u++) {
-        if (k0 + u > m || x[u] >= lim) continue;
-        if ((a[u] & HI) == tg.a) return false;
-        ins |= uint64_t(1) << (k0 + u);
-      }
-    }
-    uint32_t cnt = 0;
-    for (; ins; ins &= ins - 1) cc.tt[p + ctz64(ins)] = tg.t | (uint64_t)cnt++ << 24 | j;
-    set_fault(cc, j, cnt);
-    return true;
+    });
+    return ask && P.out[i] != 0;
   };
   // whether access j goes on from access j - 1 in a run
   auto linked = [&](int64_t j) {
@@ -312,40 +397,43 @@ __device__ __forceinline__ void chunk_starts(const Group &gr, const CacheCfg &c,
   const int64_t a0 = (int64_t)gr.b * per, a1 = min(L, a0 + per);
   int in = -1;  // start of the run that the piece's first access goes on from (-1: not known)
   for (int64_t c0 = a0; c0 < a1; c0 += CBLK) {
-    const int64_t j = c0 + threadIdx.x;
+    const int64_t j = c0 + thread_id();
     const bool lk = linked(j);
     int all = -1;
     int run = last_break(j, !lk, all);
-    if (c0 == a0 && __syncthreads_or(threadIdx.x == 0 && lk)) {
+    if (c0 == a0 && __syncthreads_or(thread_id() == 0 && lk)) {
       int back = -1;
       for (int64_t b0 = c0 - CBLK; b0 >= 0 && b0 >= c0 - 7 * CBLK && back < 0; b0 -= CBLK)
-        last_break(b0 + threadIdx.x, !linked(b0 + threadIdx.x), back);
+        last_break(b0 + thread_id(), !linked(b0 + thread_id()), back);
       in = back;
     }
     if (run < 0) run = in;
     if (all >= 0) in = all;  // for the next piece
-    bool start = false, loose = false, late = false;
-    uint32_t entry = 0;
+    bool ask = false, loose = false;
+    uint64_t p = 0, q = 0;  // its page; the page whose neighbours say whether a segment starts
+    uint32_t split = 0;
     if (j < L) {
-      const uint64_t p = pages[j];
+      p = q = pages[j];
       if (lk) {
         const uint32_t o = run < 0 ? 1u : (uint32_t)((int)j - run);  // pages into the run
-        if (o % W == 0 && o / W <= splits && is_start(pages[run])) {
-          start = true;
-          entry = (uint32_t)p | (o / W) << SPLIT_SHIFT;
+        ask = o % W == 0 && o / W <= splits;
+        if (ask) {
+          q = pages[run];
+          split = o / W;
         }
-      } else if (candidate(j, p)) {
-        const uint32_t b = before(p);
-        loose = true;
-        start = b == NONE32 && !alone(p, (uint32_t)j);
-        entry = (uint32_t)p;
-        late = b != NONE32 && b > (uint32_t)j;
+      } else {
+        ask = loose = candidate(j, p);
       }
     }
+    const uint32_t near = before(ask, q);
+    const bool late = loose && near != NONE32 && near > (uint32_t)j;
+    bool start = ask && near == NONE32;
+    if (alone(start && loose, p, (uint32_t)j)) start = false;
+    const uint32_t entry = (uint32_t)p | split << SPLIT_SHIFT;
     const uint64_t um = __ballot(loose), lm = __ballot(late);
     if (um && lane == 0)
       atomicAdd((unsigned long long *)&cc.ctl->loose[epoch & 1], (unsigned long long)popc(lm) << 32 | popc(um));
-    const uint32_t k = wave_append(&cc.ctl->nseg, start);
+    const uint32_t k = wave_append(&cc.ctl->nseg[epoch & 1], start);
     if (start && k < cc.Lmax) cc.seg[k] = entry;
   }
 }
@@ -536,9 +624,9 @@ __device__ __forceinline__ bool walk_group(Walk &w, uint64_t base, uint64_t at_c
 
 namespace {
 __device__ __forceinline__ void chunk_walk(const Group &gr, const CacheCfg &c, const ChunkCfg &cc, uint64_t R,
-                                           int64_t lim, const Tags &tg) {
+                                           int64_t lim, uint32_t epoch, const Tags &tg) {
   const uint32_t lane = lane_id(), d = c.d;
-  const uint32_t nseg_all = ld(&cc.ctl->nseg);
+  const uint32_t nseg_all = ld(&cc.ctl->nseg[epoch & 1]);
   const uint32_t nseg = nseg_all < cc.Lmax ? nseg_all : cc.Lmax;
   const uint32_t W = split_pages(d), splits = min(SPLIT_MAX, (uint32_t)(7 * CBLK) / W);
   // page state, loaded unconditionally (addresses clamped into the range;
@@ -548,7 +636,7 @@ __device__ __forceinline__ void chunk_walk(const Group &gr, const CacheCfg &c, c
   auto at_of = [&](uint64_t base) { return atg[base + lane < R ? base + lane : R - 1]; };
   auto pin_of = [&](uint64_t base) { return ping[base + lane < R ? base + lane : R - 1]; };
   // (consecutive segments to different workgroups)
-  for (uint32_t si = threadIdx.x / 64 * gr.nb + gr.b; si < nseg; si += gr.nb * CWAVES) {
+  for (uint32_t si = thread_id() / 64 * gr.nb + gr.b; si < nseg; si += gr.nb * CWAVES) {
     const uint32_t entry = ld(&cc.seg[si]), split = entry >> SPLIT_SHIFT;
     const uint64_t s = entry & ((1u << SPLIT_SHIFT) - 1);
     Walk w{s, NONE32, 0, 0, 0, false};
@@ -590,12 +678,12 @@ __device__ __forceinline__ void chunk_walk(const Group &gr, const CacheCfg &c, c
 __device__ __forceinline__ void chunk_sums(const Group &gr, const ChunkCfg &cc, int64_t L) {
   __shared__ uint64_t part[CWAVES];
   for (int64_t q = gr.b; q * SCAN < L; q += gr.nb) {
-    const int64_t j = q * SCAN + threadIdx.x;
+    const int64_t j = q * SCAN + thread_id();
     uint64_t v = j < L ? cc.S[j] : 0;
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    if (lane_id() == 0) part[threadIdx.x >> 6] = v;
+    if (lane_id() == 0) part[thread_id() >> 6] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (thread_id() == 0) {
       uint64_t t = 0;
       for (int w = 0; w < CWAVES; w++) t += part[w];
       cc.bs[q] = t;
@@ -604,51 +692,22 @@ __device__ __forceinline__ void chunk_sums(const Group &gr, const ChunkCfg &cc, 
   }
 }
 
-// The page word of r, if the fault at access A inserted it: its rank, else -1.
-__device__ __forceinline__ int owned_rank(uint64_t v, const Tags &tg, uint32_t A) {
-  return (v & (HI | 0xFFFFFFull)) == (tg.t | A) ? (int)((v >> 24) & 63u) : -1;
-}
-
-// The d + 1 pages of each fault of a wave, one per lane: as many whole faults
-// at a time as 64 lanes hold, so that a fault costs a latency or two and not
-// d + 1 of them.  load(in, src, k), then body(in, src, k, what load gave): the
-// lane (if `in`) has page k of lane src's fault; all lanes call it together.
-template <typename Load, typename Body>
-__device__ __forceinline__ void fault_pages(bool fault, uint32_t d, Load load, Body body) {
-  __shared__ uint8_t s_lane[CWAVES][64];
-  const uint64_t fm = __ballot(fault);
-  if (!fm) return;
-  const uint32_t lane = lane_id(), w = threadIdx.x >> 6, nf = popc(fm);
-  const uint32_t m = d + 1, at_once = 64 / m, own = lane / m, k = lane - own * m;
-  if (fault) s_lane[w][popc(fm & ((1ull << lane) - 1))] = (uint8_t)lane;
-  wave_lds_order();
-  auto has = [&](uint32_t f) { return own < at_once && f + own < nf; };
-  auto src = [&](uint32_t f) { return (int)s_lane[w][has(f) ? f + own : 0]; };
-  for (uint32_t f = 0; f < nf; f += 2 * at_once) {  // two rounds' loads in flight
-    const uint32_t f2 = f + at_once;
-    const auto x = load(has(f), src(f), k), y = load(has(f2), src(f2), k);
-    body(has(f), src(f), k, x);
-    if (f2 < nf) body(has(f2), src(f2), k, y);
-  }
-  wave_lds_order();
-}
-
 // Exclusive scan of the packed per-access counts: each piece's own, offset by
 // the sums of the pieces before it; then each fault in the piece (an access j whose page word names j
 // itself, rank 0) numbers its insertions: I0 + insertions before j + rank.
-__device__ __forceinline__ void chunk_scan(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+__device__ __forceinline__ void chunk_scan(const Group &gr, PageLds &P, const CacheCfg &c, const ChunkCfg &cc,
                                            const uint64_t *__restrict__ pages, int64_t L, uint64_t R, int64_t I0,
                                            const Tags &tg) {
   __shared__ uint64_t part[CWAVES], before[CWAVES];
-  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  const uint32_t lane = lane_id(), w = thread_id() >> 6;
   uint64_t pre = 0;  // the sums of the pieces before q
   int64_t done = 0;  // pieces in it
   for (int64_t q = gr.b; q * SCAN < L; q += gr.nb) {
     uint64_t p = 0;
-    for (int64_t i = done + threadIdx.x; i < q; i += CBLK) p += cc.bs[i];
+    for (int64_t i = done + thread_id(); i < q; i += CBLK) p += cc.bs[i];
     for (int o = 32; o >= 1; o >>= 1) p += __shfl_xor(p, o);
     if (lane == 0) before[w] = p;
-    const int64_t j = q * SCAN + threadIdx.x;
+    const int64_t j = q * SCAN + thread_id();
     const uint64_t v = j < L ? cc.S[j] : 0;
     uint64_t x = v;  // inclusive scan within the wave
     for (int o = 1; o < 64; o <<= 1) {
@@ -668,16 +727,13 @@ __device__ __forceinline__ void chunk_scan(const Group &gr, const CacheCfg &c, c
     const bool fault = v != 0;
     const uint64_t pg = fault ? pages[j] : 0;
     const int64_t x0 = I0 + (int64_t)(sj >> 32);
-    auto load = [&](bool in, int src, uint32_t k) {
-      const uint64_t r = __shfl(pg, src) + k;
+    auto load = [&](bool in, uint32_t i, uint32_t k) {
+      const uint64_t r = P.q[i] + k;
       return in && r < R ? cc.tt[r] : 0;
     };
-    fault_pages(fault, c.d, load, [&](bool, int src, uint32_t k, uint64_t t) {
-      const uint64_t r = __shfl(pg, src) + k;
-      const uint32_t jf = (uint32_t)__shfl((int)j, src);
-      const int64_t xf = __shfl(x0, src);
-      const int rk = owned_rank(t, tg, jf);
-      if (rk >= 0) c.pins[r] = xf + rk;
+    access_pages(P, c.d, fault, pg, (uint32_t)j, x0, 0, load, [&](bool, uint32_t i, uint32_t k, uint64_t t) {
+      const int rk = owned_rank(t, tg, P.j[i]);
+      if (rk >= 0) c.pins[P.q[i] + k] = P.x[i] + rk;
     });
   }
 }
@@ -685,34 +741,35 @@ __device__ __forceinline__ void chunk_scan(const Group &gr, const CacheCfg &c, c
 // The check: the first access whose decision does not hold -- a hit on a
 // page, or a fault that found a prefetch candidate resident, not within the
 // last F insertions at that moment -- into ctl->good.
-__device__ __forceinline__ void chunk_check(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+__device__ __forceinline__ void chunk_check(const Group &gr, PageLds &P, const CacheCfg &c, const ChunkCfg &cc,
                                             const uint64_t *__restrict__ pages, int64_t L, uint64_t R, int64_t I0,
                                             const Tags &tg) {
   uint32_t bad = NONE32;
-  const uint32_t lane = lane_id(), base = lane / (c.d + 1) * (c.d + 1);
-  const int64_t span = (L + 63) / 64 * 64;
-  for (int64_t j = gr.first(); j < span; j += gr.step()) {  // whole waves stay together
+  const uint32_t lane = lane_id();
+  const uint64_t group = access_lanes(c.d);
+  struct Word {
+    uint64_t t;
+    int64_t x;
+  };
+  const int64_t first = gr.first();
+  for (int64_t j0 = 0; j0 < L; j0 += gr.step()) {  // workgroups stay together
+    const int64_t j = j0 + first;
     const uint64_t p = j < L ? pages[j] : 0;
     const int64_t low = j < L ? I0 + (int64_t)(cc.S[j] >> 32) - (int64_t)c.F : 0;  // resident at j: pins >= low
     const bool fault = j < L && cc.tt[p] == (tg.t | (uint64_t)j);
     if (j < L && !fault && c.pins[p] < low) bad = min(bad, (uint32_t)j);
     if (c.d == 0) continue;
-    struct Word {
-      uint64_t t;
-      int64_t x;
-    };
-    auto load = [&](bool in, int src, uint32_t k) {
-      const uint64_t r = __shfl(p, src) + k;
+    auto load = [&](bool in, uint32_t i, uint32_t k) {
+      const uint64_t r = P.q[i] + k;
       in = in && r < R;
       return Word{in ? cc.tt[r] : 0, in ? c.pins[r] : INT64_MAX};  // (past the range: never a failure)
     };
-    fault_pages(fault, c.d, load, [&](bool in, int src, uint32_t, Word v) {
-      const uint32_t jf = (uint32_t)__shfl((int)j, src);
-      const int64_t lf = __shfl(low, src), x = v.x;
+    access_pages(P, c.d, fault, p, (uint32_t)j, low, 0, load, [&](bool in, uint32_t i, uint32_t, Word v) {
+      const uint32_t jf = P.j[i];
       const bool own = in && owned_rank(v.t, tg, jf) >= 0;
       // the fault's insertions before this candidate
-      const uint64_t before = __ballot(own) & ((1ull << lane) - 1) & ~((1ull << base) - 1);
-      if (in && !own && x < lf + (int64_t)popc(before)) bad = min(bad, jf);
+      const uint64_t before = __ballot(own) & group & ((1ull << lane) - 1);
+      if (in && !own && v.x < P.x[i] + (int64_t)popc(before)) bad = min(bad, jf);
     });
   }
   for (int o = 32; o >= 1; o >>= 1) bad = min(bad, (uint32_t)__shfl_xor((int)bad, o));
@@ -752,15 +809,16 @@ __device__ __forceinline__ void chunk_lost(const Group &gr, const CacheCfg &c, c
 // never hit, prefetch outputs; then the counters.  The insertions of later
 // faults are undone (a page not resident at the start stays so).  The frames
 // written here are distinct: they hold the last F insertions.
-__device__ __forceinline__ void chunk_commit(const Group &gr, const CacheCfg &c, const ChunkCfg &cc,
+__device__ __forceinline__ void chunk_commit(const Group &gr, PageLds &P, const CacheCfg &c, const ChunkCfg &cc,
                                              const uint64_t *__restrict__ pages, int64_t c0, int64_t L, int64_t T,
                                              uint64_t R, int64_t I0, int64_t npf0, const Tags &tg, uint8_t *hit,
                                              uint64_t *pf_page, int64_t *pf_src, int64_t pf_cap, int64_t *n_pf) {
   const uint64_t tot = ld(&cc.S[T]);
   const int64_t F = c.F, nf = (uint32_t)tot, M = (int64_t)(tot >> 32), I1 = I0 + M;
   int64_t lost = 0;
-  const int64_t span = (L + 63) / 64 * 64;
-  for (int64_t j = gr.first(); j < span; j += gr.step()) {  // whole waves stay together
+  const int64_t first = gr.first();
+  for (int64_t j0 = 0; j0 < L; j0 += gr.step()) {  // workgroups stay together
+    const int64_t j = j0 + first;
     const uint64_t p = j < L ? pages[j] : 0;
     const bool fault = j < L && cc.tt[p] == (tg.t | (uint64_t)j), ok = j < T;
     if (ok && hit) hit[c0 + j] = fault ? 0 : 1;
@@ -774,15 +832,15 @@ __device__ __forceinline__ void chunk_commit(const Group &gr, const CacheCfg &c,
       uint64_t t, a;
       int64_t x;
     };
-    auto load = [&](bool in, int src, uint32_t k) {
-      const uint64_t r = __shfl(p, src) + k;
+    auto load = [&](bool in, uint32_t i, uint32_t k) {
+      const uint64_t r = P.q[i] + k;
       in = in && r < R;
       return Word{in ? cc.tt[r] : 0, in ? cc.at[r] : 0, in ? c.pins[r] : 0};
     };
-    fault_pages(fault, c.d, load, [&](bool, int src, uint32_t k, Word v) {
-      const uint64_t r = __shfl(p, src) + k;
-      const uint32_t jf = (uint32_t)__shfl((int)j, src);
-      const int64_t q = __shfl(pf0, src);
+    access_pages(P, c.d, fault, p, (uint32_t)j, pf0, 0, load, [&](bool, uint32_t i, uint32_t k, Word v) {
+      const uint64_t r = P.q[i] + k;
+      const uint32_t jf = P.j[i];
+      const int64_t q = P.x[i];
       const int rk = owned_rank(v.t, tg, jf);
       if (rk < 0) return;
       if ((int64_t)jf >= T) {
@@ -806,7 +864,7 @@ __device__ __forceinline__ void chunk_commit(const Group &gr, const CacheCfg &c,
     });
   }
   lost = wave_sum(lost);
-  if (gr.b == 0 && threadIdx.x == 0) {
+  if (gr.b == 0 && thread_id() == 0) {
     lost += ld(&cc.ctl->lost_old);
     c.ctl->count[0] += T - nf;
     c.ctl->count[1] += nf;
@@ -846,11 +904,14 @@ struct ChunkRun {
 };
 
 __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
-  __shared__ RunLds S;
+  __shared__ union {  // a barrier lies between their uses
+    RunLds run;
+    PageLds pages;
+  } S;
   // A page outside the range: nothing changes.  (One thread reads the word
   // for all: a barrier that runs out writes it during the launch.)
   __shared__ uint32_t s_go;
-  if (threadIdx.x == 0) s_go = ld(A.status) == 0;
+  if (thread_id() == 0) s_go = ld(A.status) == 0;
   __syncthreads();
   if (!s_go) return;
   const uint32_t want = gridDim.x / A.groups, grp = blockIdx.x / want;
@@ -859,8 +920,8 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
   if (!gr.join(want, PATIENCE + (uint64_t)A.n / PATIENCE_PER)) return;
   for (int ci = (int)grp; ci < A.n_ids; ci += (int)A.groups) {
     const int id = A.ids[ci];
-    const CacheCfg c = A.cfgs[id];
-    const ChunkCfg cc = A.ccs[id];
+    CacheCfg c = A.cfgs[id];
+    ChunkCfg cc = A.ccs[id];
     const bool first = ci == 0;
     uint64_t *pf_page = first ? A.pf_page : nullptr;
     int64_t *n_pf = first ? A.n_pf : nullptr;
@@ -873,7 +934,7 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
     // begin past every tag in use (workgroups are at most one chunk apart).
     auto meet = [&]() {
       if (gr.sync()) return true;
-      if (threadIdx.x == 0) atomicMax(&cc.ctl->epoch, epoch + 2);
+      if (thread_id() == 0) atomicMax(&cc.ctl->epoch, epoch + 2);
       return false;
     };
     while (pos < A.n) {  // (all of it the same on every workgroup of the group)
@@ -888,25 +949,26 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
       const int64_t I0 = ld(&c.ctl->ins), lim = I0 - (int64_t)c.F, npf0 = n_pf ? ld(n_pf) : 0;
       chunk_tag(gr, cc, pages, L, epoch, tg);
       if (!meet()) return;
-      chunk_starts(gr, c, cc, pages, L, A.R, lim, epoch, tg);
+      chunk_starts(gr, S.pages, c, cc, pages, L, A.R, lim, epoch, tg);
       if (!meet()) return;
       if (!A.chunk) {
         const uint64_t lw = ld(&cc.ctl->loose[epoch & 1]);
         const uint32_t loose = (uint32_t)lw, late = (uint32_t)(lw >> 32);
-        if (loose >= DENSE_MIN && late > loose / 16 * 7) {
+        const uint32_t nseg = ld(&cc.ctl->nseg[epoch & 1]);
+        if (loose >= DENSE_MIN && late > loose / 16 * 7 && nseg < loose / DENSE_SEG) {
           len = (uint32_t)(L / 8);  // begin again with less
           continue;
         }
       }
       if (c.d > 0) {
-        chunk_walk(gr, c, cc, A.R, lim, tg);
+        chunk_walk(gr, c, cc, A.R, lim, epoch, tg);
         if (!meet()) return;
         chunk_sums(gr, cc, L);
         if (!meet()) return;
       }
-      chunk_scan(gr, c, cc, pages, L, A.R, I0, tg);
+      chunk_scan(gr, S.pages, c, cc, pages, L, A.R, I0, tg);
       if (!meet()) return;
-      chunk_check(gr, c, cc, pages, L, A.R, I0, tg);
+      chunk_check(gr, S.pages, c, cc, pages, L, A.R, I0, tg);
       if (!meet()) return;
       const int64_t T = ld(&cc.ctl->good);
       const int64_t I1 = I0 + (int64_t)(ld(&cc.S[T]) >> 32);
@@ -914,7 +976,7 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
         chunk_lost(gr, c, cc, pages, T, I0, I1, tg);
         if (!meet()) return;
       }
-      chunk_commit(gr, c, cc, pages, pos, L, T, A.R, I0, npf0, tg, hit, pf_page, A.pf_src, A.pf_cap, n_pf);
+      chunk_commit(gr, S.pages, c, cc, pages, pos, L, T, A.R, I0, npf0, tg, hit, pf_page, A.pf_src, A.pf_cap, n_pf);
       pos += T;
       if (pos >= A.n) break;  // nothing of this cache is read again
       if (!meet()) return;
@@ -926,24 +988,31 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
       len = (uint32_t)min((int64_t)most, max((int64_t)2 * T, (int64_t)SEQ_TRY));
       if (T >= SEQ_TRY) continue;
       const int64_t m = A.n - pos < (int64_t)seq ? A.n - pos : (int64_t)seq;
-      if (gr.b == 0 && threadIdx.x < 64)
-        cache_run_wave(c, S, A.R, A.pages + pos, m, hit ? hit + pos : nullptr, pf_page, A.pf_src, A.pf_cap, n_pf, pos);
+      if (gr.b == 0 && thread_id() < 64)
+        cache_run_wave(c, S.run, A.R, A.pages + pos, m, hit ? hit + pos : nullptr, pf_page, A.pf_src, A.pf_cap, n_pf,
+                       pos);
+      {  // (read again, so as not to hold its registers through the run)
+        int again = __builtin_amdgcn_readfirstlane(id);
+        asm volatile("" : "+s"(again));
+        c = A.cfgs[again];
+        cc = A.ccs[again];
+      }
       if (!meet()) return;
       pos += m;
       seq = min(seq * 2, SEQ_MAX);
       len = min(most, CHUNK_MIN);
     }
-    if (gr.b == 0 && threadIdx.x == 0) cc.ctl->epoch = epoch;
+    if (gr.b == 0 && thread_id() == 0) cc.ctl->epoch = epoch;
   }
 }
 
 __global__ __launch_bounds__(256) void k_chunk_clear(const ChunkCfg *__restrict__ ccs, const int *ids, uint64_t R) {
   const ChunkCfg cc = ccs[ids[blockIdx.y]];
-  for (uint64_t q = (uint64_t)blockIdx.x * 256 + threadIdx.x; q < R; q += (uint64_t)gridDim.x * 256) {
+  for (uint64_t q = (uint64_t)blockIdx.x * 256 + thread_id(); q < R; q += (uint64_t)gridDim.x * 256) {
     cc.at[q] = ~0ull;
     cc.tt[q] = 0;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) cc.ctl->epoch = 0;
+  if (blockIdx.x == 0 && thread_id() == 0) cc.ctl->epoch = 0;
 }
 
 hipError_t launch_chunk_clear(const ChunkCfg *dev_ccfgs, const int *cfg_ids, int n_cfg, uint64_t R, hipStream_t s) {
@@ -953,12 +1022,12 @@ hipError_t launch_chunk_clear(const ChunkCfg *dev_ccfgs, const int *cfg_ids, int
   return hipGetLastError();
 }
 
-// A workgroup for each 1,024 accesses, above 64 of them for each 2,048:
-// a scattered fault wants waves, a barrier costs more the more workgroups meet.
-// 221 K accesses of a scan 154 us at one per 1,024, 125 at one per 2,048;
-// 10 K scattered ones 258 us at one per 2,048, 133 at one per 1,024.
+// A workgroup for each 512 accesses, above 64 of them for each 2,048:
+// scattered faults and short runs want waves, a barrier costs more the more
+// workgroups meet.  10,000 accesses to 50,000 pages 115 us at one per 1,024, 94
+// at one per 512; 200,000 of them 433 at one per 1,024, 358 at one per 2,048.
 static int64_t chunk_share(int64_t n) {
-  return std::max((n + 2 * CBLK - 1) / (2 * CBLK), std::min((n + CBLK - 1) / CBLK, (int64_t)64));
+  return std::max((n + 2 * CBLK - 1) / (2 * CBLK), std::min((n + CBLK / 2 - 1) / (CBLK / 2), (int64_t)64));
 }
 
 hipError_t launch_cache_chunks(const CacheCfg *cfgs, const ChunkCfg *ccs, const int *ids, int n_cfg, uint64_t R,

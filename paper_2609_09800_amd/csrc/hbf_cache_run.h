@@ -122,10 +122,12 @@ __device__ __forceinline__ void cache_run_wave(const CacheCfg &c, RunLds &S, uin
       const int64_t view = act ? ld(&c.pins[a]) : PINS_NEVER;
       // earlier lanes of the round with the same page
       uint64_t same = 0;
+#pragma unroll
       for (uint32_t j = 0; j < 64; j++) {
         const uint32_t aj = (uint32_t)__builtin_amdgcn_readlane((int)a, (int)j);
-        same |= (j < lane && aj == a) ? (1ull << j) : 0ull;
+        same |= aj == a ? (1ull << j) : 0ull;
       }
+      same &= (1ull << lane) - 1;
       uint64_t fm = __ballot(act && view < I - F);
       for (int it = 0; it <= 64; it++) {
         const int64_t cl = (int64_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(fm >> 32),

@@ -226,10 +226,9 @@ constexpr int64_t PINS_NEVER = INT64_MIN / 4;
 // per-access insertion/fault counts and their exclusive scan (S, Lmax + 1
 // entries), the sums per 1,024 accesses and the segment starts.
 struct ChunkCtl {
-  uint32_t nseg;
+  uint32_t nseg[2];  // segments; odd or even tag
   uint32_t good;     // accesses of the chunk before the first decision that does not hold
   uint32_t epoch;    // last chunk tag used
-  uint32_t pad;
   uint64_t loose[2];  // candidates outside runs (low word), those near one accessed later (high); odd or even tag
   int64_t lost_old;  // frames filled before the chunk, evicted within it holding a prefetched page never hit
 };

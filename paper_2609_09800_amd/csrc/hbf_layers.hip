@@ -538,8 +538,10 @@ __global__ __launch_bounds__(EWBLK) void k_lay_emit_wave(const int64_t *__restri
       if ((uint32_t)__popcll(any) * 4 <= Dk) {  // few die queues reach this rank
         for (uint64_t mm = any; mm; mm &= mm - 1) count((int)__builtin_ctzll(mm));
       } else {
-#pragma unroll 8
-        for (uint32_t e = 0; e < Dk; e++) count((int)e);
+        for (uint32_t e0 = 0; e0 < Dk; e0 += 8) {  // (past Dk: no request)
+#pragma unroll
+          for (uint32_t e = 0; e < 8; e++) count((int)(e0 + e));
+        }
       }
       if (j < m)
         complete[ix[u]] = tl + imax(tR, (int64_t)(j + 1) * tR - (int64_t)n * xfer) + (int64_t)(r + 1) * xfer;

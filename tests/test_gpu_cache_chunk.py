@@ -378,3 +378,23 @@ def test_calls_side_by_side(torch, captured):
             assert np.array_equal(hit[i].cpu().numpy(), wh)
     for c in caches:
         c.close()
+
+
+@pytest.mark.parametrize("d", [1, 2, 15, 16, 31, 32, 63])
+@pytest.mark.parametrize("n", [1, 64, 511, 513, 1025, 33000])
+def test_isolated_and_dense_faults(torch, d, n):
+    """Scattered accesses that are segments of their own (the range's first
+    and last pages among them, whose windows end there), beside neighbours
+    first accessed out of order and, where many, a dense working set: a wave's
+    own accesses and ones that its workgroup shares out, in one workgroup and
+    in several."""
+    R = 70000
+    rng = np.random.default_rng(1000 * d + n)
+    far = rng.integers(0, R, n)
+    far[:: 7] = rng.choice([0, 1, d, R - 1, R - 2, R - 1 - d], far[:: 7].size)
+    near = far[rng.integers(0, n, n)] + rng.integers(-d - 2, d + 3, n)
+    pages = np.where(rng.random(n) < 0.3, np.clip(near, 0, R - 1), far)
+    if n > 10000:
+        pages[n // 2:] = rng.integers(0, 20000, n - n // 2)
+    # 16384: the length reported for a new cache, which lets it choose
+    run_both(torch, 60000, d, R, [pages, rng.integers(0, R, 700)], 16384, "isolated")
