@@ -81,7 +81,7 @@ extern "C" {
  * until that page's channel transfer has completed (the page has left the
  * register).  Channels still serve pages FCFS by (die-done, index).  The
  * die's clock after a call is its last transfer's completion.  Timed per
- * channel in service order (one wave per channel): slower than the default
+ * channel in service order (one workgroup per channel): slower than the default
  * unblocked model, which needs no such order. */
 #define HBF_FLAG_REGISTER_BLOCKING 2u
 /* Timing source: the calibrated end-to-end vmem curve (Section

@@ -8,7 +8,8 @@
 // The die and channel stages are now coupled: a die's next read waits on the
 // channel, whose order depends on every die's reads.  A channel and its die
 // queues form an independent system, so one wave runs each channel, one lane
-// per die queue.  Every die queue has at most one page pending at a time.
+// per die queue; the other waves of its workgroup share long steady stretches
+// with it.  Every die queue has at most one page pending at a time.
 // The channel takes pending pages in (die-done, index) order, and a die
 // reads its next request when its page has been transferred; each round of
 // the loop serves the whole prefix of the ranked pending pages that no

@@ -37,9 +37,9 @@
 // nothing -- and the longest segment of its walk.  1.94 M accesses of the MoE
 // stream, prefetch 7 (seven launches a chunk of 110 K accesses before, and a
 // chunk that failed its check served access by access):
-//   frames 1.77 M  1,596 -> 500 us      frames 300 K   8,360 -> 720 us
-//   frames 1.0 M  27,900 -> 2,330 us    frames 4,000   9,180 -> 620 us
-// and 64 accesses 57 -> 47 us.
+//   frames 1.77 M  1,600 -> 400 us     frames 300 K  8,330 -> 550 us
+//   frames 1.0 M   2,580 -> 410 us     frames 4,000  9,200 -> 490 us
+// and 64 accesses of a run 48 -> 50 us, scattered ones 79 -> 61.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -924,7 +924,7 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
   // A page outside the range: nothing changes.  (One thread reads the word
   // for all: a barrier that runs out writes it during the launch.)
   __shared__ uint32_t s_go;
-  if (thread_id() == 0) s_go = ld(A.status) == 0;
+  if (threadIdx.x == 0) s_go = ld(A.status) == 0;
   __syncthreads();
   if (!s_go) return;
   const uint32_t want = gridDim.x / A.groups, grp = blockIdx.x / want;
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
     // begin past every tag in use (workgroups are at most one chunk apart).
     auto meet = [&]() {
       if (gr.sync()) return true;
-      if (thread_id() == 0) atomicMax(&cc.ctl->epoch, epoch + 2);
+      if (threadIdx.x == 0) atomicMax(&cc.ctl->epoch, epoch + 2);
       return false;
     };
     while (pos < A.n) {  // (all of it the same on every workgroup of the group)

@@ -30,9 +30,7 @@ constexpr uint32_t ERR_OVERFLOW = 4u;
 constexpr uint32_t ERR_MAP = 8u;
 constexpr uint32_t ERR_INTERNAL = 16u;  // a bounded internal wait ran out (never expected)
 
-// Die stage: 256 threads (4 wave64), 16 items per thread per chunk.
 constexpr int BLK = 256;            // threads per block of the small kernels
-constexpr int WAVES = BLK / 64;
 constexpr int DBLK = 512;           // threads per block of the two die-stage passes
 constexpr int DWAVES = DBLK / 64;
 constexpr int DITEMS = 8;           // requests per thread per chunk
@@ -149,7 +147,7 @@ hipError_t launch_time_requests(const Geo &g, const RangeTable &rt, const Layout
                                 DevState *st, const uint64_t *addr, const int64_t *issue,
                                 int64_t *complete, hipStream_t s, hipEvent_t *ev, int n_ev,
                                 bool refresh);
-// Register-blocking channel stage (hbf_blocking.hip): one wave per channel.
+// Register-blocking channel stage (hbf_blocking.hip): one workgroup per channel.
 hipError_t launch_regblock(const Geo &g, const uint64_t *DDw, const uint32_t *IX, const int64_t *issue_do,
                            const uint32_t *seg_start, const uint32_t *totals, DevState *st, CallCtl *ctl,
                            int64_t *complete, int64_t *dfnew, int64_t *cfnew, bool ref, hipStream_t s);

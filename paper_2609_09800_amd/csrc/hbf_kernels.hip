@@ -848,9 +848,6 @@ struct WinLds {
 // itself (the write-out reads them conflict-free).
 DEVI uint32_t win_slot(uint32_t r) { return r ^ ((r >> 6) & 63u); }
 
-DEVI uint32_t wave_umin(uint32_t x) { return ~wave_umax(~x); }
-DEVI int64_t wave_min(int64_t x) { return -wave_max(-x); }
-
 // Look-back words: 0 = not yet published, else the value + 2^62 (every
 // published value lies in [NEG, 2^62)).
 DEVI uint64_t enc_time(int64_t x) { return (uint64_t)x + (uint64_t(1) << 62); }
