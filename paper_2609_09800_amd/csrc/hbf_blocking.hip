@@ -105,7 +105,6 @@ constexpr int QB = 128;             // staged quantum completions per write-out
 // l mod Dp (Dp: Dk rounded up to a power of two, at least 16) and every S-th
 // round (S = 64 / Dp), so a wave's batch covers `rounds` = S * FL rounds.
 constexpr uint32_t FL = 16;  // rounds per lane per batch
-constexpr uint32_t RW = 4;   // waves of a workgroup, one per SIMD (the channel loop needs its registers)
 struct SteadyData {
   int64_t is[FL];
   uint32_t ix[FL];
@@ -180,13 +179,19 @@ __device__ __forceinline__ void block_sync() {
 }
 
 // One workgroup per channel (blockIdx.x).  Wave 0 runs the channel, its lane
-// j = die queue c*Dk + j; the other waves wait for long steady stretches and
+// j = die queue c*Dk + j; the other waves, if any, wait for long steady stretches and
 // take their share of each batch: a stretch of thousands of rounds is bound
 // by its batches' load latency.  1 M requests on 16 channels, about 8,000
 // rounds each: 725 us a call with one wave per channel and steady rounds
 // only where the channel is the bottleneck, 560 with four waves, 246 with
 // the die-bound rounds too (the last dies of each channel, which the general
 // loop took a page at a time).  Eight waves spill the loop.
+// RW: waves of a workgroup.  The loop's registers leave room for one wave a
+// SIMD, so a workgroup of four has a CU to itself, and two of a single wave
+// share one.  More channels than CUs take single ones: below saturation they
+// are bound by how many run at a time (2 M requests on 1,024 x 2: 7.6 ms with
+// four waves, 4.0 with one; on 320 x 6 6.4 and 3.5), and long backlogs lose
+// little (on 1,024 x 1 242 and 270 us, on 1,024 x 2 245 and 226).
 //   DDw / IX: die-ordered request indices (packed word's low half when the
 //   cell shift is <= 32, else IX); issue_do: their issue times; seg_start /
 //   totals: each die queue's run.  ref: refresh quanta pending (each die
@@ -194,7 +199,7 @@ __device__ __forceinline__ void block_sync() {
 //   quantum's completion is written).
 // ROW: at most 16 die queues per channel, all in lanes 0-15 (one DPP row),
 // so the all-pairs comparisons of a round run on row rotations.
-template <bool ROW>
+template <bool ROW, uint32_t RW>
 __global__ __launch_bounds__(64 * RW) void k_regblock(const uint64_t *__restrict__ DDw, const uint32_t *__restrict__ IX,
                                                  const int64_t *__restrict__ issue_do,
                                                  const uint32_t *__restrict__ seg_start,
@@ -216,7 +221,7 @@ __global__ __launch_bounds__(64 * RW) void k_regblock(const uint64_t *__restrict
   // request indices: the low half of each packed die-order word, or IX
   const uint32_t *ixs = narrow ? reinterpret_cast<const uint32_t *>(DDw) : IX;
   const uint32_t ixstride = narrow ? 2u : 1u;
-  if (wave != 0) {  // batches of steady rounds until wave 0 says it is done
+  if (RW > 1 && wave != 0) {  // batches of steady rounds until wave 0 says it is done
     for (;;) {
       block_sync();
       const uint32_t j0 = s_round;
@@ -560,11 +565,15 @@ __global__ __launch_bounds__(64 * RW) void k_regblock(const uint64_t *__restrict
   }
 }
 
+constexpr uint32_t CUS = 256;  // of an MI355X
+
 hipError_t launch_regblock(const Geo &g, const uint64_t *DDw, const uint32_t *IX, const int64_t *issue_do,
                            const uint32_t *seg_start, const uint32_t *totals, DevState *st, CallCtl *ctl,
                            int64_t *complete, int64_t *dfnew, int64_t *cfnew, bool ref, hipStream_t s) {
-  hipLaunchKernelGGL(g.Dk <= 16 ? k_regblock<true> : k_regblock<false>, dim3(g.C), dim3(64 * RW), 0, s, DDw, IX,
-                     issue_do, seg_start, totals, g, st, ctl, complete, dfnew, cfnew, ref ? 1 : 0);
+  const bool single = g.C > CUS;  // (then at most 7 die queues per channel)
+  auto f = g.Dk > 16 ? k_regblock<false, 4> : single ? k_regblock<true, 1> : k_regblock<true, 4>;
+  hipLaunchKernelGGL(f, dim3(g.C), dim3(single ? 64 : 256), 0, s, DDw, IX, issue_do, seg_start, totals, g, st, ctl,
+                     complete, dfnew, cfnew, ref ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -257,3 +257,24 @@ def test_overflow_on_one_of_many_channels(torch):
     check_call(torch, g, o, addr, issue, "one channel overflows")
     rest = pages % 1024 != 3
     check_call(torch, g, o, addr[rest], issue[rest], "the others go on")
+
+
+@pytest.mark.parametrize("geo", [(256, 8), (257, 7), (1024, 2)])
+def test_many_channels(torch, geo):
+    """Up to and above 256 channels (four waves a channel, or one): a few
+    channels with long backlogs, whose steady stretches take many batches of
+    rounds, the others with a request now and then."""
+    C, D = geo
+    params = wl.geometry(C, D, 1, flags=BLOCK)
+    pages = C * D * 64
+    g, o = pair(params, [(wl.RANGE_BASE, pages * wl.PAGE)])
+    rng = np.random.default_rng(C)
+    for call in range(2):
+        n = 50000
+        pg = rng.integers(0, pages, n)
+        hot = rng.random(n) < 0.7
+        pg[hot] = C * rng.integers(0, pages // C, int(hot.sum())) + rng.integers(0, 3, int(hot.sum()))
+        steps = rng.integers(0, 30, n)
+        steps[rng.choice(n, 10, replace=False)] = 5_000_000
+        addr = np.uint64(wl.RANGE_BASE) + pg.astype(np.uint64) * np.uint64(wl.PAGE)
+        check_call(torch, g, o, addr, (call << 40) + np.cumsum(steps).astype(np.int64), f"many channels {geo} {call}")
