@@ -964,18 +964,20 @@ __global__ __launch_bounds__(CBLK) void k_chunk_run(ChunkRun A) {
       if (!meet()) return;
       chunk_starts(gr, S.pages, c, cc, pages, L, A.R, lim, epoch, tg);
       if (!meet()) return;
+      const uint32_t nseg = ld(&cc.ctl->nseg[epoch & 1]);
       if (!A.chunk) {
         const uint64_t lw = ld(&cc.ctl->loose[epoch & 1]);
         const uint32_t loose = (uint32_t)lw, late = (uint32_t)(lw >> 32);
-        const uint32_t nseg = ld(&cc.ctl->nseg[epoch & 1]);
         if (loose >= DENSE_MIN && late > loose / 16 * 7 && nseg < loose / DENSE_SEG) {
           len = (uint32_t)(L / 8);  // begin again with less
           continue;
         }
       }
       if (c.d > 0) {
-        chunk_walk(gr, c, cc, A.R, lim, epoch, tg);
-        if (!meet()) return;
+        if (nseg) {  // (scattered accesses are resolved already)
+          chunk_walk(gr, c, cc, A.R, lim, epoch, tg);
+          if (!meet()) return;
+        }
         chunk_sums(gr, cc, L);
         if (!meet()) return;
       }
@@ -1054,8 +1056,8 @@ hipError_t launch_cache_chunks(const CacheCfg *cfgs, const ChunkCfg *ccs, const 
       (e = hipDeviceGetAttribute(&blocks, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
     return e;
   ChunkRun A = {cfgs, ccs, ids, n_cfg, 0, R, pages, n, chunk, hit, pf_page, pf_src, pf_cap, status, n_pf, words};
-  // no more workgroups than a short call has work for
-  const int64_t use = chunk_share(n) * n_cfg;
+  // no more workgroups than a short call, or its chunks, have work for
+  const int64_t use = chunk_share(chunk ? std::min(n, (int64_t)chunk) : n) * n_cfg;
   if (use < blocks) blocks = (int)use;
   A.groups = (uint32_t)std::min(std::min(n_cfg, blocks), CHUNK_GROUPS);
   hipLaunchKernelGGL(k_chunk_run, dim3((uint32_t)blocks), dim3(CBLK), 0, s, A);
